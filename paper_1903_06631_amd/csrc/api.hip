@@ -78,6 +78,8 @@ size_t ws_score(uint32_t T)
            + 2 * ALIGN;                                // peak, t_peak
 }
 
+size_t ws_detect(uint32_t m) { return up((size_t)m * 8) + up((size_t)lap::DI_MAX_TILES * 8) + ALIGN; }
+
 size_t ws_validate() { return up(8 * 8); }
 
 constexpr uint32_t SELECT_MAX_LIMITS = 1024;
@@ -240,7 +242,7 @@ size_t lap_workspace_bytes(int which, uint32_t n_vars, uint32_t n_steps, uint32_
     case LAP_WS_SCORE_SWAPS: return ws_score(n_steps);
     case LAP_WS_VALIDATE: return ws_validate();
     case LAP_WS_SELECT_SWAPS: return ws_select(n_vars, n_steps, B);
-    case LAP_WS_DETECT_ITERATION: return up(((size_t)n_vars + 1) * 8);
+    case LAP_WS_DETECT_ITERATION: return ws_detect(n_vars);
     case LAP_WS_SCHEDULE_SWAPS: return ws_schedule(n_vars, n_steps);
     case LAP_WS_SIMULATE_SWAPS: return ws_simulate(n_vars, n_steps, B);
     case LAP_WS_EVALUATE_WEIGHTS: return ws_weights(n_vars, n_steps, B);
@@ -858,9 +860,13 @@ int lap_detect_iteration(const uint64_t *tokens, uint32_t n_requests, uint32_t m
 {
     if (!tokens || !period) return LAP_E_NULL;
     if (n_requests == 0 || n_requests == 0xFFFFFFFFu || min_period == 0) return LAP_E_SIZE;
-    const int rc = check_ws(ws, ws_bytes, up(((size_t)n_requests + 1) * 8));
+    const int rc = check_ws(ws, ws_bytes, ws_detect(n_requests));
     if (rc) return rc;
-    LAP_HIP(lap::launch_detect_iteration(tokens, n_requests, min_period, (uint64_t *)ws, period,
+    Carver c(ws);
+    uint64_t *hashes = c.take<uint64_t>(n_requests);
+    uint64_t *totals = c.take<uint64_t>(lap::DI_MAX_TILES);
+    uint32_t *ctrl = c.take<uint32_t>(4);
+    LAP_HIP(lap::launch_detect_iteration(tokens, n_requests, min_period, hashes, totals, ctrl, period,
                                          (hipStream_t)hip_stream));
     return LAP_OK;
 }

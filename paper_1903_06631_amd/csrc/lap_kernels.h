@@ -147,7 +147,9 @@ hipError_t launch_simulate_swaps(uint32_t n, uint32_t T, uint32_t Q, uint32_t km
                                  uint32_t n_lists = 1, const uint32_t *n_listed = nullptr);
 hipError_t launch_sched_mark(uint32_t n, uint32_t k, const uint32_t *list, uint32_t *posmap, hipStream_t st);
 
-hipError_t launch_detect_iteration(const uint64_t *tokens, uint32_t M, uint32_t min_period, uint64_t *P,
-                                   uint32_t *period, hipStream_t st);
+// Q [M] prefix hashes, totals [DI_MAX_TILES], ctrl [4]: scratch
+constexpr uint32_t DI_MAX_TILES = 4096;
+hipError_t launch_detect_iteration(const uint64_t *tokens, uint32_t M, uint32_t min_period, uint64_t *Q,
+                                   uint64_t *totals, uint32_t *ctrl, uint32_t *period, hipStream_t st);
 
 }  // namespace lap

@@ -70,3 +70,19 @@ def test_detect_argument_errors(lap):
     with pytest.raises(lap.LapError) as e:
         lap.detect_iteration(t, 0)
     assert e.value.status == -2
+
+
+@pytest.mark.parametrize("m", [6143, 6144, 6145, 9217, 12287, 16385, 70001])
+def test_detect_around_one_launch_and_tile_sizes(lap, oracle_mod, m):
+    """the list sizes at which the work is split otherwise (one workgroup up to 6144 requests, tiles of 1024 above),
+    with the list 16-byte aligned and not, a square that covers all, most and little of the list, and none"""
+    import torch
+    rng = np.random.default_rng(m)
+    for p in (m // 2, m // 3, 1500, 1, 0):
+        s = rng.integers(0, 1 << 62, m + 1).astype(np.uint64)
+        if p:
+            s[m + 1 - p:] = s[m + 1 - 2 * p:m + 1 - p]
+        t = torch.from_numpy(s.view(np.int64)).cuda()
+        for cut in (0, 1):
+            for mp in (1, max(p, 1), p + 1):
+                assert int(lap.detect_iteration(t[cut:], mp).item()) == oracle_mod.detect_iteration(s[cut:], mp), (p, cut, mp)
