@@ -35,6 +35,21 @@ struct PlanHeader {
 };
 constexpr uint32_t PLAN_CL = 6;
 
+// Placed blocks in registers (place_reg.hip): whether they may be used: 112 rows of 256 entries, 16-bit
+// steps ...
+constexpr uint32_t PLAN_REG_MAX_VARS = 112 * 256;
+inline bool reg_may_place(uint32_t n, uint32_t T) { return n <= PLAN_REG_MAX_VARS && T <= 0xFFFFu; }
+// ... and whether they are, as far as the trace decides it.  Where lifetimes are short enough for the
+// per-step lists those are faster, except for a few hundred variables (shapes of mostly one-step
+// variables, 256 orderings: 500 of them 0.19 ms in registers and 0.30 ms with the lists, 1000 of
+// them 0.57 and 0.44 ms, 6000 of them 7.1 and 2.9 ms).
+constexpr uint32_t PLAN_REG_ALWAYS_VARS = 3 * 256;
+__device__ __forceinline__ bool reg_places(const PlanHeader *hdr, uint32_t n, bool best_fit)
+{
+    if (!hdr->fast || (hdr->mode2 && !best_fit)) return false;
+    return !hdr->mode1 || n <= PLAN_REG_ALWAYS_VARS;
+}
+
 hipError_t launch_fill_u64(uint64_t *p, size_t n, uint64_t v, hipStream_t st);
 // copies n_words 32-bit words of HOST memory to the device through kernel arguments (the host
 // array is read before the call returns; nothing waits)
@@ -66,6 +81,9 @@ hipError_t launch_place_seg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
                             bool any_first, PlanHeader *hdr, const void *vrec, const uint32_t *lst,
                             uint64_t *pool, uint32_t *lens, uint32_t dir_cap, uint64_t *offs, uint64_t *fps,
                             uint64_t *ticks, hipStream_t st);
+hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *perm, const uint32_t *fits,
+                            const PlanHeader *hdr, const void *vrec, uint64_t *offs, uint64_t *fps, uint64_t *ticks,
+                            hipStream_t st);
 hipError_t launch_place_fast(uint32_t n, uint32_t T, uint32_t B, const uint64_t *size, const uint32_t *alloc,
                              const uint32_t *free_, const uint32_t *perm, const uint32_t *fits, bool any_first,
                              bool any_best, PlanHeader *hdr, const void *vrec,

@@ -31,7 +31,8 @@
 //          instead (steps_fit_pass), in turn with the ALL sweeps, until neither
 //          moves the candidate offset.
 //
-// Without the L[t] lists every variable queries ALL (the sweep).  First-fit orderings of large
+// Without the L[t] lists every variable queries ALL (the sweep): the way of traces too large for the
+// registers of a workgroup (place_reg.hip).  First-fit orderings of large
 // traces whose variables live long may instead be placed by free lists per time segment
 // (place_seg.hip); k_plan_prep2 and a trial run decide, and this kernel then leaves them alone.
 //
@@ -501,6 +502,7 @@ struct FastArgs {
     uint64_t *offs;              // [B][n] in rank order
     uint64_t *fps;               // [B]
     uint64_t *ticks;             // [B] duration of every ordering in timer ticks
+    bool reg;                    // the register kernel (place_reg.hip) takes the traces that suit it
 };
 
 constexpr int COOP_U = 4;                    // chunks per wave in one cooperative round
@@ -934,6 +936,7 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
     __shared__ uint32_t s_prio;              // wave priority in force for this workgroup
 
     if (!A.hdr->fast) return;               // the 64-bit kernel handles this trace
+    if (A.reg && reg_places(A.hdr, A.n, BEST)) return;
     if (A.hdr->mode2 && !BEST) return;      // the segment kernel places the first-fit orderings of this trace
     const uint32_t b = blockIdx.x;
     if ((A.fits[b] != 0) != BEST) return;   // the other instantiation handles this ordering
@@ -1489,7 +1492,8 @@ hipError_t launch_place_fast(uint32_t n, uint32_t T, uint32_t B, const uint64_t 
     FastArgs A{n, T, size, alloc, free_, (const uint4 *)vrec, perm, fits, hdr, lstart, {m_oe, m_oe2}, {m_life, m_life2}, {r_oe, r_oe2}, {r_life, r_life2},
                L, l_ns,
                l_nu, capL,
-               offs, fps, ticks};
+               offs, fps, ticks, reg_may_place(n, T)};
+    if (A.reg && n <= PLAN_REG_ALWAYS_VARS) return hipSuccess;    // it takes every trace of this size
     // each instantiation leaves the orderings of the other policy alone
     if (T <= 0xFFFFu) {
         if (any_first) hipLaunchKernelGGL((k_place_fast<uint32_t, false>), dim3(B), dim3(PW * WAVE), 0, st, A);

@@ -1,0 +1,56 @@
+"""GPU parity of lap_plan_pool where the placed blocks are kept in registers, at the sizes where a variant ends: a
+row is 256 blocks, and the number of waves and of rows per wave depends on the number of variables and of orderings.
+Offsets and footprints are compared element by element with the oracle's, first-fit and best-fit."""
+import numpy as np
+import pytest
+
+from gpu_util import oracle_all_orderings, u64
+from traces import make_orderings, random_trace
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lap():
+    import paper_1903_06631_amd as lap
+    lap.load_library()
+    return lap
+
+
+def _check(lap, oracle, tr, B, fits, which):
+    kinds, seeds = make_orderings(B)
+    got = lap.plan_pool(lap.DeviceTrace(tr), kinds, seeds, fits=fits)
+    all_off, fps = u64(got["all_offsets"]), u64(got["footprints"])
+    for b, (_, off, fp) in oracle_all_orderings(oracle, tr, kinds, seeds, None, which, fits).items():
+        assert np.array_equal(all_off[b], off), f"ordering {b}"
+        assert fps[b] == fp, f"ordering {b}"
+    assert int(got["best_ordering"].item()) == int(np.argmin(fps))
+
+
+# 768: the last size that is placed in registers whatever the lifetimes are; 65535: the last step count with 16-bit
+# lifetimes, 65536 leaves the registers; 28672 the largest size, 28673 leaves the registers
+@pytest.mark.parametrize("n,T,B", [(1, 1, 8), (255, 40, 8), (256, 40, 8), (257, 40, 8), (513, 65535, 8), (513, 65536, 8),
+                                   (768, 300, 8), (769, 300, 8), (1025, 90, 8), (2048, 90, 8), (2049, 200, 8), (4096, 500, 8),
+                                   (4097, 500, 8), (12289, 900, 4)])
+def test_sizes(lap, oracle_mod, n, T, B):
+    tr = random_trace(9000 + n, n, T, size_choices=[1, 1, 2, 3, 5, 8, 13, 64])
+    _check(lap, oracle_mod, tr, B, [b % 2 for b in range(B)], None)
+
+
+@pytest.mark.parametrize("n,T", [(2049, 200), (4097, 300)])
+def test_more_orderings_than_compute_units(lap, oracle_mod, n, T):
+    tr = random_trace(9100 + n, n, T, size_choices=[1, 2, 3, 7, 20])
+    _check(lap, oracle_mod, tr, 257, [b % 2 for b in range(257)], [0, 1, 2, 3, 128, 255, 256])
+
+
+@pytest.mark.parametrize("n,fits", [(28672, [0, 1]), (28673, [0, 0])])
+def test_largest(lap, oracle_mod, n, fits):
+    tr = random_trace(9200, n, 2000, size_choices=[1, 2, 3, 7, 20, 50])
+    _check(lap, oracle_mod, tr, 2, fits, None)
+
+
+def test_short_lifetimes_keep_the_per_step_lists(lap, oracle_mod):
+    """on both sides of the size up to which such a trace is placed in registers all the same"""
+    for n in (760, 780):
+        tr = random_trace(9300, n, 60, size_choices=[1, 2, 3, 7], one_step_frac=0.9, max_life=3)
+        _check(lap, oracle_mod, tr, 8, [b % 2 for b in range(8)], None)
