@@ -451,9 +451,6 @@ int lap_plan_pool(const lap_trace *tr, const lap_ordering *ords, uint32_t B, uin
                                   seg_pool_entries(n, B), g_seg_min_vars, st));
     LAP_HIP(lap::launch_seg_prep(n, T, B, tr->alloc, tr->free_, hdr, seg_cnt, seg_lst, (uint32_t)dir_cap,
                                  seg_pool_entries(n, B), st));
-    // per-step entry counts start at zero (cleared as 64-bit words, the regions are padded)
-    LAP_HIP(lap::launch_fill_u64((uint64_t *)l_ns, ((size_t)B * T + 1) / 2, 0, st));
-    LAP_HIP(lap::launch_fill_u64((uint64_t *)l_nu, (size_t)B * T, 0, st));
     {
         int trial_b = -1;                   // the first first-fit ordering shows how the segment lists' searches go
         for (uint32_t b = 0; b < B && trial_b < 0; ++b)

@@ -6,9 +6,12 @@
 // block end fits 32 bits and a placed block packs into one 64-bit word
 // (off << 32 | end), so sorting words sorts by offset.
 //
-// One workgroup of PW waves per ordering.  Two families of lists:
+// One workgroup of PW waves (4 or 8) per ordering.  Two families of lists:
 //
-//   ALL    placed blocks with their lifetimes, sorted by offset: `main` and
+//   ALL    placed blocks with their lifetimes, sorted by offset: in registers, a row of 256 per
+//          wave (block_rows.h), where only multi-step blocks enter it and there are few enough of
+//          them (up to 256 per wave, what a transformer's iteration has: a query is then one barrier,
+//          0.5 us, instead of a sweep through global memory, 2 us); else `main` and
 //          `recent` (global memory, two buffers each, merged out of place) and
 //          `pending` (LDS, unsorted, the newest).  Queried by variables that
 //          live for more than one step: all waves sweep a sorted list together,
@@ -41,12 +44,11 @@
 // owns the steps t with t % PW == w.  Multi-step variables are handled by all
 // waves between workgroup barriers.  The result is identical to placing the
 // variables one by one in rank order.
-#include "lap_dev.h"
+#include "block_rows.h"
 #include "lap_kernels.h"
 
 namespace lap {
 
-constexpr int PW = 4;               // waves per ordering
 constexpr uint32_t PEND = 128;      // room for the pending (unsorted) entries in LDS
 constexpr uint32_t PEND_FLUSH = 32; // pending entries at which they are sorted into `recent`
 constexpr uint32_t REC = PLAN_REC;  // recent (sorted) entries per buffer, global memory
@@ -63,6 +65,8 @@ __device__ __forceinline__ void lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
+
+constexpr uint32_t NONE32 = 0xFFFFFFFFu;
 
 __device__ __forceinline__ uint64_t pk(uint32_t off, uint32_t end) { return ((uint64_t)off << 32) | end; }
 
@@ -297,7 +301,7 @@ __device__ __forceinline__ uint32_t mem_find_hole(const uint64_t *Lt, uint32_t n
 
 // bitonic sort of m (power of two, >= 64) packed entries with their lifetimes, in LDS, by the
 // whole workgroup (a workgroup barrier after every compare-exchange stage)
-template <class LT>
+template <int PW, class LT>
 __device__ __forceinline__ void bitonic_sort(uint64_t *oe, LT *life, uint32_t m)
 {
     for (uint32_t k = 2; k <= m; k <<= 1) {
@@ -344,17 +348,16 @@ __device__ __forceinline__ uint32_t h_first_fit(const uint64_t *hl, uint32_t nh,
 __device__ __forceinline__ uint32_t h_best_fit(const uint64_t *hl, uint32_t nh, uint32_t s)
 {
     const int l = lane_id();
-    uint64_t best = U64_MAX;
+    uint32_t best = NONE32, at = 0;
     for (uint32_t base = 0; base + 1 < nh; base += WAVE) {
         const uint32_t idx = base + l;
         if (idx + 1 < nh) {
             const uint32_t z = (uint32_t)hl[idx];
-            if (z >= s) best = umin64(best, ((uint64_t)z << 32) | idx);
+            if (z >= s && z < best) { best = z; at = idx; }
         }
     }
-#pragma unroll
-    for (int m = WAVE / 2; m > 0; m >>= 1) best = umin64(best, shfl_xor64(best, m));
-    return uniform(best == U64_MAX ? nh - 1 : (uint32_t)best);
+    const uint32_t m = ~wave_reduce_max32(~best);
+    return m == NONE32 ? nh - 1 : ~wave_reduce_max32(best == m ? ~at : 0u);
 }
 
 // index of the hole that contains address o (start <= o < start + size); x receives the hole.
@@ -506,8 +509,6 @@ struct FastArgs {
 };
 
 constexpr int COOP_U = 4;                    // chunks per wave in one cooperative round
-constexpr int ROUND_CH = PW * COOP_U;        // chunks per round
-constexpr uint32_t NONE32 = 0xFFFFFFFFu;
 
 // Lowest offset >= P at which `s` granules are free with respect to the time-overlapping
 // entries of a short UNSORTED list: while some entry meets [P, P+s), move P to the highest
@@ -589,7 +590,7 @@ template <class LT> struct GlobalWindow {   // the list sits in global memory: 6
 // of small-list entries below each, and writes the small-list entries whose place is inside
 // it (after big-list entries of equal key).  No barrier inside; the caller synchronises
 // before reading dst.
-template <class LT, class Small>
+template <int PW, class LT, class Small>
 __device__ __forceinline__ void coop_merge(const uint64_t *src_oe, const LT *src_life, uint32_t nb, Small sm,
                                            uint32_t ns, uint64_t *dst_oe, LT *dst_life, uint32_t wave)
 {
@@ -643,11 +644,12 @@ __device__ __forceinline__ void coop_merge(const uint64_t *src_oe, const LT *src
 // of the round wins.  Two workgroup barriers per round; the next round's loads are issued
 // before the current round is processed.  All waves pass the same arguments and get the
 // same result.
-template <class LT>
+template <int PW, class LT>
 __device__ __forceinline__ uint32_t coop_sweep(const uint64_t *oe, const LT *life, uint32_t n,
                                                uint32_t &cursor, uint32_t P, uint32_t s, uint32_t a, uint32_t f,
                                                uint32_t wave, uint32_t *s_cmax, uint32_t *s_hq, uint32_t *s_hans)
 {
+    constexpr int ROUND_CH = PW * COOP_U;        // chunks per round
     const int l = lane_id();
     uint32_t i = cursor;
     uint64_t x[COOP_U], nx[COOP_U];
@@ -733,6 +735,7 @@ __device__ __forceinline__ uint32_t coop_sweep(const uint64_t *oe, const LT *lif
 constexpr uint32_t FIT_MEMO = 4;
 constexpr uint32_t FIT_WORDS = 5;   // per step: answer, end of its hole, its index, list start, index of the top hole
 static_assert(FIT_MEMO * FIT_WORDS * WAVE * sizeof(uint32_t) <= LH * sizeof(uint64_t), "the memo must fit the wave's list slice");
+template <int PW>
 __device__ __forceinline__ uint32_t steps_fit_pass(const uint64_t *__restrict__ L, const uint32_t *__restrict__ lstart,
                                                    const uint32_t *l_ns, const uint32_t *l_top, uint32_t a, uint32_t f, uint32_t o,
                                                    uint32_t s, bool &valid0, bool &valid_rest, uint32_t *memo)
@@ -839,6 +842,7 @@ __device__ __forceinline__ uint32_t steps_fit_pass(const uint64_t *__restrict__ 
 // p comes from a fixed point of steps_fit_pass, whose last pass found, for every step, the
 // hole that holds [p, p + s): its end is still in `memo` for the thread's first FIT_MEMO
 // steps; later steps look their hole up (the first whose end lies above p).
+template <int PW>
 __device__ __forceinline__ uint32_t steps_extent_pass(const uint64_t *__restrict__ L,
                                                       const uint32_t *__restrict__ lstart, const uint32_t *l_ns,
                                                       uint32_t a, uint32_t f, uint32_t p, const uint32_t *memo)
@@ -868,7 +872,7 @@ __device__ __forceinline__ uint32_t steps_extent_pass(const uint64_t *__restrict
 
 // In a sorted list: offset of the first entry at or after index `from` that overlaps [a, f) in
 // time, 0xFFFFFFFF if there is none.  All waves call it with the same arguments.
-template <class LT>
+template <int PW, class LT>
 __device__ __forceinline__ uint32_t coop_next_overlap(const uint64_t *oe, const LT *life, uint32_t n, uint32_t from,
                                                       uint32_t a, uint32_t f, uint32_t wave, uint32_t *s_x)
 {
@@ -900,11 +904,13 @@ __device__ __forceinline__ uint32_t coop_next_overlap(const uint64_t *oe, const 
 
 // A list of `tot` entries moves between global memory, registers (entry i in register i / 64
 // of lane i % 64) and LDS in chunks of 64; the chain of tests ends at the first chunk that
-// lies beyond the list, so a short list costs few branches.
+// lies beyond the list, so a short list costs few branches.  Lists of more than PFC chunks are not
+// fetched ahead.
+constexpr int PFC = 4;
 template <int C>
-__device__ __forceinline__ void regs_from_global(uint64_t (&r)[LH / WAVE], const uint64_t *src, uint32_t tot, int l)
+__device__ __forceinline__ void regs_from_global(uint64_t (&r)[PFC], const uint64_t *src, uint32_t tot, int l)
 {
-    if constexpr (C < (int)(LH / WAVE)) {
+    if constexpr (C < PFC) {
         if ((uint32_t)C * WAVE < tot) {
             const uint32_t idx = C * WAVE + l;
             r[C] = idx < tot ? src[idx] : 0ull;
@@ -913,9 +919,9 @@ __device__ __forceinline__ void regs_from_global(uint64_t (&r)[LH / WAVE], const
     }
 }
 template <int C>
-__device__ __forceinline__ void lds_from_regs(uint64_t *hl, const uint64_t (&r)[LH / WAVE], uint32_t tot, int l)
+__device__ __forceinline__ void lds_from_regs(uint64_t *hl, const uint64_t (&r)[PFC], uint32_t tot, int l)
 {
-    if constexpr (C < (int)(LH / WAVE)) {
+    if constexpr (C < PFC) {
         if ((uint32_t)C * WAVE < tot) {
             const uint32_t idx = C * WAVE + l;
             if (idx < tot) hl[idx] = r[C];
@@ -924,27 +930,72 @@ __device__ __forceinline__ void lds_from_regs(uint64_t *hl, const uint64_t (&r)[
     }
 }
 
-template <class LT, bool BEST>
-__global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
+// The hole a variable of s granules takes, the list's first holes (best-fit: all of them) in
+// registers, hole 64 c + l in y[c] of lane l: its index and the hole.  False: not among them.
+template <bool BEST, int FC>
+__device__ __forceinline__ bool reg_hole(const uint64_t (&y)[FC], uint32_t ns, uint32_t s, uint32_t &h, uint64_t &x)
 {
-    __shared__ uint64_t p_oe[PEND];
-    __shared__ LT p_life[PEND];
-    __shared__ uint64_t s_h[PW][LH];         // per-wave hole list
-    __shared__ uint32_t s_fp[PW], s_hq[PW], s_hans[PW];
-    __shared__ uint32_t s_cmax[ROUND_CH];
-    __shared__ uint32_t s_sf[2][PW];
-    __shared__ uint32_t s_prio;              // wave priority in force for this workgroup
+    const uint32_t l = (uint32_t)lane_id();
+    if constexpr (!BEST) {
+        const uint64_t m = ballot(l < ns && (uint32_t)y[0] >= s);
+        if (!m) return false;
+        h = (uint32_t)__ffsll((unsigned long long)m) - 1;
+        x = read_lane64(y[0], (int)h);
+    } else {
+        // the smallest bounded hole that fits, the lowest of equally small ones, else the top hole
+        uint32_t mine = NONE32;
+#pragma unroll
+        for (int c = 0; c < FC; ++c) {
+            const uint32_t z = (uint32_t)y[c];
+            if (c * WAVE + l + 1 < ns && z >= s) mine = min(mine, z);
+        }
+        const uint32_t best = ~wave_reduce_max32(~mine);
+        h = ns - 1;
+        if (best != NONE32) {
+#pragma unroll
+            for (int c = FC - 1; c >= 0; --c) {
+                const uint64_t m = ballot(c * WAVE + l + 1 < ns && (uint32_t)y[c] == best);
+                if (m) h = c * WAVE + (uint32_t)__ffsll((unsigned long long)m) - 1;
+            }
+        }
+        x = read_lane64(y[0], (int)(h & (WAVE - 1)));
+#pragma unroll
+        for (int c = 1; c < FC; ++c)
+            if (h >= (uint32_t)c * WAVE) x = read_lane64(y[c], (int)(h & (WAVE - 1)));
+    }
+    return true;
+}
 
-    if (!A.hdr->fast) return;               // the 64-bit kernel handles this trace
-    if (A.reg && reg_places(A.hdr, A.n, BEST)) return;
-    if (A.hdr->mode2 && !BEST) return;      // the segment kernel places the first-fit orderings of this trace
+template <class LT, int PW> struct FastShared {
+    uint64_t p_oe[PEND];
+    LT p_life[PEND];
+    uint64_t s_h[PW][LH];                    // per-wave hole list
+    uint32_t s_fp[PW], s_hq[PW], s_hans[PW];
+    uint32_t s_cmax[PW * COOP_U];
+    uint32_t s_sf[2][PW];
+    uint32_t s_prio;                         // wave priority in force for this workgroup
+    uint4 s_row[2][PW];                      // per row of multi-step blocks: its last entry, the highest end among the neighbours
+};
+
+// Per-step words of an ordering that a workgroup may keep in LDS instead of global memory: the two
+// entry counts of a step's list, where its top hole starts, where it lies in L.
+constexpr uint32_t META_WORDS = 4;
+
+// one ordering, by one workgroup
+template <class LT, int PW, bool META, bool BEST>
+__device__ __forceinline__ void place_ordering(const FastArgs &A, FastShared<LT, PW> &S, uint32_t *meta)
+{
+    uint64_t *p_oe = S.p_oe;
+    LT *p_life = S.p_life;
+    uint32_t *s_fp = S.s_fp, *s_hq = S.s_hq, *s_hans = S.s_hans, *s_cmax = S.s_cmax;
+    uint32_t (&s_sf)[2][PW] = S.s_sf;
+    constexpr int FC = BEST ? PFC : 1;
     const uint32_t b = blockIdx.x;
-    if ((A.fits[b] != 0) != BEST) return;   // the other instantiation handles this ordering
     const long long t_begin = wall_clock64();
     const bool mode1 = A.hdr->mode1 != 0;
     const uint32_t sh = A.hdr->shift;
     const int l = lane_id();
-    const uint32_t wave = threadIdx.x / WAVE;
+    const uint32_t wave = uniform(threadIdx.x / WAVE);
 
     const uint32_t n = A.n, T = A.T;
     const uint32_t *perm = A.perm + (size_t)b * n;
@@ -952,11 +1003,32 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
     LT *m_life[2] = {(LT *)A.m_life[0] + (size_t)b * n, (LT *)A.m_life[1] + (size_t)b * n};
     uint64_t *r_oe[2] = {A.r_oe[0] + (size_t)b * REC, A.r_oe[1] + (size_t)b * REC};
     LT *r_life[2] = {(LT *)A.r_life[0] + (size_t)b * REC, (LT *)A.r_life[1] + (size_t)b * REC};
-    uint64_t *hl = s_h[wave];
+    uint64_t *hl = S.s_h[wave];
     uint64_t *L = A.L + (size_t)b * A.capL;
-    uint32_t *l_ns = A.l_ns + (size_t)b * T;
-    uint32_t *l_nu = A.l_nu + (size_t)b * T;
-    uint32_t *l_top = A.l_nu + (size_t)gridDim.x * T + (size_t)b * T;
+    uint32_t *l_ns, *l_nu, *l_top;
+    const uint32_t *lstart;
+    if constexpr (META) {
+        l_ns = meta;
+        l_nu = meta + T;
+        l_top = meta + 2 * T;
+        uint32_t *ls = meta + 3 * T;
+        if (mode1)
+            for (uint32_t t = threadIdx.x; t < T; t += PW * WAVE) ls[t] = A.lstart[t];
+        lstart = ls;
+        __syncthreads();
+    } else {
+        l_ns = A.l_ns + (size_t)b * T;
+        l_nu = A.l_nu + (size_t)b * T;
+        l_top = A.l_nu + (size_t)gridDim.x * T + (size_t)b * T;
+        lstart = A.lstart;
+    }
+    // Multi-step blocks in registers, one row per wave, instead of the lists of ALL: where the trace has
+    // few enough of them.
+    const bool rows = sizeof(LT) == 4 && mode1 && A.hdr->n_multi <= PW * ROW;
+    Row row;
+#pragma unroll
+    for (int j = 0; j < EPL; ++j) { row.off[j] = NOTHING; row.end[j] = NOTHING; row.life[j] = NOTHING; }
+    uint32_t n_rowed = 0;                   // blocks in the rows
     uint64_t *offs = A.offs + (size_t)b * n;
 
     // variables that will still query ALL: every one when there are no per-step lists
@@ -975,13 +1047,14 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
     uint32_t *g_part = &A.hdr->part[BEST ? 1 : 0], *g_prog = &A.hdr->progress[BEST ? 1 : 0];
     if (threadIdx.x == 0) {
         atomicAdd(g_part, 1u);
-        s_prio = 1;
+        S.s_prio = 1;
     }
     if (mode1) {
         // every step starts with one hole covering the whole address space
         for (uint32_t t = threadIdx.x; t < T; t += PW * WAVE) {
-            L[A.lstart[t]] = pk(0u, NONE32);
+            L[lstart[t]] = pk(0u, NONE32);
             l_ns[t] = 1;
+            l_nu[t] = 0;
             l_top[t] = 0;
         }
     }
@@ -1023,7 +1096,7 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
         if (nr + np > REC) {
             GlobalWindow<LT> gw{r_oe[rb], r_life[rb], nr, 0, 0, 0};
             gw.load(0);
-            coop_merge(m_oe[mb], m_life[mb], nm, gw, nr, m_oe[mb ^ 1], m_life[mb ^ 1], wave);
+            coop_merge<PW>(m_oe[mb], m_life[mb], nm, gw, nr, m_oe[mb ^ 1], m_life[mb ^ 1], wave);
             mb ^= 1;
             nm += nr;
             nr = 0;
@@ -1033,8 +1106,8 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
         while (m < np) m <<= 1;
         for (uint32_t i = np + threadIdx.x; i < m; i += PW * WAVE) { p_oe[i] = U64_MAX; p_life[i] = 0; }
         __syncthreads();
-        bitonic_sort(p_oe, p_life, m);
-        coop_merge(r_oe[rb], r_life[rb], nr, LdsList<LT>{p_oe, p_life}, np, r_oe[rb ^ 1], r_life[rb ^ 1], wave);
+        bitonic_sort<PW>(p_oe, p_life, m);
+        coop_merge<PW>(r_oe[rb], r_life[rb], nr, LdsList<LT>{p_oe, p_life}, np, r_oe[rb ^ 1], r_life[rb ^ 1], wave);
         rb ^= 1;
         nr += np;
         np_multi = 0;
@@ -1057,9 +1130,9 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
                 const uint32_t done = atomicAdd(g_prog, 1u) + 1u;
                 const uint32_t started = max(*(volatile uint32_t *)g_part, 1u);
                 const int lag = (int)(done / started) - (int)(r0 / PACE_RANKS);
-                *(volatile uint32_t *)&s_prio = lag >= 2 ? 3u : lag >= 0 ? 2u : lag >= -2 ? 1u : 0u;
+                *(volatile uint32_t *)&S.s_prio = lag >= 2 ? 3u : lag >= 0 ? 2u : lag >= -2 ? 1u : 0u;
             }
-            const uint32_t want = uniform(*(volatile uint32_t *)&s_prio);
+            const uint32_t want = uniform(*(volatile uint32_t *)&S.s_prio);
             if (want != prio_now) {
                 prio_now = want;
                 if (want == 0) __builtin_amdgcn_s_setprio(0);
@@ -1083,16 +1156,29 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
         const uint32_t wn = (uint32_t)__popcll(im);
         const bool one_step = in && mode1 && f - a == 1;
         const bool own = one_step && (a % PW) == wave;       // only the owner of a step looks at its list
-        if (own) { plb = A.lstart[a]; pns = l_ns[a]; pnu = l_nu[a]; }
+        if (own) { plb = lstart[a]; pns = l_ns[a]; pnu = l_nu[a]; }
         if (cur_t != NONE32 && one_step && a == cur_t) { pns = cnt; pnu = 0; }   // the cached list is newer
         uint32_t p = 0;
         while (p < wn) {
             if ((mm >> p) & 1ull) {
                 // ---- a variable that queries ALL: every wave sweeps, wave 0 keeps recent ----
                 if (cur_t != NONE32) { writeback(one_step ? a : NONE32); cur_t = NONE32; }
+                const uint32_t va = read_lane(a, (int)p), vf = read_lane(f, (int)p), vs = read_lane(s, (int)p);
+                // rows: the masked ends of this wave's row; before the barrier, so that the wave that arrives first has
+                // this done while it waits
+                const uint32_t used = n_rowed / ROW + 1, rbuf = n_rowed & 1u;
+                uint32_t ends[EPL] = {0u, 0u, 0u, 0u}, incl = 0;
+                if (rows && wave < used) {
+                    incl = row_ends(row, life_bound(va, vf), ends);
+                    if (l == WAVE - 1) S.s_row[rbuf][wave] = make_uint4(row.off[EPL - 1], row.end[EPL - 1], row.life[EPL - 1], incl);
+                }
                 __syncthreads();
-                const uint32_t va = __shfl(a, (int)p, WAVE);
-                const uint32_t vf = __shfl(f, (int)p, WAVE), vs = __shfl(s, (int)p, WAVE);
+                uint32_t rows_below = 0, rows_top = 0;      // highest end among the neighbours: in the rows below this wave's, in all
+                if (rows) {
+                    const uint32_t m = wave_scan_max_u32((uint32_t)l < used ? S.s_row[rbuf][l & (PW - 1)].w : 0u);
+                    if (wave) rows_below = read_lane(m, (int)wave - 1);
+                    rows_top = read_lane(m, (int)used - 1);
+                }
                 // pending stays unsorted and is checked directly, unless many of its entries come
                 // from ALL queries: those stack on each other and would be climbed one by one
                 uint32_t np = np_multi;             // every pending entry comes from a query like this one
@@ -1107,18 +1193,56 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
                 // lowest offset >= `from` that is free of every neighbour: the sorted lists, the
                 // pending entries and (with per-step lists) the hole lists are asked in turn until
                 // none of them moves the candidate
+                uint32_t rflip = 0;
+                auto rows_fit = [&](uint32_t from) -> uint32_t {
+                    uint32_t at = NOTHING;
+                    if (wave < used) {
+                        uint32_t before[EPL], free_[EPL];
+                        row_holes(row, ends, incl, max(rows_below, from), before, free_);
+                        (void)row_first(before, free_, vs, at);
+                    }
+                    if (l == 0) S.s_sf[rflip][wave] = at;
+                    __syncthreads();
+#pragma unroll
+                    for (int w = 0; w < PW; ++w) at = min(at, S.s_sf[rflip][w]);
+                    rflip ^= 1;
+                    return min(uniform(at), max(rows_top, from));
+                };
+                auto steps_fit = [&](uint32_t from) -> uint32_t {
+                    uint32_t os = from;
+                    for (;;) {
+                        uint32_t c = steps_fit_pass<PW>(L, lstart, l_ns, l_top, va, vf, os, vs, valid0, valid_rest, (uint32_t *)hl);
+                        c = wave_reduce_max32(c);
+                        if (l == 0) S.s_sf[rflip][wave] = c;
+                        __syncthreads();
+#pragma unroll
+                        for (int w = 0; w < PW; ++w) c = max(c, S.s_sf[rflip][w]);
+                        c = uniform(c);
+                        rflip ^= 1;
+                        if (c == os) return os;
+                        os = c;
+                    }
+                };
                 auto fit_from = [&](uint32_t from) -> uint32_t {
+                    if (rows) {
+                        uint32_t o = rows_fit(from);
+                        for (;;) {
+                            const uint32_t os = steps_fit(o);
+                            if (os == o) return o;                   // rows and hole lists agree
+                            o = rows_fit(os);
+                            if (o == os) return o;
+                        }
+                    }
                     uint32_t o = from;
                     bool steps_hold = false;         // the hole lists have confirmed the current candidate
-                    uint32_t flip = 0;
                     for (;;) {
                         // the block lists: lowest offset >= o that is free of their time-overlapping entries
                         uint32_t o1 = o;
-                        if (nm) o1 = coop_sweep(m_oe[mb], m_life[mb], nm, cm, o, vs, va, vf, wave, s_cmax, s_hq, s_hans);
+                        if (nm) o1 = coop_sweep<PW>(m_oe[mb], m_life[mb], nm, cm, o, vs, va, vf, wave, s_cmax, s_hq, s_hans);
                         else __syncthreads();      // (keeps this pass's exchange slots apart from the last one's)
                         uint32_t o2 = o1;
                         if (nr)
-                            o2 = coop_sweep(r_oe[rb], r_life[rb], nr, cr, o1, vs, va, vf, wave, s_cmax, s_hq, s_hans);
+                            o2 = coop_sweep<PW>(r_oe[rb], r_life[rb], nr, cr, o1, vs, va, vf, wave, s_cmax, s_hq, s_hans);
                         // the few pending entries: every wave checks them by itself (same data, same answer)
                         if (np) o2 = fit_unsorted(p_oe, p_life, np, o2, vs, va, vf);
                         if (!mode1) {
@@ -1129,17 +1253,7 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
                         if (o2 == o && steps_hold) return o;     // nothing moved since the hole lists agreed
                         // one-step variables are not in ALL: the hole lists of the steps it lives through
                         // stand for them.  Passes repeat until no step moves the candidate.
-                        uint32_t os = o2;
-                        for (;;) {
-                            uint32_t c = steps_fit_pass(L, A.lstart, l_ns, l_top, va, vf, os, vs, valid0, valid_rest, (uint32_t *)hl);
-                            c = wave_reduce_max32(c);
-                            if (l == 0) s_sf[flip][wave] = c;
-                            __syncthreads();
-                            c = max(max(s_sf[flip][0], s_sf[flip][1]), max(s_sf[flip][2], s_sf[flip][3]));
-                            flip ^= 1;
-                            if (c == os) break;
-                            os = c;
-                        }
+                        const uint32_t os = steps_fit(o2);
                         // o2 == o1: recent and pending left main's answer alone, so all block lists accept o2;
                         // os == o2: so do the hole lists
                         if (os == o2 && o2 == o1) return os;
@@ -1161,21 +1275,29 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
                         __syncthreads();
                         // the sweeps stopped at the first entry above the hole: the next neighbour is
                         // the first time-overlapping entry from there on
-                        uint32_t e = coop_next_overlap(m_oe[mb], m_life[mb], nm, cm, va, vf, wave, s_hq);
-                        e = min(e, coop_next_overlap(r_oe[rb], r_life[rb], nr, cr, va, vf, wave, s_hq));
-                        uint32_t c = NONE32;
-                        if (wave == 0) {
-                            for (uint32_t idx = l; idx < np; idx += WAVE) {
-                                const LT lf = p_life[idx];
-                                const uint32_t po = (uint32_t)(p_oe[idx] >> 32);
-                                if (Life<LT>::a(lf) < vf && va < Life<LT>::f(lf) && po >= pp) c = min(c, po);
+                        uint32_t e = NONE32, c = NONE32;
+                        if (rows) {
+                            if (wave < used) {
+#pragma unroll
+                                for (int j = 0; j < EPL; ++j) c = ends[j] != 0 && row.off[j] >= pp ? min(c, row.off[j]) : c;
+                            }
+                        } else {
+                            e = coop_next_overlap<PW>(m_oe[mb], m_life[mb], nm, cm, va, vf, wave, s_hq);
+                            e = min(e, coop_next_overlap<PW>(r_oe[rb], r_life[rb], nr, cr, va, vf, wave, s_hq));
+                            if (wave == 0) {
+                                for (uint32_t idx = l; idx < np; idx += WAVE) {
+                                    const LT lf = p_life[idx];
+                                    const uint32_t po = (uint32_t)(p_oe[idx] >> 32);
+                                    if (Life<LT>::a(lf) < vf && va < Life<LT>::f(lf) && po >= pp) c = min(c, po);
+                                }
                             }
                         }
-                        if (mode1) c = min(c, steps_extent_pass(L, A.lstart, l_ns, va, vf, pp, (const uint32_t *)hl));
+                        if (mode1) c = min(c, steps_extent_pass<PW>(L, lstart, l_ns, va, vf, pp, (const uint32_t *)hl));
                         c = ~wave_reduce_max32(~c);
                         if (l == 0) s_sf[0][wave] = c;
                         __syncthreads();
-                        e = min(e, min(min(s_sf[0][0], s_sf[0][1]), min(s_sf[0][2], s_sf[0][3])));
+                        #pragma unroll
+                        for (int w = 0; w < PW; ++w) e = min(e, s_sf[0][w]);
                         __syncthreads();
                         if (e == NONE32) { o = best_gap == NONE32 ? pp : best_off; break; }
                         const uint32_t gap = e - pp;
@@ -1188,12 +1310,21 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
                 fp = max(fp, en);
                 if (threadIdx.x == 0) {
                     offs[r0 + p] = (uint64_t)o << sh;        // offsets are kept in rank order
-                    if (multi_left > 1) {               // someone will still query ALL
+                    if (multi_left > 1 && !rows) {               // someone will still query ALL
                         p_oe[np] = pk(o, en);
                         p_life[np] = Life<LT>::mk(va, vf);
                     }
                 }
-                if (multi_left > 1) ++np_multi;
+                if (rows) {
+                    if (wave < used) {
+                        uint4 c = make_uint4(0u, 0u, 0u, 0u);
+                        if (wave) c = S.s_row[rbuf][wave - 1];
+                        row_insert(row, o, o, en, life_word(va, vf), uniform(c.x), c.y, c.z);
+                    }
+                    ++n_rowed;
+                } else if (multi_left > 1) {
+                    ++np_multi;
+                }
                 if (mode1) {
                     // The block enters the list of every step it covers.  Where it lies in the list's
                     // top hole (nearly always) and no block is waiting there, it is taken out right
@@ -1202,7 +1333,7 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
                     const uint64_t x = pk(o, en);
                     for (uint32_t t = va + wave * WAVE + l; t < vf; t += PW * WAVE) {
                         const uint32_t ns = l_ns[t], nu = l_nu[t], tp = l_top[t];
-                        uint64_t *Lt = L + A.lstart[t];
+                        uint64_t *Lt = L + lstart[t];
                         if (nu == 0 && o >= tp) {
                             uint32_t k = ns - 1;
                             if (o > tp) {
@@ -1235,86 +1366,84 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
                 uint32_t res = 0;
                 // the list of the NEXT variable of this wave is fetched into registers while the
                 // current one is being placed
-                uint64_t pf[LH / WAVE];
+                uint64_t pf[PFC];
                 uint32_t pf_t = NONE32;
-                uint64_t fc = 0;                    // ... or, for the short path below, its first 64 holes only
+                uint64_t fc[FC];                    // ... or, for the short path below, its first FC * 64 holes only
+#pragma unroll
+                for (int c = 0; c < FC; ++c) fc[c] = 0;
                 uint32_t fc_t = NONE32;
                 uint32_t fail_t = NONE32;           // step whose last variable needed the full path
 #pragma unroll
-                for (int c = 0; c < (int)(LH / WAVE); ++c) pf[c] = 0;
+                for (int c = 0; c < PFC; ++c) pf[c] = 0;
                 while (mine) {
                     int j = __ffsll((unsigned long long)mine) - 1;
                     mine &= mine - 1;
                     const uint32_t t = read_lane(a, j);
                     uint32_t vs = read_lane(s, j), o = 0;
-                    // Nearly every one-step variable finds its hole among the first few of its
-                    // step's list (at the benchmark's configuration 97 % among the first 16) and
+                    // First-fit: nearly every one-step variable finds its hole among the first few of
+                    // its step's list (at the benchmark's configuration 97 % among the first 16) and
                     // takes its lower end: the first 64 holes, fetched ahead while the variable
-                    // before was placed, one ballot, one entry written back.  Everything else
-                    // (blocks waiting in the list's tail, no fit among the first 64, a hole used up,
-                    // the list already in LDS, best-fit) takes the full path below.
+                    // before was placed, one ballot, one entry written back.  Best-fit: the same with the
+                    // whole list in registers.  Everything else (blocks waiting in the list's tail, no
+                    // fit among the first 64 or a longer list, a hole used up, the list already in LDS)
+                    // takes the full path below.
                     bool placed = false;
                     const bool same_next = mine != 0 && read_lane(a, __ffsll((unsigned long long)mine) - 1) == t;
-                    if (!BEST && t != cur_t && read_lane(pnu, j) == 0) {
+                    if (t != cur_t && read_lane(pnu, j) == 0 && (!BEST || read_lane(pns, j) <= FC * WAVE)) {
                         const uint32_t base = read_lane(plb, j), ns = read_lane(pns, j);
-                        uint64_t y = fc;
-                        if (fc_t != t) {
-                            if (wmask & (1ull << ((t / PW) & 63))) { wave_fence(); wmask = 0; }
-                            y = (uint32_t)l < ns ? L[base + l] : 0ull;
+                        uint64_t y[FC];
+                        if (fc_t != t && (wmask & (1ull << ((t / PW) & 63)))) { wave_fence(); wmask = 0; }
+#pragma unroll
+                        for (int c = 0; c < FC; ++c) {
+                            y[c] = fc[c];
+                            if (fc_t != t && (c == 0 || c * WAVE < ns)) y[c] = c * WAVE + l < ns ? L[base + c * WAVE + l] : 0ull;
                         }
                         fc_t = NONE32;
-                        const uint64_t m = ballot((uint32_t)l < ns && (uint32_t)y >= vs);
-                        if (m) {
-                            const int h = __ffsll((unsigned long long)m) - 1;
-                            const uint64_t x = read_lane64(y, h);
-                            if ((uint32_t)x != vs) {              // the hole shrinks from below
-                                // the next variable's first holes are asked for only now that this
-                                // one's have arrived: the wait for these must not take in that read
-                                if (mine && !same_next) {
-                                    const int jn = __ffsll((unsigned long long)mine) - 1;
-                                    const uint32_t tn = read_lane(a, jn);
-                                    if (tn != t && tn != cur_t && read_lane(pnu, jn) == 0 && !(wmask & (1ull << ((tn / PW) & 63)))) {
-                                        fc = (uint32_t)l < read_lane(pns, jn) ? L[read_lane(plb, jn) + l] : 0ull;
-                                        fc_t = tn;
-                                    }
+                        uint32_t h;
+                        uint64_t x;
+                        if (reg_hole<BEST>(y, ns, vs, h, x) && (uint32_t)x != vs) {      // the hole shrinks from below
+                            // the next variable's holes are asked for only now that this one's have
+                            // arrived: the wait for these must not take in that read
+                            if (mine && !same_next) {
+                                const int jn = __ffsll((unsigned long long)mine) - 1;
+                                const uint32_t tn = read_lane(a, jn);
+                                if (tn != t && tn != cur_t && read_lane(pnu, jn) == 0 && (!BEST || read_lane(pns, jn) <= FC * WAVE) &&
+                                    !(wmask & (1ull << ((tn / PW) & 63)))) {
+                                    const uint32_t nb = read_lane(plb, jn), nn = read_lane(pns, jn);
+#pragma unroll
+                                    for (int c = 0; c < FC; ++c)
+                                        if (c == 0 || c * WAVE < nn) fc[c] = c * WAVE + l < nn ? L[nb + c * WAVE + l] : 0ull;
+                                    fc_t = tn;
                                 }
+                            }
+                            for (;;) {
                                 o = (uint32_t)(x >> 32);
                                 const uint64_t z = pk(o + vs, (uint32_t)x - vs);
                                 if (l == 0) {
                                     L[base + h] = z;
-                                    if ((uint32_t)h + 1 == ns) l_top[t] = o + vs;
+                                    if (h + 1 == ns) l_top[t] = o + vs;
                                 }
-                                if (l == h) y = z;
-                                // The wave's next variables of the same step (in orders that keep a
-                                // step's variables together, all of them) are placed from these
-                                // registers, nothing read: a ballot, one entry stored.
-                                while (mine) {
-                                    const int jn = __ffsll((unsigned long long)mine) - 1;
-                                    if (read_lane(a, jn) != t) break;
-                                    const uint32_t vn = read_lane(s, jn);
-                                    const uint64_t mn = ballot((uint32_t)l < ns && (uint32_t)y >= vn);
-                                    if (!mn) break;
-                                    const int hn = __ffsll((unsigned long long)mn) - 1;
-                                    const uint64_t xn = read_lane64(y, hn);
-                                    if ((uint32_t)xn == vn) break;
-                                    fp = max(fp, o + vs);       // the one before is done
-                                    if (l == j) res = o;
-                                    mine &= mine - 1;
-                                    j = jn;
-                                    vs = vn;
-                                    o = (uint32_t)(xn >> 32);
-                                    const uint64_t zn = pk(o + vn, (uint32_t)xn - vn);
-                                    if (l == 0) {
-                                        L[base + hn] = zn;
-                                        if ((uint32_t)hn + 1 == ns) l_top[t] = o + vn;
-                                    }
-                                    if (l == hn) y = zn;
-                                }
-                                wmask |= 1ull << ((t / PW) & 63);
-                                pf_t = NONE32;      // (a whole list fetched ahead by the full path is stale now, if it is this one)
-                                fail_t = NONE32;
-                                placed = true;
+#pragma unroll
+                                for (int c = 0; c < FC; ++c)
+                                    if ((uint32_t)(c * WAVE + l) == h) y[c] = z;
+                                // The wave's next variables of the same step (in orders that keep a step's
+                                // variables together, all of them) are placed from these registers, nothing
+                                // read: one entry stored.
+                                if (!mine) break;
+                                const int jn = __ffsll((unsigned long long)mine) - 1;
+                                if (read_lane(a, jn) != t) break;
+                                const uint32_t vn = read_lane(s, jn);
+                                if (!reg_hole<BEST>(y, ns, vn, h, x) || (uint32_t)x == vn) break;
+                                fp = max(fp, o + vs);           // the one before is done
+                                if (l == j) res = o;
+                                mine &= mine - 1;
+                                j = jn;
+                                vs = vn;
                             }
+                            wmask |= 1ull << ((t / PW) & 63);
+                            pf_t = NONE32;      // (a whole list fetched ahead by the full path is stale now, if it is this one)
+                            fail_t = NONE32;
+                            placed = true;
                         }
                     }
                     if (!placed) {
@@ -1374,7 +1503,7 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
                             const int jn = __ffsll((unsigned long long)mine) - 1;
                             const uint32_t tn = read_lane(a, jn);
                             const uint32_t totn = read_lane(pns, jn) + read_lane(pnu, jn);
-                            if (tn != t && totn + 1 <= LH && !(wmask & (1ull << ((tn / PW) & 63)))) {
+                            if (tn != t && totn <= PFC * WAVE && !(wmask & (1ull << ((tn / PW) & 63)))) {
                                 regs_from_global<0>(pf, L + read_lane(plb, jn), totn, l);
                                 pf_t = tn;
                             }
@@ -1404,7 +1533,7 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
                             }
                         } else {
                             // list too long for the LDS area: same steps directly in global memory
-                            uint64_t *Lt = L + A.lstart[t];
+                            uint64_t *Lt = L + lstart[t];
                             uint32_t nh = l_ns[t];
                             for (uint32_t nt = l_nu[t]; nt > 0; --nt) {
                                 const uint64_t xb = Lt[nh + nt - 1];
@@ -1437,7 +1566,7 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
                     }
                     // A run of one step's variables goes back to the registers after the odd one that
                     // needed the full path (unless the one before needed it too).
-                    if (!BEST && !placed && same_next && cur_t == t) {
+                    if (!placed && same_next && cur_t == t) {
                         if (fail_t != t) {
                             fail_t = t;
                             writeback(one_step ? a : NONE32);
@@ -1467,6 +1596,30 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
     }
 }
 
+// POLICY 0: the first-fit orderings, 1: the best-fit ones, 2: both in one launch
+template <class LT, int PW, bool META, int POLICY>
+__global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
+{
+    __shared__ FastShared<LT, PW> S;
+    extern __shared__ uint32_t meta[];      // [META_WORDS][T] if META
+    if (!A.hdr->fast) return;               // the 64-bit kernel handles this trace
+    const bool best = A.fits[blockIdx.x] != 0;
+    if (POLICY != 2 && best != (POLICY == 1)) return;
+    if (A.reg && reg_places(A.hdr, A.n, best)) return;
+    if (A.hdr->mode2 && !best) return;      // the segment kernel places the first-fit orderings of this trace
+    if (POLICY == 1 || (POLICY == 2 && best)) place_ordering<LT, PW, META, true>(A, S, meta);
+    else place_ordering<LT, PW, META, false>(A, S, meta);
+}
+
+template <class LT, int PW, bool META>
+void launch_policy(const FastArgs &A, uint32_t B, bool any_first, bool any_best, hipStream_t st)
+{
+    const size_t lds = META ? (size_t)A.T * META_WORDS * 4 : 0;
+    if (any_first && any_best) hipLaunchKernelGGL((k_place_fast<LT, PW, META, 2>), dim3(B), dim3(PW * WAVE), lds, st, A);
+    else if (any_best) hipLaunchKernelGGL((k_place_fast<LT, PW, META, 1>), dim3(B), dim3(PW * WAVE), lds, st, A);
+    else hipLaunchKernelGGL((k_place_fast<LT, PW, META, 0>), dim3(B), dim3(PW * WAVE), lds, st, A);
+}
+
 hipError_t launch_plan_prep(uint32_t n, uint32_t T, uint32_t B, const uint64_t *size, const uint32_t *alloc,
                             const uint32_t *free_, uint32_t *cntd, uint32_t *lstart, PlanHeader *hdr, void *vrec,
                             uint64_t seg_pool_entries, uint64_t seg_min_vars, hipStream_t st)
@@ -1494,14 +1647,17 @@ hipError_t launch_place_fast(uint32_t n, uint32_t T, uint32_t B, const uint64_t 
                l_nu, capL,
                offs, fps, ticks, reg_may_place(n, T)};
     if (A.reg && n <= PLAN_REG_ALWAYS_VARS) return hipSuccess;    // it takes every trace of this size
-    // each instantiation leaves the orderings of the other policy alone
-    if (T <= 0xFFFFu) {
-        if (any_first) hipLaunchKernelGGL((k_place_fast<uint32_t, false>), dim3(B), dim3(PW * WAVE), 0, st, A);
-        if (any_best) hipLaunchKernelGGL((k_place_fast<uint32_t, true>), dim3(B), dim3(PW * WAVE), 0, st, A);
-    } else {
-        if (any_first) hipLaunchKernelGGL((k_place_fast<uint64_t, false>), dim3(B), dim3(PW * WAVE), 0, st, A);
-        if (any_best) hipLaunchKernelGGL((k_place_fast<uint64_t, true>), dim3(B), dim3(PW * WAVE), 0, st, A);
-    }
+    // Waves per ordering: 16 per compute unit while the orderings fill them.  With two orderings or
+    // fewer per unit, 8 each (130 orderings of 24 571 variables: 8.4 ms, 11.0 ms with 4 waves; best-fit
+    // 13.1 and 16.0 ms); with four, 4 each (1024 orderings of 12 000: 6.4 ms, 8.6 ms with 8).
+    // The per-step words go to LDS while four workgroups of 4 waves still fit a unit (160 KB / 4 less
+    // 26.5 KB is room for 800 steps; 1024 orderings of 200 000 variables: 89 ms, 95 ms without).
+    const bool eight = B <= 512, meta = T <= 800;
+    if (T > 0xFFFFu) launch_policy<uint64_t, 4, false>(A, B, any_first, any_best, st);
+    else if (eight && meta) launch_policy<uint32_t, 8, true>(A, B, any_first, any_best, st);
+    else if (eight) launch_policy<uint32_t, 8, false>(A, B, any_first, any_best, st);
+    else if (meta) launch_policy<uint32_t, 4, true>(A, B, any_first, any_best, st);
+    else launch_policy<uint32_t, 4, false>(A, B, any_first, any_best, st);
     return hipGetLastError();
 }
 
