@@ -221,8 +221,8 @@ enum { LAP_PS_DOA = 0, LAP_PS_AOA = 1, LAP_PS_WDOA = 2, LAP_PS_SWDOA = 3, LAP_PS
  *   peak_after [K*L]     out: peak load reached for each limit
  *   load_min   [1]       out: Section VI-B1, the peak of the curve with every candidate away on
  *                             all its idle steps gap_lo+1 .. gap_hi-1 (transfers not hidden)
- * The walk is sequential: one workgroup per score kind, about n_cand * (n_cand + T) / 1024
- * steps of work each. */
+ * The orders by a fixed score take n_cand^2 comparisons each, spread over the chip; the SWDOA order is
+ * sequential, one workgroup per row. */
 int lap_select_swaps(const lap_trace *trace, double link_GBps, uint64_t min_bytes, const uint64_t *load,
                      const uint32_t *score_kinds, uint32_t K, const uint64_t *limits, uint32_t L,
                      uint32_t *order, uint32_t *rank, uint64_t *peaks, uint32_t *n_cand,

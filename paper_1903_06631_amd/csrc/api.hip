@@ -111,7 +111,8 @@ size_t ws_weights(uint32_t n, uint32_t T, uint32_t W)
 {
     const size_t N = n, w = W;
     return ws_select(n, T, 0) + up(SELECT_MAX_KINDS * 8) + up(SELECT_MAX_KINDS * 32) + ALIGN
-           + up(w * N * 8) + up(w * N * 4) + up(w * T * 8) + up(w * (N + 1) * 8) + up(w * N * 8)   // walk state, peaks, scores
+           + up(w * N * 8) + 2 * up(w * N * 4) + up(w * (N + 1) * 8) + up(w * N * 8)                // picks, peaks, scores
+           + up(N * 8) + up(N * 4) + 2 * up(((size_t)T + 1) * 8)                                    // the SWDOA walk
            + 2 * up((size_t)T * 8) + 3 * up(N * 4) + 2 * ALIGN                                      // steps, perms
            + up((w * N + 1) * 4) + 2 * up(w * N * 4) + up(w * 4) + up(w * N * 4) + up(w * N)        // replay state
            + 2 * up(w * 8);
@@ -123,7 +124,7 @@ size_t ws_select(uint32_t n, uint32_t T, uint32_t K)
     return ws_score(T) + up(N) + 4 * up(N * 8) + 2 * up(N * 4)      // scores and away windows of every variable
            + 3 * up(N * 4) + up(((size_t)T + 1) * 8) + ALIGN          // candidate slots, load_min differences, counter
            + up((size_t)SELECT_MAX_KINDS * 4) + up((size_t)SELECT_MAX_LIMITS * 8)
-           + (size_t)K * (up(N * 8) + up(N * 4) + up((size_t)T * 8)); // per kind: slot scores, slot variables, curve
+           + 2 * up(K * N * 8) + 3 * up(K * N * 4) + 2 * up(K * ((size_t)T + 1) * 8);   // per kind: picks, walk state
 }
 
 int check_trace_args(const lap_trace *tr)
@@ -556,15 +557,16 @@ int lap_select_swaps(const lap_trace *tr, double link_GBps, uint64_t min_bytes, 
     uint32_t *c_ilo = c.take<uint32_t>(n);
     uint32_t *c_ihi = c.take<uint32_t>(n);
     uint64_t *dmin = c.take<uint64_t>(t1);
-    uint32_t *nc = c.take<uint32_t>(1);
+    uint32_t *nc = c.take<uint32_t>(2);
     uint32_t *d_kinds = c.take<uint32_t>(SELECT_MAX_KINDS);
     uint64_t *d_limits = c.take<uint64_t>(SELECT_MAX_LIMITS);
-    uint64_t *r_score = c.take<uint64_t>(0);
-    c.used += (size_t)K * up((size_t)n * 8);
-    uint32_t *r_var = c.take<uint32_t>(0);
-    c.used += (size_t)K * up((size_t)n * 4);
-    uint64_t *l_cur = c.take<uint64_t>(0);
-    c.used += (size_t)K * up((size_t)T * 8);
+    uint64_t *s_size = c.take<uint64_t>((size_t)K * n);
+    uint32_t *s_lo = c.take<uint32_t>((size_t)K * n);
+    uint32_t *s_hi = c.take<uint32_t>((size_t)K * n);
+    uint64_t *g_score = c.take<uint64_t>((size_t)K * n);
+    uint32_t *g_var = c.take<uint32_t>((size_t)K * n);
+    uint64_t *g_diff = c.take<uint64_t>((size_t)K * t1);
+    uint64_t *g_sum = c.take<uint64_t>((size_t)K * t1);
 
     LAP_HIP(lap::launch_put_words(d_kinds, score_kinds, K, st));
     if (L) LAP_HIP(lap::launch_put_words(d_limits, limits, (size_t)L * 2, st));
@@ -586,8 +588,8 @@ int lap_select_swaps(const lap_trace *tr, double link_GBps, uint64_t min_bytes, 
     a.load = load; a.cand = cand; a.doa = doa; a.aoa = aoa; a.wdoa = wdoa; a.cut = cut;
     a.win_lo = win_lo; a.win_hi = win_hi; a.nc = nc; a.cidx = cidx; a.c_ilo = c_ilo; a.c_ihi = c_ihi; a.dmin = dmin;
     a.kinds = d_kinds; a.limits = d_limits;
-    // per-kind regions are laid out with the kind as the slowest index and a stride of n (or T) elements
-    a.r_score = r_score; a.r_var = r_var; a.l_cur = l_cur;
+    a.s_size = s_size; a.s_lo = s_lo; a.s_hi = s_hi;
+    a.g_score = g_score; a.g_var = g_var; a.g_diff = g_diff; a.g_sum = g_sum;
     a.order = order; a.rank = rank; a.peaks = peaks; a.n_cand = n_cand; a.n_selected = n_selected;
     a.peak_after = peak_after; a.load_min = load_min;
     a.custom = nullptr; a.pick_wdoa = nullptr;
@@ -640,14 +642,18 @@ int lap_evaluate_weights(const lap_trace *tr, double link_GBps, uint64_t min_byt
     uint32_t *c_ilo = c.take<uint32_t>(n);
     uint32_t *c_ihi = c.take<uint32_t>(n);
     uint64_t *dmin = c.take<uint64_t>(t1);
-    uint32_t *nc = c.take<uint32_t>(1);
+    uint32_t *nc = c.take<uint32_t>(2);
     uint32_t *d_kinds = c.take<uint32_t>(SELECT_MAX_KINDS);
     uint64_t *d_limits = c.take<uint64_t>(SELECT_MAX_KINDS);
     double *d_weights = c.take<double>((size_t)SELECT_MAX_KINDS * 4);
     uint64_t *load_min = c.take<uint64_t>(1);
-    uint64_t *r_score = c.take<uint64_t>((size_t)W * N);
-    uint32_t *r_var = c.take<uint32_t>((size_t)W * N);
-    uint64_t *l_cur = c.take<uint64_t>((size_t)W * T);
+    uint64_t *s_size = c.take<uint64_t>((size_t)W * N);
+    uint32_t *s_lo = c.take<uint32_t>((size_t)W * N);
+    uint32_t *s_hi = c.take<uint32_t>((size_t)W * N);
+    uint64_t *g_score = c.take<uint64_t>(N);       // one SWDOA row
+    uint32_t *g_var = c.take<uint32_t>(N);
+    uint64_t *g_diff = c.take<uint64_t>(t1);
+    uint64_t *g_sum = c.take<uint64_t>(t1);
     uint64_t *peaks = c.take<uint64_t>((size_t)W * (N + 1));
     double *bo = c.take<double>((size_t)W * N);
     uint64_t *need = c.take<uint64_t>(T);
@@ -686,7 +692,8 @@ int lap_evaluate_weights(const lap_trace *tr, double link_GBps, uint64_t min_byt
     a.load = load; a.cand = cand; a.doa = doa; a.aoa = aoa; a.wdoa = wdoa; a.cut = cut;
     a.win_lo = win_lo; a.win_hi = win_hi; a.nc = nc; a.cidx = cidx; a.c_ilo = c_ilo; a.c_ihi = c_ihi; a.dmin = dmin;
     a.kinds = d_kinds; a.limits = d_limits;
-    a.r_score = r_score; a.r_var = r_var; a.l_cur = l_cur;
+    a.s_size = s_size; a.s_lo = s_lo; a.s_hi = s_hi;
+    a.g_score = g_score; a.g_var = g_var; a.g_diff = g_diff; a.g_sum = g_sum;
     a.order = order; a.rank = nullptr; a.peaks = peaks; a.n_cand = n_cand; a.n_selected = n_selected;
     a.peak_after = peak_after; a.load_min = load_min;
     a.custom = nullptr; a.pick_wdoa = swdoa;

@@ -123,15 +123,17 @@ struct SelectArgs {
     const double *aoa;
     const uint64_t *wdoa, *cut;
     const uint32_t *win_lo, *win_hi;
-    uint32_t *nc;              // [1] number of candidates (device counter)
+    uint32_t *nc;              // [2] number of candidates (device counter), 1 if the load does not contain them
     uint32_t *cidx;            // [n] candidate slot -> variable
     uint32_t *c_ilo, *c_ihi;   // [n] idle steps [ilo, ihi) of the candidate in a slot
     uint64_t *dmin;            // [T+1] difference array of the load removed for load_min
     const uint32_t *kinds;     // [K]
     const uint64_t *limits;    // [L]
-    uint64_t *r_score;         // [K][n] current score of every slot
-    uint32_t *r_var;           // [K][n] variable of the slot, 0xFFFFFFFF once taken
-    uint64_t *l_cur;           // [K][T] current load curve
+    uint64_t *s_size;          // [K][n] size of the j-th pick
+    uint32_t *s_lo, *s_hi;     // [K][n] steps [lo, hi) that the j-th pick leaves
+    uint64_t *g_score;         // rows of kind 3, [K][n]: score of every slot when it was last computed
+    uint32_t *g_var;           // [K][n]: variable of the slot, 0xFFFFFFFF once taken
+    uint64_t *g_diff, *g_sum;  // [K][T+1]: differences and prefix sums of the current load curve
     uint32_t *order, *rank;    // [K][n] outputs (rank may be null)
     uint64_t *peaks;           // [K][n+1]
     uint32_t *n_cand;          // [1]

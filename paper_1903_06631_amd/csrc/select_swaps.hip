@@ -1,19 +1,28 @@
 // Selection of swap variables down to a load limit (Section IV-D), for K priority scores at
 // once, including the submodular WDOA order of Section IV-B (iv), and load_min (Section VI-B1).
 //
-// The walk is sequential by nature: every addition changes the curve the next decision sees.
-// One workgroup of 1024 threads runs one score kind.  Thread i owns the steps t = i (mod 1024)
-// of the current load curve and the candidate slots c = i (mod 1024); one iteration applies the
-// previous winner to the owned steps, re-scores the owned slots (SWDOA only, in closed form: a
-// slot's area drops by size * |idle steps of the slot that the winner leaves|), and finds the
-// new peak and the best remaining slot with a single fused reduction and one barrier.
+// Order and curve are computed apart.  A score that the curve does not change gives its order by counting: every
+// candidate's rank is the number of better candidates (k_sel_order, one thread per candidate).  The SWDOA order is
+// greedy and stays with one workgroup per row, but a pick only looks at a few hundred leading candidates
+// (sel_greedy).  The peaks are then taken for stretches of the order side by side: a workgroup builds the curve
+// before its stretch from the picks ahead of it and walks the stretch (k_sel_peaks).
+// A walk of one workgroup per score over all slots and steps took 9 us a pick: 113.6 ms for the five scores
+// of a 14 000-step chain, where these take 11.4 ms; bound now by the dependent reductions of the greedy picks.
 #include "lap_dev.h"
 #include "lap_kernels.h"
 
 namespace lap {
 
-constexpr int SEL_THREADS = 1024;
+constexpr int SEL_THREADS = 1024;              // of load_min
 constexpr int SEL_WAVES = SEL_THREADS / WAVE;
+constexpr int ORD_THREADS = 512, ORD_WAVES = ORD_THREADS / WAVE;
+constexpr int ORD_PER = 2;                     // leading candidates a thread holds
+constexpr int ORD_BATCH = 8;                   // independent loads of a thread in the passes over slots and steps
+constexpr uint32_t ORD_ACTIVE = ORD_THREADS * ORD_PER;
+constexpr int PK_THREADS = 256, PK_WAVES = PK_THREADS / WAVE;
+constexpr int PK_PER = 8;                      // steps a thread holds
+constexpr uint32_t PK_SLICE = PK_THREADS * PK_PER;
+constexpr uint32_t PK_MIN_STRETCH = 16;
 constexpr uint32_t NONE = 0xFFFFFFFFu;
 
 // slot list of the candidates (any order: ties are decided on the variable index) and the
@@ -21,7 +30,10 @@ constexpr uint32_t NONE = 0xFFFFFFFFu;
 __global__ __launch_bounds__(256) void k_sel_gather(SelectArgs a)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.n || !a.cand[i]) return;
+    if (i >= a.n) return;
+    if (a.rank)
+        for (uint32_t ks = 0; ks < a.K; ++ks) a.rank[(size_t)ks * a.n + i] = NONE;
+    if (!a.cand[i]) return;
     const uint32_t tl = a.gap_lo ? a.gap_lo[i] : a.alloc[i];
     const uint32_t th = a.gap_hi ? a.gap_hi[i] : a.free_[i] - 1;
     const uint32_t slot = atomicAdd(a.nc, 1u);
@@ -55,6 +67,12 @@ __device__ __forceinline__ uint64_t custom_key(double x)
     return (b >> 63) ? ~b : (b | (1ull << 63));
 }
 
+__device__ __forceinline__ uint64_t row_key(const SelectArgs &a, uint32_t ks, uint32_t kind, uint32_t v)
+{
+    return kind == 5 ? custom_key(a.custom[(size_t)ks * a.n + v]) : score_key(a, kind, v);
+}
+
+// var = NONE: no candidate; it is worse than every candidate
 struct Best {
     uint64_t score;
     uint32_t var, slot;
@@ -64,91 +82,447 @@ __device__ __forceinline__ bool better(const Best &x, const Best &y)
     return x.score > y.score || (x.score == y.score && x.var < y.var);
 }
 
-__global__ __launch_bounds__(SEL_THREADS) void k_sel_walk(SelectArgs a)
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) { return read_lane(wave_scan_max_u32(v), WAVE - 1); }
+
+__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v)
 {
-    __shared__ uint64_t p_peak[2][SEL_WAVES], p_score[2][SEL_WAVES];
-    __shared__ uint32_t p_var[2][SEL_WAVES], p_slot[2][SEL_WAVES];
-    const uint32_t ks = blockIdx.x, kind = a.kinds[ks];
-    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
-    const uint32_t n = a.n, T = a.T, nc = *a.nc;
-    uint64_t *rs = a.r_score + (size_t)ks * n;
-    uint32_t *rv = a.r_var + (size_t)ks * n;
-    uint64_t *lc = a.l_cur + (size_t)ks * T;
-    uint32_t *order = a.order + (size_t)ks * n;
-    uint32_t *rank = a.rank ? a.rank + (size_t)ks * n : nullptr;
-    uint64_t *peaks = a.peaks + (size_t)ks * ((size_t)n + 1);
+    const uint32_t hi = wave_max_u32((uint32_t)(v >> 32));
+    const uint32_t lo = wave_max_u32((uint32_t)(v >> 32) == hi ? (uint32_t)v : 0u);
+    return ((uint64_t)hi << 32) | lo;
+}
 
-    for (uint32_t c = tid; c < nc; c += SEL_THREADS) {
-        const uint32_t v = a.cidx[c];
-        rv[c] = v;
-        rs[c] = kind == 5 ? custom_key(a.custom[(size_t)ks * n + v]) : score_key(a, kind, v);
+// the best of the first LANES lanes (8 or 64; the others hold none), in every lane.  Most often the upper halves of
+// the scores decide alone
+template <int LANES>
+__device__ __forceinline__ Best wave_best(const Best &b)
+{
+    auto top = [](uint32_t v) {
+        if (LANES == WAVE) return wave_max_u32(v);
+        v = max(v, dpp_mov<0x111>(0u, v));
+        v = max(v, dpp_mov<0x112>(0u, v));
+        v = max(v, dpp_mov<0x114>(0u, v));
+        return read_lane(v, LANES - 1);
+    };
+    const uint32_t hi = (uint32_t)(b.score >> 32), lo = (uint32_t)b.score;
+    const uint32_t m_hi = top(hi);
+    bool in = hi == m_hi;
+    uint64_t at = ballot(in);
+    if (at & (at - 1)) {
+        const uint32_t m_lo = top(in ? lo : 0u);
+        in = in && lo == m_lo;
+        at = ballot(in);
+        if (at & (at - 1)) {
+            const uint32_t nv = top(in ? ~b.var : 0u);
+            at = ballot(in && ~b.var == nv);
+        }
     }
-    for (uint32_t t = tid; t < T; t += SEL_THREADS) lc[t] = a.load[t];
-    if (rank)
-        for (uint32_t i = tid; i < n; i += SEL_THREADS) rank[i] = NONE;
-    if (ks == 0 && tid == 0) *a.n_cand = nc;
+    const int src = __ffsll((unsigned long long)at) - 1;
+    return Best{read_lane64(b.score, src), read_lane(b.var, src), read_lane(b.slot, src)};
+}
 
-    bool has_w = false;
-    uint32_t w_slot = 0, w_lo = 0, w_hi = 0;
-    uint64_t w_size = 0;
-    for (uint32_t k = 0;; ++k) {
-        // the previous winner leaves the owned steps; running maximum of the owned steps
-        uint64_t mx = 0;
-        for (uint32_t t = tid; t < T; t += SEL_THREADS) {
-            uint64_t x = lc[t];
-            if (has_w && t >= w_lo && t < w_hi) { x -= w_size; lc[t] = x; }
-            mx = umax64(mx, x);
+struct GreedyLds {
+    Best part[2][ORD_WAVES];
+    uint64_t size[ORD_ACTIVE], score[ORD_ACTIVE];
+    uint32_t var[ORD_ACTIVE], slot[ORD_ACTIVE], ilo[ORD_ACTIVE], ihi[ORD_ACTIVE], wlo[ORD_ACTIVE], whi[ORD_ACTIVE];
+    uint64_t wa[ORD_WAVES], wb[ORD_WAVES];
+    uint32_t hist[256];
+    uint32_t count, fit, held;
+};
+
+// the best of the workgroup, in every thread; one barrier.  `turn` alternates between two buffers
+__device__ __forceinline__ Best block_best(const Best &mine, GreedyLds &s, int turn)
+{
+    const uint32_t lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
+    static_assert(ORD_WAVES <= 8, "one row of lanes");
+    const Best w = wave_best<WAVE>(mine);
+    if (lane == 0) s.part[turn][wave] = w;
+    __syncthreads();
+    Best o{0, NONE, NONE};
+    if (lane < ORD_WAVES) o = s.part[turn][lane];
+    return wave_best<8>(o);
+}
+
+// The SWDOA order of one row.  A score only falls while variables leave the curve (all of them are live on the steps
+// they leave, so no step goes below zero), so a score taken earlier bounds the present one.  The workgroup holds the
+// leading candidates, at most ORD_ACTIVE, in registers and corrects them after every pick (an area drops by
+// size * |idle steps the winner leaves|); as long as their best beats the best of the others, as that was when it
+// was last computed, it is the next pick.  When it does not, the curve's prefix sums give every score anew, and the
+// leading ones are chosen again through a histogram.  On a curve that does not contain the candidates (nc[1]; a
+// load given by the caller may be any) nothing is held and every pick computes all scores.
+__device__ void sel_greedy(const SelectArgs &a, uint32_t ks, GreedyLds &s)
+{
+    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
+    const uint32_t n = a.n, T = a.T, nc = a.nc[0];
+    const uint32_t cap = a.nc[1] ? 0u : ORD_ACTIVE;
+    uint64_t *score = a.g_score + (size_t)ks * n;
+    uint32_t *var = a.g_var + (size_t)ks * n;
+    unsigned long long *dcur = (unsigned long long *)a.g_diff + (size_t)ks * ((size_t)T + 1);  // curve[t] - curve[t-1]
+    uint64_t *S = a.g_sum + (size_t)ks * ((size_t)T + 1);                  // S[t] = curve[0] + .. + curve[t-1]
+    for (uint32_t c = tid; c < nc; c += ORD_THREADS) var[c] = a.cidx[c];
+    for (uint32_t t = tid; t < T; t += ORD_THREADS)
+        __hip_atomic_store(&dcur[t], (unsigned long long)(a.load[t] - (t ? a.load[t - 1] : 0)), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) S[0] = 0;
+    __syncthreads();
+
+    uint32_t k = 0;
+    int turn = 0;
+    auto pick = [&](uint32_t v, uint32_t slot, uint64_t sc, uint64_t sz, uint32_t lo, uint32_t hi) {
+        a.order[(size_t)ks * n + k] = v;
+        if (a.rank) a.rank[(size_t)ks * n + v] = k;
+        if (a.pick_wdoa) a.pick_wdoa[v] = sc;
+        a.s_size[(size_t)ks * n + k] = sz;
+        a.s_lo[(size_t)ks * n + k] = lo;
+        a.s_hi[(size_t)ks * n + k] = hi;
+        var[slot] = NONE;
+        if (hi > lo) {                           // hi < T: the last step of an idle interval is an access
+            __hip_atomic_fetch_add(&dcur[lo], 0ull - sz, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_add(&dcur[hi], (unsigned long long)sz, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        // best remaining owned slot (SWDOA: after re-scoring on the reduced curve)
+    };
+    while (k < nc) {
+        // prefix sums of the present curve; the fence drops what this compute unit cached of it before the atomics
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        uint64_t ca = 0, cb = 0;
+        for (uint32_t base = 0; base < T; base += ORD_THREADS * ORD_BATCH) {
+            const uint32_t t0 = base + tid * ORD_BATCH;
+            uint64_t d[ORD_BATCH], c1 = 0, c2 = 0;
+#pragma unroll
+            for (int e = 0; e < ORD_BATCH; ++e) d[e] = t0 + e < T ? dcur[t0 + e] : 0;
+#pragma unroll
+            for (int e = 0; e < ORD_BATCH; ++e) { c1 += d[e]; c2 += c1; }
+            // over lanes: (sum of d, sum of its prefixes) of 8, 16, .. steps
+            uint64_t i1 = c1, i2 = c2;
+#pragma unroll
+            for (int w = 1; w < WAVE; w <<= 1) {
+                const uint64_t o1 = shfl_up64(i1, w), o2 = shfl_up64(i2, w);
+                if ((int)lane >= w) {
+                    // the lower lane's steps, then the higher one's: `mine` steps of the higher part
+                    const uint64_t mine = (uint64_t)ORD_BATCH * (uint64_t)w;
+                    i2 += o2 + mine * o1;
+                    i1 += o1;
+                }
+            }
+            if (lane == WAVE - 1) { s.wa[wave] = i1; s.wb[wave] = i2; }
+            __syncthreads();
+            uint64_t pa = ca, pb = cb, qa = 0, qb = 0;
+            for (uint32_t q = 0; q < ORD_WAVES; ++q) {
+                if (q == wave) { qa = pa; qb = pb; }
+                pb += s.wb[q] + (uint64_t)(WAVE * ORD_BATCH) * pa;
+                pa += s.wa[q];
+            }
+            ca = pa;
+            cb = pb;
+            // before this thread's steps: the waves before, then the lanes before
+            const uint64_t l1 = lane_shift_up64(i1, 0), l2 = lane_shift_up64(i2, 0);
+            uint64_t cur = qa + l1, sum = qb + l2 + (uint64_t)(lane * ORD_BATCH) * qa;
+#pragma unroll
+            for (int e = 0; e < ORD_BATCH; ++e) {
+                cur += d[e];
+                sum += cur;
+                if (t0 + e < T) S[t0 + e + 1] = sum;
+            }
+            __syncthreads();
+        }
+        // every score, and the best
         Best b{0, NONE, NONE};
-        for (uint32_t c = tid; c < nc; c += SEL_THREADS) {
-            const uint32_t v = rv[c];
-            if (v == NONE) continue;
-            if (has_w && c == w_slot) { rv[c] = NONE; continue; }
-            uint64_t s = rs[c];
-            if (kind == 3 && has_w) {
-                const uint32_t lo = max(a.c_ilo[c], w_lo), hi = min(a.c_ihi[c], w_hi);
-                if (hi > lo) { s -= w_size * (uint64_t)(hi - lo); rs[c] = s; }
-            }
-            const Best x{s, v, c};
-            if (better(x, b)) b = x;
-        }
+        for (uint32_t base = tid; base < nc; base += ORD_THREADS * ORD_BATCH) {
+            uint32_t v[ORD_BATCH], lo[ORD_BATCH], hi[ORD_BATCH];
+            uint64_t x[ORD_BATCH];
 #pragma unroll
-        for (int d = 1; d < WAVE; d <<= 1) {
-            mx = umax64(mx, shfl_xor64(mx, d));
-            const Best o{shfl_xor64(b.score, d), (uint32_t)__shfl_xor((int)b.var, d, WAVE),
-                         (uint32_t)__shfl_xor((int)b.slot, d, WAVE)};
-            if (better(o, b)) b = o;
+            for (int e = 0; e < ORD_BATCH; ++e) {
+                const uint32_t c = min(base + e * ORD_THREADS, nc - 1);
+                v[e] = base + e * ORD_THREADS < nc ? var[c] : NONE;
+                lo[e] = a.c_ilo[c];
+                hi[e] = a.c_ihi[c];
+            }
+#pragma unroll
+            for (int e = 0; e < ORD_BATCH; ++e) x[e] = S[hi[e]] - S[lo[e]];
+#pragma unroll
+            for (int e = 0; e < ORD_BATCH; ++e) {
+                if (v[e] == NONE) continue;
+                const Best o{x[e], v[e], base + e * ORD_THREADS};
+                score[o.slot] = x[e];
+                if (better(o, b)) b = o;
+            }
         }
-        const int buf = k & 1;
-        if (lane == 0) { p_peak[buf][wave] = mx; p_score[buf][wave] = b.score; p_var[buf][wave] = b.var; p_slot[buf][wave] = b.slot; }
+        b = block_best(b, s, turn);
+        turn ^= 1;
+        const uint64_t M = b.score;
+        // the leading ones: 256 bins below the best score, those that hold at most `cap` candidates in all.  Where a
+        // bin is too wide, the bins up to it are cut finer; where the best score alone has too many candidates, the
+        // bins divide those by their variable
+        const bool whole = nc - k <= cap;
+        bool tied = false;
+        uint32_t sh = 0, fit = 0, held = whole ? nc - k : 0;
+        auto bin_of = [&](uint64_t x, uint32_t v) -> uint64_t {
+            if (tied) return x == M ? (uint64_t)((v - b.var) >> sh) : 256ull;
+            return (M >> sh) - (x >> sh);
+        };
+        auto load_slots = [&](uint32_t base, uint32_t (&v)[ORD_BATCH], uint64_t (&x)[ORD_BATCH]) {
+#pragma unroll
+            for (int e = 0; e < ORD_BATCH; ++e) {
+                const uint32_t c = min(base + e * ORD_THREADS, nc - 1);
+                v[e] = base + e * ORD_THREADS < nc ? var[c] : NONE;
+                x[e] = score[c];
+            }
+        };
+        if (!whole && cap) {
+            sh = M >> 8 ? 64 - 8 - __clzll(M) : 0;
+            for (;;) {
+                __syncthreads();
+                if (tid < 256) s.hist[tid] = 0;
+                __syncthreads();
+                for (uint32_t base = tid; base < nc; base += ORD_THREADS * ORD_BATCH) {
+                    uint32_t v[ORD_BATCH];
+                    uint64_t x[ORD_BATCH];
+                    load_slots(base, v, x);
+#pragma unroll
+                    for (int e = 0; e < ORD_BATCH; ++e) {
+                        if (v[e] == NONE) continue;
+                        const uint64_t bin = bin_of(x[e], v[e]);
+                        if (bin < 256) atomicAdd(&s.hist[(uint32_t)bin], 1u);
+                    }
+                }
+                __syncthreads();
+                if (wave == 0) {                 // number of bins that fit, and what they hold
+                    uint32_t h[4], t4 = 0;
+                    for (int e = 0; e < 4; ++e) { h[e] = s.hist[4 * lane + e]; t4 += h[e]; }
+                    uint32_t cum = (uint32_t)wave_scan_add(t4) - t4, bins = 0, holds = 0;
+                    for (int e = 0; e < 4; ++e) {
+                        cum += h[e];
+                        if (cum <= cap) { bins = 4 * lane + e + 1; holds = cum; }
+                    }
+                    bins = wave_max_u32(bins);
+                    holds = wave_max_u32(holds);
+                    if (lane == 0) { s.fit = bins; s.held = holds; }
+                }
+                __syncthreads();
+                fit = s.fit;                     // 0: the first bin alone is too many
+                held = s.held;
+                if (held >= cap / 2 || fit >= 127) break;
+                if (sh == 0 && (fit || tied)) break;   // a variable's bin of width 1 holds one candidate
+                if (sh == 0) {
+                    tied = true;
+                    sh = n >> 8 ? 32 - 8 - __clz(n) : 0;
+                    continue;
+                }
+                sh -= min(sh, (uint32_t)(__clz(fit + 1) - __clz(256)));
+            }
+        }
+        if (held == 0) {                         // nothing can be held: this pick alone
+            if (tid == 0) pick(b.var, b.slot, M, a.size[b.var], a.win_lo[b.var], a.win_hi[b.var]);
+            ++k;
+            __builtin_amdgcn_s_waitcnt(0);       // the curve's atomics, before the barrier that lets them be read
+            __syncthreads();
+            continue;
+        }
         __syncthreads();
-        mx = 0;
-        b = Best{0, NONE, NONE};
+        if (tid == 0) s.count = 0;
+        __syncthreads();
+        Best bound{0, NONE, NONE};
+        for (uint32_t base = tid; base < nc; base += ORD_THREADS * ORD_BATCH) {
+            uint32_t v[ORD_BATCH];
+            uint64_t x[ORD_BATCH];
+            load_slots(base, v, x);
 #pragma unroll
-        for (int q = 0; q < SEL_WAVES; ++q) {
-            mx = umax64(mx, p_peak[buf][q]);
-            const Best o{p_score[buf][q], p_var[buf][q], p_slot[buf][q]};
-            if (better(o, b)) b = o;
-        }
-        if (tid == 0) {
-            peaks[k] = mx;
-            if (b.var != NONE) {
-                order[k] = b.var;
-                if (rank) rank[b.var] = k;
-                if (kind == 3 && a.pick_wdoa) a.pick_wdoa[b.var] = b.score;
+            for (int e = 0; e < ORD_BATCH; ++e) {
+                if (v[e] == NONE) continue;
+                const Best o{x[e], v[e], base + e * ORD_THREADS};
+                if (whole || bin_of(x[e], v[e]) < fit) {
+                    const uint32_t at = atomicAdd(&s.count, 1u);
+                    s.score[at] = x[e]; s.var[at] = v[e]; s.slot[at] = o.slot;
+                } else if (better(o, bound)) bound = o;
             }
         }
-        if (b.var == NONE) break;        // k == nc: nothing left
-        has_w = true;
-        w_slot = b.slot;
-        w_size = a.size[b.var];
-        w_lo = a.win_lo[b.var];
-        w_hi = a.win_hi[b.var];
+        bound = block_best(bound, s, turn);      // its barrier also publishes the held ones
+        turn ^= 1;
+        for (uint32_t e = tid; e < held; e += ORD_THREADS) {
+            const uint32_t v = s.var[e], c = s.slot[e];
+            s.size[e] = a.size[v];
+            s.wlo[e] = a.win_lo[v]; s.whi[e] = a.win_hi[v];
+            s.ilo[e] = a.c_ilo[c]; s.ihi[e] = a.c_ihi[c];
+        }
+        __syncthreads();
+        uint64_t r_s[ORD_PER];
+        uint32_t r_v[ORD_PER], r_lo[ORD_PER], r_hi[ORD_PER];
+#pragma unroll
+        for (int r = 0; r < ORD_PER; ++r) {
+            const uint32_t e = r * ORD_THREADS + tid;
+            r_v[r] = NONE; r_s[r] = 0; r_lo[r] = r_hi[r] = 0;
+            if (e < held) { r_s[r] = s.score[e]; r_v[r] = s.var[e]; r_lo[r] = s.ilo[e]; r_hi[r] = s.ihi[e]; }
+        }
+        uint32_t w_lo = 0, w_hi = 0, w_e = NONE;
+        uint64_t w_size = 0;
+        for (;;) {
+            Best m{0, NONE, NONE};
+#pragma unroll
+            for (int r = 0; r < ORD_PER; ++r) {
+                const uint32_t e = r * ORD_THREADS + tid;
+                if (r * ORD_THREADS + wave * WAVE >= held) break;
+                const uint32_t lo = max(r_lo[r], w_lo), hi = min(r_hi[r], w_hi);
+                r_s[r] -= w_size * (uint64_t)(hi > lo ? hi - lo : 0u);
+                if (e == w_e) { r_v[r] = NONE; r_s[r] = 0; r_hi[r] = 0; }
+                const Best o{r_s[r], r_v[r], e};
+                if (better(o, m)) m = o;
+            }
+            const Best g = block_best(m, s, turn);
+            turn ^= 1;
+            if (g.var == NONE || !better(g, bound)) break;
+            w_e = g.slot;
+            w_lo = s.wlo[w_e];
+            w_hi = s.whi[w_e];
+            w_size = s.size[w_e];
+            if (tid == 0) pick(g.var, s.slot[w_e], g.score, w_size, w_lo, w_hi);
+            ++k;
+        }
+        __builtin_amdgcn_s_waitcnt(0);           // the curve's atomics, before the barrier that lets them be read
+        __syncthreads();
+    }
+}
+
+// The order of every row.  Grid: x over candidate slots (strided), y over rows.  Counting compares every pair, in
+// tiles of the workgroup's width: bound by the comparisons, 11 000 candidates need 1.2e8 a row.
+__global__ __launch_bounds__(ORD_THREADS) void k_sel_order(SelectArgs a)
+{
+    __shared__ GreedyLds g;
+    const uint32_t ks = blockIdx.y, kind = a.kinds[ks], n = a.n, nc = a.nc[0], tid = threadIdx.x;
+    uint64_t *peaks = a.peaks + (size_t)ks * ((size_t)n + 1);
+    for (uint32_t i = blockIdx.x * ORD_THREADS + tid; i <= nc; i += gridDim.x * ORD_THREADS) peaks[i] = 0;
+    if (kind == 3) {
+        if (blockIdx.x == 0) sel_greedy(a, ks, g);
+        return;
+    }
+    uint64_t *t_score = g.size;
+    uint32_t *t_var = g.var;
+    for (uint32_t base = blockIdx.x * ORD_THREADS; base < nc; base += gridDim.x * ORD_THREADS) {
+        const uint32_t c = base + tid;
+        const uint32_t v = c < nc ? a.cidx[c] : NONE;
+        const uint64_t x = c < nc ? row_key(a, ks, kind, v) : 0;
+        uint32_t before = 0;
+        for (uint32_t d0 = 0; d0 < nc; d0 += ORD_THREADS) {
+            __syncthreads();
+            const uint32_t d = d0 + tid;
+            if (d < nc) {
+                const uint32_t u = a.cidx[d];
+                t_var[tid] = u;
+                t_score[tid] = row_key(a, ks, kind, u);
+            }
+            __syncthreads();
+            const uint32_t cnt = min((uint32_t)ORD_THREADS, nc - d0);
+#pragma unroll 8
+            for (uint32_t q = 0; q < cnt; ++q) {
+                const uint64_t y = t_score[q];
+                before += (y > x || (y == x && t_var[q] < v)) ? 1u : 0u;
+            }
+        }
+        if (c < nc) {
+            const size_t o = (size_t)ks * n + before;
+            a.order[o] = v;
+            if (a.rank) a.rank[(size_t)ks * n + v] = before;
+            a.s_size[o] = a.size[v];
+            a.s_lo[o] = a.win_lo[v];
+            a.s_hi[o] = a.win_hi[v];
+        }
+    }
+}
+
+// peaks[k] for one stretch of the order and one slice of the steps.  Grid: stretches, slices, rows.  A wave holds 512
+// steps: a winner that leaves all of them lowers their maximum by its size, one that leaves none changes nothing, and
+// only at the edges of its window are the steps updated and reduced.
+__global__ __launch_bounds__(PK_THREADS) void k_sel_peaks(SelectArgs a)
+{
+    __shared__ unsigned long long diff[PK_SLICE + 1];
+    __shared__ uint64_t part[PK_WAVES][WAVE];
+    __shared__ uint64_t wsum[PK_WAVES];
+    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
+    const uint32_t ks = blockIdx.z, n = a.n, T = a.T, nc = a.nc[0];
+    const bool plain = a.nc[1] == 0;             // no step goes below zero
+    const uint32_t len = max(PK_MIN_STRETCH, nc / gridDim.x + 1);
+    const uint64_t k64 = (uint64_t)blockIdx.x * len;
+    if (k64 > nc) return;
+    const uint32_t k0 = (uint32_t)k64, k1 = (uint32_t)umin64((uint64_t)nc + 1, k64 + len);
+    const uint64_t *sz = a.s_size + (size_t)ks * n;
+    const uint32_t *slo = a.s_lo + (size_t)ks * n, *shi = a.s_hi + (size_t)ks * n;
+    uint64_t *peaks = a.peaks + (size_t)ks * ((size_t)n + 1);
+    const uint32_t base = blockIdx.y * PK_SLICE;
+    for (uint32_t i = tid; i <= PK_SLICE; i += PK_THREADS) diff[i] = 0;
+    __syncthreads();
+    for (uint32_t j = tid; j < k0; j += PK_THREADS) {
+        const uint32_t lo = max(slo[j], base) - base, end = shi[j];
+        const uint32_t hi = end > base ? min(end - base, PK_SLICE) : 0u;
+        if (hi > lo) {
+            atomicAdd(&diff[lo], (unsigned long long)sz[j]);
+            atomicAdd(&diff[hi], 0ull - sz[j]);
+        }
     }
     __syncthreads();
-    // every limit: the shortest prefix of the order whose peak is within the limit
-    for (uint32_t q = tid; q < a.L; q += SEL_THREADS) {
+    uint64_t x[PK_PER], sum = 0;
+#pragma unroll
+    for (int e = 0; e < PK_PER; ++e) { sum += diff[tid * PK_PER + e]; x[e] = sum; }
+    const uint64_t incl = wave_scan_add(sum);
+    if (lane == WAVE - 1) wsum[wave] = incl;
+    __syncthreads();
+    uint64_t pre = incl - sum;
+    for (uint32_t q = 0; q < wave; ++q) pre += wsum[q];
+    const uint32_t t0 = base + tid * PK_PER;
+    uint64_t mx = 0;
+#pragma unroll
+    for (int e = 0; e < PK_PER; ++e) {
+        x[e] = t0 + e < T ? a.load[t0 + e] - (pre + x[e]) : 0;
+        mx = umax64(mx, x[e]);
+    }
+    mx = wave_max_u64(mx);
+    // steps past the end are zero and stay out of every window (a window ends before T)
+    const uint32_t w0 = base + wave * WAVE * PK_PER, w1 = min(T, w0 + WAVE * PK_PER);
+    uint64_t off = 0;                            // what the whole span has been lowered by and x does not show yet
+    for (uint32_t kb = k0; kb < k1; kb += WAVE) {
+        // lane j: the pick that leads from peak kb+j to the next one
+        const uint32_t kj = kb + lane;
+        uint64_t m_sz = 0;
+        uint32_t m_lo = 0, m_hi = 0;
+        if (kj < nc) { m_sz = sz[kj]; m_lo = slo[kj]; m_hi = shi[kj]; }
+        uint64_t res = 0;
+        const uint32_t cnt = min((uint32_t)WAVE, k1 - kb);
+        for (uint32_t j = 0; j < cnt; ++j) {
+            if (lane == j) res = mx;
+            const uint64_t s = read_lane64(m_sz, (int)j);
+            const uint32_t lo = read_lane(m_lo, (int)j), hi = read_lane(m_hi, (int)j);
+            if (hi <= lo || hi <= w0 || lo >= w1) continue;
+            if (plain && lo <= w0 && hi >= w1) {
+                off += s;
+                mx -= s;
+                continue;
+            }
+            mx = 0;
+#pragma unroll
+            for (int e = 0; e < PK_PER; ++e) {
+                const uint32_t t = t0 + e;
+                if (t < T) x[e] -= off;
+                if (t >= lo && t < hi) x[e] -= s;
+                mx = umax64(mx, x[e]);
+            }
+            off = 0;
+            mx = wave_max_u64(mx);
+        }
+        part[wave][lane] = res;
+        __syncthreads();
+        if (wave == 0 && lane < cnt) {
+            for (int q = 1; q < PK_WAVES; ++q) res = umax64(res, part[q][lane]);
+            if (gridDim.y == 1) peaks[kj] = res;
+            else atomicMax((unsigned long long *)&peaks[kj], (unsigned long long)res);
+        }
+        __syncthreads();
+    }
+}
+
+// every limit: the shortest prefix of the order whose peak is within the limit
+__global__ __launch_bounds__(256) void k_sel_limits(SelectArgs a)
+{
+    const uint32_t ks = blockIdx.x, nc = a.nc[0];
+    const uint64_t *peaks = a.peaks + (size_t)ks * ((size_t)a.n + 1);
+    if (ks == 0 && threadIdx.x == 0) *a.n_cand = nc;
+    for (uint32_t q = threadIdx.x; q < a.L; q += blockDim.x) {
         const uint64_t lim = a.limits[q];
         uint32_t lo = 0, hi = nc;        // first k in [0, nc] with peaks[k] <= lim, else nc
         while (lo < hi) {
@@ -160,10 +534,11 @@ __global__ __launch_bounds__(SEL_THREADS) void k_sel_walk(SelectArgs a)
     }
 }
 
-// load_min: prefix sum of the difference array = load that leaves each step; one workgroup
+// load_min: prefix sum of the difference array = load that leaves each step; one workgroup.  *irregular is set if a
+// step would go below zero or the area under the curve may not fit in 64 bits (possible with a caller's load only)
 __global__ __launch_bounds__(SEL_THREADS) void k_load_min(uint32_t T, const uint64_t *__restrict__ load,
                                                          const uint64_t *__restrict__ dmin,
-                                                         uint64_t *__restrict__ out)
+                                                         uint64_t *__restrict__ out, uint32_t *irregular)
 {
     __shared__ uint64_t wsum[SEL_WAVES], wmax[SEL_WAVES];
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
@@ -177,7 +552,11 @@ __global__ __launch_bounds__(SEL_THREADS) void k_load_min(uint32_t T, const uint
         uint64_t pre = 0, tot = 0;
         for (int q = 0; q < SEL_WAVES; ++q) { const uint64_t x = wsum[q]; if (q < (int)wave) pre += x; tot += x; }
         __syncthreads();
-        if (t < T) mx = umax64(mx, load[t] - (carry + pre + incl));
+        if (t < T) {
+            const uint64_t x = load[t], gone = carry + pre + incl;
+            if (x < gone || x > U64_MAX / T) *irregular = 1u;
+            mx = umax64(mx, x - gone);
+        }
         carry += tot;
     }
 #pragma unroll
@@ -195,9 +574,17 @@ hipError_t launch_select_swaps(const SelectArgs &a, bool gather, hipStream_t st)
 {
     if (gather) {
         hipLaunchKernelGGL(k_sel_gather, dim3((a.n + 255) / 256), dim3(256), 0, st, a);
-        hipLaunchKernelGGL(k_load_min, dim3(1), dim3(SEL_THREADS), 0, st, a.T, a.load, a.dmin, a.load_min);
+        hipLaunchKernelGGL(k_load_min, dim3(1), dim3(SEL_THREADS), 0, st, a.T, a.load, a.dmin, a.load_min, a.nc + 1);
     }
-    hipLaunchKernelGGL(k_sel_walk, dim3(a.K), dim3(SEL_THREADS), 0, st, a);
+    // the number of candidates is not known here: enough workgroups for many, and few enough that the idle ones of a
+    // small list cost little
+    const uint32_t groups = (a.n + ORD_THREADS - 1) / ORD_THREADS, slices = (a.T + PK_SLICE - 1) / PK_SLICE;
+    hipLaunchKernelGGL(k_sel_order, dim3(groups < 128 ? groups : 128, a.K), dim3(ORD_THREADS), 0, st, a);
+    uint32_t stretches = 8192 / (slices * a.K);
+    stretches = stretches < 32 ? 32 : stretches > 256 ? 256 : stretches;
+    const uint32_t most = a.n / PK_MIN_STRETCH + 1;
+    hipLaunchKernelGGL(k_sel_peaks, dim3(stretches < most ? stretches : most, slices, a.K), dim3(PK_THREADS), 0, st, a);
+    hipLaunchKernelGGL(k_sel_limits, dim3(a.K), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

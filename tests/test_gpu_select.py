@@ -91,6 +91,38 @@ def test_select_config4_static_scores(lap, oracle_mod):
     _check(lap, oracle_mod, tr, tr.meta["link_GBps"], tr.meta["min_bytes"], [2, 4], [peak // 2, peak // 50])
 
 
+@pytest.mark.parametrize("n,T,spread", [(1023, 50, 1), (1025, 50, 1), (2600, 50, 1), (3000, 2500, 40), (5000, 40, 3)])
+def test_select_more_candidates_than_are_held(lap, oracle_mod, n, T, spread):
+    # equal sizes and few different idle intervals: many equal scores, zero among them (an idle interval without a step)
+    rng = np.random.default_rng(n)
+    lo = T // 2 - 2 - rng.integers(0, spread, n)
+    hi = np.where(rng.random(n) < 0.3, lo + 1, T // 2 + 4 + rng.integers(0, spread, n))
+    tr = mk_trace([1 << 20] * n, [0] * n, [T] * n, T=T, gap_lo=lo, gap_hi=hi)
+    assert _check(lap, oracle_mod, tr, 64.0, 1, [3, 2, 3], [n << 19, 0]) == n
+
+
+@pytest.mark.parametrize("n,T", [(1500, 30), (40, 5000)])
+def test_select_with_a_load_that_does_not_contain_the_candidates(lap, n, T):
+    import torch
+    rng = np.random.default_rng(n)
+    lo, hi = rng.integers(0, T // 2, n), rng.integers(T // 2 + 1, T, n)
+    size = rng.integers(1, 1 << 20, n).astype(np.uint64)
+    tr = mk_trace(size, [0] * n, [T] * n, T=T, gap_lo=lo, gap_hi=hi)
+    load = rng.integers(0, 1 << 22, T).astype(np.uint64)
+    got = lap.select_swaps(lap.DeviceTrace(tr), 64.0, 1, [3], [], load=torch.from_numpy(load.view(np.int64)).cuda())
+    left, cur, order, peaks = list(range(n)), load.copy(), [], [int(load.max())]
+    with np.errstate(over="ignore"):
+        for _ in range(n):
+            area = [int(cur[lo[i] + 1:hi[i]].sum(dtype=np.uint64)) for i in left]
+            i = left.pop(area.index(max(area)))
+            if hi[i] - 1 > lo[i] + 2:                      # a transfer takes less than one step of 1 ms
+                cur[lo[i] + 2:hi[i] - 1] -= size[i]
+            order.append(i)
+            peaks.append(int(cur.max()))
+    assert np.array_equal(got["order"].cpu().numpy().view(np.uint32)[0], order)
+    assert u64(got["peaks"])[0].tolist() == peaks
+
+
 def test_select_argument_errors(lap):
     tr = random_trace(1, 100, 10)
     dt = lap.DeviceTrace(tr)
