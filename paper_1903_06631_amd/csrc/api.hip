@@ -504,8 +504,7 @@ int lap_score_swaps(const lap_trace *tr, double link_GBps, uint64_t min_bytes, c
         if (rc) return rc;
         load = load_ws;
     }
-    LAP_HIP(lap::launch_swap_prefix(T, load, tr->step_ns, C, S, PM, SM, peak, t_peak, st));
-    LAP_HIP(lap::launch_sparse_table(T, load, table, levels, st));
+    LAP_HIP(lap::launch_swap_prefix(T, load, tr->step_ns, C, S, PM, SM, peak, t_peak, table, levels, st));
     {
         ProfScope p(LAP_K_SCORE, st);
         LAP_HIP(lap::launch_score(n, T, tr->size, tr->alloc, tr->free_, tr->gap_lo, tr->gap_hi, (uint64_t)bpus,
@@ -576,8 +575,7 @@ int lap_select_swaps(const lap_trace *tr, double link_GBps, uint64_t min_bytes, 
         if (rc) return rc;
         load = load_ws;
     }
-    LAP_HIP(lap::launch_swap_prefix(T, load, tr->step_ns, C, S, PM, SM, peak, t_peak, st));
-    LAP_HIP(lap::launch_sparse_table(T, load, table, levels, st));
+    LAP_HIP(lap::launch_swap_prefix(T, load, tr->step_ns, C, S, PM, SM, peak, t_peak, table, levels, st));
     LAP_HIP(lap::launch_score(n, T, tr->size, tr->alloc, tr->free_, tr->gap_lo, tr->gap_hi, (uint64_t)bpus, min_bytes,
                               load, C, S, PM, SM, table, peak, t_peak, cand, doa, aoa, wdoa, cut, win_lo, win_hi, st));
     LAP_HIP(lap::launch_fill_u64(dmin, t1, 0, st));
@@ -678,8 +676,7 @@ int lap_evaluate_weights(const lap_trace *tr, double link_GBps, uint64_t min_byt
         if (rc) return rc;
         load = load_ws;
     }
-    LAP_HIP(lap::launch_swap_prefix(T, load, tr->step_ns, C, S, PM, SM, peak, t_peak, st));
-    LAP_HIP(lap::launch_sparse_table(T, load, table, levels, st));
+    LAP_HIP(lap::launch_swap_prefix(T, load, tr->step_ns, C, S, PM, SM, peak, t_peak, table, levels, st));
     LAP_HIP(lap::launch_score(n, T, tr->size, tr->alloc, tr->free_, tr->gap_lo, tr->gap_hi, (uint64_t)bpus, min_bytes,
                               load, C, S, PM, SM, table, peak, t_peak, cand, doa, aoa, wdoa, cut, win_lo, win_hi, st));
     LAP_HIP(lap::launch_fill_u64(dmin, t1, 0, st));
@@ -769,7 +766,7 @@ int lap_schedule_swaps(const lap_trace *tr, double link_GBps, const uint64_t *lo
         if (rc) return rc;
         load = load_ws;
     }
-    LAP_HIP(lap::launch_swap_prefix(T, load, tr->step_ns, C, S, PM, SM, peak, t_peak, st));
+    LAP_HIP(lap::launch_swap_prefix(T, load, tr->step_ns, C, S, PM, SM, peak, t_peak, nullptr, 0, st));
     // all variables by (first access, index) and by (next access, index): the ascending-step sort of
     // the placement orders, fed with the access steps
     const uint32_t h_kind = LAP_ORD_ALLOC_ASC;
@@ -840,7 +837,7 @@ int lap_simulate_swaps(const lap_trace *tr, double link_GBps, const uint32_t *sw
     // the step start times come from the same prefix kernel as the scores (it needs a load curve)
     rc = load_profile_impl(tr, load_ws, peak, t_peak, delta, st);
     if (rc) return rc;
-    LAP_HIP(lap::launch_swap_prefix(T, load_ws, tr->step_ns, C, S, PM, SM, peak, t_peak, st));
+    LAP_HIP(lap::launch_swap_prefix(T, load_ws, tr->step_ns, C, S, PM, SM, peak, t_peak, nullptr, 0, st));
     const uint32_t h_kind = LAP_ORD_ALLOC_ASC;
     LAP_HIP(lap::launch_put_words(kinds, &h_kind, 1, st));
     LAP_HIP(lap::launch_fill_u64(seeds, 1, 0, st));

@@ -103,8 +103,8 @@ hipError_t launch_select(uint32_t n, uint32_t B, const uint64_t *fps, const uint
                          hipStream_t st);
 
 hipError_t launch_swap_prefix(uint32_t T, const uint64_t *load, const uint64_t *step_ns, uint64_t *C, uint64_t *S,
-                              uint64_t *PM, uint64_t *SM, uint64_t *peak, uint32_t *t_peak, hipStream_t st);
-hipError_t launch_sparse_table(uint32_t T, const uint64_t *load, uint64_t *table, uint32_t levels, hipStream_t st);
+                              uint64_t *PM, uint64_t *SM, uint64_t *peak, uint32_t *t_peak, uint64_t *table,
+                              uint32_t levels, hipStream_t st);
 hipError_t launch_score(uint32_t n, uint32_t T, const uint64_t *size, const uint32_t *alloc, const uint32_t *free_,
                         const uint32_t *gap_lo, const uint32_t *gap_hi, uint64_t bpus, uint64_t min_bytes,
                         const uint64_t *load, const uint64_t *C, const uint64_t *S, const uint64_t *PM,

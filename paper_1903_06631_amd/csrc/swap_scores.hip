@@ -1,6 +1,6 @@
 // Swap-candidate filter and priority scores (Section IV-A, IV-B).
 //
-// Prefix arrays over the T steps are built once by a single workgroup:
+// Prefix arrays over the T steps are built first, a workgroup each:
 //   C[t]  wall-clock start of step t (prefix sum of step_ns), C[T] = total
 //   S[t]  sum of load over steps < t (area under the load curve)
 //   PM[t] max load over steps < t,   SM[t] max load over steps >= t
@@ -11,80 +11,154 @@
 
 namespace lap {
 
-constexpr int PFX_THREADS = 1024;
+constexpr int PFX_THREADS = 1024, PFX_WAVES = PFX_THREADS / WAVE;
+constexpr int PFX_ITEMS = 4;             // steps per thread and round of a scan
+constexpr int PFX_SCANS = 4;             // workgroups 0..3: C, S, PM (with the peak), SM
+constexpr uint32_t TAB_STEPS = PFX_THREADS;   // steps of a table workgroup, one per thread
+constexpr uint32_t TAB_LOW = 10;         // levels that two such stretches of the load decide: 2^10 = TAB_STEPS
+constexpr uint32_t TAB_HIGH = 4;         // further levels per launch of k_table_high
 
-__device__ __forceinline__ uint64_t block_scan(uint64_t v, bool is_max, uint64_t *wtmp, uint64_t &total)
+struct PfxScan {
+    uint64_t wtot[2][PFX_WAVES];         // wave totals, alternating: one barrier per round
+    uint64_t best[PFX_WAVES];
+    uint32_t first[PFX_WAVES];
+};
+
+template <bool MAX> __device__ __forceinline__ uint64_t pfx_join(uint64_t a, uint64_t b)
 {
-    // inclusive scan over the workgroup (sum or max); total = reduction of all
-    const int tid = threadIdx.x, l = tid & (WAVE - 1), w = tid / WAVE;
-    uint64_t incl = is_max ? wave_scan_max(v) : wave_scan_add(v);
-    if (l == WAVE - 1) wtmp[w] = incl;
-    __syncthreads();
-    uint64_t pre = 0, tot = 0;
-    for (int k = 0; k < PFX_THREADS / WAVE; ++k) {
-        const uint64_t x = wtmp[k];
-        if (is_max) { if (k < w) pre = umax64(pre, x); tot = umax64(tot, x); }
-        else        { if (k < w) pre += x;             tot += x; }
-    }
-    __syncthreads();
-    total = tot;
-    return is_max ? umax64(pre, incl) : pre + incl;
+    return MAX ? umax64(a, b) : a + b;
 }
 
+// Inclusive scan (sum or maximum, identity 0) of get(0..T-1); put(t, value) receives the results.
+template <bool MAX, class Get, class Put>
+__device__ __forceinline__ void scan_steps(uint32_t T, PfxScan &s, Get get, Put put)
+{
+    const uint32_t tid = threadIdx.x, l = tid & (WAVE - 1), w = tid / WAVE;
+    uint64_t carry = 0;
+    int buf = 0;
+    for (uint64_t base = 0; base < T; base += PFX_THREADS * PFX_ITEMS, buf ^= 1) {
+        const uint64_t t0 = base + tid * PFX_ITEMS;
+        uint64_t v[PFX_ITEMS];
+#pragma unroll
+        for (int j = 0; j < PFX_ITEMS; ++j) v[j] = t0 + j < T ? get((uint32_t)(t0 + j)) : 0;
+#pragma unroll
+        for (int j = 1; j < PFX_ITEMS; ++j) v[j] = pfx_join<MAX>(v[j - 1], v[j]);
+        const uint64_t incl = MAX ? wave_scan_max(v[PFX_ITEMS - 1]) : wave_scan_add(v[PFX_ITEMS - 1]);
+        if (l == WAVE - 1) s.wtot[buf][w] = incl;
+        __syncthreads();
+        uint64_t pre = lane_shift_up64(incl, 0), tot = carry;
+#pragma unroll
+        for (uint32_t k = 0; k < PFX_WAVES; ++k) {
+            if (k == w) pre = pfx_join<MAX>(pre, tot);
+            tot = pfx_join<MAX>(tot, s.wtot[buf][k]);
+        }
+        carry = tot;
+#pragma unroll
+        for (int j = 0; j < PFX_ITEMS; ++j)
+            if (t0 + j < T) put((uint32_t)(t0 + j), pfx_join<MAX>(pre, v[j]));
+    }
+}
+
+// The four scans, and levels 0 .. min(10, levels - 1) of the sparse table (level k of it:
+// M[k][t] = max load[t .. t + 2^k)), side by side.  What bounds it is latency: a few KB of curve,
+// read by launches that wait for each other.  One workgroup that scanned everything in turn and one
+// launch per level took 11 launches at 580 steps and 15 at 14 000; the scans and the stretches of
+// the table depend on nothing but the load, so each has a workgroup.  A table workgroup holds its
+// 1024 steps and the 1024 after them in LDS, which is what levels up to 10 of its steps cover.
 __global__ __launch_bounds__(PFX_THREADS) void k_swap_prefix(uint32_t T, const uint64_t *__restrict__ load,
                                                              const uint64_t *__restrict__ step_ns,
                                                              uint64_t *__restrict__ C, uint64_t *__restrict__ S,
                                                              uint64_t *__restrict__ PM, uint64_t *__restrict__ SM,
                                                              uint64_t *__restrict__ peak_out,
-                                                             uint32_t *__restrict__ tpeak_out)
+                                                             uint32_t *__restrict__ tpeak_out,
+                                                             uint64_t *__restrict__ table, uint32_t levels)
 {
-    __shared__ uint64_t wtmp[PFX_THREADS / WAVE];
-    __shared__ uint64_t s_peak;
-    const uint32_t tid = threadIdx.x;
-    uint64_t cC = 0, cS = 0, cM = 0, tot;
-    if (tid == 0) { C[0] = 0; S[0] = 0; PM[0] = 0; SM[T] = 0; }
-    for (uint32_t base = 0; base < T; base += PFX_THREADS) {
-        const uint32_t t = base + tid;
+    __shared__ union {
+        PfxScan scan;
+        uint64_t row[2][2 * TAB_STEPS];
+    } s;
+    const uint32_t tid = threadIdx.x, l = tid & (WAVE - 1), w = tid / WAVE;
+    if (blockIdx.x >= PFX_SCANS) {
+        const uint32_t t = (blockIdx.x - PFX_SCANS) * TAB_STEPS + tid;
         const bool in = t < T;
-        const uint64_t ns = in ? (step_ns ? step_ns[t] : 1000000ull) : 0;
-        const uint64_t ld = in ? load[t] : 0;
-        const uint64_t c = cC + block_scan(ns, false, wtmp, tot); cC += tot;
-        const uint64_t s = cS + block_scan(ld, false, wtmp, tot); cS += tot;
-        const uint64_t m = umax64(cM, block_scan(ld, true, wtmp, tot)); cM = umax64(cM, tot);
-        if (in) { C[t + 1] = c; S[t + 1] = s; PM[t + 1] = m; }
+        // a: this thread's step, b: the one TAB_STEPS later; steps past the end count as 0
+        uint64_t a = in ? load[t] : 0, b = (uint64_t)t + TAB_STEPS < T ? load[t + TAB_STEPS] : 0;
+        if (in) table[t] = a;
+        for (uint32_t k = 1; k < levels && k <= TAB_LOW; ++k) {
+            uint64_t *row = s.row[k & 1];
+            row[tid] = a;
+            row[tid + TAB_STEPS] = b;
+            __syncthreads();
+            const uint32_t half = 1u << (k - 1), far = tid + TAB_STEPS + half;
+            a = umax64(a, row[tid + half]);
+            // the last entries of the second stretch lack the values past it: level k is right up to
+            // entry 2048 - 2^k, the first 1024 entries need no more
+            if (far < 2 * TAB_STEPS) b = umax64(b, row[far]);
+            if (in) table[(size_t)k * T + t] = a;
+        }
+        return;
     }
-    if (tid == 0) s_peak = cM;
-    // suffix maxima: scan the reversed array
-    uint64_t cR = 0;
-    for (uint32_t base = 0; base < T; base += PFX_THREADS) {
-        const uint32_t k = base + tid;             // k-th element from the end
-        const bool in = k < T;
-        const uint64_t ld = in ? load[T - 1 - k] : 0;
-        const uint64_t m = umax64(cR, block_scan(ld, true, wtmp, tot)); cR = umax64(cR, tot);
-        if (in) SM[T - 1 - k] = m;
+    if (blockIdx.x == 0) {
+        if (tid == 0) C[0] = 0;
+        scan_steps<false>(T, s.scan, [=](uint32_t t) { return step_ns ? step_ns[t] : 1000000ull; },
+                          [=](uint32_t t, uint64_t v) { C[t + 1] = v; });
+    } else if (blockIdx.x == 1) {
+        if (tid == 0) S[0] = 0;
+        scan_steps<false>(T, s.scan, [=](uint32_t t) { return load[t]; },
+                          [=](uint32_t t, uint64_t v) { S[t + 1] = v; });
+    } else if (blockIdx.x == 2) {
+        if (tid == 0) PM[0] = 0;
+        // the peak and the earliest step that attains it: a thread meets its steps in ascending order
+        uint64_t best = 0;
+        uint32_t first = 0xFFFFFFFFu;
+        scan_steps<true>(T, s.scan,
+                         [&](uint32_t t) {
+                             const uint64_t v = load[t];
+                             if (v > best || first == 0xFFFFFFFFu) { best = v; first = t; }
+                             return v;
+                         },
+                         [=](uint32_t t, uint64_t v) { PM[t + 1] = v; });
+        const uint64_t wave_best = wave_reduce_max(best);
+        if (best != wave_best) first = 0xFFFFFFFFu;
+#pragma unroll
+        for (int m = WAVE / 2; m > 0; m >>= 1) first = min(first, (uint32_t)__shfl_xor(first, m, WAVE));
+        if (l == 0) { s.scan.best[w] = wave_best; s.scan.first[w] = first; }
+        __syncthreads();
+        if (tid == 0) {
+            uint64_t pk = 0;
+            uint32_t at = 0xFFFFFFFFu;
+            for (int k = 0; k < PFX_WAVES; ++k) {
+                const uint64_t x = s.scan.best[k];
+                if (x > pk) { pk = x; at = s.scan.first[k]; }
+                else if (x == pk) at = min(at, s.scan.first[k]);
+            }
+            *peak_out = pk; *tpeak_out = at;
+        }
+    } else {
+        if (tid == 0) SM[T] = 0;
+        scan_steps<true>(T, s.scan, [=](uint32_t t) { return load[T - 1 - t]; },
+                         [=](uint32_t t, uint64_t v) { SM[T - 1 - t] = v; });
     }
-    __syncthreads();
-    // earliest step that attains the peak
-    const uint64_t pk = s_peak;
-    uint32_t first = 0xFFFFFFFFu;
-    for (uint32_t t = tid; t < T; t += PFX_THREADS)
-        if (load[t] == pk) { first = t; break; }
-    __shared__ uint32_t s_first;
-    if (tid == 0) s_first = 0xFFFFFFFFu;
-    __syncthreads();
-    if (first != 0xFFFFFFFFu) atomicMin(&s_first, first);
-    __syncthreads();
-    if (tid == 0) { *peak_out = pk; *tpeak_out = s_first; }
 }
 
-// level k of the sparse table: M[k][t] = max load[t .. t + 2^k)
-__global__ void k_sparse_level(uint32_t T, uint32_t half, const uint64_t *__restrict__ prev, uint64_t *__restrict__ cur)
+// levels k0 + 1 .. k0 + TAB_HIGH (below `levels`) of the sparse table from its level k0: a level-k entry
+// covers 2^(k - k0) entries of level k0, 2^k0 steps apart
+__global__ __launch_bounds__(256) void k_table_high(uint32_t T, uint64_t *__restrict__ table, uint32_t k0,
+                                                    uint32_t levels)
 {
     const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= T) return;
-    const uint64_t a = prev[t];
-    const uint64_t b = (t + half < T) ? prev[t + half] : 0;
-    cur[t] = umax64(a, b);
+    const uint64_t *src = table + (size_t)k0 * T;
+    uint64_t m = src[t];
+    for (uint32_t k = k0 + 1; k < levels && k <= k0 + TAB_HIGH; ++k) {
+        const uint32_t hi = 1u << (k - k0);
+#pragma unroll 8
+        for (uint32_t j = hi / 2; j < hi; ++j) {
+            const uint64_t at = t + ((uint64_t)j << k0);
+            if (at < T) m = umax64(m, src[at]);
+        }
+        table[(size_t)k * T + t] = m;
+    }
 }
 
 __global__ __launch_bounds__(256) void k_score(uint32_t n, uint32_t T, const uint64_t *__restrict__ size,
@@ -141,22 +215,17 @@ __global__ __launch_bounds__(256) void k_score(uint32_t n, uint32_t T, const uin
     if (win_lo) { win_lo[i] = wl; win_hi[i] = wh; }
 }
 
+// levels = 0: no table
 hipError_t launch_swap_prefix(uint32_t T, const uint64_t *load, const uint64_t *step_ns, uint64_t *C, uint64_t *S,
-                              uint64_t *PM, uint64_t *SM, uint64_t *peak, uint32_t *t_peak, hipStream_t st)
+                              uint64_t *PM, uint64_t *SM, uint64_t *peak, uint32_t *t_peak, uint64_t *table,
+                              uint32_t levels, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_swap_prefix, dim3(1), dim3(PFX_THREADS), 0, st, T, load, step_ns, C, S, PM, SM, peak, t_peak);
-    return hipGetLastError();
-}
-
-// table holds levels 1.. ; level 0 is `load` itself, so table level k lives at table + (k) * T with
-// level 0 copied in by the first launch (half = 0 copies).
-hipError_t launch_sparse_table(uint32_t T, const uint64_t *load, uint64_t *table, uint32_t levels, hipStream_t st)
-{
-    const uint32_t blocks = (T + 255) / 256;
-    hipLaunchKernelGGL(k_sparse_level, dim3(blocks), dim3(256), 0, st, T, T /* no partner */, load, table);
-    for (uint32_t k = 1; k < levels; ++k)
-        hipLaunchKernelGGL(k_sparse_level, dim3(blocks), dim3(256), 0, st, T, 1u << (k - 1),
-                           table + (size_t)(k - 1) * T, table + (size_t)k * T);
+    const uint32_t stretches = levels ? (uint32_t)(((uint64_t)T + TAB_STEPS - 1) / TAB_STEPS) : 0;
+    hipLaunchKernelGGL(k_swap_prefix, dim3(PFX_SCANS + stretches), dim3(PFX_THREADS), 0, st, T, load, step_ns, C, S,
+                       PM, SM, peak, t_peak, table, levels);
+    for (uint32_t k0 = TAB_LOW; k0 + 1 < levels; k0 += TAB_HIGH)
+        hipLaunchKernelGGL(k_table_high, dim3((uint32_t)(((uint64_t)T + 255) / 256)), dim3(256), 0, st, T, table, k0,
+                           levels);
     return hipGetLastError();
 }
 

@@ -343,6 +343,15 @@ def test_score_swaps_random(lap, oracle_mod, seed, n, T, link):
     _check_scores(lap, oracle_mod, tr, link, 1 << 14, use_gaps=False)
 
 
+@pytest.mark.parametrize("T", [1023, 1024, 1025, 2047, 2049, 4096, 4097, 16383, 16385, 40001, 300_001])
+def test_score_swaps_around_scan_and_table_edges(lap, oracle_mod, T):
+    """step counts around a workgroup's stretch of the range-maximum table (1024), a round of the scans
+    (4096) and the levels at which another launch of the table starts (2^11 and 2^15 steps and more); every
+    score is exact, and long idle windows ask for the highest levels"""
+    tr = random_trace(5300 + T, 600, T, with_step_ns=True)
+    _check_scores(lap, oracle_mod, tr, 900.0, 1 << 12)
+
+
 @pytest.mark.parametrize("cfg", [1, 3, 5])
 def test_score_swaps_configs(lap, oracle_mod, cfg):
     tr = make_config(cfg)
