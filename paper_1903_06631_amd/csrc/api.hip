@@ -102,7 +102,7 @@ size_t ws_simulate(uint32_t n, uint32_t T, uint32_t Q)
            + 2 * up((size_t)T * 8)                                 // bytes allocated / freed per step
            + 6 * up(N * 4) + 3 * ALIGN                             // posmap, perm x2, sort scratch, jobs x2; kinds, seeds, m
            + up((size_t)SIM_MAX_RUNS * 4) + up((size_t)SIM_MAX_RUNS * 8)   // prefix lengths, limits
-           + (size_t)Q * (up(N * 4) + up(N));                      // per run: issue boundaries, swap-out flags
+           + (size_t)Q * up(N * 4);                                // per run: issue boundaries
 }
 
 size_t ws_select(uint32_t n, uint32_t T, uint32_t K);
@@ -114,7 +114,7 @@ size_t ws_weights(uint32_t n, uint32_t T, uint32_t W)
            + up(w * N * 8) + 2 * up(w * N * 4) + up(w * (N + 1) * 8) + up(w * N * 8)                // picks, peaks, scores
            + up(N * 8) + up(N * 4) + 2 * up(((size_t)T + 1) * 8)                                    // the SWDOA walk
            + 2 * up((size_t)T * 8) + 3 * up(N * 4) + 2 * ALIGN                                      // steps, perms
-           + up((w * N + 1) * 4) + 2 * up(w * N * 4) + up(w * 4) + up(w * N * 4) + up(w * N)        // replay state
+           + up((w * N + 1) * 4) + 2 * up(w * N * 4) + up(w * 4) + up(w * N * 4)                   // replay state
            + 2 * up(w * 8);
 }
 
@@ -666,7 +666,6 @@ int lap_evaluate_weights(const lap_trace *tr, double link_GBps, uint64_t min_byt
     uint32_t *jobs_hi = c.take<uint32_t>((size_t)W * N);
     uint32_t *m = c.take<uint32_t>(W);
     uint32_t *kb = c.take<uint32_t>((size_t)W * N);
-    uint8_t *out_done = c.take<uint8_t>((size_t)W * N);
     uint64_t *total_ns = c.take<uint64_t>(W);
     uint64_t *peak_res = c.take<uint64_t>(W);
 
@@ -720,7 +719,7 @@ int lap_evaluate_weights(const lap_trace *tr, double link_GBps, uint64_t min_byt
     LAP_HIP(lap::launch_fill_u64(rel, T, 0, st));
     LAP_HIP(lap::launch_simulate_swaps(n, T, W, n, tr->size, tr->alloc, tr->free_, step_lo, step_hi,
                                        tr->gap_hi ? 0u : 1u, C, need, rel, order, perm_lo, perm_hi, posmap, jobs_lo,
-                                       jobs_hi, m, n_selected, d_limits, kb, out_done, (uint64_t)bpus, total_ns,
+                                       jobs_hi, m, n_selected, d_limits, kb, (uint64_t)bpus, total_ns,
                                        overhead_ns, peak_res, forced, st, W, n_cand));
     LAP_HIP(lap::launch_argmin_u64(W, overhead_ns, best, st));
     return LAP_OK;
@@ -829,8 +828,6 @@ int lap_simulate_swaps(const lap_trace *tr, double link_GBps, const uint32_t *sw
     uint64_t *d_limits = c.take<uint64_t>(SIM_MAX_RUNS);
     uint32_t *kb = c.take<uint32_t>(0);
     c.used += (size_t)Q * up((size_t)n * 4);
-    uint8_t *out_done = c.take<uint8_t>(0);
-    c.used += (size_t)Q * up((size_t)n);
 
     LAP_HIP(lap::launch_put_words(d_prefix, prefix_len, Q, st));
     LAP_HIP(lap::launch_put_words(d_limits, limits, (size_t)Q * 2, st));
@@ -852,7 +849,7 @@ int lap_simulate_swaps(const lap_trace *tr, double link_GBps, const uint32_t *sw
     // the per-run regions use a stride of n entries
     LAP_HIP(lap::launch_simulate_swaps(n, T, Q, n, tr->size, tr->alloc, tr->free_, step_lo, step_hi,
                                        tr->gap_hi ? 0u : 1u, C, need, rel, swap_list, perm_lo, perm_hi, posmap,
-                                       jobs_lo, jobs_hi, m, d_prefix, d_limits, kb, out_done, (uint64_t)bpus,
+                                       jobs_lo, jobs_hi, m, d_prefix, d_limits, kb, (uint64_t)bpus,
                                        total_ns, overhead_ns, peak_resident, forced, st));
     return LAP_OK;
 }

@@ -162,7 +162,7 @@ hipError_t launch_simulate_swaps(uint32_t n, uint32_t T, uint32_t Q, uint32_t km
                                  uint64_t *rel, const uint32_t *list, const uint32_t *perm_lo,
                                  const uint32_t *perm_hi, const uint32_t *posmap, uint32_t *jobs_lo,
                                  uint32_t *jobs_hi, uint32_t *m, const uint32_t *prefix, const uint64_t *limits,
-                                 uint32_t *kb, uint8_t *out_done, uint64_t bpus, uint64_t *total_ns,
+                                 uint32_t *kb, uint64_t bpus, uint64_t *total_ns,
                                  uint64_t *overhead_ns, uint64_t *peak_resident, uint32_t *forced, hipStream_t st,
                                  uint32_t n_lists = 1, const uint32_t *n_listed = nullptr);
 hipError_t launch_sched_mark(uint32_t n, uint32_t k, const uint32_t *list, uint32_t *posmap, hipStream_t st);

@@ -4,17 +4,22 @@
 // swap-in stream); the result is the time lost against the plain iteration.
 //
 // The machine is sequential; the parallel dimension is the set of (swap list prefix, limit) pairs to
-// evaluate -- a sweep of limits, several priority orders -- one wave each, lane 0 running the
-// machine.  Shared by all of them and built by data-parallel kernels: bytes allocated and freed per
+// evaluate -- a sweep of limits, several priority orders -- one workgroup each, whose first wave runs
+// the machine.  Shared by all of them and built by data-parallel kernels: bytes allocated and freed per
 // step, and the listed variables in swap-out order and in swap-in order (positions in the list, so
 // that "the first k of the list" is a filter).
 #include "lap_dev.h"
 #include "lap_kernels.h"
+#include "stream_scan.h"
 
 namespace lap {
 
 constexpr int SIM_THREADS = 1024;
 constexpr int SIM_WAVES = SIM_THREADS / WAVE;
+constexpr int SIM_PER = 8;                         // ranks per thread and round of the job lists
+constexpr int RUN_THREADS = 512, RUN_WAVES = RUN_THREADS / WAVE;
+constexpr int RUN_BATCH = 4;                       // entries a lane loads side by side
+constexpr uint32_t RUN_WIN = RUN_BATCH * WAVE;     // entries of each stream held in LDS
 constexpr uint32_t SIM_NONE = 0xFFFFFFFFu;
 
 __global__ __launch_bounds__(256) void k_sim_steps(uint32_t n, const uint64_t *__restrict__ size,
@@ -39,39 +44,52 @@ __global__ __launch_bounds__(256) void k_sim_mark_rows(uint32_t n, const uint32_
 }
 
 // jobs[0..m) = list positions of the listed variables that have an idle gap, in the order of perm;
-// one workgroup per list (rows of n entries of posmap and jobs, one count each)
-__global__ __launch_bounds__(SIM_THREADS) void k_sim_jobs(uint32_t n, const uint32_t *__restrict__ perm,
+// one workgroup per list (rows of n entries of posmap and jobs, one count each) and direction
+// (blockIdx.y: swap-outs, swap-ins).  Every round waits for two dependent loads, so a thread takes
+// SIM_PER ranks per round.
+__global__ __launch_bounds__(SIM_THREADS) void k_sim_jobs(uint32_t n, const uint32_t *__restrict__ perm_lo,
+                                                          const uint32_t *__restrict__ perm_hi,
                                                           const uint32_t *__restrict__ posmap_all,
                                                           const uint32_t *__restrict__ step_lo,
                                                           const uint32_t *__restrict__ step_hi, uint32_t hi_minus,
-                                                          uint32_t *__restrict__ jobs_all,
+                                                          uint32_t *__restrict__ jobs_lo,
+                                                          uint32_t *__restrict__ jobs_hi,
                                                           uint32_t *__restrict__ m_all)
 {
-    __shared__ uint32_t wsum[SIM_WAVES];
+    __shared__ uint32_t wsum[2][SIM_WAVES];
+    const uint32_t *perm = blockIdx.y ? perm_hi : perm_lo;
     const uint32_t *posmap = posmap_all + (size_t)blockIdx.x * n;
-    uint32_t *jobs = jobs_all + (size_t)blockIdx.x * n;
-    uint32_t *m_out = m_all + blockIdx.x;
+    uint32_t *jobs = (blockIdx.y ? jobs_hi : jobs_lo) + (size_t)blockIdx.x * n;
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
+    const uint64_t below = (1ull << lane) - 1ull;
     uint32_t carry = 0;
-    for (uint32_t base = 0; base < n; base += SIM_THREADS) {
-        const uint32_t r = base + tid;
-        uint32_t pos = SIM_NONE;
-        if (r < n) {
-            const uint32_t v = perm[r];
-            pos = posmap[v];
-            if (pos != SIM_NONE && step_hi[v] - hi_minus <= step_lo[v]) pos = SIM_NONE;
+    int buf = 0;
+    for (uint64_t base = 0; base < n; base += SIM_THREADS * SIM_PER, buf ^= 1) {
+        const uint64_t r0 = base + wave * (WAVE * SIM_PER) + lane;
+        uint32_t v[SIM_PER], pos[SIM_PER];
+        uint64_t mine[SIM_PER];
+#pragma unroll
+        for (int j = 0; j < SIM_PER; ++j) v[j] = r0 + j * WAVE < n ? perm[r0 + j * WAVE] : SIM_NONE;
+#pragma unroll
+        for (int j = 0; j < SIM_PER; ++j) pos[j] = v[j] != SIM_NONE ? posmap[v[j]] : SIM_NONE;
+        uint32_t tot = 0;
+#pragma unroll
+        for (int j = 0; j < SIM_PER; ++j) {
+            if (pos[j] != SIM_NONE && step_hi[v[j]] - hi_minus <= step_lo[v[j]]) pos[j] = SIM_NONE;
+            mine[j] = ballot(pos[j] != SIM_NONE);
+            tot += (uint32_t)__popcll(mine[j]);
         }
-        const uint64_t mine = ballot(pos != SIM_NONE);
-        const uint32_t before = (uint32_t)__popcll(mine & ((1ull << lane) - 1ull));
-        if (lane == 0) wsum[wave] = (uint32_t)__popcll(mine);
+        if (lane == 0) wsum[buf][wave] = tot;
         __syncthreads();
-        uint32_t pre = 0, tot = 0;
-        for (int q = 0; q < SIM_WAVES; ++q) { const uint32_t x = wsum[q]; if (q < (int)wave) pre += x; tot += x; }
-        __syncthreads();
-        if (pos != SIM_NONE) jobs[carry + pre + before] = pos;
-        carry += tot;
+        uint32_t at = carry;
+        for (int q = 0; q < SIM_WAVES; ++q) { const uint32_t x = wsum[buf][q]; if (q < (int)wave) at += x; carry += x; }
+#pragma unroll
+        for (int j = 0; j < SIM_PER; ++j) {
+            if (pos[j] != SIM_NONE) jobs[at + (uint32_t)__popcll(mine[j] & below)] = pos[j];
+            at += (uint32_t)__popcll(mine[j]);
+        }
     }
-    if (tid == 0) *m_out = carry;
+    if (tid == 0 && blockIdx.y == 0) m_all[blockIdx.x] = carry;     // the same number both ways
 }
 
 struct SimArgs {
@@ -85,100 +103,194 @@ struct SimArgs {
     const uint32_t *jobs_lo, *jobs_hi, *m;
     const uint32_t *prefix;            // [Q]
     const uint64_t *limits;            // [Q]
-    uint32_t *kb;                      // [Q][kmax] issue boundary of a swap-in, by list position
-    uint8_t *out_done;                 // [Q][kmax]
+    uint32_t *kb;                      // [Q][kmax] issue boundary of a swap-in, by its place in jobs_hi
     uint32_t per_run_lists;            // 1: run q has its own list (row q of list / jobs / m), 0: all share row 0
     uint64_t bpus;
     uint64_t *total_ns, *overhead_ns, *peak_resident;
     uint32_t *forced;
 };
 
-__global__ __launch_bounds__(WAVE) void k_sim_run(SimArgs A)
+// What the machine reads next of each of its three streams.  Its state goes from event to event in
+// registers; the entries come from here, RUN_WIN of a stream fetched by the whole wave at a time, so
+// that an event waits for LDS and not for the chain jobs -> list -> size, steps in global memory.
+// All swap planning calls, 21 limits, 14 000 steps, 50 000 variables: 80.0 -> 29.4 ms; 348 steps, 3000
+// variables: 1.89 -> 0.87 ms; 64 weight vectors on 200 000 variables: 7.31 -> 5.09 ms.
+struct SimWin {
+    uint64_t need[RUN_WIN], rel[RUN_WIN], dt[RUN_WIN];
+    uint64_t osize[RUN_WIN], odur[RUN_WIN], okey[RUN_WIN];      // key: step << 32 | variable, the order of the jobs
+    uint64_t isize[RUN_WIN], idur[RUN_WIN], ikey[RUN_WIN];      // ikey: the key of the same variable's swap-out
+    uint32_t ihi[RUN_WIN], ikb[RUN_WIN];
+};
+
+__device__ __forceinline__ void win_sync()
 {
-    if (threadIdx.x != 0) return;
-    const uint32_t q = blockIdx.x;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+__device__ __forceinline__ uint64_t sim_dur(uint64_t size, uint64_t bpus) { return (size * 1000ull + bpus - 1) / bpus; }
+
+// The next swap-outs or swap-ins of the prefix from jobs[raw..m): returns how many entries the window
+// holds (0: none left) and moves raw behind them.
+template <bool OUT>
+__device__ uint32_t win_fill(const SimArgs &A, const uint32_t *jobs, const uint32_t *list, const uint32_t *kb,
+                             uint32_t k, uint32_t m, uint32_t &raw, SimWin &W)
+{
+    const uint32_t lane = threadIdx.x & (WAVE - 1);
+    const uint64_t below = (1ull << lane) - 1ull;
+    uint32_t cnt = 0;
+    win_sync();
+    while (cnt == 0 && raw < m) {
+        uint32_t pos[RUN_BATCH], v[RUN_BATCH];
+#pragma unroll
+        for (int j = 0; j < RUN_BATCH; ++j) {
+            const uint32_t r = raw + j * WAVE + lane;
+            pos[j] = r < m ? jobs[r] : SIM_NONE;
+        }
+#pragma unroll
+        for (int j = 0; j < RUN_BATCH; ++j) v[j] = pos[j] < k ? min(list[pos[j]], A.n - 1) : 0;
+#pragma unroll
+        for (int j = 0; j < RUN_BATCH; ++j) {
+            const bool on = pos[j] < k;
+            const uint64_t who = ballot(on);
+            if (on) {
+                const uint32_t at = cnt + (uint32_t)__popcll(who & below);
+                const uint64_t sz = A.size[v[j]], key = (uint64_t)A.step_lo[v[j]] << 32 | v[j];
+                if (OUT) {
+                    W.osize[at] = sz; W.odur[at] = sim_dur(sz, A.bpus); W.okey[at] = key;
+                } else {
+                    W.isize[at] = sz; W.idur[at] = sim_dur(sz, A.bpus); W.ikey[at] = key;
+                    W.ihi[at] = A.step_hi[v[j]] - A.hi_minus;
+                    W.ikb[at] = kb[raw + j * WAVE + lane];
+                }
+            }
+            cnt += (uint32_t)__popcll(who);
+        }
+        raw = m - raw > RUN_WIN ? raw + RUN_WIN : m;
+    }
+    win_sync();
+    return cnt;
+}
+
+// One run.  First the plan's swap-in starts, from the last access backwards, which are a scan (stream_scan.h):
+// all threads, RUN_THREADS jobs a round.  Then the first wave runs the machine, all lanes with the same state.
+// Transfers are served in order, so "the swap-out of this variable is done" is a comparison of its key with
+// that of the last one done, and "the swap-in is issued" one of the largest issue boundary up to it.
+// Bound by the chain of a few hundred cycles per event.
+__global__ __launch_bounds__(RUN_THREADS) void k_sim_run(SimArgs A)
+{
+    __shared__ SimWin W;
+    __shared__ Fn wtmp[RUN_WAVES];
+    const uint32_t q = blockIdx.x, tid = threadIdx.x;
     const size_t row = A.per_run_lists ? (size_t)q * A.n : 0;
-    A.list += row;
-    A.jobs_lo += row;
-    A.jobs_hi += row;
+    const uint32_t *list = A.list + row, *jobs_lo = A.jobs_lo + row, *jobs_hi = A.jobs_hi + row;
     const uint32_t k = A.prefix[q], m = A.m[A.per_run_lists ? q : 0], T = A.T;
     const uint64_t limit = A.limits[q];
     uint32_t *kb = A.kb + (size_t)q * A.kmax;
-    uint8_t *odone = A.out_done + (size_t)q * A.kmax;
-    auto dur = [&](uint32_t v) { return (A.size[v] * 1000ull + A.bpus - 1) / A.bpus; };
-    auto lo_of = [&](uint32_t pos) { return A.step_lo[A.list[pos]]; };
-    auto hi_of = [&](uint32_t pos) { return A.step_hi[A.list[pos]] - A.hi_minus; };
 
-    // the plan's swap-in starts, from the last access backwards; each gives the step boundary at
-    // which the swap-in is issued
-    {
-        long long next_start = (1ll << 62);
-        for (uint32_t jj = m; jj-- > 0;) {
-            const uint32_t pos = A.jobs_hi[jj];
-            if (pos >= k) continue;
-            const uint32_t v = A.list[pos], th = hi_of(pos);
-            const long long due = (long long)A.C[th];
-            const long long st = (due < next_start ? due : next_start) - (long long)dur(v);
-            next_start = st;
-            uint32_t l0 = 0, h0 = th;                      // last t <= th with C[t] <= st (0 if none)
-            while (l0 < h0) { const uint32_t mid = (l0 + h0 + 1) >> 1; if ((long long)A.C[mid] <= st) l0 = mid; else h0 = mid - 1; }
-            kb[pos] = max(l0, lo_of(pos) + 1);
-            odone[pos] = 0;
+    // each planned start gives the step boundary at which the swap-in is issued
+    Fn carry{0, SC_POS};
+    for (uint32_t base = 0; base < m; base += RUN_THREADS) {
+        const uint32_t back = base + tid, jj = m - 1 - back;
+        Fn f{0, SC_POS};
+        uint32_t lo = 0, th = 0;
+        bool on = false;
+        if (back < m) {
+            const uint32_t pos = jobs_hi[jj];
+            if (pos < k) {
+                const uint32_t v = min(list[pos], A.n - 1);
+                const long long d = (long long)sim_dur(A.size[v], A.bpus);
+                on = true;
+                lo = A.step_lo[v];
+                th = A.step_hi[v] - A.hi_minus;
+                f = Fn{d, (long long)A.C[th] - d};
+            }
+        }
+        const Fn g = block_scan_fn<false, RUN_WAVES>(f, carry, wtmp);
+        if (on) {
+            uint32_t l0 = 0, h0 = th;                      // last t <= th with C[t] <= start (0 if none)
+            while (l0 < h0) { const uint32_t mid = (l0 + h0 + 1) >> 1; if ((long long)A.C[mid] <= g.b) l0 = mid; else h0 = mid - 1; }
+            kb[jj] = max(l0, lo + 1);
         }
     }
+    __syncthreads();
+    if (tid >= WAVE) return;
 
     uint64_t now = 0, R = 0, peak = 0;
-    uint32_t t = 0, nforced = 0, boundary = 0;
+    uint32_t t = 0, nforced = 0;                           // t is also the last step boundary reached
     bool step_run = false, out_run = false, in_run = false;
     uint64_t step_end = 0, out_end = 0, in_end = 0;
-    uint32_t o_iss = 0, o_next = 0, i_iss = 0, i_next = 0;   // indices into jobs_lo / jobs_hi
-    auto skip_lo = [&](uint32_t p) { while (p < m && A.jobs_lo[p] >= k) ++p; return p; };
-    auto skip_hi = [&](uint32_t p) { while (p < m && A.jobs_hi[p] >= k) ++p; return p; };
-    auto issue_ins = [&]() {
-        while (i_iss < m && (A.jobs_hi[i_iss] >= k || kb[A.jobs_hi[i_iss]] <= boundary)) ++i_iss;
+    // the current entry of each stream; `_at` inside the window of `_cnt` entries, `_raw` what follows it
+    uint64_t need = 0, rel = 0, dt = 0, osize = 0, odur = 0, okey = 0, isize = 0, idur = 0, ikey = 0;
+    uint64_t done = 0;                                     // key of the last swap-out done, plus one
+    uint32_t ihi = 0, issue = 0;
+    uint32_t o_at = 0, o_cnt = 0, o_raw = 0, i_at = 0, i_cnt = 0, i_raw = 0;
+    bool o_any, i_any;
+    auto step_load = [&]() {
+        if (t >= T) return;
+        if (t % RUN_WIN == 0) {
+            win_sync();
+#pragma unroll
+            for (int j = 0; j < RUN_BATCH; ++j) {
+                const uint32_t e = j * WAVE + tid;
+                if (e < T - t) { W.need[e] = A.need[t + e]; W.rel[e] = A.rel[t + e]; W.dt[e] = A.C[t + e + 1] - A.C[t + e]; }
+            }
+            win_sync();
+        }
+        const uint32_t e = t % RUN_WIN;
+        need = W.need[e]; rel = W.rel[e]; dt = W.dt[e];
     };
-    o_next = skip_lo(0);
-    i_next = skip_hi(0);
-    issue_ins();
+    auto out_load = [&]() {
+        if (o_at == o_cnt) { o_cnt = win_fill<true>(A, jobs_lo, list, kb, k, m, o_raw, W); o_at = 0; }
+        o_any = o_cnt != 0;
+        if (o_any) { osize = W.osize[o_at]; odur = W.odur[o_at]; okey = W.okey[o_at]; ++o_at; }
+    };
+    auto in_load = [&]() {
+        if (i_at == i_cnt) { i_cnt = win_fill<false>(A, jobs_hi, list, kb, k, m, i_raw, W); i_at = 0; }
+        i_any = i_cnt != 0;
+        if (i_any) {
+            isize = W.isize[i_at]; idur = W.idur[i_at]; ikey = W.ikey[i_at]; ihi = W.ihi[i_at];
+            issue = max(issue, W.ikb[i_at]);
+            ++i_at;
+        }
+    };
+    step_load();
+    out_load();
+    in_load();
     for (;;) {
         // ends at this instant
         if (step_run && step_end == now) {
             step_run = false;
-            R -= A.rel[t];
-            while (o_iss < m && (A.jobs_lo[o_iss] >= k || lo_of(A.jobs_lo[o_iss]) <= t)) ++o_iss;
+            R -= rel;
             ++t;
-            boundary = t;
-            issue_ins();
+            step_load();
         }
         if (out_run && out_end == now) {
             out_run = false;
-            const uint32_t pos = A.jobs_lo[o_next];
-            R -= A.size[A.list[pos]];
-            odone[pos] = 1;
-            o_next = skip_lo(o_next + 1);
+            R -= osize;
+            done = okey + 1;
+            out_load();
         }
         if (in_run && in_end == now) {
             in_run = false;
-            i_next = skip_hi(i_next + 1);
+            in_load();
         }
         if (t == T && !step_run) break;
         // starts: swap-out, step, swap-in
-        if (!out_run && o_next < o_iss) {
+        if (!out_run && o_any && (uint32_t)(okey >> 32) < t) {
             out_run = true;
-            out_end = now + dur(A.list[A.jobs_lo[o_next]]);
+            out_end = now + odur;
         }
         bool step_blocked = false, in_blocked = false;
-        if (!step_run && t < T && (i_next >= m || hi_of(A.jobs_hi[i_next]) > t)) {
-            const uint64_t nd = A.need[t];
-            if (nd == 0 || R + nd <= limit) {
-                step_run = true; R += nd; step_end = now + (A.C[t + 1] - A.C[t]);
+        if (!step_run && t < T && (!i_any || ihi > t)) {
+            if (need == 0 || R + need <= limit) {
+                step_run = true; R += need; step_end = now + dt;
                 peak = umax64(peak, R);
             } else step_blocked = true;
         }
-        if (!in_run && i_next < i_iss && odone[A.jobs_hi[i_next]]) {
-            const uint32_t v = A.list[A.jobs_hi[i_next]];
-            if (R + A.size[v] <= limit) {
-                in_run = true; R += A.size[v]; in_end = now + dur(v);
+        if (!in_run && i_any && issue <= t && ikey < done) {
+            if (R + isize <= limit) {
+                in_run = true; R += isize; in_end = now + idur;
                 peak = umax64(peak, R);
             } else in_blocked = true;
         }
@@ -186,10 +298,9 @@ __global__ __launch_bounds__(WAVE) void k_sim_run(SimArgs A)
             // nothing will change by itself: the limit is overridden once
             ++nforced;
             if (step_blocked) {
-                step_run = true; R += A.need[t]; step_end = now + (A.C[t + 1] - A.C[t]);
+                step_run = true; R += need; step_end = now + dt;
             } else if (in_blocked) {
-                const uint32_t v = A.list[A.jobs_hi[i_next]];
-                in_run = true; R += A.size[v]; in_end = now + dur(v);
+                in_run = true; R += isize; in_end = now + idur;
             } else {
                 nforced = SIM_NONE;           // an inconsistent trace; leave rather than spin
                 break;
@@ -202,10 +313,12 @@ __global__ __launch_bounds__(WAVE) void k_sim_run(SimArgs A)
         if (in_run) nx = umin64(nx, in_end);
         now = nx;
     }
-    A.total_ns[q] = now;
-    A.overhead_ns[q] = now - A.C[T];
-    A.peak_resident[q] = peak;
-    A.forced[q] = nforced;
+    if (tid == 0) {
+        A.total_ns[q] = now;
+        A.overhead_ns[q] = now - A.C[T];
+        A.peak_resident[q] = peak;
+        A.forced[q] = nforced;
+    }
 }
 
 hipError_t launch_simulate_swaps(uint32_t n, uint32_t T, uint32_t Q, uint32_t kmax, const uint64_t *size,
@@ -214,7 +327,7 @@ hipError_t launch_simulate_swaps(uint32_t n, uint32_t T, uint32_t Q, uint32_t km
                                  uint64_t *rel, const uint32_t *list, const uint32_t *perm_lo,
                                  const uint32_t *perm_hi, const uint32_t *posmap, uint32_t *jobs_lo,
                                  uint32_t *jobs_hi, uint32_t *m, const uint32_t *prefix, const uint64_t *limits,
-                                 uint32_t *kb, uint8_t *out_done, uint64_t bpus, uint64_t *total_ns,
+                                 uint32_t *kb, uint64_t bpus, uint64_t *total_ns,
                                  uint64_t *overhead_ns, uint64_t *peak_resident, uint32_t *forced, hipStream_t st,
                                  uint32_t n_lists, const uint32_t *n_listed)
 {
@@ -225,15 +338,13 @@ hipError_t launch_simulate_swaps(uint32_t n, uint32_t T, uint32_t Q, uint32_t km
                            const_cast<uint32_t *>(posmap));
     hipLaunchKernelGGL(k_sim_steps, dim3((n + 255) / 256), dim3(256), 0, st, n, size, alloc, free_,
                        (unsigned long long *)need, (unsigned long long *)rel);
-    hipLaunchKernelGGL(k_sim_jobs, dim3(n_lists), dim3(SIM_THREADS), 0, st, n, perm_lo, posmap, step_lo, step_hi,
-                       hi_minus, jobs_lo, m);
-    hipLaunchKernelGGL(k_sim_jobs, dim3(n_lists), dim3(SIM_THREADS), 0, st, n, perm_hi, posmap, step_lo, step_hi,
-                       hi_minus, jobs_hi, m);
+    hipLaunchKernelGGL(k_sim_jobs, dim3(n_lists, 2), dim3(SIM_THREADS), 0, st, n, perm_lo, perm_hi, posmap, step_lo,
+                       step_hi, hi_minus, jobs_lo, jobs_hi, m);
     SimArgs A{n, T, Q, kmax, size, step_lo, step_hi, hi_minus, C, (const unsigned long long *)need,
-              (const unsigned long long *)rel, list, jobs_lo, jobs_hi, m, prefix, limits, kb, out_done,
+              (const unsigned long long *)rel, list, jobs_lo, jobs_hi, m, prefix, limits, kb,
               n_listed ? 1u : 0u, bpus,
               total_ns, overhead_ns, peak_resident, forced};
-    hipLaunchKernelGGL(k_sim_run, dim3(Q), dim3(WAVE), 0, st, A);
+    hipLaunchKernelGGL(k_sim_run, dim3(Q), dim3(RUN_THREADS), 0, st, A);
     return hipGetLastError();
 }
 

@@ -68,6 +68,17 @@ def test_simulate_random(lap, oracle_mod, seed, n, T):
     _check(lap, oracle_mod, tr, 1.0, sl, [(len(sl), peak * 2 // 3)], use_gaps=False)
 
 
+@pytest.mark.parametrize("n,T", [(600, 255), (600, 256), (601, 257), (4000, 513), (8193, 40)])
+def test_simulate_window_edges(lap, oracle_mod, n, T):
+    """steps and transfers are fetched 256 at a time, swap-in starts scanned 512 at a time, job lists built 8192 at a time"""
+    tr = random_trace(2300 + n + T, n, T, with_step_ns=True)
+    _, peak, _ = oracle_mod.load_profile(tr)
+    with_gap = np.nonzero(tr.gap_hi > tr.gap_lo)[0]
+    sl = np.random.default_rng(n).permutation(with_gap).astype(np.uint32)
+    ks = sorted({min(k, len(sl)) for k in (1, 255, 256, 257, 511, 512, 513, len(sl) - 1, len(sl))})
+    _check(lap, oracle_mod, tr, 2.0, sl, [(k, lim) for k in ks for lim in (peak, peak * 3 // 5, 0)])
+
+
 @pytest.mark.parametrize("cfg", [2, 3, 5])
 def test_simulate_limit_sweep_on_configs(lap, oracle_mod, cfg):
     """what the planner is for: the selection's prefixes for a sweep of limits, each replayed under its limit"""
