@@ -25,6 +25,7 @@ constexpr int PK_THREADS = 256, PK_WAVES = PK_THREADS / WAVE;
 constexpr int PK_PER = 8;                      // steps a thread holds
 constexpr uint32_t PK_SLICE = PK_THREADS * PK_PER;
 constexpr uint32_t PK_MIN_STRETCH = 16;
+constexpr uint32_t PK_MAX_SLICES = 65535;      // of one launch: what the grid's y dimension takes (134 million steps)
 constexpr uint32_t NONE = 0xFFFFFFFFu;
 
 // slot list of the candidates (any order: ties are decided on the variable index) and the
@@ -484,10 +485,10 @@ __global__ __launch_bounds__(ORD_THREADS) void k_sel_order(SelectArgs a)
     }
 }
 
-// peaks[k] for one stretch of the order and one slice of the steps.  Grid: stretches, slices, rows.  A wave holds 512
-// steps: a winner that leaves all of them lowers their maximum by its size, one that leaves none changes nothing, and
-// only at the edges of its window are the steps updated and reduced.
-__global__ __launch_bounds__(PK_THREADS) void k_sel_peaks(SelectArgs a)
+// peaks[k] for one stretch of the order and one slice of the steps.  Grid: stretches, slices from `first` on, rows.  A
+// wave holds 512 steps: a winner that leaves all of them lowers their maximum by its size, one that leaves none
+// changes nothing, and only at the edges of its window are the steps updated and reduced.
+__global__ __launch_bounds__(PK_THREADS) void k_sel_peaks(SelectArgs a, uint32_t first)
 {
     __shared__ unsigned long long diff[PK_SLICE + 1];
     __shared__ uint64_t part[PK_WAVES][WAVE];
@@ -502,7 +503,7 @@ __global__ __launch_bounds__(PK_THREADS) void k_sel_peaks(SelectArgs a)
     const uint64_t *sz = a.s_size + (size_t)ks * n;
     const uint32_t *slo = a.s_lo + (size_t)ks * n, *shi = a.s_hi + (size_t)ks * n;
     uint64_t *peaks = a.peaks + (size_t)ks * ((size_t)n + 1);
-    const uint32_t base = blockIdx.y * PK_SLICE;
+    const uint32_t base = (first + blockIdx.y) * PK_SLICE;
     for (uint32_t i = tid; i <= PK_SLICE; i += PK_THREADS) diff[i] = 0;
     __syncthreads();
     for (uint32_t j = tid; j < k0; j += PK_THREADS) {
@@ -531,7 +532,7 @@ __global__ __launch_bounds__(PK_THREADS) void k_sel_peaks(SelectArgs a)
     }
     mx = wave_max_u64(mx);
     // steps past the end are zero and stay out of every window (a window ends before T)
-    const uint32_t w0 = base + wave * WAVE * PK_PER, w1 = min(T, w0 + WAVE * PK_PER);
+    const uint32_t w0 = base + wave * WAVE * PK_PER, w1 = w0 + min(T - w0, (uint32_t)(WAVE * PK_PER));
     uint64_t off = 0;                            // what the whole span has been lowered by and x does not show yet
     for (uint32_t kb = k0; kb < k1; kb += WAVE) {
         // lane j: the pick that leads from peak kb+j to the next one
@@ -566,7 +567,7 @@ __global__ __launch_bounds__(PK_THREADS) void k_sel_peaks(SelectArgs a)
         __syncthreads();
         if (wave == 0 && lane < cnt) {
             for (int q = 1; q < PK_WAVES; ++q) res = umax64(res, part[q][lane]);
-            if (gridDim.y == 1) peaks[kj] = res;
+            if (T <= PK_SLICE) peaks[kj] = res;
             else atomicMax((unsigned long long *)&peaks[kj], (unsigned long long)res);
         }
         __syncthreads();
@@ -635,12 +636,15 @@ hipError_t launch_select_swaps(const SelectArgs &a, bool gather, hipStream_t st)
     }
     // the number of candidates is not known here: enough workgroups for many, and few enough that the idle ones of a
     // small list cost little
-    const uint32_t groups = (a.n + ORD_THREADS - 1) / ORD_THREADS, slices = (a.T + PK_SLICE - 1) / PK_SLICE;
+    const uint32_t groups = (a.n + ORD_THREADS - 1) / ORD_THREADS, slices = (a.T - 1) / PK_SLICE + 1;
     hipLaunchKernelGGL(k_sel_order, dim3(groups < 128 ? groups : 128, a.K), dim3(ORD_THREADS), 0, st, a);
     uint32_t stretches = 8192 / (slices * a.K);
     stretches = stretches < 32 ? 32 : stretches > 256 ? 256 : stretches;
     const uint32_t most = a.n / PK_MIN_STRETCH + 1;
-    hipLaunchKernelGGL(k_sel_peaks, dim3(stretches < most ? stretches : most, slices, a.K), dim3(PK_THREADS), 0, st, a);
+    if (stretches > most) stretches = most;
+    for (uint32_t first = 0; first < slices; first += PK_MAX_SLICES)
+        hipLaunchKernelGGL(k_sel_peaks, dim3(stretches, slices - first < PK_MAX_SLICES ? slices - first : PK_MAX_SLICES, a.K),
+                           dim3(PK_THREADS), 0, st, a, first);
     hipLaunchKernelGGL(k_sel_limits, dim3(a.K), dim3(256), 0, st, a);
     return hipGetLastError();
 }

@@ -123,6 +123,14 @@ def test_select_with_a_load_that_does_not_contain_the_candidates(lap, n, T):
     assert u64(got["peaks"])[0].tolist() == peaks
 
 
+def test_select_on_a_time_line_of_134_million_steps(lap, oracle_mod):
+    """more slices of 2048 steps than a grid's y dimension takes (65 536); the peak lies in the last of them"""
+    T = 65537 * 2048 + 500
+    tr = mk_trace([8 << 20, 5 << 20, 3 << 20], [0, T - 3000, T - 450], [T, T - 10, T - 100], T=T,
+                  gap_lo=[1, T - 2990, T - 440], gap_hi=[T - 2, T - 20, T - 200])
+    assert _check(lap, oracle_mod, tr, 64.0, 1, [2], [9 << 20], want_rank=False) == 3
+
+
 def test_select_time_where_scores_lie_close_together(lap):
     """SWDOA orders of 4000 candidates.  With idle intervals spread over many steps the leading candidates lead for many
     picks (measured: under 1 us each); where all have one interval, or the caller's load does not contain them, a pick
