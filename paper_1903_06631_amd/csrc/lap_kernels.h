@@ -39,15 +39,21 @@ constexpr uint32_t PLAN_CL = 6;
 // steps ...
 constexpr uint32_t PLAN_REG_MAX_VARS = 112 * 256;
 inline bool reg_may_place(uint32_t n, uint32_t T) { return n <= PLAN_REG_MAX_VARS && T <= 0xFFFFu; }
-// ... and whether they are, as far as the trace decides it.  Where lifetimes are short enough for the
-// per-step lists those are faster, except for a few hundred variables (shapes of mostly one-step
-// variables, 256 orderings: 500 of them 0.19 ms in registers and 0.30 ms with the lists, 1000 of
-// them 0.57 and 0.44 ms, 6000 of them 7.1 and 2.9 ms).
-constexpr uint32_t PLAN_REG_ALWAYS_VARS = 3 * 256;
-__device__ __forceinline__ bool reg_places(const PlanHeader *hdr, uint32_t n, bool best_fit)
+// ... and whether they are, as far as the trace decides it.  Where lifetimes are short enough for the per-step lists, a
+// one-step variable costs those next to nothing and a multi-step one 3 to 5 us, while every variable costs the
+// registers 0.25 us and more for each row it asks.  Up to three rows the registers win from a share of multi-step
+// variables on that grows with the rows (times in registers over times with the lists, 16 best-fit orderings: 256
+// variables, one row, 1.16 at 2 % and 0.89 at 4 %; 512 variables 1.12 and 0.87 at 4 and 6 %; 768 variables 1.09 and
+// 0.90 at 6 and 8 %), and is that of one row less where orderings share the compute units (1024 of them: 256 variables
+// 0.89 at 2 %, 512 variables 1.02 and 0.91 at 2 and 4 %, 768 variables 1.08 and 0.98 at 4 and 6 %).  Larger traces
+// always go to the lists (6000 variables, mostly one-step: 7.1 and 2.9 ms).  Up to 128 variables there is nothing in it
+// (150 of them at 2 %: 0.97 to 1.09), the registers take all and the lists' launch is saved.
+constexpr uint32_t PLAN_REG_ALWAYS_VARS = 128, PLAN_REG_FEW_VARS = 3 * 256;
+__device__ __forceinline__ bool reg_places(const PlanHeader *hdr, uint32_t n, uint32_t B, bool best_fit)
 {
     if (!hdr->fast || (hdr->mode2 && !best_fit)) return false;
-    return !hdr->mode1 || n <= PLAN_REG_ALWAYS_VARS;
+    if (!hdr->mode1 || n <= PLAN_REG_ALWAYS_VARS) return true;
+    return n <= PLAN_REG_FEW_VARS && hdr->n_multi * 40u >= n * ((n + 255) / 256 - (B > 512 ? 1u : 0u));
 }
 
 hipError_t launch_fill_u64(uint64_t *p, size_t n, uint64_t v, hipStream_t st);
