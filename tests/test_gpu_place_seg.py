@@ -155,26 +155,30 @@ def test_segment_lists_configs(lap, oracle_mod, cfg):
     _check(lap, oracle_mod, tr, kinds[:32], seeds[:32], fits=[1] * min(32, B))
 
 
-def test_default_threshold_keeps_small_traces_on_the_sweep(lap, oracle_mod):
-    """Same results whichever structure places the trace: the default threshold against the forced path."""
-    tr = _long_lived(30, 2000, 300)
+# 28 700 variables: too many for the register kernel, so that what is not placed by the segment lists is swept
+@pytest.mark.parametrize("n,T,max_life", [(2000, 300, None), (28700, 3000, 40)])
+def test_default_threshold_keeps_small_traces_off_the_segment_lists(lap, oracle_mod, n, T, max_life):
+    """Same results whichever structure places the trace: the default threshold (registers or sweep) against the forced
+    path."""
+    tr = _long_lived(30, n, T, max_life=max_life)
     kinds, seeds = make_orderings(16)
     dt = lap.DeviceTrace(tr)
     forced = u64(lap.plan_pool(dt, kinds, seeds)["all_offsets"])
     lap.set_option(lap.OPT_SEG_MIN_VARS, lap.SEG_MIN_VARS_DEFAULT)
     try:
-        swept = u64(lap.plan_pool(dt, kinds, seeds)["all_offsets"])
+        default = u64(lap.plan_pool(dt, kinds, seeds)["all_offsets"])
     finally:
         lap.set_option(lap.OPT_SEG_MIN_VARS, 0)
-    assert np.array_equal(forced, swept)
+    assert np.array_equal(forced, default)
 
 
-def test_trial_run_hands_random_lifetimes_back_to_the_sweep(lap, oracle_mod):
-    """With the trial on, a trace with lifetimes at random (searches of many rounds) is placed by the sweep
-    and a nested one by the lists; the offsets are the oracle's either way."""
+@pytest.mark.parametrize("n,T,max_life", [(3000, 900, None), (28700, 3000, 40)])
+def test_trial_run_hands_random_lifetimes_back(lap, oracle_mod, n, T, max_life):
+    """With the trial on, a trace with lifetimes at random (searches of many rounds) is placed by the registers or the
+    sweep and a nested one by the lists; the offsets are the oracle's either way."""
     lap.set_option(lap.OPT_SEG_TRIAL_PERCENT, lap.SEG_TRIAL_PERCENT_DEFAULT)
     try:
-        tr = _long_lived(40, 3000, 900)
+        tr = _long_lived(40, n, T, max_life=max_life)
         kinds, seeds = make_orderings(8)
         _check(lap, oracle_mod, tr, kinds, seeds)
         _check(lap, oracle_mod, make_config(3), kinds, seeds)
