@@ -61,8 +61,8 @@ def read_profile_values(path):
 # dominant placement kernel of every benchmark configuration: its name, the sources it is built
 # from, and the stem of its counter summaries under profiles/
 PLACE_KERNEL = {
-    5: ("k_place_fast<u32,false>", ("place_fast.hip", "lap_dev.h"), "k_place_fast_transformer_B1024"),
-    4: ("k_place_seg", ("place_seg.hip", "seg_core.h", "lap_dev.h"), "k_place_seg_deepchain_B4096"),
+    5: ("k_place_fast<unsigned int, 4, true, 0>", ("place_fast.hip", "block_rows.h", "lap_dev.h"), "k_place_fast_transformer_B1024"),
+    4: ("k_place_seg<false>", ("place_seg.hip", "seg_core.h", "lap_dev.h"), "k_place_seg_deepchain_B4096"),
 }
 
 
@@ -155,7 +155,7 @@ def main() -> int:
     # command, kept under profiles/ with a stamp of the kernel source: if the source has changed
     # since, the bytes are not used and achieved / frac are null.
     k_ms = float(np.mean(place_ms))
-    k_name, k_src, k_stem = PLACE_KERNEL.get(args.config, ("k_place_*", ("place_fast.hip", "lap_dev.h"), None))
+    k_name, k_src, k_stem = PLACE_KERNEL.get(args.config, ("k_place_*", ("place_fast.hip", "block_rows.h", "lap_dev.h"), None))
     traffic, counters = None, {}
     if k_stem and B == tr.meta["B"]:
         tv = read_profile_values(os.path.join(ROOT, "profiles", k_stem + "_hbm_traffic.txt"))

@@ -30,7 +30,8 @@ def test_every_stamped_summary_matches_the_kernel_sources():
     """also the summaries bench.py does not read (the best-fit kernel's): a stamp names the sources of the
     kernel family the file is named for"""
     bench = _bench()
-    families = {"k_place_fast": ("place_fast.hip", "lap_dev.h"), "k_place_seg": ("place_seg.hip", "seg_core.h", "lap_dev.h")}
+    families = {"k_place_fast": ("place_fast.hip", "block_rows.h", "lap_dev.h"),
+                "k_place_seg": ("place_seg.hip", "seg_core.h", "lap_dev.h")}
     seen = 0
     for name in sorted(os.listdir(os.path.join(ROOT, "profiles"))):
         tv = bench.read_profile_values(os.path.join(ROOT, "profiles", name))
@@ -41,6 +42,17 @@ def test_every_stamped_summary_matches_the_kernel_sources():
         assert tv["source_sha256_16"] == bench.source_stamp(*families[fam[0]]), f"profiles/{name}: measure again"
         seen += 1
     assert seen >= 6
+
+
+def test_stamps_cover_the_kernel_headers():
+    """a stamped kernel's own headers with device code are part of its stamp (lap_kernels.h holds launch wrappers)"""
+    import re
+    bench = _bench()
+    for kernel, sources, stem in bench.PLACE_KERNEL.values():
+        for name in sources:
+            with open(os.path.join(ROOT, "paper_1903_06631_amd", "csrc", name)) as fh:
+                used = set(re.findall(r'#include "([^"]+)"', fh.read()))
+            assert used <= set(sources) | {"lap_kernels.h"}, f"{kernel}: {name} is built from {used}"
 
 
 def test_profiles_hold_text_summaries_only():
