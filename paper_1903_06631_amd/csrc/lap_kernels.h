@@ -31,7 +31,7 @@ struct PlanHeader {
     uint32_t seg_trial_rounds;     // trial run: search rounds of its multi-step variables, summed
     uint32_t seg_trial_vars;       // ... and how many those were
     uint32_t seg_next;             // next ordering to hand to a workgroup of the segment kernel
-    uint32_t seg_pad;
+    uint32_t reg;                  // 1: the register kernel suits the trace (if it may be used at all)
 };
 constexpr uint32_t PLAN_CL = 6;
 
@@ -39,21 +39,24 @@ constexpr uint32_t PLAN_CL = 6;
 // steps ...
 constexpr uint32_t PLAN_REG_MAX_VARS = 112 * 256;
 inline bool reg_may_place(uint32_t n, uint32_t T) { return n <= PLAN_REG_MAX_VARS && T <= 0xFFFFu; }
-// ... and whether they are, as far as the trace decides it.  Where lifetimes are short enough for the per-step lists, a
-// one-step variable costs those next to nothing and a multi-step one 3 to 5 us, while every variable costs the
-// registers 0.25 us and more for each row it asks.  Up to three rows the registers win from a share of multi-step
-// variables on that grows with the rows (times in registers over times with the lists, 16 best-fit orderings: 256
-// variables, one row, 1.16 at 2 % and 0.89 at 4 %; 512 variables 1.12 and 0.87 at 4 and 6 %; 768 variables 1.09 and
-// 0.90 at 6 and 8 %), and is that of one row less where orderings share the compute units (1024 of them: 256 variables
-// 0.89 at 2 %, 512 variables 1.02 and 0.91 at 2 and 4 %, 768 variables 1.08 and 0.98 at 4 and 6 %).  Larger traces
-// always go to the lists (6000 variables, mostly one-step: 7.1 and 2.9 ms).  Up to 128 variables there is nothing in it
-// (150 of them at 2 %: 0.97 to 1.09), the registers take all and the lists' launch is saved.
+// ... and whether they are, as far as the trace decides it (k_plan_prep2, into the header).  Where lifetimes are short
+// enough for the per-step lists, a one-step variable costs those next to nothing and a multi-step one 3 to 5 us, while
+// every variable costs the registers 0.25 us and more for each row it asks.  Up to three rows the registers win from a
+// share of multi-step variables on that grows with the rows (times in registers over times with the lists, 16 best-fit
+// orderings: 256 variables, one row, 1.16 at 2 % and 0.89 at 4 %; 512 variables 1.12 and 0.87 at 4 and 6 %; 768
+// variables 1.09 and 0.90 at 6 and 8 %), and is that of one row less where orderings share the compute units (1024 of
+// them: 256 variables 0.89 at 2 %, 512 variables 1.02 and 0.91 at 2 and 4 %, 768 variables 1.08 and 0.98 at 4 and 6 %).
+// Larger traces always go to the lists (6000 variables, mostly one-step: 7.1 and 2.9 ms).  Up to 128 variables there is
+// nothing in it (150 of them at 2 %: 0.97 to 1.09), the registers take all and the lists' launch is saved.
 constexpr uint32_t PLAN_REG_ALWAYS_VARS = 128, PLAN_REG_FEW_VARS = 3 * 256;
-__device__ __forceinline__ bool reg_places(const PlanHeader *hdr, uint32_t n, uint32_t B, bool best_fit)
+__device__ __forceinline__ bool reg_suits(bool per_step_lists, uint32_t n, uint32_t n_multi, uint32_t B)
 {
-    if (!hdr->fast || (hdr->mode2 && !best_fit)) return false;
-    if (!hdr->mode1 || n <= PLAN_REG_ALWAYS_VARS) return true;
-    return n <= PLAN_REG_FEW_VARS && hdr->n_multi * 40u >= n * ((n + 255) / 256 - (B > 512 ? 1u : 0u));
+    if (!per_step_lists || n <= PLAN_REG_ALWAYS_VARS) return true;
+    return n <= PLAN_REG_FEW_VARS && n_multi * 40u >= n * ((n + 255) / 256 - (B > 512 ? 1u : 0u));
+}
+__device__ __forceinline__ bool reg_places(const PlanHeader *hdr, bool best_fit)
+{
+    return hdr->fast && hdr->reg && !(hdr->mode2 && !best_fit);
 }
 
 hipError_t launch_fill_u64(uint64_t *p, size_t n, uint64_t v, hipStream_t st);
