@@ -11,7 +11,7 @@
 // launches that fill the chip: tile totals, prefix hashes, candidates, and the check, whose last
 // workgroup to finish writes the answer -- or, when the hashes of a wrong candidate agreed, goes on
 // by itself.  What bounds them is the latency of four dependent launches: 2 000 003 requests (16 MB
-// of tokens and as much of hashes, all of it in the last-level cache) take 39 us
+// of tokens and as much of hashes, all of it in the last-level cache) take 38 us
 // (7.5 ms when one workgroup did all of it).
 #include "lap_dev.h"
 #include "lap_kernels.h"

@@ -10,8 +10,9 @@
 //
 //   ALL    placed blocks with their lifetimes, sorted by offset: in registers, a row of 256 per
 //          wave (block_rows.h), where only multi-step blocks enter it and there are few enough of
-//          them (up to 256 per wave, what a transformer's iteration has: a query is then one barrier,
-//          0.5 us, instead of a sweep through global memory, 2 us); else `main` and
+//          them (up to 256 per wave: a transformer's iteration of 200 000 variables has about a
+//          thousand, on either side of what four waves take, and eight take them all; a query is then
+//          one barrier, 0.5 us, instead of a sweep through global memory, 2 us); else `main` and
 //          `recent` (global memory, two buffers each, merged out of place) and
 //          `pending` (LDS, unsorted, the newest).  Queried by variables that
 //          live for more than one step: all waves sweep a sorted list together,
