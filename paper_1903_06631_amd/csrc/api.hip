@@ -448,25 +448,30 @@ int lap_plan_pool(const lap_trace *tr, const lap_ordering *ords, uint32_t B, uin
     static_assert(sizeof(lap::PlanHeader) % 8 == 0, "header is cleared in 64-bit words");
     LAP_HIP(lap::launch_fill_u64((uint64_t *)hdr, sizeof(lap::PlanHeader) / 8, 0, st));
     LAP_HIP(lap::launch_fill_u64((uint64_t *)cntd, ((size_t)T + 2) / 2, 0, st));
+    const uint64_t seg_min_vars = g_seg_min_vars;
+    const bool may_seg = n >= seg_min_vars;         // below, the header rules the segment lists out: no launches for them
     LAP_HIP(lap::launch_plan_prep(n, T, B, tr->size, tr->alloc, tr->free_, cntd, lstart, hdr, vrec,
-                                  seg_pool_entries(n, B), g_seg_min_vars, st));
-    LAP_HIP(lap::launch_seg_prep(n, T, B, tr->alloc, tr->free_, hdr, seg_cnt, seg_lst, (uint32_t)dir_cap,
-                                 seg_pool_entries(n, B), st));
+                                  seg_pool_entries(n, B), seg_min_vars, st));
+    if (may_seg)
+        LAP_HIP(lap::launch_seg_prep(n, T, B, tr->alloc, tr->free_, hdr, seg_cnt, seg_lst, (uint32_t)dir_cap,
+                                     seg_pool_entries(n, B), st));
     {
         int trial_b = -1;                   // the first first-fit ordering shows how the segment lists' searches go
         for (uint32_t b = 0; b < B && trial_b < 0; ++b)
             if (ords[b].fit == LAP_FIT_FIRST) trial_b = (int)b;
         ProfScope p(LAP_K_PLACE, st);
-        LAP_HIP(lap::launch_seg_trial(n, T, B, perm, fits, trial_b, (uint32_t)g_seg_trial_percent, hdr, vrec, seg_lst,
-                                      seg_pool, seg_len, (uint32_t)dir_cap, offs, fps, ticks, st));
+        if (may_seg)
+            LAP_HIP(lap::launch_seg_trial(n, T, B, perm, fits, trial_b, (uint32_t)g_seg_trial_percent, hdr, vrec, seg_lst,
+                                          seg_pool, seg_len, (uint32_t)dir_cap, offs, fps, ticks, st));
         LAP_HIP(lap::launch_place_reg(n, T, B, perm, fits, hdr, vrec, offs, fps, ticks, st));
         LAP_HIP(lap::launch_place_fast(n, T, B, tr->size, tr->alloc, tr->free_, perm, fits, any_first, any_best, hdr, vrec,
                                        lstart, f_oe, f_life, f_oe2,
                                        f_life2, f_roe, f_rlife, f_roe2, f_rlife2, f_L, capL, l_ns, l_nu, offs, fps, ticks, st));
         LAP_HIP(lap::launch_place_wide(n, B, tr->size, tr->alloc, tr->free_, perm, fits, hdr, m_off, m_end, m_life, offs,
                                        fps, ticks, st));
-        LAP_HIP(lap::launch_place_seg(n, T, B, perm, fits, any_first, hdr, vrec, seg_lst, seg_pool, seg_len,
-                                      (uint32_t)dir_cap, offs, fps, ticks, st));
+        if (may_seg)
+            LAP_HIP(lap::launch_place_seg(n, T, B, perm, fits, any_first, hdr, vrec, seg_lst, seg_pool, seg_len,
+                                          (uint32_t)dir_cap, offs, fps, ticks, st));
     }
     LAP_HIP(lap::launch_select(n, B, fps, offs, perm, best_footprint, best_ordering, best_offsets, all_offsets, st));
     return LAP_OK;
