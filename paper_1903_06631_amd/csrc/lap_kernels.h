@@ -18,7 +18,7 @@ struct PlanHeader {
     uint32_t n_multi;              // variables that live for more than one step
     uint32_t shift;                // log2 of the offset granule: ctz(or_sizes)
     uint32_t fast;                 // 1: sum_sizes >> shift fits 32 bits -> packed 32-bit path
-    uint32_t mode1;                // 1: per-step lists are in use (sum of lifetimes <= PLAN_CL * N)
+    uint32_t mode1;                // 1: per-step lists are in use (sum of lifetimes <= PLAN_CL * N, unless registers suit the trace better)
     uint32_t part[2];              // placement workgroups that have started, per fit policy
     uint32_t progress[2];          // their progress, in units of 512 ranks, summed
     // segment lists (place_seg.hip), used when per-step lists are not and the pool has room
@@ -31,7 +31,7 @@ struct PlanHeader {
     uint32_t seg_trial_rounds;     // trial run: search rounds of its multi-step variables, summed
     uint32_t seg_trial_vars;       // ... and how many those were
     uint32_t seg_next;             // next ordering to hand to a workgroup of the segment kernel
-    uint32_t reg;                  // 1: the register kernel suits the trace (if it may be used at all)
+    uint32_t seg_pad;
 };
 constexpr uint32_t PLAN_CL = 6;
 
@@ -39,24 +39,25 @@ constexpr uint32_t PLAN_CL = 6;
 // steps ...
 constexpr uint32_t PLAN_REG_MAX_VARS = 112 * 256;
 inline bool reg_may_place(uint32_t n, uint32_t T) { return n <= PLAN_REG_MAX_VARS && T <= 0xFFFFu; }
-// ... and whether they are, as far as the trace decides it (k_plan_prep2, into the header).  Where lifetimes are short
-// enough for the per-step lists, a one-step variable costs those next to nothing and a multi-step one 3 to 5 us, while
-// every variable costs the registers 0.25 us and more for each row it asks.  Up to three rows the registers win from a
-// share of multi-step variables on that grows with the rows (times in registers over times with the lists, 16 best-fit
+// ... and whether they are, as far as the trace decides it: where per-step lists are not in use.  Up to 128 variables,
+// and up to 768 where the second rule says so (k_plan_prep2 asks it), these are not used although lifetimes are short
+// enough for them.  A one-step variable costs the lists next to nothing and a multi-step one 3 to 5 us, while every
+// variable costs the registers 0.25 us and more for each row it asks: up to three rows the registers win from a share
+// of multi-step variables on that grows with the rows (times in registers over times with the lists, 16 best-fit
 // orderings: 256 variables, one row, 1.16 at 2 % and 0.89 at 4 %; 512 variables 1.12 and 0.87 at 4 and 6 %; 768
 // variables 1.09 and 0.90 at 6 and 8 %), and is that of one row less where orderings share the compute units (1024 of
 // them: 256 variables 0.89 at 2 %, 512 variables 1.02 and 0.91 at 2 and 4 %, 768 variables 1.08 and 0.98 at 4 and 6 %).
 // Larger traces always go to the lists (6000 variables, mostly one-step: 7.1 and 2.9 ms).  Up to 128 variables there is
 // nothing in it (150 of them at 2 %: 0.97 to 1.09), the registers take all and the lists' launch is saved.
 constexpr uint32_t PLAN_REG_ALWAYS_VARS = 128, PLAN_REG_FEW_VARS = 3 * 256;
-__device__ __forceinline__ bool reg_suits(bool per_step_lists, uint32_t n, uint32_t n_multi, uint32_t B)
+__device__ __forceinline__ bool reg_places(const PlanHeader *hdr, uint32_t n, bool best_fit)
 {
-    if (!per_step_lists || n <= PLAN_REG_ALWAYS_VARS) return true;
-    return n <= PLAN_REG_FEW_VARS && n_multi * 40u >= n * ((n + 255) / 256 - (B > 512 ? 1u : 0u));
+    if (!hdr->fast || (hdr->mode2 && !best_fit)) return false;
+    return !hdr->mode1 || n <= PLAN_REG_ALWAYS_VARS;
 }
-__device__ __forceinline__ bool reg_places(const PlanHeader *hdr, bool best_fit)
+__device__ __forceinline__ bool reg_before_lists(uint32_t n, uint32_t T, uint32_t n_multi, uint32_t B)
 {
-    return hdr->fast && hdr->reg && !(hdr->mode2 && !best_fit);
+    return n <= PLAN_REG_FEW_VARS && T <= 0xFFFFu && n_multi * 40u >= n * ((n + 255) / 256 - (B > 512 ? 1u : 0u));
 }
 
 hipError_t launch_fill_u64(uint64_t *p, size_t n, uint64_t v, hipStream_t st);

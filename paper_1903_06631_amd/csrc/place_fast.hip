@@ -200,8 +200,7 @@ __global__ __launch_bounds__(PREP_THREADS) void k_plan_prep2(uint32_t n, uint32_
         const bool lists = fast && c2 <= (uint64_t)CL * n;
         hdr->shift = shift;
         hdr->fast = fast ? 1u : 0u;
-        hdr->mode1 = lists ? 1u : 0u;
-        hdr->reg = reg_suits(lists, n, hdr->n_multi, B) ? 1u : 0u;
+        hdr->mode1 = lists && !reg_before_lists(n, T, hdr->n_multi, B) ? 1u : 0u;
         // Segment lists: the width that enters the fewest blocks into lists; every list has one
         // entry more than the blocks it sees.  Taken when per-step lists are not, the trace has
         // enough variables for them to pay (below that, sweeping the sorted blocks is faster), the
@@ -1607,7 +1606,7 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
     if (!A.hdr->fast) return;               // the 64-bit kernel handles this trace
     const bool best = A.fits[blockIdx.x] != 0;
     if (POLICY != 2 && best != (POLICY == 1)) return;
-    if (A.reg && reg_places(A.hdr, best)) return;
+    if (A.reg && reg_places(A.hdr, A.n, best)) return;
     if (A.hdr->mode2 && !best) return;      // the segment kernel places the first-fit orderings of this trace
     if (POLICY == 1 || (POLICY == 2 && best)) place_ordering<LT, PW, META, true>(A, S, meta);
     else place_ordering<LT, PW, META, false>(A, S, meta);

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(NW *WAVE) void k_place_reg(RegArgs A)
 
     const uint32_t b = blockIdx.x;
     const bool best_fit = A.fits[b] != 0;
-    if (!reg_places(A.hdr, best_fit)) return;
+    if (!reg_places(A.hdr, A.n, best_fit)) return;
     const long long t_begin = wall_clock64();
     const uint32_t n = A.n, sh = A.hdr->shift;
     const int l = lane_id();
