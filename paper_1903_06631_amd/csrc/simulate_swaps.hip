@@ -189,6 +189,12 @@ __global__ __launch_bounds__(RUN_THREADS) void k_sim_run(SimArgs A)
     uint32_t *kb = A.kb + (size_t)q * A.kmax;
 
     // each planned start gives the step boundary at which the swap-in is issued
+    auto boundary = [&](uint32_t lo, uint32_t th, long long start) {
+        uint32_t l0 = 0, h0 = th;                          // last t <= th with C[t] <= start (0 if none)
+        while (l0 < h0) { const uint32_t mid = (l0 + h0 + 1) >> 1; if ((long long)A.C[mid] <= start) l0 = mid; else h0 = mid - 1; }
+        return max(l0, lo + 1);
+    };
+    uint64_t served = 0;                                   // this thread's durations, up to 2^61
     Fn carry{0, SC_POS};
     for (uint32_t base = 0; base < m; base += RUN_THREADS) {
         const uint32_t back = base + tid, jj = m - 1 - back;
@@ -200,6 +206,7 @@ __global__ __launch_bounds__(RUN_THREADS) void k_sim_run(SimArgs A)
             if (pos < k) {
                 const uint32_t v = min(list[pos], A.n - 1);
                 const long long d = (long long)sim_dur(A.size[v], A.bpus);
+                served = umin64(served + umin64((uint64_t)d, 1ull << 60), 1ull << 61);
                 on = true;
                 lo = A.step_lo[v];
                 th = A.step_hi[v] - A.hi_minus;
@@ -207,10 +214,19 @@ __global__ __launch_bounds__(RUN_THREADS) void k_sim_run(SimArgs A)
             }
         }
         const Fn g = block_scan_fn<false, RUN_WAVES>(f, carry, wtmp);
-        if (on) {
-            uint32_t l0 = 0, h0 = th;                      // last t <= th with C[t] <= start (0 if none)
-            while (l0 < h0) { const uint32_t mid = (l0 + h0 + 1) >> 1; if ((long long)A.C[mid] <= g.b) l0 = mid; else h0 = mid - 1; }
-            kb[jj] = max(l0, lo + 1);
+        if (on) kb[jj] = boundary(lo, th, g.b);
+    }
+    // The scan adds durations up.  Where they may not fit (transfers of years: 52 days in one thread's share), starts
+    // wrap around, and where they do depends on the order: one job after the other, then.
+    if (__syncthreads_or(served >= 1ull << 52) && tid == 0) {
+        long long next = SC_POS;
+        for (uint32_t jj = m; jj-- > 0;) {
+            const uint32_t pos = jobs_hi[jj];
+            if (pos >= k) continue;
+            const uint32_t v = min(list[pos], A.n - 1), th = A.step_hi[v] - A.hi_minus;
+            const long long due = (long long)A.C[th];
+            next = (long long)((uint64_t)(due < next ? due : next) - sim_dur(A.size[v], A.bpus));
+            kb[jj] = boundary(A.step_lo[v], th, next);
         }
     }
     __syncthreads();

@@ -68,6 +68,21 @@ def test_simulate_random(lap, oracle_mod, seed, n, T):
     _check(lap, oracle_mod, tr, 1.0, sl, [(len(sl), peak * 2 // 3)], use_gaps=False)
 
 
+@pytest.mark.parametrize("n,T", [(12, 20), (300, 40), (1500, 100)])
+def test_simulate_transfers_whose_times_do_not_fit_64_bits(lap, oracle_mod, n, T):
+    """sizes near the largest legal ones over the slowest links: the planned starts wrap around, as the oracle's do"""
+    rng = np.random.default_rng(n)
+    a = rng.integers(0, T - 4, n)
+    f = a + 3 + rng.integers(0, T - a - 2)
+    size = rng.integers(1 << 49, 1 << 52, n).astype(np.uint64)
+    tr = mk_trace(size, a, f, T=T, step_ns=rng.integers(1, 1 << 40, T))
+    assert oracle_mod.validate_trace(tr) == 0
+    _, peak, _ = oracle_mod.load_profile(tr)
+    sl = rng.permutation(n).astype(np.uint32)
+    for link in (0.001, 0.002, 0.05, 64.0):
+        _check(lap, oracle_mod, tr, link, sl, [(k, lim) for k in (n, n // 2, 9, 1) for lim in (peak, peak * 3 // 5, peak // 4)])
+
+
 @pytest.mark.parametrize("n,T", [(600, 255), (600, 256), (601, 257), (4000, 513), (8193, 40)])
 def test_simulate_window_edges(lap, oracle_mod, n, T):
     """steps and transfers are fetched 256 at a time, swap-in starts scanned 512 at a time, job lists built 8192 at a time"""
