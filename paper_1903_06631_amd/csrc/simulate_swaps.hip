@@ -4,8 +4,8 @@
 // swap-in stream); the result is the time lost against the plain iteration.
 //
 // The machine is sequential; the parallel dimension is the set of (swap list prefix, limit) pairs to
-// evaluate -- a sweep of limits, several priority orders -- one workgroup each, whose first wave runs
-// the machine.  Shared by all of them and built by data-parallel kernels: bytes allocated and freed per
+// evaluate -- a sweep of limits, several priority orders -- one workgroup each for the planned swap-in
+// starts and one wave each for the machine.  Shared by all of them and built by data-parallel kernels: bytes allocated and freed per
 // step, and the listed variables in swap-out order and in swap-in order (positions in the list, so
 // that "the first k of the list" is a filter).
 #include "lap_dev.h"
@@ -113,8 +113,8 @@ struct SimArgs {
 // What the machine reads next of each of its three streams.  Its state goes from event to event in
 // registers; the entries come from here, RUN_WIN of a stream fetched by the whole wave at a time, so
 // that an event waits for LDS and not for the chain jobs -> list -> size, steps in global memory.
-// All swap planning calls, 21 limits, 14 000 steps, 50 000 variables: 80.0 -> 29.4 ms; 348 steps, 3000
-// variables: 1.89 -> 0.87 ms; 64 weight vectors on 200 000 variables: 7.31 -> 5.09 ms.
+// All swap planning calls, 21 limits, 14 000 steps, 50 000 variables: 80.0 -> 28.8 ms; 348 steps, 3000
+// variables: 1.89 -> 0.86 ms; 64 weight vectors on 200 000 variables: 7.31 -> 5.08 ms.
 struct SimWin {
     uint64_t need[RUN_WIN], rel[RUN_WIN], dt[RUN_WIN];
     uint64_t osize[RUN_WIN], odur[RUN_WIN], okey[RUN_WIN];      // key: step << 32 | variable, the order of the jobs
@@ -172,28 +172,25 @@ __device__ uint32_t win_fill(const SimArgs &A, const uint32_t *jobs, const uint3
     return cnt;
 }
 
-// One run.  First the plan's swap-in starts, from the last access backwards, which are a scan (stream_scan.h):
-// all threads, RUN_THREADS jobs a round.  Then the first wave runs the machine, all lanes with the same state.
-// Transfers are served in order, so "the swap-out of this variable is done" is a comparison of its key with
-// that of the last one done, and "the swap-in is issued" one of the largest issue boundary up to it.
-// Bound by the chain of a few hundred cycles per event.
-__global__ __launch_bounds__(RUN_THREADS) void k_sim_run(SimArgs A)
+// last step boundary t <= th with C[t] <= start (0 if none), and not before lo + 1
+__device__ __forceinline__ uint32_t sim_boundary(const uint64_t *C, uint32_t lo, uint32_t th, long long start)
 {
-    __shared__ SimWin W;
+    uint32_t l0 = 0, h0 = th;
+    while (l0 < h0) { const uint32_t mid = (l0 + h0 + 1) >> 1; if ((long long)C[mid] <= start) l0 = mid; else h0 = mid - 1; }
+    return max(l0, lo + 1);
+}
+
+// The plan's swap-in starts of one run, from the last access backwards, which are a scan (stream_scan.h): RUN_THREADS
+// jobs a round.  Each gives the step boundary at which the swap-in is issued.
+__global__ __launch_bounds__(RUN_THREADS) void k_sim_starts(SimArgs A)
+{
     __shared__ Fn wtmp[RUN_WAVES];
     const uint32_t q = blockIdx.x, tid = threadIdx.x;
     const size_t row = A.per_run_lists ? (size_t)q * A.n : 0;
-    const uint32_t *list = A.list + row, *jobs_lo = A.jobs_lo + row, *jobs_hi = A.jobs_hi + row;
-    const uint32_t k = A.prefix[q], m = A.m[A.per_run_lists ? q : 0], T = A.T;
-    const uint64_t limit = A.limits[q];
+    const uint32_t *list = A.list + row, *jobs_hi = A.jobs_hi + row;
+    const uint32_t k = A.prefix[q], m = A.m[A.per_run_lists ? q : 0];
     uint32_t *kb = A.kb + (size_t)q * A.kmax;
 
-    // each planned start gives the step boundary at which the swap-in is issued
-    auto boundary = [&](uint32_t lo, uint32_t th, long long start) {
-        uint32_t l0 = 0, h0 = th;                          // last t <= th with C[t] <= start (0 if none)
-        while (l0 < h0) { const uint32_t mid = (l0 + h0 + 1) >> 1; if ((long long)A.C[mid] <= start) l0 = mid; else h0 = mid - 1; }
-        return max(l0, lo + 1);
-    };
     uint64_t served = 0;                                   // this thread's durations, up to 2^61
     Fn carry{0, SC_POS};
     for (uint32_t base = 0; base < m; base += RUN_THREADS) {
@@ -214,7 +211,7 @@ __global__ __launch_bounds__(RUN_THREADS) void k_sim_run(SimArgs A)
             }
         }
         const Fn g = block_scan_fn<false, RUN_WAVES>(f, carry, wtmp);
-        if (on) kb[jj] = boundary(lo, th, g.b);
+        if (on) kb[jj] = sim_boundary(A.C, lo, th, g.b);
     }
     // The scan adds durations up.  Where they may not fit (transfers of years: 52 days in one thread's share), starts
     // wrap around, and where they do depends on the order: one job after the other, then.
@@ -226,11 +223,24 @@ __global__ __launch_bounds__(RUN_THREADS) void k_sim_run(SimArgs A)
             const uint32_t v = min(list[pos], A.n - 1), th = A.step_hi[v] - A.hi_minus;
             const long long due = (long long)A.C[th];
             next = (long long)((uint64_t)(due < next ? due : next) - sim_dur(A.size[v], A.bpus));
-            kb[jj] = boundary(A.step_lo[v], th, next);
+            kb[jj] = sim_boundary(A.C, A.step_lo[v], th, next);
         }
     }
-    __syncthreads();
-    if (tid >= WAVE) return;
+}
+
+// The machine of one run, by one wave, all lanes with the same state.  Transfers are served in order, so "the swap-out
+// of this variable is done" is a comparison of its key with that of the last one done, and "the swap-in is issued" one of
+// the largest issue boundary up to it.  Bound by the chain of one event: 370 ns each (200 000 steps, 74 ms; 77 ms in one
+// kernel with the scan, whose state it then carried along).
+__global__ __launch_bounds__(WAVE) void k_sim_run(SimArgs A)
+{
+    __shared__ SimWin W;
+    const uint32_t q = blockIdx.x, tid = threadIdx.x;
+    const size_t row = A.per_run_lists ? (size_t)q * A.n : 0;
+    const uint32_t *list = A.list + row, *jobs_lo = A.jobs_lo + row, *jobs_hi = A.jobs_hi + row;
+    const uint32_t k = A.prefix[q], m = A.m[A.per_run_lists ? q : 0], T = A.T;
+    const uint64_t limit = A.limits[q];
+    const uint32_t *kb = A.kb + (size_t)q * A.kmax;
 
     uint64_t now = 0, R = 0, peak = 0;
     uint32_t t = 0, nforced = 0;                           // t is also the last step boundary reached
@@ -360,7 +370,8 @@ hipError_t launch_simulate_swaps(uint32_t n, uint32_t T, uint32_t Q, uint32_t km
               (const unsigned long long *)rel, list, jobs_lo, jobs_hi, m, prefix, limits, kb,
               n_listed ? 1u : 0u, bpus,
               total_ns, overhead_ns, peak_resident, forced};
-    hipLaunchKernelGGL(k_sim_run, dim3(Q), dim3(RUN_THREADS), 0, st, A);
+    hipLaunchKernelGGL(k_sim_starts, dim3(Q), dim3(RUN_THREADS), 0, st, A);
+    hipLaunchKernelGGL(k_sim_run, dim3(Q), dim3(WAVE), 0, st, A);
     return hipGetLastError();
 }
 
