@@ -18,7 +18,7 @@ struct PlanHeader {
     uint32_t n_multi;              // variables that live for more than one step
     uint32_t shift;                // log2 of the offset granule: ctz(or_sizes)
     uint32_t fast;                 // 1: sum_sizes >> shift fits 32 bits -> packed 32-bit path
-    uint32_t mode1;                // 1: per-step lists are in use (sum of lifetimes <= PLAN_CL * N, unless registers suit the trace better)
+    uint32_t mode1;                // 1: per-step lists are in use (sum of lifetimes <= PLAN_CL * N, and not reg_before_lists)
     uint32_t part[2];              // placement workgroups that have started, per fit policy
     uint32_t progress[2];          // their progress, in units of 512 ranks, summed
     // segment lists (place_seg.hip), used when per-step lists are not and the pool has room

@@ -5,9 +5,9 @@
 //
 // The machine is sequential; the parallel dimension is the set of (swap list prefix, limit) pairs to
 // evaluate -- a sweep of limits, several priority orders -- one workgroup each for the planned swap-in
-// starts and one wave each for the machine.  Shared by all of them and built by data-parallel kernels: bytes allocated and freed per
-// step, and the listed variables in swap-out order and in swap-in order (positions in the list, so
-// that "the first k of the list" is a filter).
+// starts and one wave each for the machine.  Shared by all of them and built by data-parallel kernels:
+// bytes allocated and freed per step, and the listed variables in swap-out order and in swap-in order
+// (positions in the list, so that "the first k of the list" is a filter).
 #include "lap_dev.h"
 #include "lap_kernels.h"
 #include "stream_scan.h"
