@@ -10,6 +10,7 @@
 
 #include "lap_dev.h"
 #include "lap_kernels.h"
+#include "step_runs.h"
 
 namespace lap {
 
@@ -42,10 +43,13 @@ __global__ __launch_bounds__(256) void k_delta_lds(uint32_t n, uint32_t nbins,
     for (uint32_t i = threadIdx.x; i < nbins; i += blockDim.x) bins[i] = 0;
     __syncthreads();
     const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const uint64_t s = size[i];
-        atomicAdd(&bins[alloc[i]], (unsigned long long)s);
-        atomicAdd(&bins[free_[i]], (unsigned long long)(0ull - s));
+    for (uint64_t base = (uint64_t)blockIdx.x * blockDim.x; base < n; base += stride) {
+        const uint64_t i = base + threadIdx.x;
+        const bool in = i < n;
+        const uint64_t s = in ? size[i] : 0;
+        const auto add = [&](uint32_t t, uint64_t v) { atomicAdd(&bins[t], (unsigned long long)v); };
+        wave_add_runs(in ? alloc[i] : NO_KEY, s, add);
+        wave_add_runs(in ? free_[i] : NO_KEY, 0ull - s, add);
     }
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < nbins; i += blockDim.x) {
@@ -57,7 +61,11 @@ __global__ __launch_bounds__(256) void k_delta_lds(uint32_t n, uint32_t nbins,
 // Time-local variant for long time lines: a workgroup owns 4096 consecutive variables, reads
 // them once (16-byte vector loads, kept in registers), finds the step range their events
 // fall into and, when that range fits the LDS bins, accumulates there and flushes the bins
-// with global atomics; otherwise it adds to global memory directly.
+// with global atomics; otherwise it adds to global memory directly.  Bound by the memory it reads once
+// runs of equal steps are summed before they reach the bins: 50 million variables in the order in which
+// they are allocated, about 345 a step, take 136 us = 5.9 TB/s (340 us when every variable added to the
+// bins itself and the LDS served a wave's adds one by one); 134 million with temporaries at random
+// steps, where few neighbours agree, 390 us either way.
 constexpr int DW_THREADS = 256;
 constexpr int DW_GROUPS = 4;                       // groups of 4 variables per thread
 constexpr uint32_t DW_PER_BLOCK = DW_THREADS * DW_GROUPS * 4;
@@ -113,14 +121,28 @@ __global__ __launch_bounds__(DW_THREADS) void k_delta_window(uint32_t n, uint32_
         const uint32_t nb = hi - lo + 1;
         for (uint32_t i = threadIdx.x; i < nb; i += blockDim.x) bins[i] = 0;
         __syncthreads();
+        const auto add = [&](uint32_t t, uint64_t v) { atomicAdd(&bins[t - lo], (unsigned long long)v); };
+        // a lane's four neighbours first, then the lanes
+        const auto add4 = [&](const uint32_t (&t)[4], const uint64_t (&v)[4], uint64_t sign) {
+            uint32_t key = NO_KEY;
+            uint64_t sum = 0;
 #pragma unroll
-        for (int g = 0; g < DW_GROUPS; ++g)
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (sz[g][k]) {
-                    atomicAdd(&bins[al[g][k] - lo], (unsigned long long)sz[g][k]);
-                    atomicAdd(&bins[fr[g][k] - lo], (unsigned long long)(0ull - sz[g][k]));
+            for (int k = 0; k < 4; ++k) {
+                if (!v[k]) continue;
+                if (t[k] != key) {
+                    if (key != NO_KEY) add(key, (sum ^ sign) - sign);
+                    key = t[k];
+                    sum = 0;
                 }
+                sum += v[k];
+            }
+            wave_add_runs(key, (sum ^ sign) - sign, add);
+        };
+#pragma unroll
+        for (int g = 0; g < DW_GROUPS; ++g) {
+            add4(al[g], sz[g], 0);
+            add4(fr[g], sz[g], ~0ull);
+        }
         __syncthreads();
         for (uint32_t i = threadIdx.x; i < nb; i += blockDim.x) {
             const unsigned long long v = bins[i];

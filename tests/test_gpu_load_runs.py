@@ -1,0 +1,34 @@
+"""Load profile of variables that arrive in the order in which they are allocated: neighbouring lanes meet the same
+step, and the scatter kernels add runs of equal steps as one.  Both kernels (short and long time lines), run lengths on
+either side of where runs are merged, and list lengths at the edges of waves, groups and workgroups."""
+import numpy as np
+import pytest
+
+from gpu_util import u64
+from helpers import mk_trace
+
+pytestmark = pytest.mark.gpu
+
+
+# lanes of a wave form 64 / run runs (short time lines, one variable a lane) or 256 / run (long ones, four): 1 to 64
+# runs, and 32 and 33 of them
+@pytest.mark.parametrize("long_line", [False, True])
+@pytest.mark.parametrize("n,run", [(1, 1), (3, 2), (63, 64), (64, 64), (65, 2), (257, 8), (1023, 3), (1025, 1), (4095, 7),
+                                   (4096, 8), (4097, 9), (8193, 345), (20011, 16), (12288, 100000)])
+def test_load_profile_sorted_runs(oracle_mod, long_line, n, run):
+    import paper_1903_06631_amd as lap
+    rng = np.random.default_rng(n * 7 + run)
+    alloc = np.arange(n) // run
+    top = int(alloc[-1]) + 600
+    T = max(top, 8192 + 57) if long_line else min(top, 8191)
+    alloc = np.minimum(alloc, T - 1)
+    free = alloc + 1
+    far = rng.random(n) < 0.03                                     # a few live longer: they break the runs of releases
+    free[far] = np.minimum(T, free[far] + rng.integers(1, 580, int(far.sum())))
+    size = rng.integers(1, 1 << 40, n)
+    size[rng.random(n) < 0.1] = (1 << 46) + 1                      # sums of a run pass 2^53
+    tr = mk_trace(size, alloc, free, T=T)
+    got = lap.load_profile(lap.DeviceTrace(tr))
+    load, peak, at = oracle_mod.load_profile(tr)
+    assert np.array_equal(u64(got["load"]), load)
+    assert int(u64(got["peak"])[0]) == peak and int(got["t_peak"].item()) == at
