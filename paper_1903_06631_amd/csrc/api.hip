@@ -722,9 +722,10 @@ int lap_evaluate_weights(const lap_trace *tr, double link_GBps, uint64_t min_byt
     LAP_HIP(lap::launch_fill_u64((uint64_t *)posmap, ((size_t)W * N + 1) / 2, ~0ull, st));
     LAP_HIP(lap::launch_fill_u64(need, T, 0, st));
     LAP_HIP(lap::launch_fill_u64(rel, T, 0, st));
+    // (the picks' windows have served: s_lo is scratch here)
     LAP_HIP(lap::launch_simulate_swaps(n, T, W, n, tr->size, tr->alloc, tr->free_, step_lo, step_hi,
                                        tr->gap_hi ? 0u : 1u, C, need, rel, order, perm_lo, perm_hi, posmap, jobs_lo,
-                                       jobs_hi, m, n_selected, d_limits, kb, (uint64_t)bpus, total_ns,
+                                       jobs_hi, m, n_selected, d_limits, kb, s_lo, (uint64_t)bpus, total_ns,
                                        overhead_ns, peak_res, forced, st, W, n_cand));
     LAP_HIP(lap::launch_argmin_u64(W, overhead_ns, best, st));
     return LAP_OK;
@@ -851,10 +852,10 @@ int lap_simulate_swaps(const lap_trace *tr, double link_GBps, const uint32_t *sw
     LAP_HIP(lap::launch_sched_mark(n, k_max, swap_list, posmap, st));
     LAP_HIP(lap::launch_fill_u64(need, T, 0, st));
     LAP_HIP(lap::launch_fill_u64(rel, T, 0, st));
-    // the per-run regions use a stride of n entries
+    // the per-run regions use a stride of n entries; the sort's scratch has served
     LAP_HIP(lap::launch_simulate_swaps(n, T, Q, n, tr->size, tr->alloc, tr->free_, step_lo, step_hi,
                                        tr->gap_hi ? 0u : 1u, C, need, rel, swap_list, perm_lo, perm_hi, posmap,
-                                       jobs_lo, jobs_hi, m, d_prefix, d_limits, kb, (uint64_t)bpus,
+                                       jobs_lo, jobs_hi, m, d_prefix, d_limits, kb, tmp, (uint64_t)bpus,
                                        total_ns, overhead_ns, peak_resident, forced, st));
     return LAP_OK;
 }

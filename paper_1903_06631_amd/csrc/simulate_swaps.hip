@@ -10,6 +10,7 @@
 // (positions in the list, so that "the first k of the list" is a filter).
 #include "lap_dev.h"
 #include "lap_kernels.h"
+#include "step_runs.h"
 #include "stream_scan.h"
 
 namespace lap {
@@ -21,6 +22,8 @@ constexpr int RUN_THREADS = 512, RUN_WAVES = RUN_THREADS / WAVE;
 constexpr int RUN_BATCH = 4;                       // entries a lane loads side by side
 constexpr uint32_t RUN_WIN = RUN_BATCH * WAVE;     // entries of each stream held in LDS
 constexpr uint32_t SIM_NONE = 0xFFFFFFFFu;
+constexpr uint32_t SIM_NEVER = 0x7FFFFFFFu;        // what the narrow machine does not hold: times, sums of sizes, steps
+constexpr uint32_t SIM_WIDE = 64;                  // instead of a granule's shift
 
 __global__ __launch_bounds__(256) void k_sim_steps(uint32_t n, const uint64_t *__restrict__ size,
                                                    const uint32_t *__restrict__ alloc,
@@ -43,10 +46,42 @@ __global__ __launch_bounds__(256) void k_sim_mark_rows(uint32_t n, const uint32_
     if (j < *n_listed) posmap[(size_t)r * n + min(lists[(size_t)r * n + j], n - 1)] = j;
 }
 
+// The bytes resident when nothing is swapped, at their highest, and the bitwise or of all that a step allocates or
+// frees: what the machine's numbers have to hold.  One workgroup.
+__device__ void sim_extent(uint32_t T, const unsigned long long *__restrict__ need, const unsigned long long *__restrict__ rel,
+                           uint64_t *__restrict__ peak, uint64_t *__restrict__ bits)
+{
+    __shared__ uint64_t wsum[2][SIM_WAVES], wmax[SIM_WAVES], wor[SIM_WAVES];
+    const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
+    uint64_t carry = 0, mx = 0, all = 0;
+    int buf = 0;
+    for (uint64_t base = 0; base < T; base += SIM_THREADS, buf ^= 1) {
+        const uint64_t t = base + tid;
+        const uint64_t a = t < T ? need[t] : 0, r = t < T ? rel[t] : 0;
+        const uint64_t incl = wave_scan_add_dpp(a - r);
+        if (lane == WAVE - 1) wsum[buf][wave] = incl;
+        __syncthreads();
+        uint64_t at = carry + incl + r;                // during the step: what it frees is still there
+        for (int q = 0; q < SIM_WAVES; ++q) { const uint64_t x = wsum[buf][q]; if (q < (int)wave) at += x; carry += x; }
+        mx = umax64(mx, at);
+        all |= a | r;
+    }
+    mx = wave_reduce_max(mx);
+#pragma unroll
+    for (int d = WAVE / 2; d > 0; d >>= 1) all |= shfl_xor64(all, d);
+    if (lane == 0) { wmax[wave] = mx; wor[wave] = all; }
+    __syncthreads();
+    if (tid == 0) {
+        for (int q = 1; q < SIM_WAVES; ++q) { mx = umax64(mx, wmax[q]); all |= wor[q]; }
+        *peak = mx;
+        *bits = all;
+    }
+}
+
 // jobs[0..m) = list positions of the listed variables that have an idle gap, in the order of perm;
 // one workgroup per list (rows of n entries of posmap and jobs, one count each) and direction
-// (blockIdx.y: swap-outs, swap-ins).  Every round waits for two dependent loads, so a thread takes
-// SIM_PER ranks per round.
+// (blockIdx.y: swap-outs, swap-ins); place_lo: the place of a list position in jobs_lo.  Every round
+// waits for two dependent loads, so a thread takes SIM_PER ranks per round.
 __global__ __launch_bounds__(SIM_THREADS) void k_sim_jobs(uint32_t n, const uint32_t *__restrict__ perm_lo,
                                                           const uint32_t *__restrict__ perm_hi,
                                                           const uint32_t *__restrict__ posmap_all,
@@ -54,9 +89,18 @@ __global__ __launch_bounds__(SIM_THREADS) void k_sim_jobs(uint32_t n, const uint
                                                           const uint32_t *__restrict__ step_hi, uint32_t hi_minus,
                                                           uint32_t *__restrict__ jobs_lo,
                                                           uint32_t *__restrict__ jobs_hi,
-                                                          uint32_t *__restrict__ m_all)
+                                                          uint32_t *__restrict__ place_lo_all,
+                                                          uint32_t *__restrict__ m_all, uint32_t T,
+                                                          const unsigned long long *__restrict__ need,
+                                                          const unsigned long long *__restrict__ rel,
+                                                          uint64_t *__restrict__ extent_peak, uint64_t *__restrict__ extent_bits)
 {
     __shared__ uint32_t wsum[2][SIM_WAVES];
+    if (blockIdx.y == 2) {
+        if (blockIdx.x == 0) sim_extent(T, need, rel, extent_peak, extent_bits);
+        return;
+    }
+    uint32_t *place_lo = place_lo_all + (size_t)blockIdx.x * n;
     const uint32_t *perm = blockIdx.y ? perm_hi : perm_lo;
     const uint32_t *posmap = posmap_all + (size_t)blockIdx.x * n;
     uint32_t *jobs = (blockIdx.y ? jobs_hi : jobs_lo) + (size_t)blockIdx.x * n;
@@ -85,7 +129,11 @@ __global__ __launch_bounds__(SIM_THREADS) void k_sim_jobs(uint32_t n, const uint
         for (int q = 0; q < SIM_WAVES; ++q) { const uint32_t x = wsum[buf][q]; if (q < (int)wave) at += x; carry += x; }
 #pragma unroll
         for (int j = 0; j < SIM_PER; ++j) {
-            if (pos[j] != SIM_NONE) jobs[at + (uint32_t)__popcll(mine[j] & below)] = pos[j];
+            if (pos[j] != SIM_NONE) {
+                const uint32_t to = at + (uint32_t)__popcll(mine[j] & below);
+                jobs[to] = pos[j];
+                if (blockIdx.y == 0) place_lo[pos[j]] = to;
+            }
             at += (uint32_t)__popcll(mine[j]);
         }
     }
@@ -100,7 +148,7 @@ struct SimArgs {
     const uint64_t *C;
     const unsigned long long *need, *rel;
     const uint32_t *list;
-    const uint32_t *jobs_lo, *jobs_hi, *m;
+    const uint32_t *jobs_lo, *jobs_hi, *place_lo, *m;
     const uint32_t *prefix;            // [Q]
     const uint64_t *limits;            // [Q]
     uint32_t *kb;                      // [Q][kmax] issue boundary of a swap-in, by its place in jobs_hi
@@ -191,6 +239,13 @@ __global__ __launch_bounds__(RUN_THREADS) void k_sim_starts(SimArgs A)
     const uint32_t k = A.prefix[q], m = A.m[A.per_run_lists ? q : 0];
     uint32_t *kb = A.kb + (size_t)q * A.kmax;
 
+    // whether the run fits the narrow machine, and with which granule
+    __shared__ uint32_t s_shift;
+    const uint64_t extent = A.peak_resident[0], bits = A.total_ns[0];      // sim_extent left them there
+    if (tid == 0) s_shift = bits ? (uint32_t)__ffsll((unsigned long long)bits) - 1 : 0;
+    bool wide = A.T >= SIM_NEVER;
+    for (uint32_t t = tid; t < A.T; t += RUN_THREADS) wide |= A.C[t + 1] - A.C[t] - 1 >= SIM_NEVER;
+    uint64_t sizes = 0;                                    // bitwise or of this thread's
     uint64_t served = 0;                                   // this thread's durations, up to 2^61
     Fn carry{0, SC_POS};
     for (uint32_t base = 0; base < m; base += RUN_THREADS) {
@@ -204,6 +259,8 @@ __global__ __launch_bounds__(RUN_THREADS) void k_sim_starts(SimArgs A)
                 const uint32_t v = min(list[pos], A.n - 1);
                 const long long d = (long long)sim_dur(A.size[v], A.bpus);
                 served = umin64(served + umin64((uint64_t)d, 1ull << 60), 1ull << 61);
+                wide |= (uint64_t)d - 1 >= SIM_NEVER;
+                sizes |= A.size[v];
                 on = true;
                 lo = A.step_lo[v];
                 th = A.step_hi[v] - A.hi_minus;
@@ -213,6 +270,10 @@ __global__ __launch_bounds__(RUN_THREADS) void k_sim_starts(SimArgs A)
         const Fn g = block_scan_fn<false, RUN_WAVES>(f, carry, wtmp);
         if (on) kb[jj] = sim_boundary(A.C, lo, th, g.b);
     }
+    if (sizes) atomicMin(&s_shift, (uint32_t)__ffsll((unsigned long long)sizes) - 1);
+    wide = __syncthreads_or(wide) != 0;
+    // (all workgroups have read what the first run's outputs held before: they are written by the next launch)
+    if (tid == 0) A.forced[q] = wide || (extent >> s_shift) >= SIM_NEVER ? SIM_WIDE : s_shift;
     // The scan adds durations up.  Where they may not fit (transfers of years: 52 days in one thread's share), starts
     // wrap around, and where they do depends on the order: one job after the other, then.
     if (__syncthreads_or(served >= 1ull << 52) && tid == 0) {
@@ -230,11 +291,9 @@ __global__ __launch_bounds__(RUN_THREADS) void k_sim_starts(SimArgs A)
 
 // The machine of one run, by one wave, all lanes with the same state.  Transfers are served in order, so "the swap-out
 // of this variable is done" is a comparison of its key with that of the last one done, and "the swap-in is issued" one of
-// the largest issue boundary up to it.  Bound by the chain of one event: 370 ns each (200 000 steps, 74 ms; 77 ms in one
-// kernel with the scan, whose state it then carried along).
-__global__ __launch_bounds__(WAVE) void k_sim_run(SimArgs A)
+// the largest issue boundary up to it.  Here with 64 bits throughout, for what sim_run_narrow does not hold.
+__device__ void sim_run_wide(const SimArgs &A, SimWin &W)
 {
-    __shared__ SimWin W;
     const uint32_t q = blockIdx.x, tid = threadIdx.x;
     const size_t row = A.per_run_lists ? (size_t)q * A.n : 0;
     const uint32_t *list = A.list + row, *jobs_lo = A.jobs_lo + row, *jobs_hi = A.jobs_hi + row;
@@ -347,13 +406,209 @@ __global__ __launch_bounds__(WAVE) void k_sim_run(SimArgs A)
     }
 }
 
+// The same machine in scalar registers, sizes in granules and times in nanoseconds in 31 bits.  One event after the other
+// is a chain that its instructions and branches make long, not memory: 4 cycles an instruction, 17 to 24 a branch, 20 from
+// the vector to the scalar unit.  So an event is one straight line of scalar instructions.  The entries to come are in
+// vector registers, one per lane, 64 of a stream at a time by way of the window in LDS, the first of them in the highest
+// lane: the lane counts down and is negative when the chunk is used up.  Every event reads the current entry of each stream
+// from its lane whether it has changed or not, and conditions are signs, so that several are one `and`.  An actor's word
+// is its remaining time less one, and -1 when it does nothing: max(word - elapsed, -1) is the next word in all cases.
+// The limit is kept as what it leaves.
+struct NarrowWin {
+    uint32_t need[RUN_WIN], rel[RUN_WIN], dt[RUN_WIN];               // dt, like all times here, less one
+    uint32_t osize[RUN_WIN], odur[RUN_WIN], olo[RUN_WIN], oplace[RUN_WIN];
+    uint32_t isize[RUN_WIN], idur[RUN_WIN], iplace[RUN_WIN], ihi[RUN_WIN], ikb[RUN_WIN];
+};
+
+__device__ __forceinline__ bool negative(uint32_t x) { return (int32_t)x < 0; }
+// (of two and more of these the compiler makes one in the vector unit, and a detour)
+__device__ __forceinline__ uint32_t s_min(uint32_t a, uint32_t b)
+{
+    uint32_t r;
+    asm("s_min_u32 %0, %1, %2" : "=s"(r) : "s"(a), "s"(b) : "scc");
+    return r;
+}
+
+// as win_fill
+template <bool OUT>
+__device__ uint32_t narrow_fill(const SimArgs &A, const uint32_t *jobs, const uint32_t *list, const uint32_t *place_lo,
+                                const uint32_t *kb, uint32_t k, uint32_t m, uint32_t shift, uint32_t &raw, NarrowWin &W)
+{
+    const uint32_t lane = threadIdx.x & (WAVE - 1);
+    const uint64_t below = (1ull << lane) - 1ull;
+    uint32_t cnt = 0;
+    win_sync();
+    while (cnt == 0 && raw < m) {
+        uint32_t pos[RUN_BATCH], v[RUN_BATCH];
+#pragma unroll
+        for (int j = 0; j < RUN_BATCH; ++j) {
+            const uint32_t r = raw + j * WAVE + lane;
+            pos[j] = r < m ? jobs[r] : SIM_NONE;
+        }
+#pragma unroll
+        for (int j = 0; j < RUN_BATCH; ++j) v[j] = pos[j] < k ? min(list[pos[j]], A.n - 1) : 0;
+#pragma unroll
+        for (int j = 0; j < RUN_BATCH; ++j) {
+            const bool on = pos[j] < k;
+            const uint64_t who = ballot(on);
+            if (on) {
+                const uint32_t at = cnt + (uint32_t)__popcll(who & below);
+                const uint64_t sz = A.size[v[j]];
+                const uint32_t dur = (uint32_t)sim_dur(sz, A.bpus) - 1u;
+                if (OUT) {
+                    W.osize[at] = (uint32_t)(sz >> shift); W.odur[at] = dur; W.olo[at] = A.step_lo[v[j]];
+                    W.oplace[at] = raw + j * WAVE + lane;
+                } else {
+                    W.isize[at] = (uint32_t)(sz >> shift); W.idur[at] = dur; W.iplace[at] = place_lo[pos[j]];
+                    W.ihi[at] = A.step_hi[v[j]] - A.hi_minus;
+                    W.ikb[at] = kb[raw + j * WAVE + lane];
+                }
+            }
+            cnt += (uint32_t)__popcll(who);
+        }
+        raw = m - raw > RUN_WIN ? raw + RUN_WIN : m;
+    }
+    win_sync();
+    return cnt;
+}
+
+__device__ void sim_run_narrow(const SimArgs &A, uint32_t shift, NarrowWin &W)
+{
+    const uint32_t q = blockIdx.x, lane = threadIdx.x;
+    const size_t row = A.per_run_lists ? (size_t)q * A.n : 0;
+    const uint32_t *list = A.list + row, *jobs_lo = A.jobs_lo + row, *jobs_hi = A.jobs_hi + row, *place_lo = A.place_lo + row;
+    const uint32_t *kb = A.kb + (size_t)q * A.kmax;
+    const uint32_t T = A.T;
+    const uint32_t k = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.prefix[q]);
+    const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.m[A.per_run_lists ? q : 0]);
+    // all that is resident is below SIM_NEVER, so a limit beyond that is none
+    const uint32_t limit = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)umin64(A.limits[q] >> shift, SIM_NEVER));
+
+    uint32_t c_need = 0, c_rel = 0, c_dt = 0;                             // a step's time shares its word with the sign "needs nothing"
+    uint32_t c_osize = 0, c_odur = 0, c_olo = 0, c_oplace = 0;
+    uint32_t c_isize = 0, c_idur = 0, c_iplace = 0, c_ihi = 0, c_issue = 0;
+    // nothing has happened: everything is idle before its first entry
+    uint32_t t = 0, te = ~0u, oe = ~0u, ie = ~0u;                         // the step; the lanes of the current entries
+    uint32_t o_at = 0, o_cnt = 0, o_raw = 0, i_at = 0, i_cnt = 0, i_raw = 0, issued = 0, nforced = 0;
+    uint32_t step = ~0u, out = ~0u, in = ~0u;                             // the actors' words
+    uint64_t now = 0;
+    uint32_t left = limit, least = limit;                                 // what the limit leaves; its smallest after a start
+    do {
+        if (__builtin_expect(negative(te | oe | ie), 0)) {
+            if (negative(te)) {
+                if (t % RUN_WIN == 0) {
+                    win_sync();
+#pragma unroll
+                    for (int j = 0; j < RUN_BATCH; ++j) {
+                        const uint32_t e = j * WAVE + lane;
+                        if (e >= T - t) continue;
+                        const uint64_t need = A.need[t + e];
+                        W.need[e] = (uint32_t)(need >> shift);
+                        W.rel[e] = (uint32_t)(A.rel[t + e] >> shift);
+                        W.dt[e] = ((uint32_t)(A.C[t + e + 1] - A.C[t + e]) - 1u) | (need ? 0u : 1u << 31);
+                    }
+                    win_sync();
+                }
+                const uint32_t have = min(T - t, (uint32_t)WAVE), e = t % RUN_WIN + (have - 1 - min(lane, have - 1));
+                c_need = W.need[e]; c_rel = W.rel[e]; c_dt = W.dt[e];
+                te = have - 1;
+            }
+            // entries that are not there: a swap-out after all steps, a swap-in that no step waits for and that is never
+            // issued; their words stay idle
+            if (negative(oe)) {
+                if (o_at == o_cnt) { o_cnt = narrow_fill<true>(A, jobs_lo, list, place_lo, kb, k, m, shift, o_raw, W); o_at = 0; }
+                const uint32_t have = min(o_cnt - o_at, (uint32_t)WAVE), e = lane < have ? o_at + have - 1 - lane : 0;
+                c_osize = W.osize[e]; c_odur = W.odur[e];
+                c_olo = lane < have ? W.olo[e] : SIM_NEVER;
+                c_oplace = lane < have ? W.oplace[e] : SIM_NEVER;
+                oe = have ? have - 1 : 0;
+                o_at += have;
+            }
+            if (negative(ie)) {
+                if (i_at == i_cnt) { i_cnt = narrow_fill<false>(A, jobs_hi, list, place_lo, kb, k, m, shift, i_raw, W); i_at = 0; }
+                const uint32_t have = min(i_cnt - i_at, (uint32_t)WAVE), e = lane < have ? i_at + have - 1 - lane : 0;
+                c_isize = W.isize[e]; c_idur = W.idur[e]; c_iplace = W.iplace[e];
+                c_ihi = lane < have ? W.ihi[e] : SIM_NEVER;
+                // a swap-in is issued when the largest boundary up to it is reached
+                const uint32_t upto = max(wave_scan_max_u32(lane < have ? W.ikb[i_at + lane] : 0u), issued);
+                issued = read_lane(upto, WAVE - 1);
+                const uint32_t mine = (uint32_t)__shfl((int)upto, (int)(lane < have ? have - 1 - lane : 0), WAVE);
+                c_issue = lane < have ? mine : SIM_NEVER;
+                ie = have ? have - 1 : 0;
+                i_at += have;
+            }
+        }
+        uint32_t need = read_lane(c_need, (int)te), rel = read_lane(c_rel, (int)te), dt = read_lane(c_dt, (int)te);
+        uint32_t olo = read_lane(c_olo, (int)oe), odur = read_lane(c_odur, (int)oe), osize = read_lane(c_osize, (int)oe),
+                 oplace = read_lane(c_oplace, (int)oe);
+        uint32_t ihi = read_lane(c_ihi, (int)ie), issue = read_lane(c_issue, (int)ie), isize = read_lane(c_isize, (int)ie),
+                 iplace = read_lane(c_iplace, (int)ie), idur = read_lane(c_idur, (int)ie);
+        // all of them before the first scalar instruction: one that follows a read of a lane waits 20 cycles, and they
+        // would alternate
+        asm volatile("" : "+s"(need), "+s"(rel), "+s"(dt), "+s"(olo), "+s"(odur), "+s"(osize), "+s"(oplace), "+s"(ihi),
+                     "+s"(issue), "+s"(isize), "+s"(iplace), "+s"(idur));
+        // starts: swap-out, step, swap-in (its variable is out if the current swap-out is one behind it)
+        out = negative(out & (olo - t)) ? odur : out;
+        const uint32_t step_may = step & (t - ihi), after_step = left - need;
+        const uint32_t step_go = step_may & (dt | ~after_step);
+        step = negative(step_go) ? dt & SIM_NEVER : step;
+        left = negative(step_go) ? after_step : left;
+        const uint32_t in_may = in & ~(t - issue) & (iplace - oplace), after_in = left - isize;
+        const uint32_t in_go = in_may & ~after_in;
+        in = negative(in_go) ? idur : in;
+        left = negative(in_go) ? after_in : left;
+        uint32_t soon = s_min(s_min(step, out), in);
+        if (__builtin_expect(negative(soon), 0)) {
+            // nothing will change by itself: the limit is overridden once
+            if (negative(step_may)) { soon = step = dt & SIM_NEVER; left = after_step; }
+            else if (negative(in_may)) { soon = in = idur; left = after_in; }
+            else { nforced = SIM_NONE - 1; t = T; }        // an inconsistent trace; leave rather than spin
+            ++nforced;
+        }
+        least = (uint32_t)min((int32_t)left, (int32_t)least);
+        const uint32_t nx = soon + 1u;
+        now += nx;
+        // ends at the next instant
+        const uint32_t step_next = (uint32_t)max((int32_t)(step - nx), -1), out_next = (uint32_t)max((int32_t)(out - nx), -1),
+                       in_next = (uint32_t)max((int32_t)(in - nx), -1);
+        const uint32_t step_ends = (uint32_t)((int32_t)(step_next & ~step) >> 31),
+                       out_ends = (uint32_t)((int32_t)(out_next & ~out) >> 31),
+                       in_ends = (uint32_t)((int32_t)(in_next & ~in) >> 31);
+        left += (rel & step_ends) + (osize & out_ends);
+        t -= step_ends;
+        te += step_ends;
+        oe += out_ends;
+        ie += in_ends;
+        step = step_next;
+        out = out_next;
+        in = in_next;
+    } while (t != T);
+    if (lane == 0) {
+        A.total_ns[q] = now;
+        A.overhead_ns[q] = now - A.C[T];
+        A.peak_resident[q] = (uint64_t)(limit - least) << shift;
+        A.forced[q] = nforced;
+    }
+}
+
+__global__ __launch_bounds__(WAVE) void k_sim_run(SimArgs A)
+{
+    __shared__ union {
+        SimWin wide;
+        NarrowWin narrow;
+    } W;
+    const uint32_t shift = (uint32_t)__builtin_amdgcn_readfirstlane((int)A.forced[blockIdx.x]);     // (of the launch before)
+    if (shift >= SIM_WIDE) sim_run_wide(A, W.wide);
+    else sim_run_narrow(A, shift, W.narrow);
+}
+
 hipError_t launch_simulate_swaps(uint32_t n, uint32_t T, uint32_t Q, uint32_t kmax, const uint64_t *size,
                                  const uint32_t *alloc, const uint32_t *free_, const uint32_t *step_lo,
                                  const uint32_t *step_hi, uint32_t hi_minus, const uint64_t *C, uint64_t *need,
                                  uint64_t *rel, const uint32_t *list, const uint32_t *perm_lo,
                                  const uint32_t *perm_hi, const uint32_t *posmap, uint32_t *jobs_lo,
                                  uint32_t *jobs_hi, uint32_t *m, const uint32_t *prefix, const uint64_t *limits,
-                                 uint32_t *kb, uint64_t bpus, uint64_t *total_ns,
+                                 uint32_t *kb, uint32_t *place_lo, uint64_t bpus, uint64_t *total_ns,
                                  uint64_t *overhead_ns, uint64_t *peak_resident, uint32_t *forced, hipStream_t st,
                                  uint32_t n_lists, const uint32_t *n_listed)
 {
@@ -364,10 +619,11 @@ hipError_t launch_simulate_swaps(uint32_t n, uint32_t T, uint32_t Q, uint32_t km
                            const_cast<uint32_t *>(posmap));
     hipLaunchKernelGGL(k_sim_steps, dim3((n + 255) / 256), dim3(256), 0, st, n, size, alloc, free_,
                        (unsigned long long *)need, (unsigned long long *)rel);
-    hipLaunchKernelGGL(k_sim_jobs, dim3(n_lists, 2), dim3(SIM_THREADS), 0, st, n, perm_lo, perm_hi, posmap, step_lo,
-                       step_hi, hi_minus, jobs_lo, jobs_hi, m);
+    hipLaunchKernelGGL(k_sim_jobs, dim3(n_lists, 3), dim3(SIM_THREADS), 0, st, n, perm_lo, perm_hi, posmap, step_lo,
+                       step_hi, hi_minus, jobs_lo, jobs_hi, place_lo, m, T, (const unsigned long long *)need,
+                       (const unsigned long long *)rel, peak_resident, total_ns);
     SimArgs A{n, T, Q, kmax, size, step_lo, step_hi, hi_minus, C, (const unsigned long long *)need,
-              (const unsigned long long *)rel, list, jobs_lo, jobs_hi, m, prefix, limits, kb,
+              (const unsigned long long *)rel, list, jobs_lo, jobs_hi, place_lo, m, prefix, limits, kb,
               n_listed ? 1u : 0u, bpus,
               total_ns, overhead_ns, peak_resident, forced};
     hipLaunchKernelGGL(k_sim_starts, dim3(Q), dim3(RUN_THREADS), 0, st, A);

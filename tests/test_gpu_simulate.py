@@ -94,6 +94,38 @@ def test_simulate_window_edges(lap, oracle_mod, n, T):
     _check(lap, oracle_mod, tr, 2.0, sl, [(k, lim) for k in ks for lim in (peak, peak * 3 // 5, 0)])
 
 
+EDGE = (1 << 31) - 1
+
+
+@pytest.mark.parametrize("what", ["step", "transfer", "resident"])
+@pytest.mark.parametrize("edge", [EDGE - 1, EDGE, EDGE + 1, EDGE + 2])
+@pytest.mark.parametrize("granule", [1, 512])
+def test_simulate_on_both_sides_of_31_bits(lap, oracle_mod, what, edge, granule):
+    """the longest step, the longest transfer and the bytes resident (in granules) where 31 bits end, each with 70
+    transfers, steps that allocate nothing and limits that block every step"""
+    rng = np.random.default_rng(edge * 3 + granule)
+    n, T, link = 100, 90, 1.0                                   # 1 GB/s: a byte takes 1 ns
+    a = np.sort(rng.integers(0, T // 3, n) * 2)
+    f = a + 8 + rng.integers(0, T - a - 8)
+    size = rng.integers(1, 1 << 20, n).astype(np.uint64) * granule
+    step_ns = rng.integers(1, 1 << 21, T).astype(np.uint64)
+    if what == "step":
+        step_ns[T // 2] = edge
+    else:
+        # variable 0: alone beyond the edge as a transfer, or up to the peak; its granule is the trace's
+        a[0], f[0] = 0, T
+        size[0] = edge if what == "transfer" else granule
+        if what == "resident":
+            peak = oracle_mod.load_profile(mk_trace(size, a, f, T=T))[1]
+            size[0] = granule * edge - (peak - granule)
+    tr = mk_trace(size, a, f, T=T, gap_lo=a, gap_hi=f - 1, step_ns=step_ns)
+    peak = oracle_mod.load_profile(tr)[1]
+    assert what != "resident" or peak == granule * edge
+    sl = np.concatenate([[0], 1 + rng.permutation(n - 1)[:70]]).astype(np.uint32)
+    _check(lap, oracle_mod, tr, link, sl, [(71, 0), (71, peak // 2), (71, peak - 1), (71, peak), (64, peak * 3 // 4), (1, peak // 3),
+                                           (0, 0), (71, (1 << 64) - 1)])
+
+
 @pytest.mark.parametrize("cfg", [2, 3, 5])
 def test_simulate_limit_sweep_on_configs(lap, oracle_mod, cfg):
     """what the planner is for: the selection's prefixes for a sweep of limits, each replayed under its limit"""
