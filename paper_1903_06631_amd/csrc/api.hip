@@ -193,6 +193,11 @@ int load_profile_impl(const lap_trace *tr, uint64_t *load, uint64_t *peak, uint3
                       hipStream_t st)
 {
     const uint32_t n = tr->n_vars, T = tr->n_steps;
+    if (n <= lap::LOAD_SMALL_VARS && T <= lap::LOAD_SMALL_STEPS) {
+        ProfScope p(LAP_K_LOAD_SCATTER, st);
+        LAP_HIP(lap::launch_load_small(n, T, tr->size, tr->alloc, tr->free_, load, peak, t_peak, st));
+        return LAP_OK;
+    }
     LAP_HIP(lap::launch_fill_u64(delta, (size_t)T + 1, 0, st));
     {
         ProfScope p(LAP_K_LOAD_SCATTER, st);

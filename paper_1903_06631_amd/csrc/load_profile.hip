@@ -31,37 +31,11 @@ __global__ __launch_bounds__(256) void k_put_words(uint32_t *dst, uint32_t count
     for (uint32_t i = threadIdx.x; i < count; i += blockDim.x) dst[i] = c.w[i];
 }
 
-// Bins kept in LDS per workgroup, flushed once with global atomics.  Arithmetic
-// is modulo 2^64; the prefix sums are non-negative so wrap-around cancels.
-__global__ __launch_bounds__(256) void k_delta_lds(uint32_t n, uint32_t nbins,
-                                                   const uint64_t *__restrict__ size,
-                                                   const uint32_t *__restrict__ alloc,
-                                                   const uint32_t *__restrict__ free_,
-                                                   unsigned long long *delta)
-{
-    extern __shared__ unsigned long long bins[];
-    for (uint32_t i = threadIdx.x; i < nbins; i += blockDim.x) bins[i] = 0;
-    __syncthreads();
-    const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint64_t base = (uint64_t)blockIdx.x * blockDim.x; base < n; base += stride) {
-        const uint64_t i = base + threadIdx.x;
-        const bool in = i < n;
-        const uint64_t s = in ? size[i] : 0;
-        const auto add = [&](uint32_t t, uint64_t v) { atomicAdd(&bins[t], (unsigned long long)v); };
-        wave_add_runs(in ? alloc[i] : NO_KEY, s, add);
-        wave_add_runs(in ? free_[i] : NO_KEY, 0ull - s, add);
-    }
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < nbins; i += blockDim.x) {
-        const unsigned long long v = bins[i];
-        if (v) atomicAdd(&delta[i], v);
-    }
-}
-
-// Time-local variant for long time lines: a workgroup owns 4096 consecutive variables, reads
-// them once (16-byte vector loads, kept in registers), finds the step range their events
-// fall into and, when that range fits the LDS bins, accumulates there and flushes the bins
-// with global atomics; otherwise it adds to global memory directly.  Bound by the memory it reads once
+// A workgroup owns 4096 consecutive variables, reads them once (16-byte vector loads where the arrays
+// are aligned for them, kept in registers), finds the step range their events fall into and, when that
+// range fits the LDS bins, accumulates there and flushes the bins with global atomics; otherwise it adds
+// to global memory directly.  Arithmetic is modulo 2^64; the prefix sums are non-negative so wrap-around
+// cancels.  Bound by the memory it reads once
 // runs of equal steps are summed before they reach the bins: 50 million variables in the order in which
 // they are allocated, about 345 a step, take 136 us = 5.9 TB/s (340 us when every variable added to the
 // bins itself and the LDS served a wave's adds one by one); 134 million with temporaries at random
@@ -69,6 +43,56 @@ __global__ __launch_bounds__(256) void k_delta_lds(uint32_t n, uint32_t nbins,
 constexpr int DW_THREADS = 256;
 constexpr int DW_GROUPS = 4;                       // groups of 4 variables per thread
 constexpr uint32_t DW_PER_BLOCK = DW_THREADS * DW_GROUPS * 4;
+
+// four neighbouring variables; size 0 marks an empty slot.  vec: the arrays are aligned for 16-byte loads
+struct Four {
+    uint64_t sz[4];
+    uint32_t al[4], fr[4];
+};
+__device__ __forceinline__ void load_four(Four &x, uint32_t i0, uint32_t n, bool vec, const uint64_t *__restrict__ size,
+                                          const uint32_t *__restrict__ alloc, const uint32_t *__restrict__ free_)
+{
+    if (vec && i0 + 3 < n) {
+        const ulonglong2 s01 = *(const ulonglong2 *)(size + i0);
+        const ulonglong2 s23 = *(const ulonglong2 *)(size + i0 + 2);
+        const uint4 a4 = *(const uint4 *)(alloc + i0);
+        const uint4 f4 = *(const uint4 *)(free_ + i0);
+        x.sz[0] = s01.x; x.sz[1] = s01.y; x.sz[2] = s23.x; x.sz[3] = s23.y;
+        x.al[0] = a4.x; x.al[1] = a4.y; x.al[2] = a4.z; x.al[3] = a4.w;
+        x.fr[0] = f4.x; x.fr[1] = f4.y; x.fr[2] = f4.z; x.fr[3] = f4.w;
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool in = i0 + k < n;
+            x.sz[k] = in ? size[i0 + k] : 0;
+            x.al[k] = in ? alloc[i0 + k] : 0;
+            x.fr[k] = in ? free_[i0 + k] : 0;
+        }
+    }
+}
+
+// adds what four variables a lane do to the bins, bins[0] being step lo: a lane's neighbours are summed first, then the lanes'
+__device__ __forceinline__ void bin_four(const Four &x, unsigned long long *bins, uint32_t lo)
+{
+    const auto add = [&](uint32_t t, uint64_t v) { atomicAdd(&bins[t - lo], (unsigned long long)v); };
+    const auto side = [&](const uint32_t (&t)[4], uint64_t sign) {
+        uint32_t key = NO_KEY;
+        uint64_t sum = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (!x.sz[k]) continue;
+            if (t[k] != key) {
+                if (key != NO_KEY) add(key, (sum ^ sign) - sign);
+                key = t[k];
+                sum = 0;
+            }
+            sum += x.sz[k];
+        }
+        wave_add_runs(key, (sum ^ sign) - sign, add);
+    };
+    side(x.al, 0);
+    side(x.fr, ~0ull);
+}
 
 __global__ __launch_bounds__(DW_THREADS) void k_delta_window(uint32_t n, uint32_t lds_bins,
                                                              const uint64_t *__restrict__ size,
@@ -79,34 +103,17 @@ __global__ __launch_bounds__(DW_THREADS) void k_delta_window(uint32_t n, uint32_
     extern __shared__ unsigned long long bins[];
     __shared__ uint32_t s_lo, s_hi;
     const uint32_t begin = blockIdx.x * DW_PER_BLOCK;
+    const bool vec = (((uintptr_t)size | (uintptr_t)alloc | (uintptr_t)free_) & 15) == 0;
     if (threadIdx.x == 0) { s_lo = 0xFFFFFFFFu; s_hi = 0; }
     __syncthreads();
-    uint64_t sz[DW_GROUPS][4];
-    uint32_t al[DW_GROUPS][4], fr[DW_GROUPS][4];
+    Four x[DW_GROUPS];
     uint32_t lo = 0xFFFFFFFFu, hi = 0;
 #pragma unroll
     for (int g = 0; g < DW_GROUPS; ++g) {
-        const uint32_t i0 = begin + (g * DW_THREADS + threadIdx.x) * 4;
-        if (i0 + 3 < n) {
-            const ulonglong2 s01 = *(const ulonglong2 *)(size + i0);
-            const ulonglong2 s23 = *(const ulonglong2 *)(size + i0 + 2);
-            const uint4 a4 = *(const uint4 *)(alloc + i0);
-            const uint4 f4 = *(const uint4 *)(free_ + i0);
-            sz[g][0] = s01.x; sz[g][1] = s01.y; sz[g][2] = s23.x; sz[g][3] = s23.y;
-            al[g][0] = a4.x; al[g][1] = a4.y; al[g][2] = a4.z; al[g][3] = a4.w;
-            fr[g][0] = f4.x; fr[g][1] = f4.y; fr[g][2] = f4.z; fr[g][3] = f4.w;
-        } else {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const bool in = i0 + k < n;
-                sz[g][k] = in ? size[i0 + k] : 0;          // size 0 marks an empty slot
-                al[g][k] = in ? alloc[i0 + k] : 0;
-                fr[g][k] = in ? free_[i0 + k] : 0;
-            }
-        }
+        load_four(x[g], begin + (g * DW_THREADS + threadIdx.x) * 4, n, vec, size, alloc, free_);
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            if (sz[g][k]) { lo = min(lo, al[g][k]); hi = max(hi, fr[g][k]); }
+            if (x[g].sz[k]) { lo = min(lo, x[g].al[k]); hi = max(hi, x[g].fr[k]); }
     }
     for (int m = WAVE / 2; m > 0; m >>= 1) {
         lo = min(lo, (uint32_t)__shfl_xor(lo, m, WAVE));
@@ -121,28 +128,8 @@ __global__ __launch_bounds__(DW_THREADS) void k_delta_window(uint32_t n, uint32_
         const uint32_t nb = hi - lo + 1;
         for (uint32_t i = threadIdx.x; i < nb; i += blockDim.x) bins[i] = 0;
         __syncthreads();
-        const auto add = [&](uint32_t t, uint64_t v) { atomicAdd(&bins[t - lo], (unsigned long long)v); };
-        // a lane's four neighbours first, then the lanes
-        const auto add4 = [&](const uint32_t (&t)[4], const uint64_t (&v)[4], uint64_t sign) {
-            uint32_t key = NO_KEY;
-            uint64_t sum = 0;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (!v[k]) continue;
-                if (t[k] != key) {
-                    if (key != NO_KEY) add(key, (sum ^ sign) - sign);
-                    key = t[k];
-                    sum = 0;
-                }
-                sum += v[k];
-            }
-            wave_add_runs(key, (sum ^ sign) - sign, add);
-        };
-#pragma unroll
-        for (int g = 0; g < DW_GROUPS; ++g) {
-            add4(al[g], sz[g], 0);
-            add4(fr[g], sz[g], ~0ull);
-        }
+        for (int g = 0; g < DW_GROUPS; ++g) bin_four(x[g], bins, lo);
         __syncthreads();
         for (uint32_t i = threadIdx.x; i < nb; i += blockDim.x) {
             const unsigned long long v = bins[i];
@@ -153,9 +140,9 @@ __global__ __launch_bounds__(DW_THREADS) void k_delta_window(uint32_t n, uint32_
         for (int g = 0; g < DW_GROUPS; ++g)
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                if (sz[g][k]) {
-                    atomicAdd(&delta[al[g][k]], (unsigned long long)sz[g][k]);
-                    atomicAdd(&delta[fr[g][k]], (unsigned long long)(0ull - sz[g][k]));
+                if (x[g].sz[k]) {
+                    atomicAdd(&delta[x[g].al[k]], (unsigned long long)x[g].sz[k]);
+                    atomicAdd(&delta[x[g].fr[k]], (unsigned long long)(0ull - x[g].sz[k]));
                 }
     }
 }
@@ -166,9 +153,8 @@ __global__ __launch_bounds__(DW_THREADS) void k_delta_window(uint32_t n, uint32_
 constexpr int SCAN_THREADS = 1024;
 constexpr int SCAN_ITEMS = 4;
 
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_peak(uint32_t T, const uint64_t *__restrict__ delta,
-                                                            uint64_t *__restrict__ load,
-                                                            uint64_t *__restrict__ peak, uint32_t *__restrict__ t_peak)
+__device__ __forceinline__ void scan_peak(uint32_t T, const uint64_t *delta, uint64_t *__restrict__ load,
+                                          uint64_t *__restrict__ peak, uint32_t *__restrict__ t_peak)
 {
     __shared__ uint64_t wsum[SCAN_THREADS / WAVE];
     __shared__ uint64_t wmax[SCAN_THREADS / WAVE];
@@ -220,6 +206,40 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_peak(uint32_t T, const ui
         *peak = best;
         *t_peak = best_t;
     }
+}
+
+__global__ __launch_bounds__(SCAN_THREADS) void k_scan_peak(uint32_t T, const uint64_t *__restrict__ delta,
+                                                            uint64_t *__restrict__ load,
+                                                            uint64_t *__restrict__ peak, uint32_t *__restrict__ t_peak)
+{
+    scan_peak(T, delta, load, peak, t_peak);
+}
+
+// The whole load profile of a small trace: the bins of the time line and the scan over them, one workgroup.
+// Bound by the latency of one pass over the variables and one over the steps; that of two more launches goes
+// (plan of 120 variables 101.6 -> 98.7 us; the rule and its figures are in lap_kernels.h).
+__global__ __launch_bounds__(SCAN_THREADS) void k_load_small(uint32_t n, uint32_t T, const uint64_t *__restrict__ size,
+                                                             const uint32_t *__restrict__ alloc,
+                                                             const uint32_t *__restrict__ free_,
+                                                             uint64_t *__restrict__ load, uint64_t *__restrict__ peak,
+                                                             uint32_t *__restrict__ t_peak)
+{
+    extern __shared__ unsigned long long bins[];
+    const bool vec = (((uintptr_t)size | (uintptr_t)alloc | (uintptr_t)free_) & 15) == 0;
+    for (uint32_t t = threadIdx.x; t <= T; t += SCAN_THREADS) bins[t] = 0;
+    __syncthreads();
+    // (waves beyond the last variable have nothing to add; two batches of loads in flight)
+    const uint32_t wave0 = (threadIdx.x & ~(WAVE - 1u)) * 4;
+    for (uint32_t base = 0; base + wave0 < n; base += 2 * SCAN_THREADS * 4) {
+        const uint32_t second = base + SCAN_THREADS * 4;
+        Four x, y;
+        load_four(x, base + threadIdx.x * 4, n, vec, size, alloc, free_);
+        load_four(y, second + threadIdx.x * 4, n, vec, size, alloc, free_);
+        bin_four(x, bins, 0);
+        if (second + wave0 < n) bin_four(y, bins, 0);
+    }
+    __syncthreads();
+    scan_peak(T, (const uint64_t *)bins, load, peak, t_peak);
 }
 
 // Long time lines: the same scan in four small launches, tiles of SCAN_THREADS * SCAN_ITEMS steps.
@@ -408,19 +428,14 @@ hipError_t launch_put_words(void *dst, const void *host_src, size_t n_words, hip
 hipError_t launch_delta(uint32_t n, uint32_t T, const uint64_t *size, const uint32_t *alloc, const uint32_t *free_,
                         uint64_t *delta, hipStream_t st)
 {
-    const uint32_t nbins = T + 1;
-    constexpr uint32_t LDS_BINS = 8192;            // 64 KiB of u64 bins per workgroup
-    if (nbins <= LDS_BINS) {
-        uint32_t blocks = (n + 256 * 16 - 1) / (256 * 16);
-        blocks = blocks < 1 ? 1 : (blocks > 1024 ? 1024 : blocks);
-        hipLaunchKernelGGL(k_delta_lds, dim3(blocks), dim3(256), nbins * sizeof(uint64_t), st, n, nbins, size, alloc,
-                           free_, (unsigned long long *)delta);
-    } else {
-        constexpr uint32_t WIN_BINS = 2048;        // 16 KiB of bins: several workgroups per CU
-        const uint32_t blocks = (n + DW_PER_BLOCK - 1) / DW_PER_BLOCK;
-        hipLaunchKernelGGL(k_delta_window, dim3(blocks), dim3(DW_THREADS), WIN_BINS * sizeof(uint64_t), st, n,
-                           WIN_BINS, size, alloc, free_, (unsigned long long *)delta);
-    }
+    // Up to 8192 bins (64 KiB, two workgroups on a compute unit) hold the whole time line, so any order of the variables
+    // stays in the LDS; of longer ones 2048 (16 KiB) hold what a workgroup's variables mostly span.  (2.6 million variables
+    // over 7540 steps, the whole call: 44.8 us with bins for all steps in every workgroup and one load at a time, 24.9 us.)
+    constexpr uint32_t ALL_BINS = 8192, WIN_BINS = 2048;
+    const uint32_t bins = T < ALL_BINS ? T + 1 : WIN_BINS;
+    const uint32_t blocks = (n - 1) / DW_PER_BLOCK + 1;
+    hipLaunchKernelGGL(k_delta_window, dim3(blocks), dim3(DW_THREADS), bins * sizeof(uint64_t), st, n, bins, size, alloc,
+                       free_, (unsigned long long *)delta);
     return hipGetLastError();
 }
 
@@ -437,6 +452,14 @@ hipError_t launch_scan_peak(uint32_t T, uint64_t *delta, uint64_t *load, uint64_
     hipLaunchKernelGGL(k_scan_tile_offsets, dim3(1), dim3(SCAN_THREADS), 0, st, T, nb, load, delta);
     hipLaunchKernelGGL(k_scan_tile_apply, dim3(nb), dim3(SCAN_THREADS), 0, st, T, nb, load, delta);
     hipLaunchKernelGGL(k_scan_tile_peak, dim3(1), dim3(SCAN_THREADS), 0, st, nb, delta, peak, t_peak);
+    return hipGetLastError();
+}
+
+hipError_t launch_load_small(uint32_t n, uint32_t T, const uint64_t *size, const uint32_t *alloc, const uint32_t *free_,
+                             uint64_t *load, uint64_t *peak, uint32_t *t_peak, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_load_small, dim3(1), dim3(SCAN_THREADS), ((size_t)T + 1) * sizeof(uint64_t), st, n, T, size, alloc,
+                       free_, load, peak, t_peak);
     return hipGetLastError();
 }
 

@@ -1,6 +1,7 @@
 """Load profile of variables that arrive in the order in which they are allocated: neighbouring lanes meet the same
-step, and the scatter kernels add runs of equal steps as one.  Both kernels (short and long time lines), run lengths on
-either side of where runs are merged, and list lengths at the edges of waves, groups and workgroups."""
+step, and the scatter kernels add runs of equal steps as one.  All kernels (small traces in one launch, short and long time
+lines), run lengths on either side of where runs are merged, and list lengths at the edges of waves, groups and
+workgroups."""
 import numpy as np
 import pytest
 
@@ -10,11 +11,11 @@ from helpers import mk_trace
 pytestmark = pytest.mark.gpu
 
 
-# lanes of a wave form 64 / run runs (short time lines, one variable a lane) or 256 / run (long ones, four): 1 to 64
-# runs, and 32 and 33 of them
+# a wave's 256 variables form 256 / run runs: 1 to 64 of its lanes, and 32 and 33
 @pytest.mark.parametrize("long_line", [False, True])
 @pytest.mark.parametrize("n,run", [(1, 1), (3, 2), (63, 64), (64, 64), (65, 2), (257, 8), (1023, 3), (1025, 1), (4095, 7),
-                                   (4096, 8), (4097, 9), (8193, 345), (20011, 16), (12288, 100000)])
+                                   (4096, 8), (4097, 9), (8193, 345), (20011, 16), (12288, 100000),
+                                   (16384, 5), (16385, 5)])
 def test_load_profile_sorted_runs(oracle_mod, long_line, n, run):
     import paper_1903_06631_amd as lap
     rng = np.random.default_rng(n * 7 + run)
@@ -29,6 +30,28 @@ def test_load_profile_sorted_runs(oracle_mod, long_line, n, run):
     size[rng.random(n) < 0.1] = (1 << 46) + 1                      # sums of a run pass 2^53
     tr = mk_trace(size, alloc, free, T=T)
     got = lap.load_profile(lap.DeviceTrace(tr))
+    load, peak, at = oracle_mod.load_profile(tr)
+    assert np.array_equal(u64(got["load"]), load)
+    assert int(u64(got["peak"])[0]) == peak and int(got["t_peak"].item()) == at
+
+
+@pytest.mark.parametrize("n,T", [(257, 30), (20000, 500), (20000, 20000)])
+@pytest.mark.parametrize("off", [(1, 0, 0), (0, 1, 0), (0, 0, 3), (1, 2, 2)])
+def test_load_profile_unaligned_arrays(oracle_mod, n, T, off):
+    """arrays that are aligned to their elements only: no 16-byte loads"""
+    import torch
+    import paper_1903_06631_amd as lap
+    from traces import random_trace
+    tr = random_trace(n + T, n, T)
+    dt = lap.DeviceTrace(tr, use_gaps=False)
+
+    def moved(t, by):
+        big = torch.empty(t.numel() + by, dtype=t.dtype, device=t.device)
+        big[by:] = t
+        return big[by:]
+
+    dt.size, dt.alloc, dt.free = moved(dt.size, off[0]), moved(dt.alloc, off[1]), moved(dt.free, off[2])
+    got = lap.load_profile(dt)
     load, peak, at = oracle_mod.load_profile(tr)
     assert np.array_equal(u64(got["load"]), load)
     assert int(u64(got["peak"])[0]) == peak and int(got["t_peak"].item()) == at
