@@ -113,7 +113,7 @@ size_t ws_weights(uint32_t n, uint32_t T, uint32_t W)
     return ws_select(n, T, 0) + up(SELECT_MAX_KINDS * 8) + up(SELECT_MAX_KINDS * 32) + ALIGN
            + up(w * N * 8) + 2 * up(w * N * 4) + up(w * (N + 1) * 8) + up(w * N * 8)                // picks, peaks, scores
            + up(N * 8) + up(N * 4) + 2 * up(((size_t)T + 1) * 8)                                    // the SWDOA walk
-           + 2 * up((size_t)T * 8) + 3 * up(N * 4) + 2 * ALIGN                                      // steps, perms
+           + 2 * up((size_t)T * 8) + 2 * up(N * 4)                                                  // steps, perms
            + up((w * N + 1) * 4) + 2 * up(w * N * 4) + up(w * 4) + up(w * N * 4)                   // replay state
            + 2 * up(w * 8);
 }
@@ -233,6 +233,29 @@ int static_scratch(void **out)
         g_scratch_ptr[dev] = p;
     }
     *out = g_scratch_ptr[dev];
+    return LAP_OK;
+}
+
+// The variables of a swap list in the order of their access steps, into perm_lo and perm_hi; *count is how many entries
+// those have: the listed variables, or all of them where the list is long (then posmap tells which are listed).
+int order_swap_list(uint32_t n, const uint32_t *list, uint32_t k, const lap_trace *tr, const uint32_t *step_lo,
+                    const uint32_t *step_hi, uint32_t *posmap, uint32_t *perm_lo, uint32_t *perm_hi, uint32_t *tmp,
+                    uint32_t *kinds, uint64_t *seeds, uint32_t *count, hipStream_t st)
+{
+    if (k <= lap::RANK_LISTED) {
+        *count = k;
+        LAP_HIP(lap::launch_order_listed({n, k, nullptr, list, step_lo, step_hi, posmap, perm_lo, perm_hi}, st));
+        return LAP_OK;
+    }
+    // the ascending-step sort of the placement orders, fed with the access steps
+    *count = n;
+    const uint32_t h_kind = LAP_ORD_ALLOC_ASC;
+    LAP_HIP(lap::launch_put_words(kinds, &h_kind, 1, st));
+    LAP_HIP(lap::launch_fill_u64(seeds, 1, 0, st));
+    LAP_HIP(lap::launch_sort_perm(n, 1, tr->size, step_lo, tr->free_, kinds, seeds, perm_lo, tmp, false, st));
+    LAP_HIP(lap::launch_sort_perm(n, 1, tr->size, step_hi, tr->free_, kinds, seeds, perm_hi, tmp, false, st));
+    LAP_HIP(lap::launch_fill_u64((uint64_t *)posmap, ((size_t)n + 1) / 2, ~0ull, st));
+    LAP_HIP(lap::launch_sched_mark(n, k, list, posmap, st));
     return LAP_OK;
 }
 
@@ -668,9 +691,6 @@ int lap_evaluate_weights(const lap_trace *tr, double link_GBps, uint64_t min_byt
     uint64_t *rel = c.take<uint64_t>(T);
     uint32_t *perm_lo = c.take<uint32_t>(n);
     uint32_t *perm_hi = c.take<uint32_t>(n);
-    uint32_t *tmp = c.take<uint32_t>(n);
-    uint32_t *s_kind = c.take<uint32_t>(1);
-    uint64_t *s_seed = c.take<uint64_t>(1);
     uint32_t *posmap = c.take<uint32_t>((size_t)W * N + 1);
     uint32_t *jobs_lo = c.take<uint32_t>((size_t)W * N);
     uint32_t *jobs_hi = c.take<uint32_t>((size_t)W * N);
@@ -717,18 +737,12 @@ int lap_evaluate_weights(const lap_trace *tr, double link_GBps, uint64_t min_byt
         LAP_HIP(lap::launch_select_swaps(a, false, st));
     }
     // 4. every selection replayed under the limit, 5. the vector that loses the least time
-    const uint32_t h_kind = LAP_ORD_ALLOC_ASC;
-    LAP_HIP(lap::launch_put_words(s_kind, &h_kind, 1, st));
-    LAP_HIP(lap::launch_fill_u64(s_seed, 1, 0, st));
     const uint32_t *step_lo = tr->gap_lo ? tr->gap_lo : tr->alloc;
     const uint32_t *step_hi = tr->gap_hi ? tr->gap_hi : tr->free_;
-    LAP_HIP(lap::launch_sort_perm(n, 1, tr->size, step_lo, tr->free_, s_kind, s_seed, perm_lo, tmp, false, st));
-    LAP_HIP(lap::launch_sort_perm(n, 1, tr->size, step_hi, tr->free_, s_kind, s_seed, perm_hi, tmp, false, st));
-    LAP_HIP(lap::launch_fill_u64((uint64_t *)posmap, ((size_t)W * N + 1) / 2, ~0ull, st));
-    LAP_HIP(lap::launch_fill_u64(need, T, 0, st));
-    LAP_HIP(lap::launch_fill_u64(rel, T, 0, st));
+    LAP_HIP(lap::launch_order_listed({n, 0, n_cand, cidx, step_lo, step_hi, nullptr, perm_lo, perm_hi}, st));
+    LAP_HIP(lap::launch_fill_u64(need, 2 * up((size_t)T * 8) / 8, 0, st));      // and rel
     // (the picks' windows have served: s_lo is scratch here)
-    LAP_HIP(lap::launch_simulate_swaps(n, T, W, n, tr->size, tr->alloc, tr->free_, step_lo, step_hi,
+    LAP_HIP(lap::launch_simulate_swaps(n, T, W, n, 0, n_cand, tr->size, tr->alloc, tr->free_, step_lo, step_hi,
                                        tr->gap_hi ? 0u : 1u, C, need, rel, order, perm_lo, perm_hi, posmap, jobs_lo,
                                        jobs_hi, m, n_selected, d_limits, kb, s_lo, (uint64_t)bpus, total_ns,
                                        overhead_ns, peak_res, forced, st, W, n_cand));
@@ -777,19 +791,14 @@ int lap_schedule_swaps(const lap_trace *tr, double link_GBps, const uint64_t *lo
         load = load_ws;
     }
     LAP_HIP(lap::launch_swap_prefix(T, load, tr->step_ns, C, S, PM, SM, peak, t_peak, nullptr, 0, st));
-    // all variables by (first access, index) and by (next access, index): the ascending-step sort of
-    // the placement orders, fed with the access steps
-    const uint32_t h_kind = LAP_ORD_ALLOC_ASC;
-    LAP_HIP(lap::launch_put_words(kinds, &h_kind, 1, st));
-    LAP_HIP(lap::launch_fill_u64(seeds, 1, 0, st));
     const uint32_t *step_lo = tr->gap_lo ? tr->gap_lo : tr->alloc;
     const uint32_t *step_hi = tr->gap_hi ? tr->gap_hi : tr->free_;
-    LAP_HIP(lap::launch_sort_perm(n, 1, tr->size, step_lo, tr->free_, kinds, seeds, perm_lo, tmp, false, st));
-    LAP_HIP(lap::launch_sort_perm(n, 1, tr->size, step_hi, tr->free_, kinds, seeds, perm_hi, tmp, false, st));
-    LAP_HIP(lap::launch_fill_u64((uint64_t *)posmap, ((size_t)n + 1) / 2, ~0ull, st));
+    uint32_t count = 0;
+    rc = order_swap_list(n, swap_list, k, tr, step_lo, step_hi, posmap, perm_lo, perm_hi, tmp, kinds, seeds, &count, st);
+    if (rc) return rc;
     LAP_HIP(lap::launch_fill_u64(diff, t1, 0, st));
     LAP_HIP(lap::launch_fill_u64(late_ns, 1, 0, st));
-    LAP_HIP(lap::launch_schedule_swaps(n, T, k, tr->size, step_lo, step_hi, tr->gap_hi ? 0u : 1u, C, perm_lo, perm_hi,
+    LAP_HIP(lap::launch_schedule_swaps(n, T, k, count, tr->size, step_lo, step_hi, tr->gap_hi ? 0u : 1u, C, perm_lo, perm_hi,
                                        posmap, swap_list, (uint64_t)bpus, out_start, out_end, in_start, in_end, diff,
                                        late_ns, load, load_sched, peak_sched, st));
     return LAP_OK;
@@ -846,19 +855,14 @@ int lap_simulate_swaps(const lap_trace *tr, double link_GBps, const uint32_t *sw
     rc = load_profile_impl(tr, load_ws, peak, t_peak, delta, st);
     if (rc) return rc;
     LAP_HIP(lap::launch_swap_prefix(T, load_ws, tr->step_ns, C, S, PM, SM, peak, t_peak, nullptr, 0, st));
-    const uint32_t h_kind = LAP_ORD_ALLOC_ASC;
-    LAP_HIP(lap::launch_put_words(kinds, &h_kind, 1, st));
-    LAP_HIP(lap::launch_fill_u64(seeds, 1, 0, st));
     const uint32_t *step_lo = tr->gap_lo ? tr->gap_lo : tr->alloc;
     const uint32_t *step_hi = tr->gap_hi ? tr->gap_hi : tr->free_;
-    LAP_HIP(lap::launch_sort_perm(n, 1, tr->size, step_lo, tr->free_, kinds, seeds, perm_lo, tmp, false, st));
-    LAP_HIP(lap::launch_sort_perm(n, 1, tr->size, step_hi, tr->free_, kinds, seeds, perm_hi, tmp, false, st));
-    LAP_HIP(lap::launch_fill_u64((uint64_t *)posmap, ((size_t)n + 1) / 2, ~0ull, st));
-    LAP_HIP(lap::launch_sched_mark(n, k_max, swap_list, posmap, st));
-    LAP_HIP(lap::launch_fill_u64(need, T, 0, st));
-    LAP_HIP(lap::launch_fill_u64(rel, T, 0, st));
+    uint32_t count = 0;
+    rc = order_swap_list(n, swap_list, k_max, tr, step_lo, step_hi, posmap, perm_lo, perm_hi, tmp, kinds, seeds, &count, st);
+    if (rc) return rc;
+    LAP_HIP(lap::launch_fill_u64(need, 2 * up((size_t)T * 8) / 8, 0, st));      // and rel
     // the per-run regions use a stride of n entries; the sort's scratch has served
-    LAP_HIP(lap::launch_simulate_swaps(n, T, Q, n, tr->size, tr->alloc, tr->free_, step_lo, step_hi,
+    LAP_HIP(lap::launch_simulate_swaps(n, T, Q, n, count, nullptr, tr->size, tr->alloc, tr->free_, step_lo, step_hi,
                                        tr->gap_hi ? 0u : 1u, C, need, rel, swap_list, perm_lo, perm_hi, posmap,
                                        jobs_lo, jobs_hi, m, d_prefix, d_limits, kb, tmp, (uint64_t)bpus,
                                        total_ns, overhead_ns, peak_resident, forced, st));

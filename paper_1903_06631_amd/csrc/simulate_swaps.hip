@@ -25,15 +25,18 @@ constexpr uint32_t SIM_NONE = 0xFFFFFFFFu;
 constexpr uint32_t SIM_NEVER = 0x7FFFFFFFu;        // what the narrow machine does not hold: times, sums of sizes, steps
 constexpr uint32_t SIM_WIDE = 64;                  // instead of a granule's shift
 
+// Bytes allocated and freed per step.  Neighbours allocate at the same step and long-lived ones free at the same: a wave's
+// runs are summed before they reach memory (200 000 variables over 580 steps: 4.4 us, 114 with an atomic per variable).
 __global__ __launch_bounds__(256) void k_sim_steps(uint32_t n, const uint64_t *__restrict__ size,
                                                    const uint32_t *__restrict__ alloc,
                                                    const uint32_t *__restrict__ free_, unsigned long long *need,
                                                    unsigned long long *rel)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    atomicAdd(&need[alloc[i]], (unsigned long long)size[i]);
-    atomicAdd(&rel[free_[i] - 1], (unsigned long long)size[i]);
+    const bool in = i < n;
+    const uint64_t s = in ? size[i] : 0;
+    wave_add_runs(in ? alloc[i] : NO_KEY, s, [&](uint32_t t, uint64_t v) { atomicAdd(&need[t], (unsigned long long)v); });
+    wave_add_runs(in ? free_[i] - 1 : NO_KEY, s, [&](uint32_t t, uint64_t v) { atomicAdd(&rel[t], (unsigned long long)v); });
 }
 
 // several lists, one row of n entries each: position map of list r = row r.  Row r lists the first
@@ -78,11 +81,13 @@ __device__ void sim_extent(uint32_t T, const unsigned long long *__restrict__ ne
     }
 }
 
-// jobs[0..m) = list positions of the listed variables that have an idle gap, in the order of perm;
+// jobs[0..m) = list positions of the listed variables that have an idle gap, in the order of perm (count entries);
 // one workgroup per list (rows of n entries of posmap and jobs, one count each) and direction
 // (blockIdx.y: swap-outs, swap-ins); place_lo: the place of a list position in jobs_lo.  Every round
 // waits for two dependent loads, so a thread takes SIM_PER ranks per round.
-__global__ __launch_bounds__(SIM_THREADS) void k_sim_jobs(uint32_t n, const uint32_t *__restrict__ perm_lo,
+__global__ __launch_bounds__(SIM_THREADS) void k_sim_jobs(uint32_t n, uint32_t count,
+                                                          const uint32_t *__restrict__ count_dev,
+                                                          const uint32_t *__restrict__ perm_lo,
                                                           const uint32_t *__restrict__ perm_hi,
                                                           const uint32_t *__restrict__ posmap_all,
                                                           const uint32_t *__restrict__ step_lo,
@@ -106,14 +111,15 @@ __global__ __launch_bounds__(SIM_THREADS) void k_sim_jobs(uint32_t n, const uint
     uint32_t *jobs = (blockIdx.y ? jobs_hi : jobs_lo) + (size_t)blockIdx.x * n;
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
     const uint64_t below = (1ull << lane) - 1ull;
+    if (count_dev) count = *count_dev;
     uint32_t carry = 0;
     int buf = 0;
-    for (uint64_t base = 0; base < n; base += SIM_THREADS * SIM_PER, buf ^= 1) {
+    for (uint64_t base = 0; base < count; base += SIM_THREADS * SIM_PER, buf ^= 1) {
         const uint64_t r0 = base + wave * (WAVE * SIM_PER) + lane;
         uint32_t v[SIM_PER], pos[SIM_PER];
         uint64_t mine[SIM_PER];
 #pragma unroll
-        for (int j = 0; j < SIM_PER; ++j) v[j] = r0 + j * WAVE < n ? perm[r0 + j * WAVE] : SIM_NONE;
+        for (int j = 0; j < SIM_PER; ++j) v[j] = r0 + j * WAVE < count ? perm[r0 + j * WAVE] : SIM_NONE;
 #pragma unroll
         for (int j = 0; j < SIM_PER; ++j) pos[j] = v[j] != SIM_NONE ? posmap[v[j]] : SIM_NONE;
         uint32_t tot = 0;
@@ -161,8 +167,6 @@ struct SimArgs {
 // What the machine reads next of each of its three streams.  Its state goes from event to event in
 // registers; the entries come from here, RUN_WIN of a stream fetched by the whole wave at a time, so
 // that an event waits for LDS and not for the chain jobs -> list -> size, steps in global memory.
-// All swap planning calls, 21 limits, 14 000 steps, 50 000 variables: 80.0 -> 28.8 ms; 348 steps, 3000
-// variables: 1.89 -> 0.86 ms; 64 weight vectors on 200 000 variables: 7.31 -> 5.08 ms.
 struct SimWin {
     uint64_t need[RUN_WIN], rel[RUN_WIN], dt[RUN_WIN];
     uint64_t osize[RUN_WIN], odur[RUN_WIN], okey[RUN_WIN];      // key: step << 32 | variable, the order of the jobs
@@ -413,7 +417,8 @@ __device__ void sim_run_wide(const SimArgs &A, SimWin &W)
 // lane: the lane counts down and is negative when the chunk is used up.  Every event reads the current entry of each stream
 // from its lane whether it has changed or not, and conditions are signs, so that several are one `and`.  An actor's word
 // is its remaining time less one, and -1 when it does nothing: max(word - elapsed, -1) is the next word in all cases.
-// The limit is kept as what it leaves.
+// The limit is kept as what it leaves.  14 000 steps and 11 000 transfers, every one blocked: 7.4 ms = 205 ns an event
+// (14.8 ms with 64-bit state and a branch a question); 348 steps and 257 transfers 0.18 ms (0.36 ms).
 struct NarrowWin {
     uint32_t need[RUN_WIN], rel[RUN_WIN], dt[RUN_WIN];               // dt, like all times here, less one
     uint32_t osize[RUN_WIN], odur[RUN_WIN], olo[RUN_WIN], oplace[RUN_WIN];
@@ -602,7 +607,8 @@ __global__ __launch_bounds__(WAVE) void k_sim_run(SimArgs A)
     else sim_run_narrow(A, shift, W.narrow);
 }
 
-hipError_t launch_simulate_swaps(uint32_t n, uint32_t T, uint32_t Q, uint32_t kmax, const uint64_t *size,
+hipError_t launch_simulate_swaps(uint32_t n, uint32_t T, uint32_t Q, uint32_t kmax, uint32_t count,
+                                 const uint32_t *count_dev, const uint64_t *size,
                                  const uint32_t *alloc, const uint32_t *free_, const uint32_t *step_lo,
                                  const uint32_t *step_hi, uint32_t hi_minus, const uint64_t *C, uint64_t *need,
                                  uint64_t *rel, const uint32_t *list, const uint32_t *perm_lo,
@@ -613,13 +619,13 @@ hipError_t launch_simulate_swaps(uint32_t n, uint32_t T, uint32_t Q, uint32_t km
                                  uint32_t n_lists, const uint32_t *n_listed)
 {
     // n_listed given: run q replays row q of `list` (n_lists rows of n entries, *n_listed valid entries
-    // each); the caller has cleared the n_lists position maps, they are filled here
+    // each, the same variables in all rows and in perm); the n_lists position maps are filled here
     if (n_listed)
         hipLaunchKernelGGL(k_sim_mark_rows, dim3((n + 255) / 256, n_lists), dim3(256), 0, st, n, list, n_listed,
                            const_cast<uint32_t *>(posmap));
     hipLaunchKernelGGL(k_sim_steps, dim3((n + 255) / 256), dim3(256), 0, st, n, size, alloc, free_,
                        (unsigned long long *)need, (unsigned long long *)rel);
-    hipLaunchKernelGGL(k_sim_jobs, dim3(n_lists, 3), dim3(SIM_THREADS), 0, st, n, perm_lo, perm_hi, posmap, step_lo,
+    hipLaunchKernelGGL(k_sim_jobs, dim3(n_lists, 3), dim3(SIM_THREADS), 0, st, n, count, count_dev, perm_lo, perm_hi, posmap, step_lo,
                        step_hi, hi_minus, jobs_lo, jobs_hi, place_lo, m, T, (const unsigned long long *)need,
                        (const unsigned long long *)rel, peak_resident, total_ns);
     SimArgs A{n, T, Q, kmax, size, step_lo, step_hi, hi_minus, C, (const unsigned long long *)need,

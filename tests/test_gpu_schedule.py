@@ -56,6 +56,15 @@ def test_schedule_random(lap, oracle_mod, seed, n, T):
     _check(lap, oracle_mod, tr, 1.0, np.arange(n, dtype=np.uint32))             # everything, several chunks of 1024
 
 
+@pytest.mark.parametrize("k", [0, 1, 63, 64, 65, 1023, 1025, 2049, 16384, 16385])
+def test_schedule_list_lengths(lap, oracle_mod, k):
+    """listed variables are ordered by counting up to 16 384 of them, 64 to a workgroup, beyond by the sort of all
+    variables; many share an access step"""
+    tr = random_trace(4100, 16500, 300, with_step_ns=True)
+    sl = np.random.default_rng(k).permutation(16500)[:k].astype(np.uint32)
+    _check(lap, oracle_mod, tr, 3.0, sl)
+
+
 @pytest.mark.parametrize("cfg", [2, 3, 5])
 def test_schedule_of_selected_variables(lap, oracle_mod, cfg):
     """the lists the selection produces: a prefix of the SWDOA order and all candidates"""

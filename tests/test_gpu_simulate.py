@@ -94,6 +94,15 @@ def test_simulate_window_edges(lap, oracle_mod, n, T):
     _check(lap, oracle_mod, tr, 2.0, sl, [(k, lim) for k in ks for lim in (peak, peak * 3 // 5, 0)])
 
 
+@pytest.mark.parametrize("k", [63, 65, 1025, 16384, 16385])
+def test_simulate_list_lengths(lap, oracle_mod, k):
+    """ordered by counting up to 16 384 variables, beyond by the sort of all variables"""
+    tr = random_trace(4200, 16500, 200, with_step_ns=True)
+    _, peak, _ = oracle_mod.load_profile(tr)
+    sl = np.random.default_rng(k).permutation(16500)[:k].astype(np.uint32)
+    _check(lap, oracle_mod, tr, 3.0, sl, [(k, peak), (k, peak // 2), (k * 2 // 3, peak // 3), (k, 0), (0, peak)])
+
+
 EDGE = (1 << 31) - 1
 
 
