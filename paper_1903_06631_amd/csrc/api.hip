@@ -618,7 +618,7 @@ int lap_select_swaps(const lap_trace *tr, double link_GBps, uint64_t min_bytes, 
     a.size = tr->size; a.gap_lo = tr->gap_lo; a.gap_hi = tr->gap_hi; a.alloc = tr->alloc; a.free_ = tr->free_;
     a.load = load; a.cand = cand; a.doa = doa; a.aoa = aoa; a.wdoa = wdoa; a.cut = cut;
     a.win_lo = win_lo; a.win_hi = win_hi; a.nc = nc; a.cidx = cidx; a.c_ilo = c_ilo; a.c_ihi = c_ihi; a.dmin = dmin;
-    a.kinds = d_kinds; a.limits = d_limits;
+    a.kinds = d_kinds; a.greedy = std::find(score_kinds, score_kinds + K, (uint32_t)LAP_PS_SWDOA) != score_kinds + K; a.limits = d_limits;
     a.s_size = s_size; a.s_lo = s_lo; a.s_hi = s_hi;
     a.g_score = g_score; a.g_var = g_var; a.g_diff = g_diff; a.g_sum = g_sum;
     a.order = order; a.rank = rank; a.peaks = peaks; a.n_cand = n_cand; a.n_selected = n_selected;
@@ -717,7 +717,7 @@ int lap_evaluate_weights(const lap_trace *tr, double link_GBps, uint64_t min_byt
     a.size = tr->size; a.gap_lo = tr->gap_lo; a.gap_hi = tr->gap_hi; a.alloc = tr->alloc; a.free_ = tr->free_;
     a.load = load; a.cand = cand; a.doa = doa; a.aoa = aoa; a.wdoa = wdoa; a.cut = cut;
     a.win_lo = win_lo; a.win_hi = win_hi; a.nc = nc; a.cidx = cidx; a.c_ilo = c_ilo; a.c_ihi = c_ihi; a.dmin = dmin;
-    a.kinds = d_kinds; a.limits = d_limits;
+    a.kinds = d_kinds; a.greedy = true; a.limits = d_limits;
     a.s_size = s_size; a.s_lo = s_lo; a.s_hi = s_hi;
     a.g_score = g_score; a.g_var = g_var; a.g_diff = g_diff; a.g_sum = g_sum;
     a.order = order; a.rank = nullptr; a.peaks = peaks; a.n_cand = n_cand; a.n_selected = n_selected;
@@ -731,7 +731,7 @@ int lap_evaluate_weights(const lap_trace *tr, double link_GBps, uint64_t min_byt
     LAP_HIP(lap::launch_put_words(d_weights, weights, (size_t)W * 8, st));
     LAP_HIP(lap::launch_weighted_scores(n, W, d_weights, aoa, doa, wdoa, swdoa, bo, st));
     LAP_HIP(lap::launch_put_words(d_kinds, hk.data(), W, st));
-    a.K = W; a.L = 1; a.custom = bo; a.pick_wdoa = nullptr;
+    a.K = W; a.L = 1; a.greedy = false; a.custom = bo; a.pick_wdoa = nullptr;
     {
         ProfScope p(LAP_K_SELECT, st);
         LAP_HIP(lap::launch_select_swaps(a, false, st));

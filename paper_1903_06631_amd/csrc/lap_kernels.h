@@ -144,6 +144,7 @@ struct SelectArgs {
     uint32_t *c_ilo, *c_ihi;   // [n] idle steps [ilo, ihi) of the candidate in a slot
     uint64_t *dmin;            // [T+1] difference array of the load removed for load_min
     const uint32_t *kinds;     // [K]
+    bool greedy;               // whether one of them is 3
     const uint64_t *limits;    // [L]
     uint64_t *s_size;          // [K][n] size of the j-th pick
     uint32_t *s_lo, *s_hi;     // [K][n] steps [lo, hi) that the j-th pick leaves

@@ -7,9 +7,10 @@
 // (sel_greedy).  The peaks are then taken for stretches of the order side by side: a workgroup builds the curve
 // before its stretch from the picks ahead of it and walks the stretch (k_sel_peaks).
 // A walk of one workgroup per score over all slots and steps took 9 us a pick: 113.6 ms for the five scores
-// of a 14 000-step chain, where these take 11.4 ms; bound now by the dependent reductions of the greedy picks.
+// of a 14 000-step chain, where these take 10 ms; bound now by the dependent reductions of the greedy picks.
 #include "lap_dev.h"
 #include "lap_kernels.h"
+#include "step_runs.h"
 
 namespace lap {
 
@@ -19,6 +20,8 @@ constexpr int ORD_THREADS = 512, ORD_WAVES = ORD_THREADS / WAVE;
 constexpr int ORD_PER = 2;                     // leading candidates a thread holds
 constexpr int ORD_BATCH = 8;                   // independent loads of a thread in the passes over slots and steps
 constexpr uint32_t ORD_ACTIVE = ORD_THREADS * ORD_PER;
+constexpr uint32_t ORD_FEW = 2 * WAVE;         // of these, the ones that one wave picks from at a time
+constexpr uint32_t ORD_FEW_YIELD = 24, ORD_SIDE_MAX = 16 * ORD_FEW;
 constexpr uint32_t ORD_YIELD = 10;             // picks that a choice of leading candidates has to last for
 constexpr uint32_t ORD_WALK_MIN = 8, ORD_WALK_MAX = 128;   // picks without one after a choice that did not
 constexpr int PK_THREADS = 256, PK_WAVES = PK_THREADS / WAVE;
@@ -94,10 +97,10 @@ __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v)
     return ((uint64_t)hi << 32) | lo;
 }
 
-// the best of the first LANES lanes (8 or 64; the others hold none), in every lane.  Most often the upper halves of
-// the scores decide alone
+// the lane among the first LANES (8 or 64; the others hold none) with the best.  Most often the upper halves of the
+// scores decide alone
 template <int LANES>
-__device__ __forceinline__ Best wave_best(const Best &b)
+__device__ __forceinline__ int best_lane(uint64_t score, uint32_t var)
 {
     auto top = [](uint32_t v) {
         if (LANES == WAVE) return wave_max_u32(v);
@@ -106,7 +109,7 @@ __device__ __forceinline__ Best wave_best(const Best &b)
         v = max(v, dpp_mov<0x114>(0u, v));
         return read_lane(v, LANES - 1);
     };
-    const uint32_t hi = (uint32_t)(b.score >> 32), lo = (uint32_t)b.score;
+    const uint32_t hi = (uint32_t)(score >> 32), lo = (uint32_t)score;
     const uint32_t m_hi = top(hi);
     bool in = hi == m_hi;
     uint64_t at = ballot(in);
@@ -115,18 +118,34 @@ __device__ __forceinline__ Best wave_best(const Best &b)
         in = in && lo == m_lo;
         at = ballot(in);
         if (at & (at - 1)) {
-            const uint32_t nv = top(in ? ~b.var : 0u);
-            at = ballot(in && ~b.var == nv);
+            const uint32_t nv = top(in ? ~var : 0u);
+            at = ballot(in && ~var == nv);
         }
     }
-    const int src = __ffsll((unsigned long long)at) - 1;
+    return __ffsll((unsigned long long)at) - 1;
+}
+
+// the best of the first LANES lanes, in every lane
+template <int LANES>
+__device__ __forceinline__ Best wave_best(const Best &b)
+{
+    const int src = best_lane<LANES>(b.score, b.var);
     return Best{read_lane64(b.score, src), read_lane(b.var, src), read_lane(b.slot, src)};
 }
 
+// a wave's best with all that a pick needs
+struct alignas(16) Lead {
+    uint64_t score, size;
+    uint32_t var, slot, lo, hi;
+};
+
 struct GreedyLds {
     Best part[2][ORD_WAVES];
-    uint64_t size[ORD_ACTIVE], score[ORD_ACTIVE];
-    uint32_t var[ORD_ACTIVE], slot[ORD_ACTIVE], ilo[ORD_ACTIVE], ihi[ORD_ACTIVE], wlo[ORD_ACTIVE], whi[ORD_ACTIVE];
+    Lead lead[2][ORD_WAVES];
+    uint64_t score[ORD_ACTIVE];
+    uint32_t var[ORD_ACTIVE], slot[ORD_ACTIVE];
+    Lead few[ORD_FEW], picked[ORD_FEW];
+    uint32_t few_lo[ORD_FEW], few_hi[ORD_FEW], picks;
     uint64_t wa[ORD_WAVES], wb[ORD_WAVES];
     uint32_t hist[256];
     uint32_t count, fit, held;
@@ -152,14 +171,21 @@ __device__ __forceinline__ Best block_best(const Best &mine, GreedyLds &s, int t
 // was last computed, it is the next pick.  When it does not, the curve's prefix sums give every score anew, and the
 // leading ones are chosen again through a histogram.
 //
+// A pick is a chain of dependent instructions, so the shortest chain wins: of the held ones the few best, at most
+// ORD_FEW, go to one wave, two a lane, which picks without a barrier as long as its best leads the rest; then the
+// workgroup corrects the held ones by all of its picks at once and chooses the few again.  Where the few lead for less
+// than ORD_FEW_YIELD picks all waves pick together for a while, with one barrier a pick.  3000 variables, 348 steps:
+// 0.8 us a pick when all waves did every pick and one lane wrote each, 0.5 now; 4000 candidates, 1000 steps 3.34 and
+// 2.28 ms.
+//
 // Where the scores lie close together (thousands of variables with one idle interval: every pick lowers all of them
 // alike) the others soon lead and choosing anew would go with every pick.  A choice that lasts for less than ORD_YIELD
 // picks is therefore followed by picks that correct every candidate's score in memory and need no choice, more of
 // them each time in a row (a choice costs as much as about ten of them).  5000 candidates with one idle interval,
-// 1000 steps: 144 ms when every pick chose anew, 17 ms; 12 000 of them, 14 000 steps: 842 and 66 ms.
+// 1000 steps: 144 ms when every pick chose anew, 12 ms; 12 000 of them, 14 000 steps: 842 and 54 ms.
 //
 // On a curve that does not contain the candidates (nc[1]; a load given by the caller may be any) scores may rise:
-// nothing is held and every pick corrects every score.  20 000 candidates, 10 000 steps: 190 ms (569 ms when every
+// nothing is held and every pick corrects every score.  20 000 candidates, 10 000 steps: 154 ms (569 ms when every
 // pick took the prefix sums and all scores).
 __device__ void sel_greedy(const SelectArgs &a, uint32_t ks, GreedyLds &s)
 {
@@ -179,13 +205,13 @@ __device__ void sel_greedy(const SelectArgs &a, uint32_t ks, GreedyLds &s)
 
     uint32_t k = 0;
     int turn = 0;
-    auto pick = [&](uint32_t v, uint32_t slot, uint64_t sc, uint64_t sz, uint32_t lo, uint32_t hi) {
-        a.order[(size_t)ks * n + k] = v;
-        if (a.rank) a.rank[(size_t)ks * n + v] = k;
+    auto pick = [&](uint32_t at, uint32_t v, uint32_t slot, uint64_t sc, uint64_t sz, uint32_t lo, uint32_t hi) {
+        a.order[(size_t)ks * n + at] = v;
+        if (a.rank) a.rank[(size_t)ks * n + v] = at;
         if (a.pick_wdoa) a.pick_wdoa[v] = sc;
-        a.s_size[(size_t)ks * n + k] = sz;
-        a.s_lo[(size_t)ks * n + k] = lo;
-        a.s_hi[(size_t)ks * n + k] = hi;
+        a.s_size[(size_t)ks * n + at] = sz;
+        a.s_lo[(size_t)ks * n + at] = lo;
+        a.s_hi[(size_t)ks * n + at] = hi;
         var[slot] = NONE;
         if (hi > lo) {                           // hi < T: the last step of an idle interval is an access
             __hip_atomic_fetch_add(&dcur[lo], 0ull - sz, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -194,7 +220,7 @@ __device__ void sel_greedy(const SelectArgs &a, uint32_t ks, GreedyLds &s)
     };
     Best b{0, NONE, NONE};                       // the best of all, while `score` is up to date
     bool current = false;                        // whether it is
-    uint32_t walk = cap ? 0u : nc, next_walk = ORD_WALK_MIN;
+    uint32_t walk = cap ? 0u : nc, next_walk = ORD_WALK_MIN, side = 0, next_side = ORD_FEW;
     // prefix sums of the present curve, every score, and the best
     auto all_scores = [&]() {
         // the fence drops what this compute unit cached of it before the atomics
@@ -264,38 +290,92 @@ __device__ void sel_greedy(const SelectArgs &a, uint32_t ks, GreedyLds &s)
         b = block_best(b, s, turn);
         turn ^= 1;
     };
-    // up to `count` picks, each followed by a correction of every candidate's score
+    // one wave: how many of the 256 bins hold at most `most` candidates together, and how many those are
+    auto bins_that_fit = [&](uint32_t most) {
+        uint32_t h[4], t4 = 0;
+        for (int e = 0; e < 4; ++e) { h[e] = s.hist[4 * lane + e]; t4 += h[e]; }
+        uint32_t cum = (uint32_t)wave_scan_add_dpp(t4) - t4, bins = 0, holds = 0;
+        for (int e = 0; e < 4; ++e) {
+            cum += h[e];
+            if (cum <= most) { bins = 4 * lane + e + 1; holds = cum; }
+        }
+        bins = wave_max_u32(bins);
+        holds = wave_max_u32(holds);
+        if (lane == 0) { s.fit = bins; s.held = holds; }
+    };
+    // The last wave keeps the picks, one a lane, and writes 64 of them at a time: nothing else waits for a pick's eight
+    // stores.  They are written before the curve or the slots are read again.
+    const bool keeps = wave == ORD_WAVES - 1;
+    Lead kept{0, 0, NONE, 0, 0, 0};              // pick k_kept + lane
+    uint32_t k_kept = 0;
+    auto write_kept = [&]() {
+        if (keeps && lane < k - k_kept) pick(k_kept + lane, kept.var, kept.slot, kept.score, kept.size, kept.lo, kept.hi);
+        k_kept = k;
+    };
+    auto keep = [&](const Lead &w) {
+        if (keeps && lane == k - k_kept) kept = w;
+        ++k;
+        if (k - k_kept == WAVE) write_kept();
+    };
+    // up to `count` picks, each followed by a correction of every candidate's score.  The first 4096 candidates' are
+    // in registers meanwhile: what a pick waits for is the winner's size and window
+    // (4000 candidates with one idle interval, 1000 steps: 3 us a pick when all were read and written, 1.6 now)
     auto walk_on = [&](uint32_t count) {
+        constexpr uint32_t IN_REGS = ORD_THREADS * ORD_BATCH;
+        uint32_t v[ORD_BATCH], lo[ORD_BATCH], hi[ORD_BATCH];
+        uint64_t x[ORD_BATCH];
+#pragma unroll
+        for (int e = 0; e < ORD_BATCH; ++e) {
+            const uint32_t c = min(tid + e * ORD_THREADS, nc - 1);
+            v[e] = tid + e * ORD_THREADS < nc ? var[c] : NONE;
+            lo[e] = a.c_ilo[c];
+            hi[e] = a.c_ihi[c];
+            x[e] = score[c];
+        }
         while (count > 0 && k < nc) {
-            const Best w = b;
-            const uint64_t w_size = a.size[w.var];
-            const uint32_t w_lo = a.win_lo[w.var], w_hi = a.win_hi[w.var];
-            if (tid == 0) pick(w.var, w.slot, w.score, w_size, w_lo, w_hi);
-            ++k;
+            const Lead w{b.score, a.size[b.var], b.var, b.slot, a.win_lo[b.var], a.win_hi[b.var]};
+            keep(w);
             --count;
             b = Best{0, NONE, NONE};
-            for (uint32_t base = tid; base < nc; base += ORD_THREADS * ORD_BATCH) {
-                uint32_t v[ORD_BATCH], lo[ORD_BATCH], hi[ORD_BATCH];
-                uint64_t x[ORD_BATCH];
 #pragma unroll
-                for (int e = 0; e < ORD_BATCH; ++e) {
-                    const uint32_t c = min(base + e * ORD_THREADS, nc - 1);
-                    v[e] = base + e * ORD_THREADS < nc && c != w.slot ? var[c] : NONE;
-                    lo[e] = max(a.c_ilo[c], w_lo);
-                    hi[e] = min(a.c_ihi[c], w_hi);
-                    x[e] = score[c];
-                }
+            for (int e = 0; e < ORD_BATCH; ++e) {
+                if (e * ORD_THREADS + wave * WAVE >= nc) break;
+                const uint32_t l = max(lo[e], w.lo), h = min(hi[e], w.hi);
+                x[e] -= w.size * (uint64_t)(h > l ? h - l : 0u);
+                if (v[e] == w.var) v[e] = NONE;
+                const Best o{x[e], v[e], tid + e * ORD_THREADS};
+                if (v[e] != NONE && better(o, b)) b = o;
+            }
+            if (nc > IN_REGS) {
+                if (tid == 0) var[w.slot] = NONE;
+                for (uint32_t base = IN_REGS + tid; base < nc; base += IN_REGS) {
+                    uint32_t u[ORD_BATCH], l[ORD_BATCH], h[ORD_BATCH];
+                    uint64_t y[ORD_BATCH];
 #pragma unroll
-                for (int e = 0; e < ORD_BATCH; ++e) {
-                    if (v[e] == NONE) continue;
-                    const Best o{x[e] - w_size * (uint64_t)(hi[e] > lo[e] ? hi[e] - lo[e] : 0u), v[e], base + e * ORD_THREADS};
-                    if (hi[e] > lo[e]) score[o.slot] = o.score;
-                    if (better(o, b)) b = o;
+                    for (int e = 0; e < ORD_BATCH; ++e) {
+                        const uint32_t c = min(base + e * ORD_THREADS, nc - 1);
+                        u[e] = base + e * ORD_THREADS < nc && c != w.slot ? var[c] : NONE;
+                        l[e] = max(a.c_ilo[c], w.lo);
+                        h[e] = min(a.c_ihi[c], w.hi);
+                        y[e] = score[c];
+                    }
+#pragma unroll
+                    for (int e = 0; e < ORD_BATCH; ++e) {
+                        if (u[e] == NONE) continue;
+                        const Best o{y[e] - w.size * (uint64_t)(h[e] > l[e] ? h[e] - l[e] : 0u), u[e], base + e * ORD_THREADS};
+                        if (h[e] > l[e]) score[o.slot] = o.score;
+                        if (better(o, b)) b = o;
+                    }
                 }
             }
             b = block_best(b, s, turn);          // its barrier also orders the winner's slot before the next pass
             turn ^= 1;
         }
+#pragma unroll
+        for (int e = 0; e < ORD_BATCH; ++e)
+            if (v[e] != NONE) score[tid + e * ORD_THREADS] = x[e];
+        write_kept();
+        __syncthreads();                         // the slots of the last picks
     };
     while (k < nc) {
         if (!current) all_scores();
@@ -344,18 +424,7 @@ __device__ void sel_greedy(const SelectArgs &a, uint32_t ks, GreedyLds &s)
                     }
                 }
                 __syncthreads();
-                if (wave == 0) {                 // number of bins that fit, and what they hold
-                    uint32_t h[4], t4 = 0;
-                    for (int e = 0; e < 4; ++e) { h[e] = s.hist[4 * lane + e]; t4 += h[e]; }
-                    uint32_t cum = (uint32_t)wave_scan_add(t4) - t4, bins = 0, holds = 0;
-                    for (int e = 0; e < 4; ++e) {
-                        cum += h[e];
-                        if (cum <= cap) { bins = 4 * lane + e + 1; holds = cum; }
-                    }
-                    bins = wave_max_u32(bins);
-                    holds = wave_max_u32(holds);
-                    if (lane == 0) { s.fit = bins; s.held = holds; }
-                }
+                if (wave == 0) bins_that_fit(cap);
                 __syncthreads();
                 fit = s.fit;                     // 0: the first bin alone is too many
                 held = s.held;
@@ -389,44 +458,177 @@ __device__ void sel_greedy(const SelectArgs &a, uint32_t ks, GreedyLds &s)
         }
         bound = block_best(bound, s, turn);      // its barrier also publishes the held ones
         turn ^= 1;
-        for (uint32_t e = tid; e < held; e += ORD_THREADS) {
-            const uint32_t v = s.var[e], c = s.slot[e];
-            s.size[e] = a.size[v];
-            s.wlo[e] = a.win_lo[v]; s.whi[e] = a.win_hi[v];
-            s.ilo[e] = a.c_ilo[c]; s.ihi[e] = a.c_ihi[c];
-        }
-        __syncthreads();
-        uint64_t r_s[ORD_PER];
-        uint32_t r_v[ORD_PER], r_lo[ORD_PER], r_hi[ORD_PER];
+        uint64_t r_s[ORD_PER], r_size[ORD_PER];
+        uint32_t r_v[ORD_PER], r_slot[ORD_PER], r_lo[ORD_PER], r_hi[ORD_PER], r_wlo[ORD_PER], r_whi[ORD_PER];
 #pragma unroll
         for (int r = 0; r < ORD_PER; ++r) {
             const uint32_t e = r * ORD_THREADS + tid;
-            r_v[r] = NONE; r_s[r] = 0; r_lo[r] = r_hi[r] = 0;
-            if (e < held) { r_s[r] = s.score[e]; r_v[r] = s.var[e]; r_lo[r] = s.ilo[e]; r_hi[r] = s.ihi[e]; }
+            r_v[r] = NONE; r_s[r] = r_size[r] = 0; r_slot[r] = r_lo[r] = r_hi[r] = r_wlo[r] = r_whi[r] = 0;
+            if (e < held) {
+                const uint32_t v = s.var[e], c = s.slot[e];
+                r_s[r] = s.score[e]; r_v[r] = v; r_slot[r] = c;
+                r_lo[r] = a.c_ilo[c]; r_hi[r] = a.c_ihi[c];
+                r_wlo[r] = a.win_lo[v]; r_whi[r] = a.win_hi[v];
+                r_size[r] = a.size[v];
+            }
         }
-        uint32_t w_lo = 0, w_hi = 0, w_e = NONE;
-        uint64_t w_size = 0;
-        for (;;) {
-            Best m{0, NONE, NONE};
+        auto correct = [&](const Lead &w) {      // the held ones after a pick
 #pragma unroll
             for (int r = 0; r < ORD_PER; ++r) {
-                const uint32_t e = r * ORD_THREADS + tid;
                 if (r * ORD_THREADS + wave * WAVE >= held) break;
-                const uint32_t lo = max(r_lo[r], w_lo), hi = min(r_hi[r], w_hi);
-                r_s[r] -= w_size * (uint64_t)(hi > lo ? hi - lo : 0u);
-                if (e == w_e) { r_v[r] = NONE; r_s[r] = 0; r_hi[r] = 0; }
-                const Best o{r_s[r], r_v[r], e};
-                if (better(o, m)) m = o;
+                const uint32_t lo = max(r_lo[r], w.lo), hi = min(r_hi[r], w.hi);
+                r_s[r] -= w.size * (uint64_t)(hi > lo ? hi - lo : 0u);
+                if (r_v[r] == w.var) { r_v[r] = NONE; r_s[r] = 0; r_hi[r] = 0; }
             }
-            const Best g = block_best(m, s, turn);
+        };
+        uint32_t sh_few = M >> 8 ? 64 - 8 - __clzll(M) : 0;
+        for (;;) {
+            Best top{0, NONE, NONE};
+#pragma unroll
+            for (int r = 0; r < ORD_PER; ++r) {
+                const Best o{r_s[r], r_v[r], NONE};
+                if (better(o, top)) top = o;
+            }
+            top = block_best(top, s, turn);
             turn ^= 1;
-            if (g.var == NONE || !better(g, bound)) break;
-            w_e = g.slot;
-            w_lo = s.wlo[w_e];
-            w_hi = s.whi[w_e];
-            w_size = s.size[w_e];
-            if (tid == 0) pick(g.var, s.slot[w_e], g.score, w_size, w_lo, w_hi);
-            ++k;
+            if (top.var == NONE || !better(top, bound)) break;
+            // the few that lead the held ones: bins below the best score again, in the width that served last
+            uint32_t few_bins = 0, few = 0;
+            auto few_bin = [&](uint64_t x) { return (top.score >> sh_few) - (x >> sh_few); };
+            for (int tries = 0; side == 0; ++tries) {
+                if (tid < 256) s.hist[tid] = 0;
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < ORD_PER; ++r)
+                    if (r_v[r] != NONE) {
+                        const uint64_t bin = few_bin(r_s[r]);
+                        if (bin < 256) atomicAdd(&s.hist[(uint32_t)bin], 1u);
+                    }
+                __syncthreads();
+                if (wave == 0) bins_that_fit(ORD_FEW);
+                __syncthreads();
+                few_bins = s.fit;
+                few = s.held;
+                if (few >= ORD_FEW / 2 || tries == 3) break;
+                if (few_bins >= 255) {           // all there is nearby: a wider look, unless it is all
+                    if (sh_few >= 56 || few_bin(0) < 256) break;
+                    sh_few += 3;
+                } else {
+                    if (sh_few == 0) break;
+                    sh_few -= min(sh_few, (uint32_t)(__clz(few_bins + 1) - __clz(256)));
+                }
+            }
+            if (few == 0 || side > 0) {
+                // Too many share the best score, or the few did not lead for long: all waves look for the next picks.
+                // Every wave publishes its best with
+                // all that the pick needs of it, so that after the barrier one look at eight entries gives the winner
+                // and what it takes from the others
+                Lead w{0, 0, NONE, 0, 0, 0};
+                for (uint32_t picks = 0;; ++picks) {
+                    correct(w);
+                    if (picks == max(side, ORD_FEW)) break;
+                    Best m{0, NONE, 0};
+#pragma unroll
+                    for (int r = 0; r < ORD_PER; ++r) {
+                        const Best o{r_s[r], r_v[r], (uint32_t)r};
+                        if (better(o, m)) m = o;
+                    }
+                    if ((int)lane == best_lane<WAVE>(m.score, m.var)) {
+                        Lead o{m.score, r_size[0], m.var, r_slot[0], r_wlo[0], r_whi[0]};
+#pragma unroll
+                        for (int r = 1; r < ORD_PER; ++r)
+                            if (m.slot == (uint32_t)r) { o.size = r_size[r]; o.slot = r_slot[r]; o.lo = r_wlo[r]; o.hi = r_whi[r]; }
+                        s.lead[turn][wave] = o;
+                    }
+                    __syncthreads();
+                    Lead g{0, 0, NONE, 0, 0, 0};
+                    if (lane < ORD_WAVES) g = s.lead[turn][lane];
+                    turn ^= 1;
+                    const int src = best_lane<8>(g.score, g.var);
+                    w.score = read_lane64(g.score, src);
+                    w.var = read_lane(g.var, src);
+                    if (w.var == NONE || !better(Best{w.score, w.var, 0}, bound)) break;
+                    w.size = read_lane64(g.size, src);
+                    w.slot = read_lane(g.slot, src);
+                    w.lo = read_lane(g.lo, src);
+                    w.hi = read_lane(g.hi, src);
+                    keep(w);
+                }
+                write_kept();
+                side = 0;
+                continue;
+            }
+            if (tid == 0) s.count = 0;
+            __syncthreads();
+            Best rest = Best{0, NONE, NONE};
+#pragma unroll
+            for (int r = 0; r < ORD_PER; ++r) {
+                if (r_v[r] == NONE) continue;
+                if (few_bin(r_s[r]) < few_bins) {
+                    const uint32_t at = atomicAdd(&s.count, 1u);
+                    s.few[at] = Lead{r_s[r], r_size[r], r_v[r], r_slot[r], r_wlo[r], r_whi[r]};
+                    s.few_lo[at] = r_lo[r];
+                    s.few_hi[at] = r_hi[r];
+                } else {
+                    const Best o{r_s[r], r_v[r], NONE};
+                    if (better(o, rest)) rest = o;
+                }
+            }
+            rest = block_best(rest, s, turn);    // its barrier also publishes the few
+            turn ^= 1;
+            if (better(bound, rest)) rest = bound;
+            if (wave == 0) {
+                // one wave picks alone as long as its best leads: no barrier and no LDS between one pick and the next
+                Lead c[ORD_FEW / WAVE];
+                uint32_t c_lo[ORD_FEW / WAVE], c_hi[ORD_FEW / WAVE], picks = 0;
+#pragma unroll
+                for (int r = 0; r < (int)(ORD_FEW / WAVE); ++r) {
+                    const uint32_t at = r * WAVE + lane;
+                    c[r] = Lead{0, 0, NONE, 0, 0, 0};
+                    c_lo[r] = c_hi[r] = 0;
+                    if (at < few) { c[r] = s.few[at]; c_lo[r] = s.few_lo[at]; c_hi[r] = s.few_hi[at]; }
+                }
+                while (picks < ORD_FEW) {
+                    Lead m = c[0];
+#pragma unroll
+                    for (int r = 1; r < (int)(ORD_FEW / WAVE); ++r)
+                        if (better(Best{c[r].score, c[r].var, 0}, Best{m.score, m.var, 0})) m = c[r];
+                    const int src = best_lane<WAVE>(m.score, m.var);
+                    Lead w;
+                    w.score = read_lane64(m.score, src);
+                    w.var = read_lane(m.var, src);
+                    if (w.var == NONE || !better(Best{w.score, w.var, 0}, rest)) break;
+                    w.size = read_lane64(m.size, src);
+                    w.slot = read_lane(m.slot, src);
+                    w.lo = read_lane(m.lo, src);
+                    w.hi = read_lane(m.hi, src);
+                    if ((int)lane == src) s.picked[picks] = m;
+                    ++picks;
+#pragma unroll
+                    for (int r = 0; r < (int)(ORD_FEW / WAVE); ++r) {
+                        const uint32_t lo = max(c_lo[r], w.lo), hi = min(c_hi[r], w.hi);
+                        c[r].score -= w.size * (uint64_t)(hi > lo ? hi - lo : 0u);
+                        if (c[r].var == w.var) { c[r].var = NONE; c[r].score = 0; c_hi[r] = 0; }
+                    }
+                }
+                if (lane == 0) s.picks = picks;
+            }
+            __syncthreads();
+            const uint32_t picks = s.picks;
+            if (tid < picks) {
+                const Lead w = s.picked[tid];
+                pick(k + tid, w.var, w.slot, w.score, w.size, w.lo, w.hi);
+            }
+            for (uint32_t q = 0; q < picks; ++q) correct(s.picked[q]);
+            k += picks;
+            k_kept = k;
+            // a choice of the few costs as much as about a dozen picks by all waves
+            if (picks < ORD_FEW_YIELD) {
+                side = next_side;
+                next_side = min(2 * next_side, ORD_SIDE_MAX);
+            } else {
+                next_side = ORD_FEW;
+            }
         }
         if (k - k_chosen < ORD_YIELD) {
             walk = next_walk;
@@ -440,19 +642,25 @@ __device__ void sel_greedy(const SelectArgs &a, uint32_t ks, GreedyLds &s)
 }
 
 // The order of every row.  Grid: x over candidate slots (strided), y over rows.  Counting compares every pair, in
-// tiles of the workgroup's width: bound by the comparisons, 11 000 candidates need 1.2e8 a row.
+// tiles of the workgroup's width: bound by the comparisons, 11 000 candidates need 1.2e8 a row.  Greedy rows run beside
+// the counted ones (one launch after the other: swap planning of 50 000 variables 1 ms longer); calls without them have
+// a form of their own, since most workgroups of many rows find nothing to do and start faster with a tenth of the
+// registers (64 weight vectors on 200 000 variables: 0.2 ms of 1.1).
+template <bool GREEDY>
 __global__ __launch_bounds__(ORD_THREADS) void k_sel_order(SelectArgs a)
 {
-    __shared__ GreedyLds g;
+    __shared__ uint64_t t_score[ORD_THREADS];
+    __shared__ uint32_t t_var[ORD_THREADS];
     const uint32_t ks = blockIdx.y, kind = a.kinds[ks], n = a.n, nc = a.nc[0], tid = threadIdx.x;
     uint64_t *peaks = a.peaks + (size_t)ks * ((size_t)n + 1);
     for (uint32_t i = blockIdx.x * ORD_THREADS + tid; i <= nc; i += gridDim.x * ORD_THREADS) peaks[i] = 0;
-    if (kind == 3) {
-        if (blockIdx.x == 0) sel_greedy(a, ks, g);
-        return;
+    if constexpr (GREEDY) {
+        __shared__ GreedyLds g;
+        if (kind == 3) {
+            if (blockIdx.x == 0) sel_greedy(a, ks, g);
+            return;
+        }
     }
-    uint64_t *t_score = g.size;
-    uint32_t *t_var = g.var;
     for (uint32_t base = blockIdx.x * ORD_THREADS; base < nc; base += gridDim.x * ORD_THREADS) {
         const uint32_t c = base + tid;
         const uint32_t v = c < nc ? a.cidx[c] : NONE;
@@ -637,7 +845,11 @@ hipError_t launch_select_swaps(const SelectArgs &a, bool gather, hipStream_t st)
     // the number of candidates is not known here: enough workgroups for many, and few enough that the idle ones of a
     // small list cost little
     const uint32_t groups = (a.n + ORD_THREADS - 1) / ORD_THREADS, slices = (a.T - 1) / PK_SLICE + 1;
-    hipLaunchKernelGGL(k_sel_order, dim3(groups < 128 ? groups : 128, a.K), dim3(ORD_THREADS), 0, st, a);
+    uint32_t wide = 2048 / a.K;
+    wide = wide < 16 ? 16 : wide > 128 ? 128 : wide;
+    const dim3 grid(groups < wide ? groups : wide, a.K);
+    if (a.greedy) hipLaunchKernelGGL(k_sel_order<true>, grid, dim3(ORD_THREADS), 0, st, a);
+    else hipLaunchKernelGGL(k_sel_order<false>, grid, dim3(ORD_THREADS), 0, st, a);
     uint32_t stretches = 8192 / (slices * a.K);
     stretches = stretches < 32 ? 32 : stretches > 256 ? 256 : stretches;
     const uint32_t most = a.n / PK_MIN_STRETCH + 1;

@@ -101,6 +101,16 @@ def test_select_more_candidates_than_are_held(lap, oracle_mod, n, T, spread):
     assert _check(lap, oracle_mod, tr, 64.0, 1, [3, 2, 3], [n << 19, 0]) == n
 
 
+# the few leading ones of one wave (128) and the candidates a walk keeps in registers (4096), with equal scores or spread
+@pytest.mark.parametrize("n,T,spread", [(64, 60, 20), (127, 60, 20), (128, 60, 1), (129, 60, 1), (129, 60, 20), (900, 300, 100),
+                                        (1024, 200, 60), (4096, 50, 1), (4097, 50, 1), (4097, 80, 12)])
+def test_select_few_that_lead(lap, oracle_mod, n, T, spread):
+    rng = np.random.default_rng(n + spread)
+    lo, hi = 1 + rng.integers(0, spread, n), T - 2 - rng.integers(0, spread, n)
+    tr = mk_trace(rng.integers(1, 4, n) << 20, [0] * n, [T] * n, T=T, gap_lo=lo, gap_hi=hi)
+    assert _check(lap, oracle_mod, tr, 64.0, 1, [3], [n << 19, 0]) == n
+
+
 @pytest.mark.parametrize("n,T", [(1500, 30), (40, 5000)])
 def test_select_with_a_load_that_does_not_contain_the_candidates(lap, n, T):
     import torch
