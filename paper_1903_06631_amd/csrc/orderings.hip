@@ -254,6 +254,54 @@ __global__ __launch_bounds__(SW *WAVE) void k_sort_perm(uint32_t n, const uint64
     }
 }
 
+// The same order for few variables, by counting: a variable's rank is the number of smaller keys, and of equal ones with a
+// smaller index.  All keys lie in LDS and a wave reads them one after the other, alike in all lanes; the comparisons
+// bound it and grow with the square.  16 orderings of 120 variables 20.6 us by the radix sort, 5.4 us by this; 256 of 600
+// 28.4 and 23.3; 16 of 1024 32.0 and 35.0, 1024 of 1024 58 and 108.
+constexpr uint32_t RANK_VARS = 640;
+constexpr int RANK_THREADS = 512;
+__global__ __launch_bounds__(RANK_THREADS) void k_rank_perm(uint32_t n, const uint64_t *__restrict__ size,
+                                                            const uint32_t *__restrict__ alloc,
+                                                            const uint32_t *__restrict__ free_,
+                                                            const uint32_t *__restrict__ kinds,
+                                                            const uint64_t *__restrict__ seeds, uint32_t *perm_all)
+{
+    __shared__ uint64_t key[RANK_VARS];
+    const uint32_t b = blockIdx.x, kind = kinds[b];
+    const uint64_t seed = seeds[b];
+    uint32_t *perm = perm_all + (size_t)b * n;
+    if (kind == 5) {                             // caller-supplied: as in k_sort_perm
+        const uint32_t *src = (const uint32_t *)(uintptr_t)seed;
+        for (uint32_t i = threadIdx.x; i < n; i += RANK_THREADS) perm[i] = min(src[i], n - 1);
+        return;
+    }
+    for (uint32_t i = threadIdx.x; i < n; i += RANK_THREADS) key[i] = order_key(kind, seed, i, size, alloc, free_);
+    __syncthreads();
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    for (uint32_t i0 = wave * WAVE; i0 < n; i0 += RANK_THREADS) {
+        const uint32_t i = i0 + (uint32_t)lane_id(), i1 = min(i0 + WAVE, n);
+        const uint64_t x = key[min(i, n - 1)];
+        uint32_t rank = 0;
+        if (kind == 6) {
+            // equal keys are rare here and are decided by what the key leaves out
+            uint32_t upto = 0;
+#pragma unroll 8
+            for (uint32_t q = 0; q < n; ++q) { rank += key[q] < x ? 1u : 0u; upto += key[q] <= x ? 1u : 0u; }
+            if (upto - rank > 1)
+                for (uint32_t q = 0; q < n; ++q) rank += key[q] == x && seeded_after(kind, seed, min(i, n - 1), q, size) ? 1u : 0u;
+        } else {
+            // of the keys before this wave's 64 the equal ones count, of those behind they do not
+#pragma unroll 8
+            for (uint32_t q = 0; q < i0; ++q) rank += key[q] <= x ? 1u : 0u;
+#pragma unroll 8
+            for (uint32_t q = i0; q < i1; ++q) rank += key[q] < x || (key[q] == x && q < i) ? 1u : 0u;
+#pragma unroll 8
+            for (uint32_t q = i1; q < n; ++q) rank += key[q] < x ? 1u : 0u;
+        }
+        if (i < n) perm[rank] = i;
+    }
+}
+
 // A caller-supplied order must be a permutation of 0..N-1.  One that is not (an index out of
 // range, or one used twice) is replaced by the identity order, so that every variable is
 // still placed exactly once.  tmp is free after the sort and serves as the "seen" marks.
@@ -286,7 +334,10 @@ hipError_t launch_sort_perm(uint32_t n, uint32_t B, const uint64_t *size, const 
                             const uint32_t *kinds, const uint64_t *seeds, uint32_t *perm, uint32_t *tmp,
                             bool any_explicit, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_sort_perm, dim3(B), dim3(SW * WAVE), 0, st, n, size, alloc, free_, kinds, seeds, perm, tmp);
+    if (n <= RANK_VARS)
+        hipLaunchKernelGGL(k_rank_perm, dim3(B), dim3(RANK_THREADS), 0, st, n, size, alloc, free_, kinds, seeds, perm);
+    else
+        hipLaunchKernelGGL(k_sort_perm, dim3(B), dim3(SW * WAVE), 0, st, n, size, alloc, free_, kinds, seeds, perm, tmp);
     if (any_explicit)
         hipLaunchKernelGGL(k_sanitize_explicit, dim3(B), dim3(256), 0, st, n, kinds, seeds, perm, tmp);
     return hipGetLastError();
