@@ -35,9 +35,9 @@ struct PlanHeader {
 };
 constexpr uint32_t PLAN_CL = 6;
 
-// Placed blocks in registers (place_reg.hip): whether they may be used: 112 rows of 256 entries, 16-bit
+// Placed blocks in registers (place_reg.hip): whether they may be used: 128 rows of 256 entries, 16-bit
 // steps ...
-constexpr uint32_t PLAN_REG_MAX_VARS = 112 * 256;
+constexpr uint32_t PLAN_REG_MAX_VARS = 128 * 256;
 inline bool reg_may_place(uint32_t n, uint32_t T) { return n <= PLAN_REG_MAX_VARS && T <= 0xFFFFu; }
 // ... and whether they are, as far as the trace decides it: where per-step lists are not in use.  Up to 128 variables,
 // and up to 768 where the second rule says so (k_plan_prep2 asks it), these are not used although lifetimes are short

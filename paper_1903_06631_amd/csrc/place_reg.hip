@@ -21,8 +21,7 @@ namespace lap {
 
 namespace {
 
-// f(row number) for the rows I .. N-1 in ascending order, or N-1 .. I in descending, until it
-// returns false.  The number is a constant of the compilation: rows are registers and have no address.
+// f(row number) for the rows I .. N-1 in ascending order until it returns false.  The number is a constant of the compilation: rows are registers and have no address.
 template <int V> struct RowNo { static constexpr int value = V; };
 template <int I, int N, class F> __device__ __forceinline__ void rows_up(F &&f)
 {
@@ -30,10 +29,14 @@ template <int I, int N, class F> __device__ __forceinline__ void rows_up(F &&f)
         if (f(RowNo<I>{})) rows_up<I + 1, N>(f);
     }
 }
-template <int I, int N, class F> __device__ __forceinline__ void rows_down(F &&f)
+// ... descending, for the rows that come before `used` only (I is one of them): one branch leaves half of the rows out
+template <int I, int N, class F> __device__ __forceinline__ bool rows_down(uint32_t used, F &&f)
 {
-    if constexpr (I < N) {
-        if (f(RowNo<N - 1>{})) rows_down<I, N - 1>(f);
+    if constexpr (N - I == 1) return f(RowNo<I>{});
+    else {
+        constexpr int M = (I + N) / 2;
+        if (used > (uint32_t)M && !rows_down<M, N>(used, f)) return false;
+        return rows_down<I, M>(used, f);
     }
 }
 
@@ -130,9 +133,8 @@ __global__ __launch_bounds__(NW *WAVE) void k_place_reg(RegArgs A)
                     const uint64_t h = wave_min_hole(gap, at);
                     o = (uint32_t)(h >> 32) != NOTHING ? (uint32_t)h : P;
                 }
-                rows_down<0, R>([&](auto no) -> bool {
+                rows_down<0, R>(used, [&](auto no) -> bool {
                     constexpr int r = decltype(no)::value;
-                    if ((uint32_t)r >= used) return true;
                     uint32_t co = 0, ce = 0, cl = 0;
                     if constexpr (r > 0) {
                         co = read_lane(row[r - 1].off[EPL - 1], WAVE - 1);
@@ -144,7 +146,8 @@ __global__ __launch_bounds__(NW *WAVE) void k_place_reg(RegArgs A)
                 });
             } else {
                 const uint32_t buf = cnt & 1u;
-                constexpr int KEEP = R <= 4 ? R : 1;       // rows whose masked ends stay in registers between the steps
+                // the rows' masked ends stay in registers between the steps where there is room
+                constexpr int KEEP = R <= 5 ? R : 1;
                 uint32_t ends[KEEP][EPL], incls[KEEP];
                 rows_up<0, R>([&](auto no) -> bool {
                     constexpr int r = decltype(no)::value;
@@ -201,7 +204,7 @@ __global__ __launch_bounds__(NW *WAVE) void k_place_reg(RegArgs A)
                     o = (uint32_t)(h >> 32) != NOTHING ? (uint32_t)h : top;
                     o = (uint32_t)__builtin_amdgcn_readfirstlane((int)o);
                 }
-                rows_down<0, R>([&](auto no) -> bool {
+                rows_down<0, R>(R, [&](auto no) -> bool {
                     constexpr int r = decltype(no)::value;
                     const uint32_t id = r * NW + wave;
                     if (id >= used) return true;
@@ -241,19 +244,37 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
     const RegArgs A{n, (const uint4 *)vrec, perm, fits, hdr, offs, fps, ticks};
     const uint32_t rows = (n + ROW - 1) / ROW;
     // Up to 8 rows one wave is the fastest way through an ordering (1000 variables: 0.55 ms; 0.75 ms
-    // with 16 waves).  Beyond, 16 waves are (3000 variables: 2.6 ms instead of 3.3 ms), as long as every
-    // ordering has a compute unit to itself; where orderings share one, the same work done by fewer
-    // waves is more (1024 orderings of 3000: 4.2 ms with one wave, 6.8 ms with 16; 600 orderings of
-    // 6000: 13 ms with 4, 21 ms with 16).  More rows than fit fewer waves' registers need 16.
+    // with 16 waves).  Beyond, 12 or 16 waves are (193 orderings of 3000 variables: 2.57 ms with 12; 3.3 ms with one),
+    // as long as every ordering has a compute unit to itself; where orderings share one, the same work done by fewer
+    // waves is more: one wave up to 16 rows (1024 orderings of 3000: 4.0 ms, 4.6 with 4 waves and 5.2 with 8; 300 of
+    // 4000 4.99 ms, 5.08 with 8 and 5.13 with 16), 8 waves up to 40 rows, whose 128 registers a wave leave a unit two
+    // orderings (512 orderings of 6000: 8.7 ms, 11.6 with 4 waves and 9.2 with 12; of 8000: 13.0, 17.3 and 13.6;
+    // 1024 of 10 000: 34.6 ms, 53 with 12 or 16 waves).  More rows than that need 16.
+    // Rows that a trace cannot fill cost all the same (193 orderings of 9001: 11.5 ms with 12 waves of 3 rows, 11.8
+    // with 16), and up to 5 rows a wave keeps their ends (100 of 15 000: 22 ms with 4 rows, 30 with 7).
     const bool alone = B <= 256;
     if (rows <= 1) return launch_one<1, 1>(A, B, st);
     if (rows <= 2) return launch_one<1, 2>(A, B, st);
+    if (rows <= 3) return launch_one<1, 3>(A, B, st);
     if (rows <= 4) return launch_one<1, 4>(A, B, st);
     if (rows <= 8) return launch_one<1, 8>(A, B, st);
-    if (rows <= 16) return alone ? launch_one<16, 1>(A, B, st) : launch_one<1, 16>(A, B, st);
-    if (rows <= 40 && !alone) return launch_one<4, 10>(A, B, st);
+    if (alone) {
+        if (rows <= 12) return launch_one<12, 1>(A, B, st);
+        if (rows <= 16) return launch_one<16, 1>(A, B, st);
+        if (rows <= 24) return launch_one<12, 2>(A, B, st);
+        if (rows <= 36) return launch_one<12, 3>(A, B, st);
+    } else {
+        if (rows <= 16) return launch_one<1, 16>(A, B, st);
+        if (rows <= 24) return launch_one<8, 3>(A, B, st);
+        if (rows <= 32) return launch_one<8, 4>(A, B, st);
+        if (rows <= 40) return launch_one<8, 5>(A, B, st);
+    }
     if (rows <= 48) return launch_one<16, 3>(A, B, st);
-    return launch_one<16, 7>(A, B, st);
+    if (rows <= 64) return launch_one<16, 4>(A, B, st);
+    if (rows <= 80) return launch_one<16, 5>(A, B, st);
+    if (rows <= 112) return launch_one<16, 7>(A, B, st);
+    // 64, 256 and 1024 orderings of a residual chain of 32 767: 98, 99 and 392 ms; 436, 469 and 711 by the sweep
+    return launch_one<16, 8>(A, B, st);
 }
 
 }  // namespace lap

@@ -61,3 +61,15 @@ def test_sweep(lap, oracle_mod, B, T, fits):
     tr = random_trace(9600, 28700, T, size_choices=[1, 2, 3, 7, 20, 50], max_life=40)
     assert int((tr.free - tr.alloc).sum()) > 6 * tr.n_vars
     _check(lap, oracle_mod, tr, B, fits)
+
+
+@pytest.mark.parametrize("B,T,fits", [(8, 3000, "both"), (8, 700, "best"), (513, 3000, "first"), (513, 700, "both")])
+def test_sweep_beyond_the_registers(lap, oracle_mod, B, T, fits):
+    """one variable more than fits the registers, and no segment lists: the sweep's forms"""
+    tr = random_trace(9601, 32769, T, size_choices=[1, 2, 3, 7, 20, 50], max_life=40)
+    assert int((tr.free - tr.alloc).sum()) > 6 * tr.n_vars
+    lap.set_option(lap.OPT_SEG_MIN_VARS, 1 << 30)
+    try:
+        _check(lap, oracle_mod, tr, B, fits)
+    finally:
+        lap.set_option(lap.OPT_SEG_MIN_VARS, lap.SEG_MIN_VARS_DEFAULT)

@@ -91,3 +91,12 @@ def test_time_of_small_traces_of_one_step_variables(lap):
         lap.profile_enable(False)
     print(f"3 % multi-step {few:.3f} ms, 15 % {many:.3f} ms")
     assert few < 0.7 * many
+
+
+# the last size of every number of waves and rows, and one more; 257 orderings share the compute units
+@pytest.mark.parametrize("n,B", [(700, 8), (3072, 4), (3073, 4), (6144, 4), (6145, 4), (9216, 4), (9217, 4), (16384, 2), (16385, 2),
+                                 (20480, 2), (20481, 2), (28673, 2), (32767, 2), (4096, 257), (4097, 257), (6144, 257),
+                                 (6145, 257), (8192, 257), (8193, 257), (10240, 257), (10241, 257)])
+def test_forms(lap, oracle_mod, n, B):
+    tr = random_trace(9800 + n, n, 2000, size_choices=[1, 2, 3, 7, 20, 50])
+    _check(lap, oracle_mod, tr, B, [b % 2 for b in range(B)], [0, 1, B - 2, B - 1])
