@@ -456,15 +456,16 @@ int lap_plan_pool(const lap_trace *tr, const lap_ordering *ords, uint32_t B, uin
     uint32_t *l_ns = cf.take<uint32_t>((size_t)B * T);
     uint32_t *l_nu = cf.take<uint32_t>((size_t)B * T * 2);     // [B][T] unsorted counts, then [B][T] starts of the top holes
 
-    // The descriptors are split into three arrays; they reach the device inside kernel arguments,
-    // so nothing on the host has to outlive this call and nothing waits.
+    // The descriptors are split into three arrays that lie one after the other; they reach the device inside kernel
+    // arguments, so nothing on the host has to outlive this call and nothing waits.
     {
-        std::vector<uint32_t> hk(B), hf(B);
-        std::vector<uint64_t> hs(B);
-        for (uint32_t b = 0; b < B; ++b) { hk[b] = ords[b].kind; hf[b] = ords[b].fit; hs[b] = ords[b].seed; }
-        LAP_HIP(lap::launch_put_words(kinds, hk.data(), B, st));
-        LAP_HIP(lap::launch_put_words(fits, hf.data(), B, st));
-        LAP_HIP(lap::launch_put_words(seeds, hs.data(), (size_t)B * 2, st));
+        std::vector<uint32_t> h((uint32_t *)(seeds + B) - kinds);
+        for (uint32_t b = 0; b < B; ++b) {
+            h[b] = ords[b].kind;
+            h[(fits - kinds) + b] = ords[b].fit;
+            memcpy(&h[((uint32_t *)seeds - kinds) + 2 * (size_t)b], &ords[b].seed, 8);
+        }
+        LAP_HIP(lap::launch_put_words(kinds, h.data(), h.size(), st));
     }
 
     uint64_t *fps = footprints ? footprints : fps_ws;
@@ -473,9 +474,6 @@ int lap_plan_pool(const lap_trace *tr, const lap_ordering *ords, uint32_t B, uin
         ProfScope p(LAP_K_SORT, st);
         LAP_HIP(lap::launch_sort_perm(n, B, tr->size, tr->alloc, tr->free_, kinds, seeds, perm, tmp, any_explicit, st));
     }
-    static_assert(sizeof(lap::PlanHeader) % 8 == 0, "header is cleared in 64-bit words");
-    LAP_HIP(lap::launch_fill_u64((uint64_t *)hdr, sizeof(lap::PlanHeader) / 8, 0, st));
-    LAP_HIP(lap::launch_fill_u64((uint64_t *)cntd, ((size_t)T + 2) / 2, 0, st));
     const uint64_t seg_min_vars = g_seg_min_vars;
     const bool may_seg = n >= seg_min_vars;         // below, the header rules the segment lists out: no launches for them
     LAP_HIP(lap::launch_plan_prep(n, T, B, tr->size, tr->alloc, tr->free_, cntd, lstart, hdr, vrec,

@@ -100,7 +100,7 @@ __device__ __forceinline__ void row_insert(Row &R, uint32_t o, uint32_t xo, uint
                                            uint32_t cl)
 {
     const uint32_t po = lane_shift_up(R.off[3], co), pe = lane_shift_up(R.end[3], ce), pl = lane_shift_up(R.life[3], cl);
-    if (read_lane(R.off[0], 0) > o && co > o) {          // all of it moves
+    if (co > o) {                                        // all of it moves (no entry lies below the row's before)
 #pragma unroll
         for (int j = EPL - 1; j > 0; --j) { R.off[j] = R.off[j - 1]; R.end[j] = R.end[j - 1]; R.life[j] = R.life[j - 1]; }
         R.off[0] = po; R.end[0] = pe; R.life[0] = pl;

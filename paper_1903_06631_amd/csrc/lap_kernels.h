@@ -40,7 +40,7 @@ constexpr uint32_t PLAN_CL = 6;
 constexpr uint32_t PLAN_REG_MAX_VARS = 128 * 256;
 inline bool reg_may_place(uint32_t n, uint32_t T) { return n <= PLAN_REG_MAX_VARS && T <= 0xFFFFu; }
 // ... and whether they are, as far as the trace decides it: where per-step lists are not in use.  Up to 128 variables,
-// and up to 768 where the second rule says so (k_plan_prep2 asks it), these are not used although lifetimes are short
+// and up to 768 where the second rule says so (the preparation asks it), these are not used although lifetimes are short
 // enough for them.  A one-step variable costs the lists next to nothing and a multi-step one 3 to 5 us, while every
 // variable costs the registers 0.25 us and more for each row it asks: up to three rows the registers win from a share
 // of multi-step variables on that grows with the rows (times in registers over times with the lists, 16 best-fit

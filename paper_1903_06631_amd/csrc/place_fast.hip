@@ -22,7 +22,7 @@
 //          leaves a hole of at least `size` above it ends the sweep (first-fit,
 //          Section III-C: the lowest hole that is large enough).
 //   L[t]   (only when the sum of all lifetimes, plus one per step, is at most
-//          CL*N) the FREE address ranges ("holes") at step t, sorted by start,
+//          PLAN_CL*N) the FREE address ranges ("holes") at step t, sorted by start,
 //          packed (start << 32 | size), the last one reaching to 2^32-1;
 //          followed by an unsorted tail of multi-step blocks that were placed
 //          since and still have to be carved out.  A variable that lives for
@@ -38,7 +38,7 @@
 // Without the L[t] lists every variable queries ALL (the sweep): the way of traces too large for the
 // registers of a workgroup (place_reg.hip).  First-fit orderings of large
 // traces whose variables live long may instead be placed by free lists per time segment
-// (place_seg.hip); k_plan_prep2 and a trial run decide, and this kernel then leaves them alone.
+// (place_seg.hip); the preparation and a trial run decide, and this kernel then leaves them alone.
 //
 // One-step variables of different steps never interact, so between two
 // multi-step variables of the rank order the waves work in parallel: wave w
@@ -55,7 +55,6 @@ constexpr uint32_t PEND_FLUSH = 32; // pending entries at which they are sorted 
 constexpr uint32_t REC = PLAN_REC;  // recent (sorted) entries per buffer, global memory
 constexpr uint32_t PACE_RANKS = 512; // a workgroup reports its progress every this many ranks (power of two)
 constexpr uint32_t LH = 768;        // entries of a per-step list a wave can hold in LDS
-constexpr uint32_t CL = PLAN_CL;    // per-step lists need sum of lifetimes <= CL * N
 
 // orders this wave's earlier LDS / global accesses before its later ones (no barrier)
 __device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); }
@@ -98,156 +97,6 @@ template <> struct Life<uint32_t> {
 
 __device__ __forceinline__ uint32_t wave_scan_max32(uint32_t v) { return wave_scan_max_u32(v); }
 __device__ __forceinline__ uint32_t wave_reduce_max32(uint32_t v) { return read_lane(wave_scan_max_u32(v), WAVE - 1); }
-
-// ---------------------------------------------------------------------------
-// preparation: granule shift, lifetime statistics, per-step list layout
-// ---------------------------------------------------------------------------
-
-__global__ __launch_bounds__(256) void k_plan_prep1(uint32_t n, uint32_t T, const uint64_t *__restrict__ size,
-                                                    const uint32_t *__restrict__ alloc,
-                                                    const uint32_t *__restrict__ free_, uint32_t *cntd,
-                                                    PlanHeader *hdr)
-{
-    const uint32_t stride = gridDim.x * blockDim.x;
-    unsigned long long orv = 0, sum = 0;
-    unsigned long long seg[PLAN_SEG_CAND];
-#pragma unroll
-    for (uint32_t c = 0; c < PLAN_SEG_CAND; ++c) seg[c] = 0;
-    uint32_t multi = 0;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const uint64_t s = size[i];
-        const uint32_t a = alloc[i], f = free_[i];
-        orv |= s;
-        sum += s;
-        multi += (f - a > 1) ? 1u : 0u;
-        atomicAdd(&cntd[a], 1u);
-        atomicAdd(&cntd[f], 0xFFFFFFFFu);          // -1 modulo 2^32
-        // lists the block would enter with segments of 2^sh steps: one per segment it touches,
-        // one more per segment it lives through, one per step in the others
-#pragma unroll
-        for (uint32_t c = 0; c < PLAN_SEG_CAND; ++c) {
-            const uint32_t sh = PLAN_SEG_SHIFT0 + c, w = 1u << sh, K = (uint32_t)(((uint64_t)T + w - 1) >> sh);
-            const uint32_t k0 = a >> sh, k1 = (f - 1) >> sh;
-            const uint32_t kf0 = (uint32_t)(((uint64_t)a + w - 1) >> sh), kf1 = f == T ? K : f >> sh;
-            const uint32_t nf = kf1 > kf0 ? kf1 - kf0 : 0;
-            uint32_t steps = f - a;
-            if (nf) {
-                const uint64_t hi = (uint64_t)kf1 << sh;
-                steps -= (uint32_t)((hi < T ? hi : (uint64_t)T) - ((uint64_t)kf0 << sh));
-            }
-            seg[c] += 1ull + (k1 - k0 + 1) + nf + steps;      // (the first: the list of everything)
-        }
-    }
-    for (int m = WAVE / 2; m > 0; m >>= 1) orv |= shfl_xor64(orv, m);
-    sum = wave_reduce_add(sum);
-    multi = wave_reduce_add32(multi);
-#pragma unroll
-    for (uint32_t c = 0; c < PLAN_SEG_CAND; ++c) seg[c] = wave_reduce_add(seg[c]);
-    if ((threadIdx.x & (WAVE - 1)) == 0) {
-        atomicOr((unsigned long long *)&hdr->or_sizes, orv);
-        atomicAdd((unsigned long long *)&hdr->sum_sizes, sum);
-        atomicAdd(&hdr->n_multi, multi);
-#pragma unroll
-        for (uint32_t c = 0; c < PLAN_SEG_CAND; ++c) atomicAdd(&hdr->seg_tot[c], seg[c]);
-    }
-}
-
-constexpr int PREP_THREADS = 1024;
-
-__device__ __forceinline__ uint64_t prep_block_scan(uint64_t v, uint64_t *wtmp, uint64_t &total)
-{
-    const int tid = threadIdx.x, l = tid & (WAVE - 1), w = tid / WAVE;
-    const uint64_t incl = wave_scan_add(v);
-    if (l == WAVE - 1) wtmp[w] = incl;
-    __syncthreads();
-    uint64_t pre = 0, tot = 0;
-    for (int k = 0; k < PREP_THREADS / WAVE; ++k) {
-        const uint64_t x = wtmp[k];
-        if (k < w) pre += x;
-        tot += x;
-    }
-    __syncthreads();
-    total = tot;
-    return pre + incl;
-}
-
-// live[t] = number of variables live at step t; lstart = exclusive prefix sum of live + 1
-__global__ __launch_bounds__(PREP_THREADS) void k_plan_prep2(uint32_t n, uint32_t T, uint32_t B,
-                                                             const uint32_t *__restrict__ cntd,
-                                                             uint32_t *__restrict__ lstart, PlanHeader *hdr,
-                                                             uint64_t seg_pool_entries, uint64_t seg_min_vars)
-{
-    __shared__ uint64_t wtmp[PREP_THREADS / WAVE];
-    const uint32_t tid = threadIdx.x;
-    uint64_t c1 = 0, c2 = 0, tot;
-    for (uint32_t base = 0; base < T; base += PREP_THREADS) {
-        const uint32_t t = base + tid;
-        const bool in = t < T;
-        const uint64_t d = in ? (uint64_t)(int64_t)(int32_t)cntd[t] : 0;     // signed delta
-        const uint64_t live = c1 + prep_block_scan(d, wtmp, tot); c1 += tot;
-        // room for the holes: blocks + 1, rounded up to 16 entries so that every list starts on a
-        // 128-byte line (a fetch of n entries then touches ceil(n / 16) lines, not one more)
-        const uint64_t lv = in ? ((live + 1 + 15) & ~15ull) : 0;
-        const uint64_t incl = c2 + prep_block_scan(lv, wtmp, tot);
-        if (in) lstart[t] = (uint32_t)(incl - lv);
-        c2 += tot;
-    }
-    if (tid == 0) {
-        lstart[T] = (uint32_t)c2;
-        const uint64_t orv = hdr->or_sizes, sum = hdr->sum_sizes;
-        const uint32_t shift = orv ? (uint32_t)__ffsll((unsigned long long)orv) - 1 : 0;
-        const bool fast = (sum >> shift) < (1ull << 32);
-        const bool lists = fast && c2 <= (uint64_t)CL * n;
-        hdr->shift = shift;
-        hdr->fast = fast ? 1u : 0u;
-        hdr->mode1 = lists && !reg_before_lists(n, T, hdr->n_multi, B) ? 1u : 0u;
-        // Segment lists: the width that enters the fewest blocks into lists; every list has one
-        // entry more than the blocks it sees.  Taken when per-step lists are not, the trace has
-        // enough variables for them to pay (below that, sweeping the sorted blocks is faster), the
-        // list directory and one ordering fit 32-bit indices, addresses stay below the end marker
-        // of the top range, and the pool has room for at least one ordering.
-        uint32_t best_c = 0;
-        uint64_t best_need = ~0ull;
-        for (uint32_t c = 0; c < PLAN_SEG_CAND; ++c) {
-            const uint32_t sh = PLAN_SEG_SHIFT0 + c;
-            const uint64_t K = ((uint64_t)T + (1ull << sh) - 1) >> sh;
-            const uint64_t need = hdr->seg_tot[c] + 2 * K + T + 1;
-            if (need < best_need) { best_need = need; best_c = c; }
-        }
-        // ... or rather the narrowest width within an eighth of that: narrower segments mean fewer
-        // lists per variable (a variable asks about lifetime / w + w of them)
-        for (uint32_t c = 0; c < best_c; ++c) {
-            const uint32_t sh = PLAN_SEG_SHIFT0 + c;
-            const uint64_t K = ((uint64_t)T + (1ull << sh) - 1) >> sh;
-            const uint64_t need = hdr->seg_tot[c] + 2 * K + T + 1;
-            if (need <= best_need + best_need / 8) { best_need = need; best_c = c; break; }
-        }
-        const uint32_t ssh = PLAN_SEG_SHIFT0 + best_c;
-        const uint64_t K = ((uint64_t)T + (1ull << ssh) - 1) >> ssh;
-        const uint64_t slots = best_need ? seg_pool_entries / best_need : 0;
-        const bool seg = fast && !lists && n >= seg_min_vars && (sum >> shift) < 0xFFFFFFFEull &&
-                         best_need < 0xFFFFFFFFull && T < 0x7FFF0000u && slots >= 1;
-        hdr->mode2 = seg ? 1u : 0u;
-        hdr->seg_shift = ssh;
-        hdr->seg_K = (uint32_t)K;
-        hdr->seg_slots = (uint32_t)(slots < B ? slots : B);
-        hdr->seg_need = best_need;
-    }
-}
-
-// What the placement kernel reads of a variable, in one 16-byte record (one gather per rank
-// instead of three): first step, end of life, size in granules.  Only meaningful on the
-// 32-bit path (size >> shift fits 32 bits there).
-__global__ __launch_bounds__(256) void k_plan_pack(uint32_t n, const uint64_t *__restrict__ size,
-                                                   const uint32_t *__restrict__ alloc,
-                                                   const uint32_t *__restrict__ free_, const PlanHeader *hdr,
-                                                   uint4 *__restrict__ vrec)
-{
-    if (!hdr->fast) return;
-    const uint32_t sh = hdr->shift;
-    for (uint32_t v = blockIdx.x * 256 + threadIdx.x; v < n; v += gridDim.x * 256)
-        vrec[v] = make_uint4(alloc[v], free_[v], (uint32_t)(size[v] >> sh), 0u);
-}
 
 // ---------------------------------------------------------------------------
 // sorted lists of packed blocks (global memory or LDS), one wave
@@ -1619,19 +1468,6 @@ void launch_policy(const FastArgs &A, uint32_t B, bool any_first, bool any_best,
     if (any_first && any_best) hipLaunchKernelGGL((k_place_fast<LT, PW, META, 2>), dim3(B), dim3(PW * WAVE), lds, st, A);
     else if (any_best) hipLaunchKernelGGL((k_place_fast<LT, PW, META, 1>), dim3(B), dim3(PW * WAVE), lds, st, A);
     else hipLaunchKernelGGL((k_place_fast<LT, PW, META, 0>), dim3(B), dim3(PW * WAVE), lds, st, A);
-}
-
-hipError_t launch_plan_prep(uint32_t n, uint32_t T, uint32_t B, const uint64_t *size, const uint32_t *alloc,
-                            const uint32_t *free_, uint32_t *cntd, uint32_t *lstart, PlanHeader *hdr, void *vrec,
-                            uint64_t seg_pool_entries, uint64_t seg_min_vars, hipStream_t st)
-{
-    uint32_t blocks = (n + 255) / 256;
-    blocks = blocks > 1024 ? 1024 : blocks;
-    hipLaunchKernelGGL(k_plan_prep1, dim3(blocks), dim3(256), 0, st, n, T, size, alloc, free_, cntd, hdr);
-    hipLaunchKernelGGL(k_plan_prep2, dim3(1), dim3(PREP_THREADS), 0, st, n, T, B, cntd, lstart, hdr, seg_pool_entries,
-                       seg_min_vars);
-    hipLaunchKernelGGL(k_plan_pack, dim3(blocks), dim3(256), 0, st, n, size, alloc, free_, hdr, (uint4 *)vrec);
-    return hipGetLastError();
 }
 
 hipError_t launch_place_fast(uint32_t n, uint32_t T, uint32_t B, const uint64_t *size, const uint32_t *alloc,

@@ -242,57 +242,44 @@ __global__ __launch_bounds__(64) void k_place_wide(uint32_t n, const uint64_t *_
     }
 }
 
-// best = lowest index among the smallest footprints
-__global__ __launch_bounds__(256) void k_select(uint32_t B, const uint64_t *__restrict__ fps,
-                                                uint64_t *__restrict__ best_fp, uint32_t *__restrict__ best_idx)
+// The placement kernels leave their offsets in rank order (entry r belongs to variable perm[r]): stores of neighbouring
+// ranks fall into the same cache lines.  The results asked for are put in variable order here: all orderings' where the
+// caller wants them (a row of the grid each), and the best one's, the lowest index among the smallest footprints.  Every
+// workgroup of the first row finds that one itself: B words that lie in the L2, where a kernel of its own before the copy
+// and one after it were two launches more (each 2 to 4 us of the 100 that a plan of 120 variables took).
+constexpr int OUT_THREADS = 256;
+__global__ __launch_bounds__(OUT_THREADS) void k_plan_out(uint32_t n, uint32_t B, const uint64_t *__restrict__ fps,
+                                                          const uint64_t *__restrict__ offs_rank,
+                                                          const uint32_t *__restrict__ perm_all,
+                                                          uint64_t *__restrict__ best_fp, uint32_t *__restrict__ best_idx,
+                                                          uint64_t *__restrict__ best_offsets,
+                                                          uint64_t *__restrict__ all_offsets)
 {
-    __shared__ uint64_t sv[256];
-    __shared__ uint32_t si[256];
+    const uint32_t first = blockIdx.x * OUT_THREADS + threadIdx.x, stride = gridDim.x * OUT_THREADS;
+    if (all_offsets) {
+        const size_t row = (size_t)blockIdx.y * n;
+        for (uint32_t i = first; i < n; i += stride) all_offsets[row + perm_all[row + i]] = offs_rank[row + i];
+    }
+    if (blockIdx.y != 0) return;
+    __shared__ uint64_t sv[OUT_THREADS / WAVE];
+    __shared__ uint32_t si[OUT_THREADS / WAVE];
     uint64_t v = U64_MAX;
     uint32_t ix = 0xFFFFFFFFu;
-    for (uint32_t b = threadIdx.x; b < B; b += blockDim.x) {
-        const uint64_t x = fps[b];
+    auto take = [&](uint64_t x, uint32_t b) {
         if (x < v || (x == v && b < ix)) { v = x; ix = b; }
+    };
+    for (uint32_t b = threadIdx.x; b < B; b += OUT_THREADS) take(fps[b], b);
+#pragma unroll
+    for (int m = 1; m < WAVE; m <<= 1) {
+        const uint64_t x = shfl_xor64(v, m);
+        take(x, (uint32_t)__shfl_xor((int)ix, m, WAVE));
     }
-    sv[threadIdx.x] = v; si[threadIdx.x] = ix;
+    if (lane_id() == 0) { sv[threadIdx.x / WAVE] = v; si[threadIdx.x / WAVE] = ix; }
     __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) {
-            const uint64_t x = sv[threadIdx.x + st];
-            const uint32_t j = si[threadIdx.x + st];
-            if (x < sv[threadIdx.x] || (x == sv[threadIdx.x] && j < si[threadIdx.x])) {
-                sv[threadIdx.x] = x; si[threadIdx.x] = j;
-            }
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) { *best_fp = sv[0]; *best_idx = si[0]; }
-}
-
-// The placement kernels leave their offsets in rank order (entry r belongs to variable
-// perm[r]): stores of neighbouring ranks fall into the same cache lines.  The results asked for
-// are put in variable order here: the best ordering's, and all B when the caller wants them.
-__global__ __launch_bounds__(256) void k_copy_best(uint32_t n, const uint64_t *__restrict__ offs_rank,
-                                                   const uint32_t *__restrict__ perm_all,
-                                                   const uint32_t *__restrict__ best_idx,
-                                                   uint64_t *__restrict__ best_offsets)
-{
-    const uint64_t *src = offs_rank + (size_t)(*best_idx) * n;
-    const uint32_t *perm = perm_all + (size_t)(*best_idx) * n;
-    const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) best_offsets[perm[i]] = src[i];
-}
-
-__global__ __launch_bounds__(256) void k_unpermute(uint32_t n, const uint64_t *__restrict__ offs_rank,
-                                                   const uint32_t *__restrict__ perm_all,
-                                                   uint64_t *__restrict__ all_offsets)
-{
-    const size_t b = blockIdx.y;
-    const uint64_t *src = offs_rank + b * n;
-    const uint32_t *perm = perm_all + b * n;
-    uint64_t *dst = all_offsets + b * n;
-    const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) dst[perm[i]] = src[i];
+    for (int w = 0; w < OUT_THREADS / WAVE; ++w) take(sv[w], si[w]);
+    if (blockIdx.x == 0 && threadIdx.x == 0) { *best_fp = v; *best_idx = ix; }
+    const size_t row = (size_t)ix * n;
+    for (uint32_t i = first; i < n; i += stride) best_offsets[perm_all[row + i]] = offs_rank[row + i];
 }
 
 hipError_t launch_place_wide(uint32_t n, uint32_t B, const uint64_t *size, const uint32_t *alloc, const uint32_t *free_,
@@ -309,14 +296,11 @@ hipError_t launch_select(uint32_t n, uint32_t B, const uint64_t *fps, const uint
                          uint64_t *best_fp, uint32_t *best_idx, uint64_t *best_offsets, uint64_t *all_offsets,
                          hipStream_t st)
 {
-    hipLaunchKernelGGL(k_select, dim3(1), dim3(256), 0, st, B, fps, best_fp, best_idx);
-    uint32_t blocks = (n + 255) / 256;
-    blocks = blocks > 1024 ? 1024 : blocks;
-    hipLaunchKernelGGL(k_copy_best, dim3(blocks), dim3(256), 0, st, n, offs_rank, perm, best_idx, best_offsets);
-    if (all_offsets) {
-        blocks = blocks > 64 ? 64 : blocks;
-        hipLaunchKernelGGL(k_unpermute, dim3(blocks, B), dim3(256), 0, st, n, offs_rank, perm, all_offsets);
-    }
+    uint32_t blocks = (n + OUT_THREADS - 1) / OUT_THREADS;
+    const uint32_t most = all_offsets ? 64 : 1024;
+    if (blocks > most) blocks = most;
+    hipLaunchKernelGGL(k_plan_out, dim3(blocks, all_offsets ? B : 1), dim3(OUT_THREADS), 0, st, n, B, fps, offs_rank, perm,
+                       best_fp, best_idx, best_offsets, all_offsets);
     return hipGetLastError();
 }
 
