@@ -70,7 +70,8 @@ hipError_t launch_scan_peak(uint32_t T, uint64_t *delta, uint64_t *load, uint64_
                             hipStream_t st);
 // The load profile in one launch by one workgroup.  The three launches (fill, scatter, scan) take 11.4 to 12.9 us whatever
 // the number of variables up to 50 000; this one 6.4 us for 100 of them, 8 to 9 us for 8000, 9.6 to 11.7 us for 16 000
-// and 13 to 17 us for 32 768 (20 to 2000 steps).  8191 steps: 8.8 to 11.6 us up to 16 000, and 17 us by three.
+// and 13 to 17 us for 32 768 (20 to 2000 steps).  8191 steps: 8.8 to 11.6 us up to 16 000, and 17 us by three.  (By
+// k_delta_line the three take 1 to 3 us less: whole calls of 16 384 variables 26 to 29 us, of 16 385 29 to 33.)
 constexpr uint32_t LOAD_SMALL_VARS = 16384, LOAD_SMALL_STEPS = 8191;
 hipError_t launch_load_small(uint32_t n, uint32_t T, const uint64_t *size, const uint32_t *alloc, const uint32_t *free_,
                              uint64_t *load, uint64_t *peak, uint32_t *t_peak, hipStream_t st);

@@ -31,15 +31,14 @@ __global__ __launch_bounds__(256) void k_put_words(uint32_t *dst, uint32_t count
     for (uint32_t i = threadIdx.x; i < count; i += blockDim.x) dst[i] = c.w[i];
 }
 
-// A workgroup owns 4096 consecutive variables, reads them once (16-byte vector loads where the arrays
-// are aligned for them, kept in registers), finds the step range their events fall into and, when that
+// Long time lines: a workgroup owns 4096 consecutive variables, reads them once (16-byte vector loads where the
+// arrays are aligned for them, kept in registers), finds the step range their events fall into and, when that
 // range fits the LDS bins, accumulates there and flushes the bins with global atomics; otherwise it adds
 // to global memory directly.  Arithmetic is modulo 2^64; the prefix sums are non-negative so wrap-around
-// cancels.  Bound by the memory it reads once
-// runs of equal steps are summed before they reach the bins: 50 million variables in the order in which
-// they are allocated, about 345 a step, take 136 us = 5.9 TB/s (340 us when every variable added to the
-// bins itself and the LDS served a wave's adds one by one); 134 million with temporaries at random
-// steps, where few neighbours agree, 390 us either way.
+// cancels.  Bound by the memory it reads once runs of equal steps are summed before they reach the bins:
+// 50 million variables in the order in which they are allocated, about 345 a step, take 136 us = 5.9 TB/s
+// (340 us when every variable added to the bins itself and the LDS served a wave's adds one by one);
+// 134 million with temporaries at random steps, where few neighbours agree, 390 us either way.
 constexpr int DW_THREADS = 256;
 constexpr int DW_GROUPS = 4;                       // groups of 4 variables per thread
 constexpr uint32_t DW_PER_BLOCK = DW_THREADS * DW_GROUPS * 4;
@@ -144,6 +143,44 @@ __global__ __launch_bounds__(DW_THREADS) void k_delta_window(uint32_t n, uint32_
                     atomicAdd(&delta[x[g].al[k]], (unsigned long long)x[g].sz[k]);
                     atomicAdd(&delta[x[g].fr[k]], (unsigned long long)(0ull - x[g].sz[k]));
                 }
+    }
+}
+
+// Short time lines: the bins of all steps lie in LDS, so the variables may come in any order.  A workgroup takes a
+// stretch of them, 4096 at a time with the next 4096 on their way, and flushes its bins once at the end: what the flush
+// adds to memory grows with the workgroups, not with the variables.  One workgroup a compute unit, and none that takes
+// fewer variables than it has bins.  Bound by the memory it reads (whole calls, of which about 28 us are the other
+// launches and the host): 42 million variables at random steps of 1000, 4000 and 8191 137, 138 and 145 us = 6 TB/s,
+// and 139 to 145 us in the order in which they are allocated; 2.5 million 37 to 52 us.
+// A flush for every 4096 variables took 269, 313 and 758 us at random steps and 215 to 242 us in order (2.5 million: 40
+// to 82); 1024 workgroups of four waves that took a variable a lane at a time 207, 209 and 355, and 232 to 355 in order.
+// One million over 8191 steps, where there are as many bins as variables a workgroup: 40 us, 50 with 4096 variables each.
+constexpr int DL_THREADS = 1024;
+constexpr uint32_t DL_TILE = DL_THREADS * 4, DL_BLOCKS = 256, DL_BINS = 8192;
+__global__ __launch_bounds__(DL_THREADS) void k_delta_line(uint32_t n, uint32_t T, uint32_t per_block,
+                                                           const uint64_t *__restrict__ size,
+                                                           const uint32_t *__restrict__ alloc,
+                                                           const uint32_t *__restrict__ free_,
+                                                           unsigned long long *delta)
+{
+    extern __shared__ unsigned long long bins[];
+    const bool vec = (((uintptr_t)size | (uintptr_t)alloc | (uintptr_t)free_) & 15) == 0;
+    const uint64_t begin = (uint64_t)blockIdx.x * per_block, all = begin + per_block;
+    const uint32_t end = all < n ? (uint32_t)all : n, wave0 = (threadIdx.x & ~(WAVE - 1u)) * 4;
+    Four x, y;
+    load_four(x, (uint32_t)begin + threadIdx.x * 4, end, vec, size, alloc, free_);
+    for (uint32_t t = threadIdx.x; t <= T; t += DL_THREADS) bins[t] = 0;
+    __syncthreads();
+    // (whole waves go round: those beyond the last variable have nothing to add)
+    for (uint64_t base = begin; base + wave0 < end; base += DL_TILE) {
+        load_four(y, (uint32_t)base + DL_TILE + threadIdx.x * 4, end, vec, size, alloc, free_);
+        bin_four(x, bins, 0);
+        x = y;
+    }
+    __syncthreads();
+    for (uint32_t t = threadIdx.x; t <= T; t += DL_THREADS) {
+        const unsigned long long v = bins[t];
+        if (v) atomicAdd(&delta[t], v);
     }
 }
 
@@ -428,14 +465,21 @@ hipError_t launch_put_words(void *dst, const void *host_src, size_t n_words, hip
 hipError_t launch_delta(uint32_t n, uint32_t T, const uint64_t *size, const uint32_t *alloc, const uint32_t *free_,
                         uint64_t *delta, hipStream_t st)
 {
-    // Up to 8192 bins (64 KiB, two workgroups on a compute unit) hold the whole time line, so any order of the variables
-    // stays in the LDS; of longer ones 2048 (16 KiB) hold what a workgroup's variables mostly span.  (2.6 million variables
-    // over 7540 steps, the whole call: 44.8 us with bins for all steps in every workgroup and one load at a time, 24.9 us.)
-    constexpr uint32_t ALL_BINS = 8192, WIN_BINS = 2048;
-    const uint32_t bins = T < ALL_BINS ? T + 1 : WIN_BINS;
+    // Up to 8192 bins (64 KiB) hold the whole time line; of longer ones 2048 (16 KiB, several workgroups on a compute
+    // unit) hold what 4096 variables mostly span.
+    if (T < DL_BINS) {
+        const uint32_t least = T + 1 > DL_TILE ? T + 1 : DL_TILE;
+        uint32_t blocks = (n - 1) / least + 1;
+        if (blocks > DL_BLOCKS) blocks = DL_BLOCKS;
+        const uint32_t per_block = ((n - 1) / blocks + 4) & ~3u;       // whole 16-byte loads
+        hipLaunchKernelGGL(k_delta_line, dim3(blocks), dim3(DL_THREADS), ((size_t)T + 1) * sizeof(uint64_t), st, n, T,
+                           per_block, size, alloc, free_, (unsigned long long *)delta);
+        return hipGetLastError();
+    }
+    constexpr uint32_t WIN_BINS = 2048;
     const uint32_t blocks = (n - 1) / DW_PER_BLOCK + 1;
-    hipLaunchKernelGGL(k_delta_window, dim3(blocks), dim3(DW_THREADS), bins * sizeof(uint64_t), st, n, bins, size, alloc,
-                       free_, (unsigned long long *)delta);
+    hipLaunchKernelGGL(k_delta_window, dim3(blocks), dim3(DW_THREADS), WIN_BINS * sizeof(uint64_t), st, n, WIN_BINS, size,
+                       alloc, free_, (unsigned long long *)delta);
     return hipGetLastError();
 }
 

@@ -55,3 +55,49 @@ def test_load_profile_unaligned_arrays(oracle_mod, n, T, off):
     load, peak, at = oracle_mod.load_profile(tr)
     assert np.array_equal(u64(got["load"]), load)
     assert int(u64(got["peak"])[0]) == peak and int(got["t_peak"].item()) == at
+
+
+# on both sides of the number of steps whose bins lie in LDS together; variables for one and for several workgroups, for
+# less and more than a turn of each; with events at the first and at the last step
+@pytest.mark.parametrize("in_order", [False, True])
+@pytest.mark.parametrize("n,T", [(16385, 1), (16385, 8191), (16385, 8192), (20000, 4095), (20000, 4096), (65537, 8191),
+                                 (1_048_577, 4094), (2_100_003, 8191), (2_100_003, 3)])
+def test_load_profile_short_lines(oracle_mod, n, T, in_order):
+    import paper_1903_06631_amd as lap
+    rng = np.random.default_rng(n + T)
+    alloc = rng.integers(0, T, n)
+    alloc[:2], alloc[-2:] = 0, T - 1
+    free = np.minimum(T, alloc + rng.integers(1, 40, n))
+    free[::997] = T
+    if in_order:
+        o = np.argsort(alloc, kind="stable")
+        alloc, free = alloc[o], free[o]
+    tr = mk_trace(rng.integers(1, 1 << 40, n), alloc, free, T=T)
+    got = lap.load_profile(lap.DeviceTrace(tr, use_gaps=False))
+    load, peak, at = oracle_mod.load_profile(tr)
+    assert np.array_equal(u64(got["load"]), load)
+    assert int(u64(got["peak"])[0]) == peak and int(got["t_peak"].item()) == at
+
+
+def test_load_profile_unordered_time():
+    """On a time line whose bins all lie in LDS the order of the variables costs next to nothing (1.1 times the time of
+    variables in order; 3.1 times when a workgroup flushed its bins after every 4096 variables)."""
+    import torch
+    import paper_1903_06631_amd as lap
+    n, T = 16 << 20, 8191
+    rng = np.random.default_rng(1)
+    alloc = rng.integers(0, T, n)
+    best = []
+    lap.profile_enable(True)
+    try:
+        for a in (np.sort(alloc), alloc):
+            dt = lap.DeviceTrace(mk_trace(np.full(n, 512), a, a + 1, T=T), use_gaps=False)
+            times = []
+            for _ in range(8):
+                lap.load_profile(dt, sync=False)
+                torch.cuda.synchronize()
+                times.append(lap.profile_last_ms(lap.K_LOAD_SCATTER))
+            best.append(min(times[1:]))
+    finally:
+        lap.profile_enable(False)
+    assert best[1] < 1.8 * best[0], best
