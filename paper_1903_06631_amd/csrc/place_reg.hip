@@ -247,9 +247,13 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
     // with 16 waves).  Beyond, 12 or 16 waves are (193 orderings of 3000 variables: 2.57 ms with 12; 3.3 ms with one),
     // as long as every ordering has a compute unit to itself; where orderings share one, the same work done by fewer
     // waves is more: one wave up to 16 rows (1024 orderings of 3000: 4.0 ms, 4.6 with 4 waves and 5.2 with 8; 300 of
-    // 4000 4.99 ms, 5.08 with 8 and 5.13 with 16), 8 waves up to 40 rows, whose 128 registers a wave leave a unit two
-    // orderings (512 orderings of 6000: 8.7 ms, 11.6 with 4 waves and 9.2 with 12; of 8000: 13.0, 17.3 and 13.6;
-    // 1024 of 10 000: 34.6 ms, 53 with 12 or 16 waves).  More rows than that need 16.
+    // 4000 4.99 ms, 5.08 with 8 and 5.13 with 16), 8 waves up to 40 rows.  Of more than 24 rows, 8 waves (96 and 115
+    // registers) leave a unit two orderings and 4 waves (154) three, so what 4 waves lose in a round they win where they
+    // need one round and 8 waves two, from 513 to 768 orderings, and nowhere else (ms with 8 and with 4 waves, of
+    //   6400:   512 orderings 9.7 and 12.6, 513 15.6 and 13.9, 768 15.7 and 14.3, 800 18.8 and 22.7, 1536 27.9 and 28.2
+    //   8192:   512           13.5    18.0, 513 21.4     20.3, 768 21.7     20.7, 800 26.2     32.4, 1536 38.7     40.7
+    //   10 000: 512           17.9    24.6, 513 28.4     27.7, 768 28.7     28.5, 800 34.7     44.0, 1536 51.3     55.6).
+    // More rows than 40 need 16.
     // Rows that a trace cannot fill cost all the same (193 orderings of 9001: 11.5 ms with 12 waves of 3 rows, 11.8
     // with 16), and up to 5 rows a wave keeps their ends (100 of 15 000: 22 ms with 4 rows, 30 with 7).
     const bool alone = B <= 256;
@@ -266,6 +270,7 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
     } else {
         if (rows <= 16) return launch_one<1, 16>(A, B, st);
         if (rows <= 24) return launch_one<8, 3>(A, B, st);
+        if (rows <= 40 && B > 512 && B <= 768) return launch_one<4, 10>(A, B, st);
         if (rows <= 32) return launch_one<8, 4>(A, B, st);
         if (rows <= 40) return launch_one<8, 5>(A, B, st);
     }

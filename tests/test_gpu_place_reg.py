@@ -93,10 +93,35 @@ def test_time_of_small_traces_of_one_step_variables(lap):
     assert few < 0.7 * many
 
 
-# the last size of every number of waves and rows, and one more; 257 orderings share the compute units
+def test_time_of_orderings_that_share_compute_units(lap):
+    """25 to 40 rows: from 513 orderings on the form that has room for 512 of them at once would take a second round
+    (measured: 1.64 times the time of 512 orderings; with room for 768 1.48 times)"""
+    tr = random_trace(9700, 6400, 1536, size_choices=[1, 2, 3, 7, 20, 50])
+
+    def ms(B):
+        dt = lap.DeviceTrace(tr)
+        kinds, seeds = make_orderings(B)
+        best = float("inf")
+        for _ in range(8):
+            lap.plan_pool(dt, kinds, seeds, want_all=False)
+            best = min(best, lap.profile_last_ms(lap.K_PLACE))
+        return best
+
+    lap.profile_enable(True)
+    try:
+        one, two = ms(512), ms(700)
+    finally:
+        lap.profile_enable(False)
+    print(f"512 orderings {one:.2f} ms, 700 {two:.2f} ms")
+    assert two < 1.56 * one
+
+
+# the last size of every number of waves and rows, and one more; 257 orderings share the compute units, as many as have
+# room at once or more
 @pytest.mark.parametrize("n,B", [(700, 8), (3072, 4), (3073, 4), (6144, 4), (6145, 4), (9216, 4), (9217, 4), (16384, 2), (16385, 2),
                                  (20480, 2), (20481, 2), (28673, 2), (32767, 2), (4096, 257), (4097, 257), (6144, 257),
-                                 (6145, 257), (8192, 257), (8193, 257), (10240, 257), (10241, 257)])
+                                 (6145, 257), (8192, 257), (8193, 257), (10240, 257), (10241, 257),
+                                 (6145, 512), (6144, 513), (6145, 513), (10240, 768), (10241, 768), (6145, 769)])
 def test_forms(lap, oracle_mod, n, B):
     tr = random_trace(9800 + n, n, 2000, size_choices=[1, 2, 3, 7, 20, 50])
     _check(lap, oracle_mod, tr, B, [b % 2 for b in range(B)], [0, 1, B - 2, B - 1])
