@@ -96,11 +96,18 @@ __device__ __forceinline__ uint64_t wave_min_hole(uint32_t gap, uint32_t at)
 
 // Moves the row up by one entry behind offset o, where x = (xo, xe, xl) goes if its place is in
 // this row; c: the last entry of the row below (offset 0 if there is none).
+// FIRST: the row's first entry is compared with o as well.  No entry lies below that last one, so it changes no result and
+// costs two instructions; what it changes is where the code behind it lies, 8 bytes further on, and the long loops of
+// k_place_fast answer to that.  Best-fit with eight waves: 16 orderings of 120 000 variables 48.5 ms without and 47.2 with
+// it, of 200 000 78.3 and 76.0 (16 of 200 000 with one s_nop in its place 76.1, two 76.3, three 73.4, but then both
+// policies in one call 78.9 for 74.8; with all loops aligned to 32 or 64 bytes 77.4).  With four waves and first-fit it is
+// the other way round: 600 best-fit orderings of 200 000 112.7 and 114.1, 256 first-fit ones 50.8 and 51.8.
+template <bool FIRST = false>
 __device__ __forceinline__ void row_insert(Row &R, uint32_t o, uint32_t xo, uint32_t xe, uint32_t xl, uint32_t co, uint32_t ce,
                                            uint32_t cl)
 {
     const uint32_t po = lane_shift_up(R.off[3], co), pe = lane_shift_up(R.end[3], ce), pl = lane_shift_up(R.life[3], cl);
-    if (co > o) {                                        // all of it moves (no entry lies below the row's before)
+    if ((!FIRST || read_lane(R.off[0], 0) > o) && co > o) {        // all of it moves
 #pragma unroll
         for (int j = EPL - 1; j > 0; --j) { R.off[j] = R.off[j - 1]; R.end[j] = R.end[j - 1]; R.life[j] = R.life[j - 1]; }
         R.off[0] = po; R.end[0] = pe; R.life[0] = pl;
