@@ -489,7 +489,7 @@ int lap_plan_pool(const lap_trace *tr, const lap_ordering *ords, uint32_t B, uin
         if (may_seg)
             LAP_HIP(lap::launch_seg_trial(n, T, B, perm, fits, trial_b, (uint32_t)g_seg_trial_percent, hdr, vrec, seg_lst,
                                           seg_pool, seg_len, (uint32_t)dir_cap, offs, fps, ticks, st));
-        LAP_HIP(lap::launch_place_reg(n, T, B, perm, fits, hdr, vrec, offs, fps, ticks, st));
+        LAP_HIP(lap::launch_place_reg(n, T, B, perm, fits, any_best, hdr, vrec, offs, fps, ticks, st));
         LAP_HIP(lap::launch_place_fast(n, T, B, tr->size, tr->alloc, tr->free_, perm, fits, any_first, any_best, hdr, vrec,
                                        lstart, f_oe, f_life, f_oe2,
                                        f_life2, f_roe, f_rlife, f_roe2, f_rlife2, f_L, capL, l_ns, l_nu, offs, fps, ticks, st));

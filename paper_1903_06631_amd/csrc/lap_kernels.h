@@ -98,7 +98,7 @@ hipError_t launch_place_seg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
                             bool any_first, PlanHeader *hdr, const void *vrec, const uint32_t *lst,
                             uint64_t *pool, uint32_t *lens, uint32_t dir_cap, uint64_t *offs, uint64_t *fps,
                             uint64_t *ticks, hipStream_t st);
-hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *perm, const uint32_t *fits,
+hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *perm, const uint32_t *fits, bool any_best,
                             const PlanHeader *hdr, const void *vrec, uint64_t *offs, uint64_t *fps, uint64_t *ticks,
                             hipStream_t st);
 hipError_t launch_place_fast(uint32_t n, uint32_t T, uint32_t B, const uint64_t *size, const uint32_t *alloc,

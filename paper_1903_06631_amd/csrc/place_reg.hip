@@ -237,7 +237,7 @@ hipError_t launch_one(const RegArgs &A, uint32_t B, hipStream_t st)
 }  // namespace
 
 hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *perm, const uint32_t *fits,
-                            const PlanHeader *hdr, const void *vrec, uint64_t *offs, uint64_t *fps, uint64_t *ticks,
+                            bool any_best, const PlanHeader *hdr, const void *vrec, uint64_t *offs, uint64_t *fps, uint64_t *ticks,
                             hipStream_t st)
 {
     if (!reg_may_place(n, T)) return hipSuccess;
@@ -252,8 +252,9 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
     // need one round and 8 waves two, from 513 to 768 orderings, and nowhere else (ms with 8 and with 4 waves, of
     //   6400:   512 orderings 9.7 and 12.6, 513 15.6 and 13.9, 768 15.7 and 14.3, 800 18.8 and 22.7, 1536 27.9 and 28.2
     //   8192:   512           13.5    18.0, 513 21.4     20.3, 768 21.7     20.7, 800 26.2     32.4, 1536 38.7     40.7
-    //   10 000: 512           17.9    24.6, 513 28.4     27.7, 768 28.7     28.5, 800 34.7     44.0, 1536 51.3     55.6).
-    // More rows than 40 need 16.
+    //   10 000: 512           17.9    24.6, 513 28.4     27.7, 768 28.7     28.5, 800 34.7     44.0, 1536 51.3     55.6;
+    // best-fit, 768 orderings of 6145 18.3 and 16.9, 7224 22.7 and 21.8, 8192 27.0 and 26.7, but 9000 31.0 and 31.2, 10 000
+    // 36.2 and 37.1).  More rows than 40 need 16.
     // Rows that a trace cannot fill cost all the same (193 orderings of 9001: 11.5 ms with 12 waves of 3 rows, 11.8
     // with 16), and up to 5 rows a wave keeps their ends (100 of 15 000: 22 ms with 4 rows, 30 with 7).
     const bool alone = B <= 256;
@@ -270,7 +271,7 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
     } else {
         if (rows <= 16) return launch_one<1, 16>(A, B, st);
         if (rows <= 24) return launch_one<8, 3>(A, B, st);
-        if (rows <= 40 && B > 512 && B <= 768) return launch_one<4, 10>(A, B, st);
+        if (rows <= (any_best ? 32u : 40u) && B > 512 && B <= 768) return launch_one<4, 10>(A, B, st);
         if (rows <= 32) return launch_one<8, 4>(A, B, st);
         if (rows <= 40) return launch_one<8, 5>(A, B, st);
     }

@@ -121,7 +121,14 @@ def test_time_of_orderings_that_share_compute_units(lap):
 @pytest.mark.parametrize("n,B", [(700, 8), (3072, 4), (3073, 4), (6144, 4), (6145, 4), (9216, 4), (9217, 4), (16384, 2), (16385, 2),
                                  (20480, 2), (20481, 2), (28673, 2), (32767, 2), (4096, 257), (4097, 257), (6144, 257),
                                  (6145, 257), (8192, 257), (8193, 257), (10240, 257), (10241, 257),
-                                 (6145, 512), (6144, 513), (6145, 513), (10240, 768), (10241, 768), (6145, 769)])
+                                 (6145, 512), (6144, 513), (6145, 513), (8192, 768), (8193, 768), (6145, 769)])
 def test_forms(lap, oracle_mod, n, B):
     tr = random_trace(9800 + n, n, 2000, size_choices=[1, 2, 3, 7, 20, 50])
     _check(lap, oracle_mod, tr, B, [b % 2 for b in range(B)], [0, 1, B - 2, B - 1])
+
+
+# up to 40 rows of first-fit orderings that have room at once where those of 33 rows and more with best-fit among them have not
+@pytest.mark.parametrize("n,B", [(8193, 513), (10240, 768), (10241, 768)])
+def test_forms_first_fit(lap, oracle_mod, n, B):
+    tr = random_trace(9900 + n, n, 2000, size_choices=[1, 2, 3, 7, 20, 50])
+    _check(lap, oracle_mod, tr, B, [0] * B, [0, B - 1])
