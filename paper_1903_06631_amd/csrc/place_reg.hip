@@ -41,7 +41,7 @@ template <int I, int N, class F> __device__ __forceinline__ bool rows_down(uint3
 }
 
 struct RegArgs {
-    uint32_t n;
+    uint32_t n, B;
     const uint4 *vrec;           // [n] (first step, end of life, size in granules, -)
     const uint32_t *perm;        // [B][n]
     const uint32_t *fits;        // [B]
@@ -51,8 +51,11 @@ struct RegArgs {
     uint64_t *ticks;             // [B] duration of every ordering in timer ticks
 };
 
+// Where one wave works on an ordering, a workgroup may hold several of them side by side: its waves share nothing.
+constexpr int PACK = 4;
+
 template <int NW, int R>
-__global__ __launch_bounds__(NW *WAVE) void k_place_reg(RegArgs A)
+__global__ __launch_bounds__((NW == 1 ? PACK : NW) * WAVE) void k_place_reg(RegArgs A)
 {
     constexpr int ROWS = NW * R;
     constexpr int RL = (ROWS + WAVE - 1) / WAVE;          // rows per lane where lanes stand for rows
@@ -60,13 +63,15 @@ __global__ __launch_bounds__(NW *WAVE) void k_place_reg(RegArgs A)
     __shared__ uint32_t s_at[2];
     __shared__ unsigned long long s_hole[2];
 
-    const uint32_t b = blockIdx.x;
+    const uint32_t wg_wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    const uint32_t b = NW == 1 ? blockIdx.x * (blockDim.x / WAVE) + wg_wave : blockIdx.x;
+    if (NW == 1 && b >= A.B) return;
     const bool best_fit = A.fits[b] != 0;
     if (!reg_places(A.hdr, A.n, best_fit)) return;
     const long long t_begin = wall_clock64();
     const uint32_t n = A.n, sh = A.hdr->shift;
     const int l = lane_id();
-    const uint32_t wave = NW == 1 ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    const uint32_t wave = NW == 1 ? 0u : wg_wave;
     const uint32_t *perm = A.perm + (size_t)b * n;
     uint64_t *offs = A.offs + (size_t)b * n;
 
@@ -221,7 +226,7 @@ __global__ __launch_bounds__(NW *WAVE) void k_place_reg(RegArgs A)
         }
         if (wave == 0 && r0 + l < n) offs[r0 + l] = (uint64_t)res << sh;
     }
-    if (threadIdx.x == 0) {
+    if (l == 0 && wave == 0) {
         A.fps[b] = (uint64_t)fp << sh;
         A.ticks[b] = (uint64_t)(wall_clock64() - t_begin);
     }
@@ -230,7 +235,14 @@ __global__ __launch_bounds__(NW *WAVE) void k_place_reg(RegArgs A)
 template <int NW, int R>
 hipError_t launch_one(const RegArgs &A, uint32_t B, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_place_reg<NW, R>), dim3(B), dim3(NW * WAVE), 0, st, A);
+    // Four one-wave orderings to a workgroup where a compute unit gets four of them and more: the waves of a workgroup go
+    // to a unit's four SIMDs one by one, those of four workgroups need not (of 1024 workgroups 60 to 110 SIMDs were given
+    // two and as many none, up to chance and to what ran before, and the launch then takes 1.3 times as long).  Whole
+    // plans with one and with four to a workgroup: 800 and 1024 orderings of 500 variables 0.58 and 0.50, 0.65 and 0.56 ms,
+    // of 640 0.72 and 0.60, 0.79 and 0.66; 1024 of 3000 4.23 and 3.27 (all offsets asked for), or 3.29 and 3.21; 2048 of
+    // 2000 3.30 and 2.67.  Three to a unit spread well either way, and so do many rounds (4096 of 1500 3.41 and 3.44).
+    const uint32_t pack = NW == 1 && B > 768 && B <= 2048 ? PACK : 1;
+    hipLaunchKernelGGL((k_place_reg<NW, R>), dim3((B + pack - 1) / pack), dim3(pack * NW * WAVE), 0, st, A);
     return hipGetLastError();
 }
 
@@ -241,7 +253,7 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
                             hipStream_t st)
 {
     if (!reg_may_place(n, T)) return hipSuccess;
-    const RegArgs A{n, (const uint4 *)vrec, perm, fits, hdr, offs, fps, ticks};
+    const RegArgs A{n, B, (const uint4 *)vrec, perm, fits, hdr, offs, fps, ticks};
     const uint32_t rows = (n + ROW - 1) / ROW;
     // Up to 8 rows one wave is the fastest way through an ordering (1000 variables: 0.55 ms; 0.75 ms
     // with 16 waves).  Beyond, 12 or 16 waves are (193 orderings of 3000 variables: 2.57 ms with 12; 3.3 ms with one),

@@ -132,3 +132,34 @@ def test_forms(lap, oracle_mod, n, B):
 def test_forms_first_fit(lap, oracle_mod, n, B):
     tr = random_trace(9900 + n, n, 2000, size_choices=[1, 2, 3, 7, 20, 50])
     _check(lap, oracle_mod, tr, B, [0] * B, [0, B - 1])
+
+
+# one wave an ordering, four of them a workgroup from 769 to 2048 orderings; the last workgroup full and not
+@pytest.mark.parametrize("n,B", [(300, 768), (300, 769), (130, 770), (600, 771), (800, 772), (1500, 773), (2049, 769), (4096, 771),
+                                 (300, 2047), (300, 2048), (300, 2049)])
+def test_orderings_side_by_side(lap, oracle_mod, n, B):
+    tr = random_trace(9950 + n, n, 200, size_choices=[1, 2, 3, 7, 20])
+    _check(lap, oracle_mod, tr, B, [b % 2 for b in range(B)], [0, 1, 2, 3, 4, 767, B - 4, B - 3, B - 2, B - 1])
+
+
+def test_time_of_an_ordering_a_simd(lap):
+    """1024 orderings of one wave have a SIMD each: they take next to no longer than 768 of them (measured: 1.02 times; 1.3
+    times where two of them share a SIMD while another one has none)"""
+    tr = random_trace(9990, 640, 74, size_choices=[1, 2, 3, 7, 20])
+
+    def ms(B):
+        dt = lap.DeviceTrace(tr)
+        kinds, seeds = make_orderings(B)
+        best = float("inf")
+        for _ in range(8):
+            lap.plan_pool(dt, kinds, seeds, want_all=False)
+            best = min(best, lap.profile_last_ms(lap.K_PLACE))
+        return best
+
+    lap.profile_enable(True)
+    try:
+        three, four = ms(768), ms(1024)
+    finally:
+        lap.profile_enable(False)
+    print(f"768 orderings {three:.3f} ms, 1024 {four:.3f} ms")
+    assert four < 1.15 * three
