@@ -27,8 +27,7 @@ def _check(lap, oracle, tr, B, fits, which):
     assert int(got["best_ordering"].item()) == int(np.argmin(fps))
 
 
-# 65535: the last step count with 16-bit
-# lifetimes, 65536 leaves the registers; 28672 the largest size, 28673 leaves the registers
+# 65535: the last step count with 16-bit lifetimes, 65536 leaves the registers
 @pytest.mark.parametrize("n,T,B", [(1, 1, 8), (255, 40, 8), (256, 40, 8), (257, 40, 8), (513, 65535, 8), (513, 65536, 8),
                                    (768, 300, 8), (769, 300, 8), (1025, 90, 8), (2048, 90, 8), (2049, 200, 8), (4096, 500, 8),
                                    (4097, 500, 8), (12289, 900, 4)])
@@ -43,10 +42,16 @@ def test_more_orderings_than_compute_units(lap, oracle_mod, n, T):
     _check(lap, oracle_mod, tr, 257, [b % 2 for b in range(257)], [0, 1, 2, 3, 128, 255, 256])
 
 
-@pytest.mark.parametrize("n,fits", [(28672, [0, 1]), (28673, [0, 0])])
-def test_largest(lap, oracle_mod, n, fits):
+# 32 768 variables are the last that fit the registers; first-fit goes there only where the segment lists are not in use,
+# which may place them from the same size on
+@pytest.mark.parametrize("n,lists", [(28672, True), (28673, True), (32768, True), (32768, False), (32769, False)])
+def test_largest(lap, oracle_mod, n, lists):
     tr = random_trace(9200, n, 2000, size_choices=[1, 2, 3, 7, 20, 50])
-    _check(lap, oracle_mod, tr, 2, fits, None)
+    lap.set_option(lap.OPT_SEG_MIN_VARS, lap.SEG_MIN_VARS_DEFAULT if lists else 1 << 30)
+    try:
+        _check(lap, oracle_mod, tr, 2, [0, 1], None)
+    finally:
+        lap.set_option(lap.OPT_SEG_MIN_VARS, lap.SEG_MIN_VARS_DEFAULT)
 
 
 def _few_multi(seed, n, n_multi, T=64):

@@ -155,11 +155,11 @@ def test_segment_lists_configs(lap, oracle_mod, cfg):
     _check(lap, oracle_mod, tr, kinds[:32], seeds[:32], fits=[1] * min(32, B))
 
 
-# 28 700 variables: too many for the register kernel, so that what is not placed by the segment lists is swept
-@pytest.mark.parametrize("n,T,max_life", [(2000, 300, None), (28700, 3000, 40)])
+# The registers take up to 32 768 variables and 65 535 steps: the second trace is placed there too, the third one is swept
+@pytest.mark.parametrize("n,T,max_life", [(2000, 300, None), (28700, 3000, 40), (3000, 66000, 400)])
 def test_default_threshold_keeps_small_traces_off_the_segment_lists(lap, oracle_mod, n, T, max_life):
-    """Same results whichever structure places the trace: the default threshold (registers or sweep) against the forced
-    path."""
+    """Same results whichever structure places the trace: the default threshold (registers, or the sweep) against the
+    forced path."""
     tr = _long_lived(30, n, T, max_life=max_life)
     kinds, seeds = make_orderings(16)
     dt = lap.DeviceTrace(tr)
@@ -172,7 +172,8 @@ def test_default_threshold_keeps_small_traces_off_the_segment_lists(lap, oracle_
     assert np.array_equal(forced, default)
 
 
-@pytest.mark.parametrize("n,T,max_life", [(3000, 900, None), (28700, 3000, 40)])
+# what is handed back is placed in registers up to 32 768 variables, and swept beyond
+@pytest.mark.parametrize("n,T,max_life", [(3000, 900, None), (28700, 3000, 40), (32768, 3000, 40), (32769, 3000, 40)])
 def test_trial_run_hands_random_lifetimes_back(lap, oracle_mod, n, T, max_life):
     """With the trial on, a trace with lifetimes at random (searches of many rounds) is placed by the registers or the
     sweep and a nested one by the lists; the offsets are the oracle's either way."""

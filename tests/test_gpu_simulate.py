@@ -83,10 +83,15 @@ def test_simulate_transfers_whose_times_do_not_fit_64_bits(lap, oracle_mod, n, T
         _check(lap, oracle_mod, tr, link, sl, [(k, lim) for k in (n, n // 2, 9, 1) for lim in (peak, peak * 3 // 5, peak // 4)])
 
 
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("n,T", [(600, 255), (600, 256), (601, 257), (4000, 513), (8193, 40)])
-def test_simulate_window_edges(lap, oracle_mod, n, T):
-    """steps and transfers are fetched 256 at a time, swap-in starts scanned 512 at a time, job lists built 8192 at a time"""
+def test_simulate_window_edges(lap, oracle_mod, n, T, wide):
+    """steps and transfers are fetched 256 at a time, swap-in starts scanned 512 at a time, job lists built 8192 at a time;
+    by the machine of 31-bit numbers, and by the one of 64-bit numbers that a step of 2^31 ns and more needs"""
     tr = random_trace(2300 + n + T, n, T, with_step_ns=True)
+    assert int(tr.step_ns.max()) < 1 << 31
+    if wide:
+        tr.step_ns[T // 2] = (1 << 31) + 12345
     _, peak, _ = oracle_mod.load_profile(tr)
     with_gap = np.nonzero(tr.gap_hi > tr.gap_lo)[0]
     sl = np.random.default_rng(n).permutation(with_gap).astype(np.uint32)

@@ -80,6 +80,18 @@ def test_weights_on_configs(lap, oracle_mod, cfg, W):
         assert len(set(r["overhead_ns"].tolist())) > 1      # the vectors are not all alike
 
 
+@pytest.mark.parametrize("n", [16384, 16500])
+def test_weights_many_candidates(lap, oracle_mod, n):
+    """every variable a candidate: a workgroup ranks the access steps of 64 of them, up to 16 384 in one turn"""
+    rng = np.random.default_rng(n)
+    T = 30
+    lo, hi = rng.integers(0, T // 3, n), rng.integers(2 * T // 3, T, n)
+    tr = mk_trace(rng.integers(1, 40, n) * (512 * 64), lo, hi + 1, T=T, gap_lo=lo, gap_hi=hi)
+    _, peak, _ = oracle_mod.load_profile(tr)
+    r = _check(lap, oracle_mod, tr, 64.0, 1, [[1, 0, 0, 0], [0.3, -0.2, 1e-9, 1e-9]], peak * 6 // 10)
+    assert r["n_cand"] == n and r["n_selected"].min() > 1000
+
+
 def test_weights_argument_errors(lap):
     tr = random_trace(1, 100, 10)
     dt = lap.DeviceTrace(tr)
