@@ -51,11 +51,11 @@ struct RegArgs {
     uint64_t *ticks;             // [B] duration of every ordering in timer ticks
 };
 
-// Where one wave works on an ordering, a workgroup may hold several of them side by side: its waves share nothing.
-constexpr int PACK = 4;
-
-template <int NW, int R>
-__global__ __launch_bounds__((NW == 1 ? PACK : NW) * WAVE) void k_place_reg(RegArgs A)
+// PACK: where one wave works on an ordering, a workgroup may hold several of them side by side; its waves share nothing.
+// A constant of the compilation, since a workgroup of one that looks at what there is for a second one starts 1 us later
+// (plan of 120 variables 68.0 and 69.1 us).
+template <int NW, int R, int PACK>
+__global__ __launch_bounds__(NW *PACK *WAVE) void k_place_reg(RegArgs A)
 {
     constexpr int ROWS = NW * R;
     constexpr int RL = (ROWS + WAVE - 1) / WAVE;          // rows per lane where lanes stand for rows
@@ -63,9 +63,10 @@ __global__ __launch_bounds__((NW == 1 ? PACK : NW) * WAVE) void k_place_reg(RegA
     __shared__ uint32_t s_at[2];
     __shared__ unsigned long long s_hole[2];
 
-    const uint32_t wg_wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
-    const uint32_t b = NW == 1 ? blockIdx.x * (blockDim.x / WAVE) + wg_wave : blockIdx.x;
-    if (NW == 1 && b >= A.B) return;
+    static_assert(NW == 1 || PACK == 1, "several waves of one ordering, or one of several");
+    const uint32_t wg_wave = NW * PACK == 1 ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    const uint32_t b = blockIdx.x * PACK + (NW == 1 ? wg_wave : 0u);
+    if (PACK > 1 && b >= A.B) return;
     const bool best_fit = A.fits[b] != 0;
     if (!reg_places(A.hdr, A.n, best_fit)) return;
     const long long t_begin = wall_clock64();
@@ -241,8 +242,11 @@ hipError_t launch_one(const RegArgs &A, uint32_t B, hipStream_t st)
     // plans with one and with four to a workgroup: 800 and 1024 orderings of 500 variables 0.58 and 0.50, 0.65 and 0.56 ms,
     // of 640 0.72 and 0.60, 0.79 and 0.66; 1024 of 3000 4.23 and 3.27 (all offsets asked for), or 3.29 and 3.21; 2048 of
     // 2000 3.30 and 2.67.  Three to a unit spread well either way, and so do many rounds (4096 of 1500 3.41 and 3.44).
-    const uint32_t pack = NW == 1 && B > 768 && B <= 2048 ? PACK : 1;
-    hipLaunchKernelGGL((k_place_reg<NW, R>), dim3((B + pack - 1) / pack), dim3(pack * NW * WAVE), 0, st, A);
+    constexpr int PACK = NW == 1 ? 4 : 1;
+    if (PACK > 1 && B > 768 && B <= 2048)
+        hipLaunchKernelGGL((k_place_reg<NW, R, PACK>), dim3((B - 1) / PACK + 1), dim3(NW * PACK * WAVE), 0, st, A);
+    else
+        hipLaunchKernelGGL((k_place_reg<NW, R, 1>), dim3(B), dim3(NW * WAVE), 0, st, A);
     return hipGetLastError();
 }
 
@@ -258,7 +262,7 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
     // Up to 8 rows one wave is the fastest way through an ordering (1000 variables: 0.55 ms; 0.75 ms
     // with 16 waves).  Beyond, 12 or 16 waves are (193 orderings of 3000 variables: 2.57 ms with 12; 3.3 ms with one),
     // as long as every ordering has a compute unit to itself; where orderings share one, the same work done by fewer
-    // waves is more: one wave up to 16 rows (1024 orderings of 3000: 4.0 ms, 4.6 with 4 waves and 5.2 with 8; 300 of
+    // waves is more: one wave up to 16 rows (1024 orderings of 3000: 3.0 ms, 4.6 with 4 waves and 5.2 with 8; 300 of
     // 4000 4.99 ms, 5.08 with 8 and 5.13 with 16), 8 waves up to 40 rows.  Of more than 24 rows, 8 waves (96 and 115
     // registers) leave a unit two orderings and 4 waves (154) three, so what 4 waves lose in a round they win where they
     // need one round and 8 waves two, from 513 to 768 orderings, and nowhere else (ms with 8 and with 4 waves, of
