@@ -176,7 +176,9 @@ struct ListedOrder {
     uint32_t *posmap, *perm_lo, *perm_hi;
 };
 // Longer lists leave it to the sorts of all variables: counting grows with the square of the list (31 us for 11 000 variables,
-// about 70 for 16 384), two sorts take 0.25 ms for 16 384 variables and 0.78 ms for 50 000.
+// about 70 for 16 384), two sorts take 0.25 ms for 16 384 variables and 0.78 ms for 50 000.  A list whose length only the
+// device knows is always counted: 43 us for 16 000 variables, 0.15 ms for 30 000, 0.57 for 60 000, 2.3 for 120 000 and 6.1
+// for 200 000 (two sorts 0.13, 0.25, 0.53, 1.05 and 1.8 ms), of a call that takes 20 ms for 16 000 and 340 for 120 000.
 constexpr uint32_t RANK_LISTED = 16384;
 hipError_t launch_order_listed(const ListedOrder &L, hipStream_t st);
 hipError_t launch_sched_mark(uint32_t n, uint32_t k, const uint32_t *list, uint32_t *posmap, hipStream_t st);

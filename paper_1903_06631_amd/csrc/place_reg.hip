@@ -271,8 +271,8 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
     //   10 000: 512           17.9    24.6, 513 28.4     27.7, 768 28.7     28.5, 800 34.7     44.0, 1536 51.3     55.6;
     // best-fit, 768 orderings of 6145 18.3 and 16.9, 7224 22.7 and 21.8, 8192 27.0 and 26.7, but 9000 31.0 and 31.2, 10 000
     // 36.2 and 37.1).  More rows than 40 need 16.
-    // Rows that a trace cannot fill cost all the same (193 orderings of 9001: 11.5 ms with 12 waves of 3 rows, 11.8
-    // with 16), and up to 5 rows a wave keeps their ends (100 of 15 000: 22 ms with 4 rows, 30 with 7).
+    // Rows that a trace cannot fill cost all the same (193 orderings of 9001: 11.4 ms with 12 waves of 3 rows, 11.8
+    // with 16), and up to 5 rows a wave keeps their ends (100 of 15 000: 24 ms with 4 rows, 30 with 7).
     const bool alone = B <= 256;
     if (rows <= 1) return launch_one<1, 1>(A, B, st);
     if (rows <= 2) return launch_one<1, 2>(A, B, st);
@@ -295,7 +295,9 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
     if (rows <= 64) return launch_one<16, 4>(A, B, st);
     if (rows <= 80) return launch_one<16, 5>(A, B, st);
     if (rows <= 112) return launch_one<16, 7>(A, B, st);
-    // 64, 256 and 1024 orderings of a residual chain of 32 767: 98, 99 and 392 ms; 436, 469 and 711 by the sweep
+    // 64, 256 and 1024 orderings of a residual chain of 32 767: 98, 99 and 396 ms; 436, 469 and 711 by the sweep.  (All of
+    // its 128 registers are in use and one value is spilled, the granule's shift: 8 bytes of scratch a lane, read back once
+    // in 64 placements.)
     return launch_one<16, 8>(A, B, st);
 }
 

@@ -233,7 +233,8 @@ __global__ __launch_bounds__(SC_THREADS) void k_sched_load(uint32_t T, const uin
 
 hipError_t launch_order_listed(const ListedOrder &L, hipStream_t st)
 {
-    // (of a list whose length only the device knows, as many workgroups as take one turn for 16 384 variables)
+    // (of a list whose length only the device knows, as many workgroups as take one turn for 16 384 variables; longer ones
+    // take more turns)
     const uint32_t most = L.count_dev ? (L.n < RANK_LISTED ? L.n : RANK_LISTED) : L.count;
     if (most == 0) return hipSuccess;
     if (L.posmap) hipLaunchKernelGGL(k_sched_mark, dim3((L.count + 255) / 256), dim3(256), 0, st, L.n, L.count, L.list, L.posmap);
