@@ -2,21 +2,21 @@
 // as its access is over and the stream is free; a second stream carries the swap-ins in the
 // order of the next accesses, each as late as its access and the swap-in after it allow.
 //
-// Both are scans.  A stream that serves job j (ready r_j, duration d_j) after it is free at x is
-// free again at f_j(x) = max(x, r_j) + d_j = max(x + d_j, r_j + d_j); such functions compose as
-// (a, b) pairs -- f(x) = max(x + a, b), (f2 o f1) = (a1 + a2, max(b1 + a2, b2)) -- so the end
+// Both are scans (stream_scan.h).  A stream that serves job j (ready r_j, duration d_j) after it is
+// free at x is free again at f_j(x) = max(x, r_j) + d_j = max(x + d_j, r_j + d_j); such functions
+// compose as (a, b) pairs -- f(x) = max(x + a, b), (f2 o f1) = (a1 + a2, max(b1 + a2, b2)) -- so the end
 // times of all swap-outs are one inclusive scan in (max, +), and the start times of all swap-ins
 // the mirror image in (min, -) taken from the last job backwards.  The variables arrive sorted
 // by access step: the listed ones (k_rank_steps), or all of them where the list is long, and then
 // those that are not listed are the identity of the scan.
 #include "lap_dev.h"
 #include "lap_kernels.h"
+#include "stream_scan.h"
 
 namespace lap {
 
 constexpr int SC_THREADS = 1024;
 constexpr int SC_WAVES = SC_THREADS / WAVE;
-constexpr long long SC_NEG = -(1ll << 62), SC_POS = (1ll << 62);
 constexpr uint32_t SC_NONE = 0xFFFFFFFFu;
 
 __global__ __launch_bounds__(256) void k_sched_mark(uint32_t n, uint32_t k, const uint32_t *__restrict__ list,
@@ -76,48 +76,6 @@ __global__ __launch_bounds__(RANK_THREADS) void k_rank_steps(uint32_t n, uint32_
     }
 }
 
-struct Fn {
-    long long a, b;
-};
-// OUT: f(x) = max(x + a, b), `then` applied after `first`
-__device__ __forceinline__ Fn then_max(const Fn &first, const Fn &then)
-{
-    const long long t = first.b + then.a;
-    return Fn{first.a + then.a, t > then.b ? t : then.b};
-}
-// IN: g(y) = min(y - a, b)
-__device__ __forceinline__ Fn then_min(const Fn &first, const Fn &then)
-{
-    const long long t = first.b - then.a;
-    return Fn{first.a + then.a, t < then.b ? t : then.b};
-}
-
-template <bool OUT>
-__device__ __forceinline__ Fn block_scan_fn(Fn v, Fn &carry, Fn *wtmp)
-{
-    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
-    const Fn ident{0, OUT ? SC_NEG : SC_POS};
-#pragma unroll
-    for (int d = 1; d < WAVE; d <<= 1) {
-        Fn o;
-        o.a = (long long)shfl_up64((uint64_t)v.a, d);
-        o.b = (long long)shfl_up64((uint64_t)v.b, d);
-        if (lane >= d) v = OUT ? then_max(o, v) : then_min(o, v);
-    }
-    if (lane == WAVE - 1) wtmp[wave] = v;
-    __syncthreads();
-    Fn pre = carry, tot = carry;
-    for (int q = 0; q < SC_WAVES; ++q) {
-        const Fn x = wtmp[q];
-        if (q < wave) pre = OUT ? then_max(pre, x) : then_min(pre, x);
-        tot = OUT ? then_max(tot, x) : then_min(tot, x);
-    }
-    __syncthreads();
-    carry = tot;
-    (void)ident;
-    return OUT ? then_max(pre, v) : then_min(pre, v);
-}
-
 struct SchedArgs {
     uint32_t n, T, k, count;
     const uint64_t *size;
@@ -152,7 +110,7 @@ __global__ __launch_bounds__(SC_THREADS) void k_sched_streams(SchedArgs A)
                 f = Fn{d, (long long)A.C[A.step_lo[v] + 1] + d};
             }
         }
-        const Fn g = block_scan_fn<true>(f, carry, wtmp);
+        const Fn g = block_scan_fn<true, SC_WAVES>(f, carry, wtmp);
         if (pos != SC_NONE) { A.out_end[pos] = g.b; A.out_start[pos] = g.b - d; }
     }
     // swap-ins, last to first
@@ -170,7 +128,7 @@ __global__ __launch_bounds__(SC_THREADS) void k_sched_streams(SchedArgs A)
                 f = Fn{d, (long long)A.C[A.step_hi[v] - A.hi_minus] - d};
             }
         }
-        const Fn g = block_scan_fn<false>(f, carry, wtmp);
+        const Fn g = block_scan_fn<false, SC_WAVES>(f, carry, wtmp);
         if (pos != SC_NONE) { A.in_start[pos] = g.b; A.in_end[pos] = g.b + d; }
     }
     __syncthreads();
