@@ -64,15 +64,17 @@ __global__ __launch_bounds__(NW *PACK *WAVE) void k_place_reg(RegArgs A)
     __shared__ unsigned long long s_hole[2];
 
     static_assert(NW == 1 || PACK == 1, "several waves of one ordering, or one of several");
-    const uint32_t wg_wave = NW * PACK == 1 ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
-    const uint32_t b = blockIdx.x * PACK + (NW == 1 ? wg_wave : 0u);
-    if (PACK > 1 && b >= A.B) return;
+    uint32_t b = blockIdx.x;
+    if constexpr (PACK > 1) {
+        b = b * PACK + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+        if (b >= A.B) return;
+    }
     const bool best_fit = A.fits[b] != 0;
     if (!reg_places(A.hdr, A.n, best_fit)) return;
     const long long t_begin = wall_clock64();
     const uint32_t n = A.n, sh = A.hdr->shift;
     const int l = lane_id();
-    const uint32_t wave = NW == 1 ? 0u : wg_wave;
+    const uint32_t wave = NW == 1 ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     const uint32_t *perm = A.perm + (size_t)b * n;
     uint64_t *offs = A.offs + (size_t)b * n;
 
@@ -227,7 +229,7 @@ __global__ __launch_bounds__(NW *PACK *WAVE) void k_place_reg(RegArgs A)
         }
         if (wave == 0 && r0 + l < n) offs[r0 + l] = (uint64_t)res << sh;
     }
-    if (l == 0 && wave == 0) {
+    if (PACK > 1 ? l == 0 : threadIdx.x == 0) {
         A.fps[b] = (uint64_t)fp << sh;
         A.ticks[b] = (uint64_t)(wall_clock64() - t_begin);
     }
@@ -271,7 +273,7 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
     //   10 000: 512           17.9    24.6, 513 28.4     27.7, 768 28.7     28.5, 800 34.7     44.0, 1536 51.3     55.6;
     // best-fit, 768 orderings of 6145 18.3 and 16.9, 7224 22.7 and 21.8, 8192 27.0 and 26.7, but 9000 31.0 and 31.2, 10 000
     // 36.2 and 37.1).  More rows than 40 need 16.
-    // Rows that a trace cannot fill cost all the same (193 orderings of 9001: 11.4 ms with 12 waves of 3 rows, 11.8
+    // Rows that a trace cannot fill cost all the same (193 orderings of 9001: 11.5 ms with 12 waves of 3 rows, 11.8
     // with 16), and up to 5 rows a wave keeps their ends (100 of 15 000: 24 ms with 4 rows, 30 with 7).
     const bool alone = B <= 256;
     if (rows <= 1) return launch_one<1, 1>(A, B, st);
@@ -296,8 +298,8 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
     if (rows <= 80) return launch_one<16, 5>(A, B, st);
     if (rows <= 112) return launch_one<16, 7>(A, B, st);
     // 64, 256 and 1024 orderings of a residual chain of 32 767: 98, 99 and 396 ms; 436, 469 and 711 by the sweep.  (All of
-    // its 128 registers are in use and one value is spilled, the granule's shift: 8 bytes of scratch a lane, read back once
-    // in 64 placements.)
+    // its 128 registers are in use and two values that wait for the end of 64 placements and of the ordering, the granule's
+    // shift among them, are spilled: 12 bytes of scratch a lane.)
     return launch_one<16, 8>(A, B, st);
 }
 
