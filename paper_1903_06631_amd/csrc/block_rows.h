@@ -98,10 +98,11 @@ __device__ __forceinline__ uint64_t wave_min_hole(uint32_t gap, uint32_t at)
 // this row; c: the last entry of the row below (offset 0 if there is none).
 // FIRST: the row's first entry is compared with o as well.  No entry lies below that last one, so it changes no result and
 // costs two instructions; what it changes is where the code behind it lies, 8 bytes further on, and the long loops of
-// k_place_fast answer to that.  Best-fit with eight waves: 16 orderings of 120 000 variables 48.5 ms without and 47.2 with
-// it, of 200 000 78.3 and 76.0 (16 of 200 000 with one s_nop in its place 76.1, two 76.3, three 73.4, but then both
-// policies in one call 78.9 for 74.8; with all loops aligned to 32 or 64 bytes 77.4).  With four waves and first-fit it is
-// the other way round: 600 best-fit orderings of 200 000 112.7 and 114.1, 256 first-fit ones 50.8 and 51.8.
+// k_place_fast answer to that.  Best-fit with eight waves and the per-step words in LDS: 16 orderings of 120 000 variables
+// 48.5 ms without and 47.2 with it, of 200 000 78.3 and 76.0 (16 of 200 000 with one s_nop in its place 76.1, two 76.3, three
+// 73.4, but then both policies in one call 78.9 for 74.8; with all loops aligned to 32 or 64 bytes 77.4).  In the other forms
+// it is the other way round: 600 best-fit orderings of 200 000 (four waves) 112.7 and 114.1, 100 of 150 000 over 900 steps
+// (the words in memory) 66.8 and 67.3, 256 first-fit ones of 200 000 50.8 and 51.8.
 template <bool FIRST = false>
 __device__ __forceinline__ void row_insert(Row &R, uint32_t o, uint32_t xo, uint32_t xe, uint32_t xl, uint32_t co, uint32_t ce,
                                            uint32_t cl)

@@ -1169,7 +1169,7 @@ __device__ __forceinline__ void place_ordering(const FastArgs &A, FastShared<LT,
                     if (wave < used) {
                         uint4 c = make_uint4(0u, 0u, 0u, 0u);
                         if (wave) c = S.s_row[rbuf][wave - 1];
-                        row_insert<BEST && PW == 8>(row, o, o, en, life_word(va, vf), uniform(c.x), c.y, c.z);
+                        row_insert<BEST && PW == 8 && META>(row, o, o, en, life_word(va, vf), uniform(c.x), c.y, c.z);
                     }
                     ++n_rowed;
                 } else if (multi_left > 1) {
