@@ -60,6 +60,25 @@ __device__ __forceinline__ bool reg_before_lists(uint32_t n, uint32_t T, uint32_
     return n <= PLAN_REG_FEW_VARS && T <= 0xFFFFu && n_multi * 40u >= n * ((n + 255) / 256 - (B > 512 ? 1u : 0u));
 }
 
+// Placed blocks in LDS, up to 64 variables placed at a time (place_batch.hip): whether they take the place of the registers.
+// First-fit calls only: with best-fit orderings among them the registers place all in one launch.  ms in registers and in
+// batches, of a residual chain, a pyramid of feature maps, and random lifetimes with six sizes, whose holes take one
+// variable each (the alloc-ascending order then needs two to three times as long as the others):
+//     256 orderings of   700   0.31 0.32 0.31 and 0.28 0.28 0.53      512 of   700   0.35 0.34 0.35 and 0.30 0.31 0.60
+//                       1500   0.97 0.97      and 0.54 0.66                   1500   1.04 1.04      and 0.59 0.72
+//                       3000   2.42 2.43 2.43 and 1.18 1.54 2.25              3000   2.95           and 1.34 1.74 2.64
+//                     10 000             13.0 and           10.5            10 000             17.2 and           10.5
+//                       9001   11.2           and 4.9                         9001   15.0           and 7.9
+//     768            of 1500   1.02 1.02      and 0.99 1.09      1024 of      3000   2.86           and 2.69 2.89 3.44
+//                       2500   2.20 2.20      and 1.81 1.96                   5000   11.5 11.6      and 4.8 5.3
+//                       6400   13.8 14.2 13.7 and 6.9 7.5 7.0                 9001   29.3           and 14.4
+// 2048 orderings of 3300: 4.38 and 5.25, of 5000 20.3 and 9.0.
+constexpr uint32_t PLAN_BATCH_MAX_VARS = 52 * 256 - 1;      // rows of 512 entries of 12 bytes in 160 KB, less 4 KB
+inline bool batch_places(uint32_t n, uint32_t B, bool any_best)
+{
+    return !any_best && n <= PLAN_BATCH_MAX_VARS && (n > 4096 || (n > 2048 && B <= 768) || (n > 1024 && B <= 512));
+}
+
 hipError_t launch_fill_u64(uint64_t *p, size_t n, uint64_t v, hipStream_t st);
 // copies n_words 32-bit words of HOST memory to the device through kernel arguments (the host
 // array is read before the call returns; nothing waits)
@@ -101,6 +120,9 @@ hipError_t launch_place_seg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
 hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *perm, const uint32_t *fits, bool any_best,
                             const PlanHeader *hdr, const void *vrec, uint64_t *offs, uint64_t *fps, uint64_t *ticks,
                             hipStream_t st);
+hipError_t launch_place_batch(uint32_t n, uint32_t B, const uint32_t *perm, const PlanHeader *hdr,
+                               const void *vrec, uint64_t *offs, uint64_t *fps, uint64_t *ticks,
+                              hipStream_t st);
 hipError_t launch_place_fast(uint32_t n, uint32_t T, uint32_t B, const uint64_t *size, const uint32_t *alloc,
                              const uint32_t *free_, const uint32_t *perm, const uint32_t *fits, bool any_first,
                              bool any_best, PlanHeader *hdr, const void *vrec,

@@ -259,6 +259,8 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
                             hipStream_t st)
 {
     if (!reg_may_place(n, T)) return hipSuccess;
+    if (batch_places(n, B, any_best))
+        return launch_place_batch(n, B, perm, hdr, vrec, offs, fps, ticks, st);
     const RegArgs A{n, B, (const uint4 *)vrec, perm, fits, hdr, offs, fps, ticks};
     const uint32_t rows = (n + ROW - 1) / ROW;
     // Up to 8 rows one wave is the fastest way through an ordering (1000 variables: 0.55 ms; 0.75 ms
@@ -289,7 +291,7 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
     } else {
         if (rows <= 16) return launch_one<1, 16>(A, B, st);
         if (rows <= 24) return launch_one<8, 3>(A, B, st);
-        if (rows <= (any_best ? 32u : 40u) && B > 512 && B <= 768) return launch_one<4, 10>(A, B, st);
+        if (rows <= 32 && B > 512 && B <= 768) return launch_one<4, 10>(A, B, st);
         if (rows <= 32) return launch_one<8, 4>(A, B, st);
         if (rows <= 40) return launch_one<8, 5>(A, B, st);
     }

@@ -1,0 +1,75 @@
+"""GPU parity of first-fit plans that are placed in batches of up to 64 variables, at the sizes where a form or the rule ends
+and with traces in which a batch's variables get in each other's way.  Offsets and footprints are compared element by element
+with the oracle's."""
+import numpy as np
+import pytest
+
+from gpu_util import oracle_all_orderings, u64
+from traces import make_orderings, random_trace
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lap():
+    import paper_1903_06631_amd as lap
+    lap.load_library()
+    return lap
+
+
+def _check(lap, oracle, tr, B, which):
+    kinds, seeds = make_orderings(B)
+    got = lap.plan_pool(lap.DeviceTrace(tr), kinds, seeds)
+    all_off, fps = u64(got["all_offsets"]), u64(got["footprints"])
+    for b, (_, off, fp) in oracle_all_orderings(oracle, tr, kinds, seeds, None, which, None).items():
+        assert np.array_equal(all_off[b], off), f"ordering {b}"
+        assert fps[b] == fp, f"ordering {b}"
+    assert int(got["best_ordering"].item()) == int(np.argmin(fps))
+
+
+def _lives(tr, alloc, free):
+    tr.alloc, tr.free = np.asarray(alloc, np.uint32), np.asarray(free, np.uint32)
+    tr.gap_lo, tr.gap_hi = tr.alloc.copy(), tr.free - 1
+    return tr
+
+
+# rows of 512 blocks, one more and one less; 16 and 8 waves; the last size of the batches and the next one
+@pytest.mark.parametrize("n,T,B", [(1025, 70, 6), (1535, 65535, 6), (1536, 300, 6), (1537, 300, 6), (2048, 300, 257), (2049, 300, 513),
+                                   (4096, 500, 257), (4097, 500, 769), (6143, 900, 257), (6144, 900, 257), (8192, 900, 6),
+                                   (13311, 1500, 5), (13312, 1500, 5)])
+def test_sizes(lap, oracle_mod, n, T, B):
+    _check(lap, oracle_mod, random_trace(9000 + n, n, T, size_choices=[1, 1, 2, 3, 5, 8, 13, 64]), B,
+           sorted({0, 1, 2, 3, 4, B - 1}))
+
+
+# everything meets everything; all in one hole; holes that take one variable each (few sizes, many variables a step), so that a
+# batch ends early and further holes are asked for; two lifetimes in turn
+@pytest.mark.parametrize("what", ["all", "equal", "few sizes", "one size of each", "two"])
+def test_in_each_others_way(lap, oracle_mod, what):
+    n, T = 1500, 40
+    rng = np.random.default_rng(len(what))
+    tr = random_trace(9400 + len(what), n, T, size_choices=[1, 2, 3, 7, 20, 50] if what != "equal" else [4])
+    if what in ("all", "equal"):
+        _lives(tr, np.zeros(n), np.full(n, T))
+    elif what == "few sizes":
+        a = np.sort(rng.integers(0, T - 12, n))
+        _lives(tr, a, a + rng.integers(8, 13, n))
+    elif what == "one size of each":
+        tr.size = (rng.permutation(n) + 1).astype(np.uint64) * 512
+        a = rng.integers(0, T - 12, n)
+        _lives(tr, a, a + rng.integers(8, 13, n))
+    else:
+        a = (np.arange(n) % 2) * (T // 2 - 3)
+        _lives(tr, a, a + T // 2 + 3)
+    _check(lap, oracle_mod, tr, 5, range(5))
+
+
+# offsets and sizes up to the last bit of 32
+def test_highest_addresses(lap, oracle_mod):
+    n = 1100
+    tr = random_trace(9500, n, 60, size_choices=[1])
+    tr.size = np.full(n, ((1 << 32) - 1) // n, np.uint64)
+    tr.size[0] += ((1 << 32) - 1) - int(tr.size.sum())
+    assert int(tr.size.sum()) == (1 << 32) - 1 and int(np.bitwise_or.reduce(tr.size)) & 1
+    _lives(tr, np.zeros(n), np.full(n, 60))
+    _check(lap, oracle_mod, tr, 5, range(5))
