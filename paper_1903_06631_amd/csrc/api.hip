@@ -877,8 +877,7 @@ int lap_detect_iteration(const uint64_t *tokens, uint32_t n_requests, uint32_t m
     Carver c(ws);
     uint64_t *hashes = c.take<uint64_t>(n_requests);
     uint64_t *totals = c.take<uint64_t>(lap::DI_MAX_TILES);
-    uint32_t *ctrl = c.take<uint32_t>(4);
-    LAP_HIP(lap::launch_detect_iteration(tokens, n_requests, min_period, hashes, totals, ctrl, period,
+    LAP_HIP(lap::launch_detect_iteration(tokens, n_requests, min_period, hashes, totals, period,
                                          (hipStream_t)hip_stream));
     return LAP_OK;
 }

@@ -225,9 +225,9 @@ hipError_t launch_simulate_swaps(uint32_t n, uint32_t T, uint32_t Q, uint32_t km
                                  uint64_t *overhead_ns, uint64_t *peak_resident, uint32_t *forced, hipStream_t st,
                                  uint32_t n_lists = 1, const uint32_t *n_listed = nullptr);
 
-// Q [M] prefix hashes, totals [DI_MAX_TILES], ctrl [4]: scratch
+// Q [M] prefix hashes, totals [DI_MAX_TILES]: scratch
 constexpr uint32_t DI_MAX_TILES = 4096;
 hipError_t launch_detect_iteration(const uint64_t *tokens, uint32_t M, uint32_t min_period, uint64_t *Q,
-                                   uint64_t *totals, uint32_t *ctrl, uint32_t *period, hipStream_t st);
+                                   uint64_t *totals, uint32_t *period, hipStream_t st);
 
 }  // namespace lap

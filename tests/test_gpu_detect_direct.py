@@ -1,0 +1,61 @@
+"""GPU parity of lap_detect_iteration on lists whose end is found again at many distances: short repeats, runs of one token that
+are shorter than the iteration asked for, layers, and repeats that differ in their first token only; around the list size that
+one workgroup takes and around the tokens that are compared before all of a distance is."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lap():
+    import paper_1903_06631_amd as lap
+    lap.load_library()
+    return lap
+
+
+def _tail(rng, m, tail):
+    head = rng.integers(0, 300, max(m - len(tail), 0)).astype(np.uint64)
+    return np.concatenate([head, np.asarray(tail, np.uint64)])[-m:]
+
+
+def _lists(rng, m):
+    word = lambda n: rng.integers(0, 300, n)
+    run = m // 2
+    yield "one token", np.full(m, 7, np.uint64), (1, 64, m // 3, m // 2, m // 2 + 1)
+    yield "run", _tail(rng, m, np.full(run, 7)), (1, run // 2, run // 2 + 1, run - 40, run)
+    yield "short period", _tail(rng, m, np.tile(word(12), run // 12)), (5, 64, 1057, run // 2 - 6, run // 2 + 12)
+    block = word(max(m // 40, 3))
+    yield "layers", _tail(rng, m, np.tile(np.concatenate([word(m // 30)] + [block] * 9), 2)), (1, 64, m // 30, m // 5, m // 3)
+    for p in (31, 32, 33, 1055, 1056, 1057, m // 2):         # equal but for one token: the first, one in the middle, none
+        half = word(p)
+        for at in (0, p // 2, None):
+            other = half.copy()
+            if at is not None:
+                other[at] += 1000
+            if 2 * p <= m:
+                yield f"two halves of {p}", _tail(rng, m, np.concatenate([other, half])), (1, p, p + 1)
+
+
+@pytest.mark.parametrize("m", [2000, 6144, 6145, 9000, 33001])
+def test_many_distances(lap, oracle_mod, m):
+    import torch
+    rng = np.random.default_rng(m)
+    for what, s, periods in _lists(rng, m):
+        t = torch.from_numpy(s.view(np.int64)).cuda()
+        for mp in periods:
+            if mp >= 1:
+                assert int(lap.detect_iteration(t, mp).item()) == oracle_mod.detect_iteration(s, mp), (what, mp)
+
+
+def test_scratch_of_an_earlier_call_does_not_matter(lap, oracle_mod):
+    """the same scratch for a list that comes to the hashes and for one that does not, in turn"""
+    import torch
+    rng = np.random.default_rng(1)
+    m = 20000
+    run = _tail(rng, m, np.full(m // 2, 7))
+    it = rng.integers(0, 300, m // 3).astype(np.uint64)
+    plain = _tail(rng, m, np.concatenate([it, it]))
+    for s, mp in [(run, m // 4 + 1), (plain, 64), (run, m // 4 + 1), (run, 3), (plain, 64), (plain, m // 3 + 1)]:
+        t = torch.from_numpy(s.view(np.int64)).cuda()
+        assert int(lap.detect_iteration(t, mp).item()) == oracle_mod.detect_iteration(s, mp)
