@@ -12,6 +12,7 @@
 #include "lap_kernels.h"
 #include "step_runs.h"
 #include "stream_scan.h"
+#include <type_traits>
 
 namespace lap {
 
@@ -417,8 +418,10 @@ __device__ void sim_run_wide(const SimArgs &A, SimWin &W)
 // lane: the lane counts down and is negative when the chunk is used up.  Every event reads the current entry of each stream
 // from its lane whether it has changed or not, and conditions are signs, so that several are one `and`.  An actor's word
 // is its remaining time less one, and -1 when it does nothing: max(word - elapsed, -1) is the next word in all cases.
-// The limit is kept as what it leaves.  14 000 steps and 11 000 transfers, every one blocked: 7.4 ms = 205 ns an event
-// (14.8 ms with 64-bit state and a branch a question); 348 steps and 257 transfers 0.18 ms (0.36 ms).
+// The limit is kept as what it leaves.  A stretch in which only one of the two streams can be at work leaves the other one
+// out: 125 to 140 ns an event there, 250 where both are.  14 000 steps and 11 000 transfers, every one blocked, with
+// both at work in half of the events: 6.7 ms (7.4 ms when every event looked at both, 14.8 with 64-bit state and a branch a
+// question); the same under limits that can be met 4.0 to 1.8 ms; 348 steps and 257 transfers 0.15 ms (0.18, 0.36).
 struct NarrowWin {
     uint32_t need[RUN_WIN], rel[RUN_WIN], dt[RUN_WIN];               // dt, like all times here, less one
     uint32_t osize[RUN_WIN], odur[RUN_WIN], olo[RUN_WIN], oplace[RUN_WIN];
@@ -543,50 +546,91 @@ __device__ void sim_run_narrow(const SimArgs &A, uint32_t shift, NarrowWin &W)
                 i_at += have;
             }
         }
-        uint32_t need = read_lane(c_need, (int)te), rel = read_lane(c_rel, (int)te), dt = read_lane(c_dt, (int)te);
-        uint32_t olo = read_lane(c_olo, (int)oe), odur = read_lane(c_odur, (int)oe), osize = read_lane(c_osize, (int)oe),
-                 oplace = read_lane(c_oplace, (int)oe);
-        uint32_t ihi = read_lane(c_ihi, (int)ie), issue = read_lane(c_issue, (int)ie), isize = read_lane(c_isize, (int)ie),
-                 iplace = read_lane(c_iplace, (int)ie), idur = read_lane(c_idur, (int)ie);
-        // all of them before the first scalar instruction: one that follows a read of a lane waits 20 cycles, and they
-        // would alternate
-        asm volatile("" : "+s"(need), "+s"(rel), "+s"(dt), "+s"(olo), "+s"(odur), "+s"(osize), "+s"(oplace), "+s"(ihi),
-                     "+s"(issue), "+s"(isize), "+s"(iplace), "+s"(idur));
-        // starts: swap-out, step, swap-in (its variable is out if the current swap-out is one behind it)
-        out = negative(out & (olo - t)) ? odur : out;
-        const uint32_t step_may = step & (t - ihi), after_step = left - need;
-        const uint32_t step_go = step_may & (dt | ~after_step);
-        step = negative(step_go) ? dt & SIM_NEVER : step;
-        left = negative(step_go) ? after_step : left;
-        const uint32_t in_may = in & ~(t - issue) & (iplace - oplace), after_in = left - isize;
-        const uint32_t in_go = in_may & ~after_in;
-        in = negative(in_go) ? idur : in;
-        left = negative(in_go) ? after_in : left;
-        uint32_t soon = s_min(s_min(step, out), in);
-        if (__builtin_expect(negative(soon), 0)) {
-            // nothing will change by itself: the limit is overridden once
-            if (negative(step_may)) { soon = step = dt & SIM_NEVER; left = after_step; }
-            else if (negative(in_may)) { soon = in = idur; left = after_in; }
-            else { nforced = SIM_NONE - 1; t = T; }        // an inconsistent trace; leave rather than spin
-            ++nforced;
+        // One event.  OUT, IN: whether a swap-out, a swap-in can be under way or start; what is not is not looked at.
+        auto event = [&](auto with_out, auto with_in) {
+            constexpr bool OUT = decltype(with_out)::value, IN = decltype(with_in)::value;
+            uint32_t need = read_lane(c_need, (int)te), rel = read_lane(c_rel, (int)te), dt = read_lane(c_dt, (int)te);
+            uint32_t olo = 0, odur = 0, osize = 0, oplace = 0, ihi = 0, issue = 0, isize = 0, iplace = 0, idur = 0;
+            if constexpr (OUT) { olo = read_lane(c_olo, (int)oe); odur = read_lane(c_odur, (int)oe); osize = read_lane(c_osize, (int)oe); }
+            if constexpr (IN) {
+                ihi = read_lane(c_ihi, (int)ie); issue = read_lane(c_issue, (int)ie);
+                isize = read_lane(c_isize, (int)ie); idur = read_lane(c_idur, (int)ie);
+            }
+            if constexpr (OUT && IN) { oplace = read_lane(c_oplace, (int)oe); iplace = read_lane(c_iplace, (int)ie); }
+            // all of them before the first scalar instruction: one that follows a read of a lane waits 20 cycles, and they
+            // would alternate
+            asm volatile("" : "+s"(need), "+s"(rel), "+s"(dt));
+            if constexpr (OUT) asm volatile("" : "+s"(olo), "+s"(odur), "+s"(osize));
+            if constexpr (IN) asm volatile("" : "+s"(ihi), "+s"(issue), "+s"(isize), "+s"(idur));
+            if constexpr (OUT && IN) asm volatile("" : "+s"(oplace), "+s"(iplace));
+            // starts: swap-out, step, swap-in (its variable is out if the current swap-out is one behind it)
+            if constexpr (OUT) out = negative(out & (olo - t)) ? odur : out;
+            uint32_t step_may = step;
+            if constexpr (IN) step_may &= t - ihi;
+            const uint32_t after_step = left - need, step_go = step_may & (dt | ~after_step);
+            step = negative(step_go) ? dt & SIM_NEVER : step;
+            left = negative(step_go) ? after_step : left;
+            uint32_t in_may = 0, after_in = 0, soon = step;
+            if constexpr (OUT) soon = s_min(soon, out);
+            if constexpr (IN) {
+                in_may = in & ~(t - issue);
+                if constexpr (OUT) in_may &= iplace - oplace;
+                after_in = left - isize;
+                const uint32_t in_go = in_may & ~after_in;
+                in = negative(in_go) ? idur : in;
+                left = negative(in_go) ? after_in : left;
+                soon = s_min(soon, in);
+            }
+            if (__builtin_expect(negative(soon), 0)) {
+                // nothing will change by itself: the limit is overridden once
+                if (negative(step_may)) { soon = step = dt & SIM_NEVER; left = after_step; }
+                else if (negative(in_may)) { soon = in = idur; left = after_in; }
+                else { nforced = SIM_NONE - 1; t = T; }    // an inconsistent trace; leave rather than spin
+                ++nforced;
+            }
+            least = (uint32_t)min((int32_t)left, (int32_t)least);
+            const uint32_t nx = soon + 1u;
+            now += nx;
+            // ends at the next instant
+            const uint32_t step_next = (uint32_t)max((int32_t)(step - nx), -1);
+            const uint32_t step_ends = (uint32_t)((int32_t)(step_next & ~step) >> 31);
+            left += rel & step_ends;
+            if constexpr (OUT) {
+                const uint32_t out_next = (uint32_t)max((int32_t)(out - nx), -1);
+                const uint32_t out_ends = (uint32_t)((int32_t)(out_next & ~out) >> 31);
+                left += osize & out_ends;
+                oe += out_ends;
+                out = out_next;
+            }
+            if constexpr (IN) {
+                const uint32_t in_next = (uint32_t)max((int32_t)(in - nx), -1);
+                const uint32_t in_ends = (uint32_t)((int32_t)(in_next & ~in) >> 31);
+                ie += in_ends;
+                in = in_next;
+            }
+            t -= step_ends;
+            te += step_ends;
+            step = step_next;
+        };
+        // Two thirds of the instructions do where only one stream is at work.  No swap-in can start before the next one is
+        // issued, or before the swap-out of its variable is done, which is late in an iteration: the first one needed back
+        // was the last one to leave.
+        const uint32_t next_place = read_lane(c_iplace, (int)ie);
+        uint32_t quiet = min(read_lane(c_ihi, (int)ie), T), oe_last = 0;
+        if (read_lane(c_oplace, (int)oe) <= next_place) oe_last = (uint32_t)__ffsll((unsigned long long)ballot(c_oplace <= next_place)) - 1;
+        else quiet = min(quiet, read_lane(c_issue, (int)ie));
+        if (negative(in) && (int32_t)(t - quiet) < 0) {
+            do event(std::true_type{}, std::false_type{});
+            while (!negative(te | (oe - oe_last) | (quiet - 1u - t)));
+        } else if (negative(out) && read_lane(c_olo, (int)oe) == SIM_NEVER) {
+            do event(std::false_type{}, std::true_type{});
+            while (!negative(te | ie | (T - 1u - t)));
+        } else {
+            // (a few events before the question is asked again)
+            uint32_t more = 16;
+            do event(std::true_type{}, std::true_type{});
+            while (!negative(te | oe | ie | (T - 1u - t) | (--more - 1u)));
         }
-        least = (uint32_t)min((int32_t)left, (int32_t)least);
-        const uint32_t nx = soon + 1u;
-        now += nx;
-        // ends at the next instant
-        const uint32_t step_next = (uint32_t)max((int32_t)(step - nx), -1), out_next = (uint32_t)max((int32_t)(out - nx), -1),
-                       in_next = (uint32_t)max((int32_t)(in - nx), -1);
-        const uint32_t step_ends = (uint32_t)((int32_t)(step_next & ~step) >> 31),
-                       out_ends = (uint32_t)((int32_t)(out_next & ~out) >> 31),
-                       in_ends = (uint32_t)((int32_t)(in_next & ~in) >> 31);
-        left += (rel & step_ends) + (osize & out_ends);
-        t -= step_ends;
-        te += step_ends;
-        oe += out_ends;
-        ie += in_ends;
-        step = step_next;
-        out = out_next;
-        in = in_next;
     } while (t != T);
     if (lane == 0) {
         A.total_ns[q] = now;
