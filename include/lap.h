@@ -316,20 +316,23 @@ int lap_validate_trace(const lap_trace *trace, void *ws, size_t ws_bytes, void *
 const char *lap_status_string(int status);
 
 /* Tuning knobs, process-wide and not thread safe: set them before the calls they affect.
- *   LAP_OPT_SEG_MIN_VARS  lap_plan_pool has four ways to keep track of free addresses and picks
+ *   LAP_OPT_SEG_MIN_VARS  lap_plan_pool has five ways to keep track of free addresses and picks
  *       one per trace on the device: per-step free lists when the lifetimes are short (their sum
  *       is at most 6 N; some traces of up to 768 variables are placed in registers all the same),
  *       else, for first-fit orderings, free lists per time segment when the trace has at least
- *       this many variables (default 32768) and the workspace has room for them, else the placed
- *       blocks sorted by offset in registers for up to 32768 variables and 65535 steps, else a
- *       sweep over such a list in memory.  All four give the same offsets.  0 = segment lists
- *       whenever they apply.
+ *       this many variables and the workspace has room for them, else, where all orderings are
+ *       first-fit, 64 variables at a time against the placed blocks sorted by offset (up to 131072
+ *       variables and 65535 steps; small traces under many orderings excepted), else such blocks
+ *       in registers for up to 32768 variables and 65535 steps, else a sweep over such a list in
+ *       memory.  All five give the same offsets.  At the default, 32768, the segment lists also
+ *       leave those traces to the third way that it places faster; 0 = segment lists whenever
+ *       they apply.
  *   LAP_OPT_SEG_TRIAL_PERCENT  whether the segment lists pay also depends on how their searches
  *       converge (two to three rounds on traces with nested lifetimes, as a training iteration
  *       has; six to eight with lifetimes at random, where the others are faster).  Before they are
  *       used, one workgroup places the first 2048 variables of the first first-fit ordering with
  *       them and counts the rounds of the multi-step variables; above this many rounds per
- *       variable, times 100 (default 250), the registers or the sweep place the trace.  0 = no
+ *       variable, times 100 (default 250), the next way places the trace.  0 = no
  *       trial.
  * Returns LAP_E_ORDERING for an unknown option or value. */
 enum { LAP_OPT_SEG_MIN_VARS = 0, LAP_OPT_SEG_TRIAL_PERCENT = 1 };

@@ -144,7 +144,8 @@ int check_ws(void *ws, size_t have, size_t need)
 }
 
 // lap_set_option(LAP_OPT_SEG_MIN_VARS): variables from which on the segment lists are used
-uint64_t g_seg_min_vars = 32768;
+constexpr uint64_t SEG_MIN_VARS_DEFAULT = 32768;
+uint64_t g_seg_min_vars = SEG_MIN_VARS_DEFAULT;
 // lap_set_option(LAP_OPT_SEG_TRIAL_PERCENT): search rounds per multi-step variable (times 100) in the
 // trial run above which the segment lists are not used; 0 = no trial
 uint64_t g_seg_trial_percent = 250;
@@ -444,7 +445,7 @@ int lap_plan_pool(const lap_trace *tr, const lap_ordering *ords, uint32_t B, uin
     uint64_t *m_end = cw.take<uint64_t>(bn);
     uint64_t *m_life = cw.take<uint64_t>(bn);
     uint64_t *f_oe = cf.take<uint64_t>(bn);
-    uint64_t *f_life = cf.take<uint64_t>(bn);
+    uint64_t *f_life = cf.take<uint64_t>(bn);       // (the blocks of place_batch.hip take the place of these two)
     uint64_t *f_oe2 = cf.take<uint64_t>(bn);
     uint64_t *f_life2 = cf.take<uint64_t>(bn);
     uint64_t *f_roe = cf.take<uint64_t>((size_t)B * lap::PLAN_REC);
@@ -476,8 +477,10 @@ int lap_plan_pool(const lap_trace *tr, const lap_ordering *ords, uint32_t B, uin
     }
     const uint64_t seg_min_vars = g_seg_min_vars;
     const bool may_seg = n >= seg_min_vars;         // below, the header rules the segment lists out: no launches for them
+    // from a number of variables that was set, the segment lists are used wherever they apply
+    const uint32_t batches = !lap::batch_places(n, T, B, any_best) ? 0u : seg_min_vars == SEG_MIN_VARS_DEFAULT ? 2u : 1u;
     LAP_HIP(lap::launch_plan_prep(n, T, B, tr->size, tr->alloc, tr->free_, cntd, lstart, hdr, vrec,
-                                  seg_pool_entries(n, B), seg_min_vars, st));
+                                  seg_pool_entries(n, B), seg_min_vars, batches, st));
     if (may_seg)
         LAP_HIP(lap::launch_seg_prep(n, T, B, tr->alloc, tr->free_, hdr, seg_cnt, seg_lst, (uint32_t)dir_cap,
                                      seg_pool_entries(n, B), st));
@@ -489,7 +492,10 @@ int lap_plan_pool(const lap_trace *tr, const lap_ordering *ords, uint32_t B, uin
         if (may_seg)
             LAP_HIP(lap::launch_seg_trial(n, T, B, perm, fits, trial_b, (uint32_t)g_seg_trial_percent, hdr, vrec, seg_lst,
                                           seg_pool, seg_len, (uint32_t)dir_cap, offs, fps, ticks, st));
-        LAP_HIP(lap::launch_place_reg(n, T, B, perm, fits, any_best, hdr, vrec, offs, fps, ticks, st));
+        if (batches)
+            LAP_HIP(lap::launch_place_batch(n, B, perm, hdr, vrec, (uint32_t *)f_oe, offs, fps, ticks, st));
+        else
+            LAP_HIP(lap::launch_place_reg(n, T, B, perm, fits, any_best, hdr, vrec, offs, fps, ticks, st));
         LAP_HIP(lap::launch_place_fast(n, T, B, tr->size, tr->alloc, tr->free_, perm, fits, any_first, any_best, hdr, vrec,
                                        lstart, f_oe, f_life, f_oe2,
                                        f_life2, f_roe, f_rlife, f_roe2, f_rlife2, f_L, capL, l_ns, l_nu, offs, fps, ticks, st));

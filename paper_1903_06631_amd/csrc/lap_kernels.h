@@ -31,14 +31,15 @@ struct PlanHeader {
     uint32_t seg_trial_rounds;     // trial run: search rounds of its multi-step variables, summed
     uint32_t seg_trial_vars;       // ... and how many those were
     uint32_t seg_next;             // next ordering to hand to a workgroup of the segment kernel
-    uint32_t seg_pad;
+    uint32_t batches;              // not 0: what would be placed in registers, or swept, is placed in batches (place_batch.hip); 2: these may go
+                                   // before the segment lists
 };
 constexpr uint32_t PLAN_CL = 6;
 
-// Placed blocks in registers (place_reg.hip): whether they may be used: 128 rows of 256 entries, 16-bit
-// steps ...
-constexpr uint32_t PLAN_REG_MAX_VARS = 128 * 256;
-inline bool reg_may_place(uint32_t n, uint32_t T) { return n <= PLAN_REG_MAX_VARS && T <= 0xFFFFu; }
+// Placed blocks in registers (place_reg.hip; 128 rows of 256 entries), or in batches (place_batch.hip): whether they may be used
+// (16-bit steps) ...
+constexpr uint32_t PLAN_REG_MAX_VARS = 128 * 256, PLAN_BATCH_MAX_VARS = 1 << 17;
+inline bool reg_may_place(uint32_t n, uint32_t T) { return n <= PLAN_BATCH_MAX_VARS && T <= 0xFFFFu; }
 // ... and whether they are, as far as the trace decides it: where per-step lists are not in use.  Up to 128 variables,
 // and up to 768 where the second rule says so (the preparation asks it), these are not used although lifetimes are short
 // enough for them.  A one-step variable costs the lists next to nothing and a multi-step one 3 to 5 us, while every
@@ -53,6 +54,7 @@ constexpr uint32_t PLAN_REG_ALWAYS_VARS = 128, PLAN_REG_FEW_VARS = 3 * 256;
 __device__ __forceinline__ bool reg_places(const PlanHeader *hdr, uint32_t n, bool best_fit)
 {
     if (!hdr->fast || (hdr->mode2 && !best_fit)) return false;
+    if (n > PLAN_REG_MAX_VARS && !hdr->batches) return false;
     return !hdr->mode1 || n <= PLAN_REG_ALWAYS_VARS;
 }
 __device__ __forceinline__ bool reg_before_lists(uint32_t n, uint32_t T, uint32_t n_multi, uint32_t B)
@@ -60,7 +62,7 @@ __device__ __forceinline__ bool reg_before_lists(uint32_t n, uint32_t T, uint32_
     return n <= PLAN_REG_FEW_VARS && T <= 0xFFFFu && n_multi * 40u >= n * ((n + 255) / 256 - (B > 512 ? 1u : 0u));
 }
 
-// Placed blocks in LDS, up to 64 variables placed at a time (place_batch.hip): whether they take the place of the registers.
+// Up to 64 variables placed at a time (place_batch.hip): whether that takes the place of the registers, and of the sweep.
 // First-fit calls only: with best-fit orderings among them the registers place all in one launch.  ms in registers and in
 // batches, of a residual chain, a pyramid of feature maps, and random lifetimes with six sizes, whose holes take one
 // variable each (the alloc-ascending order then needs two to three times as long as the others):
@@ -72,11 +74,28 @@ __device__ __forceinline__ bool reg_before_lists(uint32_t n, uint32_t T, uint32_
 //     768            of 1500   1.02 1.02      and 0.99 1.09      1024 of      3000   2.86           and 2.69 2.89 3.44
 //                       2500   2.20 2.20      and 1.81 1.96                   5000   11.5 11.6      and 4.8 5.3
 //                       6400   13.8 14.2 13.7 and 6.9 7.5 7.0                 9001   29.3           and 14.4
-// 2048 orderings of 3300: 4.38 and 5.25, of 5000 20.3 and 9.0.
-constexpr uint32_t PLAN_BATCH_MAX_VARS = 52 * 256 - 1;      // rows of 512 entries of 12 bytes in 160 KB, less 4 KB
-inline bool batch_places(uint32_t n, uint32_t B, bool any_best)
+// 2048 orderings of 3300: 4.38 and 5.25, of 5000 20.3 and 9.0.  Of a chain with the blocks in memory: 256 orderings of 13 400 20.4
+// and 8.7, of 20 000 38.2 and 14.6, of 32 767 98 and 32; 1024 of 20 000 152 and 50, of 28 000 303 and 88; random lifetimes and
+// sizes: 100 of 15 000 23.4 and 19.9, 500 46.7 and 29.5, 200 of 25 000 62.9 and 43.2.  More than 32 768 take the place of the sweep
+// (40 000, random: 3.2 s by the sweep, 0.08 in batches).
+constexpr uint32_t PLAN_BATCH_LDS_VARS = 52 * 256 - 1;      // rows of 512 entries of 12 bytes in 160 KB, less 4 KB
+inline bool batch_places(uint32_t n, uint32_t T, uint32_t B, bool any_best)
 {
-    return !any_best && n <= PLAN_BATCH_MAX_VARS && (n > 4096 || (n > 2048 && B <= 768) || (n > 1024 && B <= 512));
+    return !any_best && reg_may_place(n, T) && (n > 4096 || (n > 2048 && B <= 768) || (n > 1024 && B <= 512));
+}
+
+// Whether they go before the segment lists.  A workgroup of 16 waves goes through all placed blocks for every batch, one ordering to
+// a compute unit; the lists take a time that goes with their entries and grows slowly with the orderings that share the
+// chip.  ms with the lists and in batches:
+//         residual chain, 33 000 variables, 58 entries each     16 orderings  345 32      256  427  33     1024  500 116    4096  757 448
+//                         50 000            75                  64            557 62      256  848  66     1024  764 243    4096 1114 950
+//                         70 000                                64           1720 116     256 1920 122     1024 2125 468
+//         feature maps,   33 000            18                                            256  133  41     1024  174 136
+//                         50 000            22                                                             1024  278 282
+__device__ __forceinline__ bool batches_before_segments(uint32_t n, uint32_t B, uint64_t need)
+{
+    const uint64_t rounds = (B + 255) / 256;
+    return (uint64_t)n * n * rounds < need * (7500 + 260 * rounds);
 }
 
 hipError_t launch_fill_u64(uint64_t *p, size_t n, uint64_t v, hipStream_t st);
@@ -103,7 +122,7 @@ hipError_t launch_sort_perm(uint32_t n, uint32_t B, const uint64_t *size, const 
                             bool any_explicit, hipStream_t st);
 hipError_t launch_plan_prep(uint32_t n, uint32_t T, uint32_t B, const uint64_t *size, const uint32_t *alloc,
                             const uint32_t *free_, uint32_t *cntd, uint32_t *lstart, PlanHeader *hdr, void *vrec,
-                            uint64_t seg_pool_entries, uint64_t seg_min_vars, hipStream_t st);
+                            uint64_t seg_pool_entries, uint64_t seg_min_vars, uint32_t batches, hipStream_t st);
 hipError_t launch_seg_prep(uint32_t n, uint32_t T, uint32_t B, const uint32_t *alloc, const uint32_t *free_,
                            PlanHeader *hdr, uint32_t *cnt, uint32_t *lst, uint32_t dir_cap, uint64_t pool_entries,
                            hipStream_t st);
@@ -120,9 +139,9 @@ hipError_t launch_place_seg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
 hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *perm, const uint32_t *fits, bool any_best,
                             const PlanHeader *hdr, const void *vrec, uint64_t *offs, uint64_t *fps, uint64_t *ticks,
                             hipStream_t st);
-hipError_t launch_place_batch(uint32_t n, uint32_t B, const uint32_t *perm, const PlanHeader *hdr,
-                               const void *vrec, uint64_t *offs, uint64_t *fps, uint64_t *ticks,
-                              hipStream_t st);
+// blocks [B][4 n]: scratch
+hipError_t launch_place_batch(uint32_t n, uint32_t B, const uint32_t *perm, const PlanHeader *hdr, const void *vrec,
+                              uint32_t *blocks, uint64_t *offs, uint64_t *fps, uint64_t *ticks, hipStream_t st);
 hipError_t launch_place_fast(uint32_t n, uint32_t T, uint32_t B, const uint64_t *size, const uint32_t *alloc,
                              const uint32_t *free_, const uint32_t *perm, const uint32_t *fits, bool any_first,
                              bool any_best, PlanHeader *hdr, const void *vrec,

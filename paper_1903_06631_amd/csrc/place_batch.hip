@@ -1,14 +1,17 @@
 // First-fit placement of every variable under many orderings (Section III-C), in batches: up to 64 variables of an ordering
 // are placed at a time.
 //
-// One workgroup works on one ordering.  Its placed blocks lie in LDS, sorted by offset, as offset, end and lifetime (16 + 16
-// bits) in three arrays; the entries behind the last block have the highest offset and meet nothing.
+// One workgroup works on one ordering.  Its placed blocks are sorted by offset, as offset, end and lifetime (16 + 16 bits) in
+// three arrays; the entries behind the last block have the highest offset and meet nothing.  The arrays lie in LDS up to
+// 13 311 variables, else in global memory.
 //
 // A batch is the next variables in rank order.
 //   ask      Each of them is taken by one wave, which goes through the blocks placed so far in rows of 512, eight entries a
 //            lane: entries that do not meet the variable in time are masked, a prefix maximum of the remaining ends gives
 //            the highest occupied address so far, and an entry whose offset leaves `size` free above it shows a hole.
 //            The wave notes the first hole and the next one of the same row.  The answers do not know of each other.
+//            Where the arrays lie in global memory, a wave asks for four lifetimes at a time, so that every row is read once
+//            for them, and the next row while this one is looked at; the variables of one lifetime share the question.
 //   compare  Which others of the batch a variable meets in time, and whether an earlier one of them is in its way.
 //   settle   One wave makes the answers what they would be one after the other.  An answer that nothing is in the way of
 //            stands: more blocks take places away and never give one.  Where something is, everything below the answer stays
@@ -19,9 +22,13 @@
 //            the number of new blocks below it, read by all waves, written by all waves, from the top down in as many
 //            rounds as the registers need.
 // Measured: 193 orderings of a residual chain of 9001 variables 4.9 ms (in registers, one variable a round of two barriers,
-// 11.2), of 13 000 8.1 (19.6), 256 of 3000 1.2 (2.4).
-// What bounds it: the vector instructions of the questions (two thirds of the time of 9001 variables), and one variable after
-// the other where a batch is settled, 200 cycles each (half of the time where all variables of a step follow each other).
+// 11.2), 256 of 3000 1.2 (2.4), of 13 000 8.3 (19.6), of 20 000 14.6 (38.2; row by row one variable a wave 17, without the
+// shared questions 15.7), of 32 767 32.5 (98.4), of 50 000 66 (848 by segment lists).
+// What bounds it: the vector instructions of the questions, 60 for a row of 512 entries (two thirds of the time of 9001
+// variables; at 50 000 three quarters: 1540 rows a batch, of 2450 if every lifetime asked all of them, at 74 % of the rate of
+// issue), and one variable after the other where a batch is settled, 200 cycles each (half of the time where all variables
+// of a step follow each other).  Pairs of lifetimes handed to the waves as these get free were slower (50 000: 72 ms, 66
+// dealt): waves that go through the rows together find them in the first-level cache.
 #include "block_rows.h"
 #include "lap_kernels.h"
 
@@ -43,6 +50,7 @@ struct BatchArgs {
     const uint4 *vrec;           // [n] (first step, end of life, size in granules, -)
     const uint32_t *perm;        // [B][n]
     const PlanHeader *hdr;
+    uint32_t *blocks;            // [B][4 n] the three arrays where they do not fit the LDS
     uint64_t *offs;              // [B][n] in rank order
     uint64_t *fps;               // [B]
     uint64_t *ticks;             // [B] duration of every ordering in timer ticks
@@ -100,26 +108,52 @@ __device__ __forceinline__ uint32_t first_neighbour(const Entries &R, const uint
     return any ? from + read_lane(d, first_lane(any)) : NOTHING;
 }
 
-// NW waves an ordering, which move RPW rows of 256 each at once
-template <int NW, int RPW>
+// The first hole of a row that shows one, and the next one of the row (end 0: there is none)
+__device__ __forceinline__ void row_answer(const Entries &R, const uint32_t (&e)[E], const uint32_t (&before)[E],
+                                           const uint32_t (&free_)[E], uint64_t any, uint32_t s, uint32_t &at, uint32_t &hole, uint2 &next)
+{
+    uint32_t x = before[E - 1];
+#pragma unroll
+    for (int j = E - 2; j >= 0; --j) x = pick(free_[j] >= s, before[j], x);
+    at = read_lane(x, first_lane(any));
+    // it ends at the first neighbour behind it, or at the row's last entry at least
+    const uint32_t end = read_lane(R.off[E - 1], WAVE - 1);
+    hole = min(first_neighbour(R, e, at + s), end);
+    // the next one: a lane's highest address so far where it shows a hole behind the first
+    x = NOTHING;
+#pragma unroll
+    for (int j = E - 1; j >= 0; --j) x = pick(free_[j] >= s && before[j] > at, before[j], x);
+    const uint64_t more = ballot(x != NOTHING);
+    if (more) {
+        const uint32_t at2 = read_lane(x, first_lane(more));
+        next = make_uint2(at2, min(first_neighbour(R, e, at2 + s), end));
+    }
+}
+
+// NW waves an ordering, which move RPW rows of 256 each at once; NEAR: the three arrays lie in LDS, else in global memory
+template <int NW, int RPW, bool NEAR>
 __global__ __launch_bounds__(NW *WAVE, 4) void k_place_batch(BatchArgs A)
 {
     extern __shared__ uint32_t s_blocks[];
     __shared__ uint2 s_rec[AHEAD];                         // lifetime, size of the ranks ahead, at rank % AHEAD
     __shared__ uint4 s_ask[BATCH];                         // start of the hole, size, lifetime, end of the hole
     __shared__ uint2 s_next[BATCH];                        // start and end of the next holes (0: no further one)
-    __shared__ uint64_t s_meets[BATCH];                    // the variables of the batch that meet this one
+    __shared__ uint64_t s_meets[BATCH];                    // the variables of the batch that meet this one; before: that have its lifetime
+    __shared__ uint32_t s_first[2], s_order[BATCH];        // bits: the first one of every lifetime; those, the longest first
     // bits: the variables with an earlier one in their way, and those that are in the way
     __shared__ uint32_t s_hit[4], s_task, s_acc, s_fp;
-    static_assert(sizeof(s_rec) + sizeof(s_ask) + sizeof(s_next) + sizeof(s_meets) + sizeof(s_hit) + 12 <= BATCH_LDS, "");
-    static_assert((PLAN_BATCH_MAX_VARS / ROWE + 1) * ROWE * 12 + BATCH_LDS <= 160 * 1024, "");
+    static_assert(sizeof(s_rec) + sizeof(s_ask) + sizeof(s_next) + sizeof(s_meets) + sizeof(s_hit) + sizeof(s_first) + sizeof(s_order) + 12 <= BATCH_LDS, "");
+    static_assert((PLAN_BATCH_LDS_VARS / ROWE + 1) * ROWE * 12 + BATCH_LDS <= 160 * 1024, "");
     uint2 *const s_pos = s_next;                           // where a new block goes: entries below it, and its index
 
     const uint32_t b = blockIdx.x;
     if (!reg_places(A.hdr, A.n, false)) return;
     const long long t_begin = wall_clock64();
     const uint32_t n = A.n, sh = A.hdr->shift, cap = A.cap;
-    uint32_t *const s_off = s_blocks, *const s_end = s_blocks + cap, *const s_life = s_blocks + 2 * cap;
+    uint32_t *s_off;
+    if constexpr (NEAR) s_off = s_blocks;
+    else s_off = A.blocks + (size_t)b * 4 * n;
+    uint32_t *const s_end = s_off + cap, *const s_life = s_off + 2 * cap;
     const uint32_t l = (uint32_t)lane_id(), tid = threadIdx.x;
     const uint32_t wave = uniform(tid / WAVE);
     const uint32_t *perm = A.perm + (size_t)b * n;
@@ -132,6 +166,7 @@ __global__ __launch_bounds__(NW *WAVE, 4) void k_place_batch(BatchArgs A)
     }
     if (tid == 0) { s_fp = 0; s_task = NW; }
     if (tid < 4) s_hit[tid] = 0;
+    if (tid < 2) s_first[tid] = 0;
     // one wave fetches the records of the ranks to come: those of the next 64 and the variable numbers of the 64 after
     const bool fetches = wave == NW - 1;
     uint4 rec_next = make_uint4(0u, 1u, 1u, 0u);
@@ -142,11 +177,90 @@ __global__ __launch_bounds__(NW *WAVE, 4) void k_place_batch(BatchArgs A)
     }
     __syncthreads();
 
+    constexpr uint32_t V = BATCH / NW;
     uint32_t fp = 0;
     uint32_t most = BATCH, few = 0, cut = 0;               // variables of the next batch; batches to come of few, cut short one after the other
     for (uint32_t r = 0, turn = 0; r < n; ++turn) {        // r ranks are placed
         const uint32_t lim = min(few ? FEW : most, n - r), others = few ? FEW_HOLES : 1u;
         // ---- ask
+        if (!NEAR && !few) {
+            // Variables of one lifetime ask together: a wave takes up to four lifetimes and reads every row once for all of them,
+            // ahead of its turn.  Which variables are the first of their lifetime, and their order: those that live longest, which
+            // mostly ask the most rows, are dealt to the waves first.
+            const uint32_t life = l < lim ? s_rec[(r + l) % AHEAD].x : NOTHING;
+            const uint32_t lives = (0xFFFFu - (life >> 16)) - (life & 0xFFFFu);
+            uint64_t first = 0;
+#pragma unroll
+            for (uint32_t q = 0; q < V; ++q) {
+                if (q * NW >= lim) break;
+                const uint32_t v = q * NW + wave;
+                const uint64_t m = v < lim ? ballot(l < lim && life == read_lane(life, v)) : 0;
+                if (l == v) s_meets[v] = m;
+                first |= m && first_lane(m) == v ? 1ull << v : 0;
+            }
+            if (first && l < 2) atomicOr(&s_first[l], (uint32_t)(first >> (32 * l)));
+            __syncthreads();
+            const uint64_t all = ((uint64_t)uniform(s_first[1]) << 32) | uniform(s_first[0]);
+#pragma unroll
+            for (uint32_t q = 0; q < V; ++q) {
+                const uint32_t v = q * NW + wave;
+                if (!((all >> v) & 1)) continue;
+                const uint32_t mine = read_lane(lives, v);
+                const uint32_t rank = (uint32_t)__popcll(ballot(lives > mine || (lives == mine && l < v)) & all);
+                if (l == 0) s_order[rank] = v;
+            }
+            __syncthreads();
+            const uint32_t firsts = (uint32_t)__popcll(all);
+            const uint32_t last = r / ROWE;
+            uint32_t lf[V], P[V], least[V];
+            uint64_t left[V], some = 0;
+#pragma unroll
+            for (uint32_t q = 0; q < V; ++q) {
+                const bool is = q * NW + wave < firsts;
+                const uint32_t v = is ? uniform(s_order[q * NW + wave]) : 0;
+                lf[q] = uniform(s_rec[(r + v) % AHEAD].x);
+                const uint64_t m = s_meets[v];
+                left[q] = is ? ((uint64_t)uniform((uint32_t)(m >> 32)) << 32) | uniform((uint32_t)m) : 0;
+                least[q] = 0;
+                P[q] = 0;
+                some |= left[q];
+            }
+            Entries R;
+            if (some) R.load(s_off, s_end, s_life, 0);
+            for (uint32_t i = 0; i <= last && some; ++i) {
+                Entries N;
+                N.load(s_off, s_end, s_life, min(i + 1, last));
+                some = 0;
+#pragma unroll
+                for (uint32_t q = 0; q < V; ++q) {
+                    if (!left[q]) continue;
+                    uint32_t e[E], before[E], free_[E];
+                    const uint32_t incl = batch_ends(R, bound_of(lf[q]), e);
+                    batch_holes(R, e, incl, P[q], before, free_);
+                    uint32_t f = free_[0];
+#pragma unroll
+                    for (int j = 1; j < E; ++j) f = max(f, free_[j]);
+                    if (ballot(f >= least[q])) {
+                        // those whose size it takes are answered; the smallest size of the others
+                        least[q] = NOTHING;
+                        for (uint64_t m = left[q]; m; m &= m - 1) {
+                            const uint32_t k = first_lane(m), s = uniform(s_rec[(r + k) % AHEAD].y);
+                            const uint64_t any = ballot(f >= s);
+                            if (any) {
+                                uint32_t at, hole;
+                                uint2 next = make_uint2(0, 0);
+                                row_answer(R, e, before, free_, any, s, at, hole, next);
+                                if (l == 0) { s_ask[k] = make_uint4(at, s, lf[q], hole); s_next[k] = next; }
+                                left[q] &= ~(1ull << k);
+                            } else least[q] = min(least[q], s);
+                        }
+                    }
+                    P[q] = max(P[q], read_lane(incl, WAVE - 1));
+                    some |= left[q];
+                }
+                R = N;
+            }
+        } else
         for (uint32_t v = wave, v_after; v < lim; v = uniform(v_after)) {
             v_after = l == 0 ? atomicAdd(&s_task, 1u) : 0;
             const uint2 rec = s_rec[(r + v) % AHEAD];
@@ -166,22 +280,7 @@ __global__ __launch_bounds__(NW *WAVE, 4) void k_place_batch(BatchArgs A)
                     for (int j = 1; j < E; ++j) f = max(f, free_[j]);
                     const uint64_t any = ballot(f >= s);
                     if (any) {
-                        uint32_t x = before[E - 1];
-#pragma unroll
-                        for (int j = E - 2; j >= 0; --j) x = pick(free_[j] >= s, before[j], x);
-                        at0 = read_lane(x, first_lane(any));
-                        // it ends at the first neighbour behind it, or at the row's last entry at least
-                        const uint32_t end = read_lane(R.off[E - 1], WAVE - 1);
-                        hole0 = min(first_neighbour(R, e, at0 + s), end);
-                        // the next one: a lane's highest address so far where it shows a hole behind the first
-                        x = NOTHING;
-#pragma unroll
-                        for (int j = E - 1; j >= 0; --j) x = pick(free_[j] >= s && before[j] > at0, before[j], x);
-                        const uint64_t more = ballot(x != NOTHING);
-                        if (more) {
-                            at = read_lane(x, first_lane(more));
-                            next = make_uint2(at, min(first_neighbour(R, e, at + s), end));
-                        }
+                        row_answer(R, e, before, free_, any, s, at0, hole0, next);
                         break;
                     }
                     P = max(P, read_lane(incl, WAVE - 1));
@@ -287,6 +386,7 @@ __global__ __launch_bounds__(NW *WAVE, 4) void k_place_batch(BatchArgs A)
             }
             if (l == 0) { s_acc = acc; s_task = NW; }
             if (l < 4) s_hit[l] = 0;
+            if (l < 2) s_first[l] = 0;
         }
         __syncthreads();
         // ---- insert: lane k has the batch's block k.  First how many entries each has below it (or at the same offset):
@@ -377,27 +477,28 @@ __global__ __launch_bounds__(NW *WAVE, 4) void k_place_batch(BatchArgs A)
     }
 }
 
-template <int NW, int RPW>
+template <int NW, int RPW, bool NEAR>
 hipError_t launch_one(const BatchArgs &A, uint32_t B, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_place_batch<NW, RPW>), dim3(B), dim3(NW * WAVE), (size_t)A.cap * 12, st, A);
+    hipLaunchKernelGGL((k_place_batch<NW, RPW, NEAR>), dim3(B), dim3(NW * WAVE), NEAR ? (size_t)A.cap * 12 : 0, st, A);
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_place_batch(uint32_t n, uint32_t B, const uint32_t *perm,
-                              const PlanHeader *hdr, const void *vrec, uint64_t *offs, uint64_t *fps, uint64_t *ticks,
-                              hipStream_t st)
+                              const PlanHeader *hdr, const void *vrec, uint32_t *blocks, uint64_t *offs, uint64_t *fps,
+                              uint64_t *ticks, hipStream_t st)
 {
-    const BatchArgs A{n, (n / ROWE + 1) * ROWE, (const uint4 *)vrec, perm, hdr, offs, fps, ticks};
+    const BatchArgs A{n, (n / ROWE + 1) * ROWE, (const uint4 *)vrec, perm, hdr, blocks, offs, fps, ticks};
+    if (n > PLAN_BATCH_LDS_VARS) return launch_one<16, 2, false>(A, B, st);
     // 16 waves where an ordering has a compute unit to itself, 8 where two share one (registers: 20 waves a unit); ms with 8
     // and with 16 waves, of a residual chain of 5000 variables: 256 orderings 2.49 and 2.25, 512 2.49 and 3.59, 1024
     // 4.78 and 6.39; of 6400, whose blocks take more than half of the LDS: 300 orderings 4.81 and 3.95, 1024 10.5 and 8.8.
     // (Four waves, four orderings to a unit: 1024 orderings of 3000 2.68 ms, 2.86 in registers, but random lifetimes and few
     // sizes 3.67 and 2.80.)
-    if (B <= 256 || 2 * (A.cap * 12 + BATCH_LDS) > 160u * 1024) return launch_one<16, 2>(A, B, st);
-    return launch_one<8, 2>(A, B, st);
+    if (B <= 256 || 2 * (A.cap * 12 + BATCH_LDS) > 160u * 1024) return launch_one<16, 2, true>(A, B, st);
+    return launch_one<8, 2, true>(A, B, st);
 }
 
 }  // namespace lap

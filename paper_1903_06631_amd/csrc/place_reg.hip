@@ -258,9 +258,7 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
                             bool any_best, const PlanHeader *hdr, const void *vrec, uint64_t *offs, uint64_t *fps, uint64_t *ticks,
                             hipStream_t st)
 {
-    if (!reg_may_place(n, T)) return hipSuccess;
-    if (batch_places(n, B, any_best))
-        return launch_place_batch(n, B, perm, hdr, vrec, offs, fps, ticks, st);
+    if (n > PLAN_REG_MAX_VARS || T > 0xFFFFu) return hipSuccess;
     const RegArgs A{n, B, (const uint4 *)vrec, perm, fits, hdr, offs, fps, ticks};
     const uint32_t rows = (n + ROW - 1) / ROW;
     // Up to 8 rows one wave is the fastest way through an ordering (1000 variables: 0.55 ms; 0.75 ms

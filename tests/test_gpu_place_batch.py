@@ -33,10 +33,12 @@ def _lives(tr, alloc, free):
     return tr
 
 
-# rows of 512 blocks, one more and one less; 16 and 8 waves; the last size of the batches and the next one
+# rows of 512 blocks, one more and one less; 16 and 8 waves; the last size whose blocks are in LDS and the next one; the last of the
+# registers and the next one
 @pytest.mark.parametrize("n,T,B", [(1025, 70, 6), (1535, 65535, 6), (1536, 300, 6), (1537, 300, 6), (2048, 300, 257), (2049, 300, 513),
                                    (4096, 500, 257), (4097, 500, 769), (6143, 900, 257), (6144, 900, 257), (8192, 900, 6),
-                                   (13311, 1500, 5), (13312, 1500, 5)])
+                                   (13311, 1500, 5), (13312, 1500, 5), (13313, 65535, 5), (16384, 1500, 5),
+                                   (32768, 3000, 5), (32769, 3000, 5)])
 def test_sizes(lap, oracle_mod, n, T, B):
     _check(lap, oracle_mod, random_trace(9000 + n, n, T, size_choices=[1, 1, 2, 3, 5, 8, 13, 64]), B,
            sorted({0, 1, 2, 3, 4, B - 1}))
@@ -44,9 +46,10 @@ def test_sizes(lap, oracle_mod, n, T, B):
 
 # everything meets everything; all in one hole; holes that take one variable each (few sizes, many variables a step), so that a
 # batch ends early and further holes are asked for; two lifetimes in turn
+@pytest.mark.parametrize("n", [1500, 13400])
 @pytest.mark.parametrize("what", ["all", "equal", "few sizes", "one size of each", "two"])
-def test_in_each_others_way(lap, oracle_mod, what):
-    n, T = 1500, 40
+def test_in_each_others_way(lap, oracle_mod, what, n):
+    T = 40 * n // 1500
     rng = np.random.default_rng(len(what))
     tr = random_trace(9400 + len(what), n, T, size_choices=[1, 2, 3, 7, 20, 50] if what != "equal" else [4])
     if what in ("all", "equal"):
@@ -73,3 +76,51 @@ def test_highest_addresses(lap, oracle_mod):
     assert int(tr.size.sum()) == (1 << 32) - 1 and int(np.bitwise_or.reduce(tr.size)) & 1
     _lives(tr, np.zeros(n), np.full(n, 60))
     _check(lap, oracle_mod, tr, 5, range(5))
+
+
+# more variables than registers take: the segment lists, forced, whose trial run refuses random lifetimes, so that the batches
+# place them after all; no room for the lists' steps in 16 bits; best-fit orderings beside the others
+@pytest.mark.parametrize("T,forced,best", [(1500, True, False), (65536, False, False), (1500, False, True)])
+def test_other_ways(lap, oracle_mod, T, forced, best):
+    n, B = 33000, 4
+    tr = random_trace(9600 + T, n, T, size_choices=[1, 2, 3, 7, 20, 50])
+    kinds, seeds = make_orderings(B)
+    fits = np.zeros(B, np.uint32)
+    fits[3] = lap.FIT_BEST if best else lap.FIT_FIRST
+    lap.set_option(lap.OPT_SEG_MIN_VARS, n if forced else lap.SEG_MIN_VARS_DEFAULT)
+    try:
+        got = lap.plan_pool(lap.DeviceTrace(tr), kinds, seeds, fits=fits)
+    finally:
+        lap.set_option(lap.OPT_SEG_MIN_VARS, lap.SEG_MIN_VARS_DEFAULT)
+    all_off = u64(got["all_offsets"])
+    for b, (_, off, fp) in oracle_all_orderings(oracle_mod, tr, kinds, seeds, None, [1, 2], None).items():
+        assert np.array_equal(all_off[b], off) and u64(got["footprints"])[b] == fp, f"ordering {b}"
+
+
+# blocks in memory: plans in two streams at once, then the two in a graph that is replayed with other work between
+def test_streams_and_graph(lap):
+    import torch
+    traces = [lap.DeviceTrace(random_trace(9700 + i, 14000, 900, size_choices=[1, 2, 3, 5, 64])) for i in range(2)]
+    kinds, seeds = make_orderings(5)
+    want = [u64(lap.plan_pool(t, kinds, seeds)["all_offsets"]) for t in traces]
+    lap.profile_enable(False)
+    side = [torch.cuda.Stream() for _ in traces]
+    got = []
+    for t, st in zip(traces, side):
+        with torch.cuda.stream(st):
+            got.append(lap.plan_pool(t, kinds, seeds, sync=False))
+    torch.cuda.synchronize()
+    for g, w in zip(got, want):
+        assert np.array_equal(u64(g["all_offsets"]), w)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side[0]):
+        with torch.cuda.graph(graph, stream=side[0]):
+            got = [lap.plan_pool(t, kinds, seeds, sync=False) for t in traces]
+    for _ in range(3):
+        for g in got:
+            g["all_offsets"].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for g, w in zip(got, want):
+            assert np.array_equal(u64(g["all_offsets"]), w)
+        lap.plan_pool(traces[0], kinds[::-1].copy(), seeds[::-1].copy())
