@@ -62,7 +62,7 @@ def read_profile_values(path):
 # from, and the stem of its counter summaries under profiles/
 PLACE_KERNEL = {
     5: ("k_place_fast<unsigned int, 4, true, 0>", ("place_fast.hip", "block_rows.h", "lap_dev.h"), "k_place_fast_transformer_B1024"),
-    4: ("k_place_seg<false>", ("place_seg.hip", "seg_core.h", "lap_dev.h"), "k_place_seg_deepchain_B4096"),
+    4: ("k_place_batch<8, 2, false>", ("place_batch.hip", "block_rows.h", "lap_dev.h"), "k_place_batch_deepchain_B4096"),
 }
 
 
@@ -171,7 +171,8 @@ def main() -> int:
     pair_bytes = B * (16 * n_edges + 24 * n)
     roofline = dict(bound="hbm", kernel=k_name, achieved=achieved, peak=HBM_PEAK_GBPS, unit="GB/s",
                     frac=achieved / HBM_PEAK_GBPS if achieved else None, traffic=traffic, kernel_ms=k_ms,
-                    limited_by="the dependent memory accesses of one placement (latency and number of scattered "
+                    limited_by="the vector instructions of the questions (see counters), not HBM bandwidth" if "batch" in k_name else
+                               "the dependent memory accesses of one placement (latency and number of scattered "
                                "requests, see counters), not HBM bandwidth",
                     counters=counters or None, copy_GBps=copy_GBps,
                     # the launch ends with its slowest ordering

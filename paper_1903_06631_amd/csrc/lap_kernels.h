@@ -75,8 +75,8 @@ __device__ __forceinline__ bool reg_before_lists(uint32_t n, uint32_t T, uint32_
 //                       2500   2.20 2.20      and 1.81 1.96                   5000   11.5 11.6      and 4.8 5.3
 //                       6400   13.8 14.2 13.7 and 6.9 7.5 7.0                 9001   29.3           and 14.4
 // 2048 orderings of 3300: 4.38 and 5.25, of 5000 20.3 and 9.0.  Of a chain with the blocks in memory: 256 orderings of 13 400 20.4
-// and 8.7, of 20 000 38.2 and 14.6, of 32 767 98 and 32; 1024 of 20 000 152 and 50, of 28 000 303 and 88; random lifetimes and
-// sizes: 100 of 15 000 23.4 and 19.9, 500 46.7 and 29.5, 200 of 25 000 62.9 and 43.2.  More than 32 768 take the place of the sweep
+// and 8.6, of 20 000 38.2 and 14.4, of 32 767 98 and 32; 1024 of 20 000 152 and 43; random lifetimes and six sizes: 100 of 15 000
+// 23.4 and 19.7, 200 of 25 000 62.9 and 42.5.  More than 32 768 take the place of the sweep
 // (40 000, random: 3.2 s by the sweep, 0.08 in batches).
 constexpr uint32_t PLAN_BATCH_LDS_VARS = 52 * 256 - 1;      // rows of 512 entries of 12 bytes in 160 KB, less 4 KB
 inline bool batch_places(uint32_t n, uint32_t T, uint32_t B, bool any_best)
@@ -84,18 +84,18 @@ inline bool batch_places(uint32_t n, uint32_t T, uint32_t B, bool any_best)
     return !any_best && reg_may_place(n, T) && (n > 4096 || (n > 2048 && B <= 768) || (n > 1024 && B <= 512));
 }
 
-// Whether they go before the segment lists.  A workgroup of 16 waves goes through all placed blocks for every batch, one ordering to
-// a compute unit; the lists take a time that goes with their entries and grows slowly with the orderings that share the
-// chip.  ms with the lists and in batches:
-//         residual chain, 33 000 variables, 58 entries each     16 orderings  345 32      256  427  33     1024  500 116    4096  757 448
-//                         50 000            75                  64            557 62      256  848  66     1024  764 243    4096 1114 950
-//                         70 000                                64           1720 116     256 1920 122     1024 2125 468
-//         feature maps,   33 000            18                                            256  133  41     1024  174 136
-//                         50 000            22                                                             1024  278 282
+// Whether they go before the segment lists.  All placed blocks are gone through for every batch, one ordering of 16 waves or two of
+// 8 to a compute unit; the lists take a time that goes with their entries, and from some 1000 orderings on with these as
+// well.  ms with the lists and in batches:
+//         residual chain, 33 000 variables, 58 entries each     256 orderings 427 32      1024  500 103     4096  757 387
+//                         50 000            75                                848 65            764 215          1114 811
+//                         70 000                                             1920 122
+//         feature maps,   33 000            18                                133  39            176 121           552 452
+//                         50 000            22                                209  72            274 256           908 955
 __device__ __forceinline__ bool batches_before_segments(uint32_t n, uint32_t B, uint64_t need)
 {
     const uint64_t rounds = (B + 255) / 256;
-    return (uint64_t)n * n * rounds < need * (7500 + 260 * rounds);
+    return (uint64_t)n * n * rounds < need * (6700 + 1600 * rounds);
 }
 
 hipError_t launch_fill_u64(uint64_t *p, size_t n, uint64_t v, hipStream_t st);

@@ -10,8 +10,8 @@
 //            lane: entries that do not meet the variable in time are masked, a prefix maximum of the remaining ends gives
 //            the highest occupied address so far, and an entry whose offset leaves `size` free above it shows a hole.
 //            The wave notes the first hole and the next one of the same row.  The answers do not know of each other.
-//            Where the arrays lie in global memory, a wave asks for four lifetimes at a time, so that every row is read once
-//            for them, and the next row while this one is looked at; the variables of one lifetime share the question.
+//            Where the arrays lie in global memory, their rows come to the LDS some at a time, the next ones on their way
+//            while these are looked at, and the variables of one lifetime share the question.
 //   compare  Which others of the batch a variable meets in time, and whether an earlier one of them is in its way.
 //   settle   One wave makes the answers what they would be one after the other.  An answer that nothing is in the way of
 //            stands: more blocks take places away and never give one.  Where something is, everything below the answer stays
@@ -22,13 +22,14 @@
 //            the number of new blocks below it, read by all waves, written by all waves, from the top down in as many
 //            rounds as the registers need.
 // Measured: 193 orderings of a residual chain of 9001 variables 4.9 ms (in registers, one variable a round of two barriers,
-// 11.2), 256 of 3000 1.2 (2.4), of 13 000 8.3 (19.6), of 20 000 14.6 (38.2; row by row one variable a wave 17, without the
-// shared questions 15.7), of 32 767 32.5 (98.4), of 50 000 66 (848 by segment lists).
+// 11.2), 256 of 3000 1.2 (2.4), of 13 000 8.3 (19.6), of 20 000 14.4 (38.2), of 32 767 32 (98), of 50 000 65 (848 by segment
+// lists), 4096 of them 811 (1114).  Without the shared questions 50 000 took 77; in LDS sharing does not pay (9001: 9.9).
 // What bounds it: the vector instructions of the questions, 60 for a row of 512 entries (two thirds of the time of 9001
-// variables; at 50 000 three quarters: 1540 rows a batch, of 2450 if every lifetime asked all of them, at 74 % of the rate of
-// issue), and one variable after the other where a batch is settled, 200 cycles each (half of the time where all variables
-// of a step follow each other).  Pairs of lifetimes handed to the waves as these get free were slower (50 000: 72 ms, 66
-// dealt): waves that go through the rows together find them in the first-level cache.
+// variables; at 50 000 a batch asks 1540 rows, of 2450 if every lifetime asked all of them, 38 of its 83 us), the waits where a
+// chunk's lifetimes do not come out even over the waves (22 us), and one variable after the other where a batch is settled,
+// 200 cycles each (half of the time where all variables of a step follow each other).  A second ordering on the compute unit
+// fills those waits.  Rows that every wave reads for itself, four lifetimes at a time, took as long under one ordering a unit and
+// read them 2.5 times over (4096 orderings: 5.3 TB/s; 948 ms).
 #include "block_rows.h"
 #include "lap_kernels.h"
 
@@ -69,6 +70,19 @@ struct Entries {
 #pragma unroll
         for (int j = 0; j < E; j += 4) {
             const uint4 x = *(const uint4 *)(o + i + j), y = *(const uint4 *)(e + i + j), z = *(const uint4 *)(f + i + j);
+            off[j] = x.x; off[j + 1] = x.y; off[j + 2] = x.z; off[j + 3] = x.w;
+            end[j] = y.x; end[j + 1] = y.y; end[j + 2] = y.z; end[j + 3] = y.w;
+            life[j] = z.x; life[j + 1] = z.y; life[j + 2] = z.z; life[j + 3] = z.w;
+        }
+    }
+    // arrays `stride` words apart, in which a row has the first half of every lane's entries before the second
+    __device__ __forceinline__ void load_halves(const uint32_t *o, uint32_t stride, uint32_t row)
+    {
+        const uint32_t i = row * ROWE + (uint32_t)lane_id() * 4;
+#pragma unroll
+        for (int j = 0; j < E; j += 4) {
+            const uint4 x = *(const uint4 *)(o + i + j * WAVE), y = *(const uint4 *)(o + stride + i + j * WAVE),
+                        z = *(const uint4 *)(o + 2 * stride + i + j * WAVE);
             off[j] = x.x; off[j + 1] = x.y; off[j + 2] = x.z; off[j + 3] = x.w;
             end[j] = y.x; end[j + 1] = y.y; end[j + 2] = y.z; end[j + 3] = y.w;
             life[j] = z.x; life[j + 1] = z.y; life[j + 2] = z.z; life[j + 3] = z.w;
@@ -134,15 +148,17 @@ __device__ __forceinline__ void row_answer(const Entries &R, const uint32_t (&e)
 template <int NW, int RPW, bool NEAR>
 __global__ __launch_bounds__(NW *WAVE, 4) void k_place_batch(BatchArgs A)
 {
-    extern __shared__ uint32_t s_blocks[];
+    // (read 16 bytes a lane: eight times slower where it only starts at a multiple of 8)
+    extern __shared__ __attribute__((aligned(16))) uint32_t s_blocks[];
     __shared__ uint2 s_rec[AHEAD];                         // lifetime, size of the ranks ahead, at rank % AHEAD
     __shared__ uint4 s_ask[BATCH];                         // start of the hole, size, lifetime, end of the hole
     __shared__ uint2 s_next[BATCH];                        // start and end of the next holes (0: no further one)
-    __shared__ uint64_t s_meets[BATCH];                    // the variables of the batch that meet this one; before: that have its lifetime
-    __shared__ uint32_t s_first[2], s_order[BATCH];        // bits: the first one of every lifetime; those, the longest first
+    __shared__ uint64_t s_meets[BATCH];                    // the variables of the batch that meet this one; before: that have its lifetime, not answered
+    __shared__ uint2 s_state[BATCH];                       // per lifetime: highest address so far, smallest size not answered
+    __shared__ uint32_t s_open[2], s_done[4];              // bits: the first variable of every lifetime; those that are answered, by chunk
     // bits: the variables with an earlier one in their way, and those that are in the way
     __shared__ uint32_t s_hit[4], s_task, s_acc, s_fp;
-    static_assert(sizeof(s_rec) + sizeof(s_ask) + sizeof(s_next) + sizeof(s_meets) + sizeof(s_hit) + sizeof(s_first) + sizeof(s_order) + 12 <= BATCH_LDS, "");
+    static_assert(sizeof(s_rec) + sizeof(s_ask) + sizeof(s_next) + sizeof(s_meets) + sizeof(s_hit) + sizeof(s_state) + sizeof(s_open) + sizeof(s_done) + 12 <= BATCH_LDS, "");
     static_assert((PLAN_BATCH_LDS_VARS / ROWE + 1) * ROWE * 12 + BATCH_LDS <= 160 * 1024, "");
     uint2 *const s_pos = s_next;                           // where a new block goes: entries below it, and its index
 
@@ -166,7 +182,8 @@ __global__ __launch_bounds__(NW *WAVE, 4) void k_place_batch(BatchArgs A)
     }
     if (tid == 0) { s_fp = 0; s_task = NW; }
     if (tid < 4) s_hit[tid] = 0;
-    if (tid < 2) s_first[tid] = 0;
+    if (tid < 2) s_open[tid] = 0;
+    if (tid < 4) s_done[tid] = 0;
     // one wave fetches the records of the ranks to come: those of the next 64 and the variable numbers of the 64 after
     const bool fetches = wave == NW - 1;
     uint4 rec_next = make_uint4(0u, 1u, 1u, 0u);
@@ -177,88 +194,90 @@ __global__ __launch_bounds__(NW *WAVE, 4) void k_place_batch(BatchArgs A)
     }
     __syncthreads();
 
-    constexpr uint32_t V = BATCH / NW;
+    constexpr uint32_t CHUNK = NW * WAVE * 4 / ROWE;       // rows that come to the LDS at a time: four entries a thread
     uint32_t fp = 0;
     uint32_t most = BATCH, few = 0, cut = 0;               // variables of the next batch; batches to come of few, cut short one after the other
     for (uint32_t r = 0, turn = 0; r < n; ++turn) {        // r ranks are placed
         const uint32_t lim = min(few ? FEW : most, n - r), others = few ? FEW_HOLES : 1u;
         // ---- ask
         if (!NEAR && !few) {
-            // Variables of one lifetime ask together: a wave takes up to four lifetimes and reads every row once for all of them,
-            // ahead of its turn.  Which variables are the first of their lifetime, and their order: those that live longest, which
-            // mostly ask the most rows, are dealt to the waves first.
+            // The rows come through the LDS, CHUNK at a time, the next ones on their way while these are looked at.  Variables of
+            // one lifetime ask together; the lifetimes that are not answered yet are dealt to the waves anew for every chunk.
+            const uint32_t last = r / ROWE;
+            uint4 xo, xe, xl;
+            auto fetch = [&](uint32_t c) {
+                const uint32_t i = c * CHUNK * ROWE + 4 * tid;
+                if (i < cap) { xo = *(const uint4 *)(s_off + i); xe = *(const uint4 *)(s_end + i); xl = *(const uint4 *)(s_life + i); }
+            };
+            auto put = [&](uint32_t c) {                   // (a lane's first and last four entries apart: no two lanes meet in a bank)
+                uint4 *const to = (uint4 *)(s_blocks + c % 2 * 3 * CHUNK * ROWE) + tid / 128 * 128 + tid % 2 * 64 + tid % 128 / 2;
+                to[0] = xo; to[CHUNK * ROWE / 4] = xe; to[2 * CHUNK * ROWE / 4] = xl;
+            };
+            fetch(0);
             const uint32_t life = l < lim ? s_rec[(r + l) % AHEAD].x : NOTHING;
-            const uint32_t lives = (0xFFFFu - (life >> 16)) - (life & 0xFFFFu);
             uint64_t first = 0;
 #pragma unroll
-            for (uint32_t q = 0; q < V; ++q) {
+            for (uint32_t q = 0; q < BATCH / NW; ++q) {
                 if (q * NW >= lim) break;
                 const uint32_t v = q * NW + wave;
                 const uint64_t m = v < lim ? ballot(l < lim && life == read_lane(life, v)) : 0;
-                if (l == v) s_meets[v] = m;
+                if (l == v) { s_meets[v] = m; s_state[v] = make_uint2(0, 0); }
                 first |= m && first_lane(m) == v ? 1ull << v : 0;
             }
-            if (first && l < 2) atomicOr(&s_first[l], (uint32_t)(first >> (32 * l)));
+            if (first && l < 2) atomicOr(&s_open[l], (uint32_t)(first >> (32 * l)));
+            put(0);
             __syncthreads();
-            const uint64_t all = ((uint64_t)uniform(s_first[1]) << 32) | uniform(s_first[0]);
+            uint64_t open = ((uint64_t)uniform(s_open[1]) << 32) | uniform(s_open[0]);
+            for (uint32_t c = 0;; ++c) {
+                const bool more = (c + 1) * CHUNK <= last;
+                if (more) fetch(c + 1);
+                const uint32_t *const buf = s_blocks + c % 2 * 3 * CHUNK * ROWE;
+                uint64_t mine = ballot(((open >> l) & 1) && (uint32_t)__popcll(open & ((1ull << l) - 1)) % NW == wave);
+                for (; mine; mine &= mine - 1) {
+                    const uint32_t v = first_lane(mine), lf = uniform(s_rec[(r + v) % AHEAD].x), bound = bound_of(lf);
+                    const uint64_t has = s_meets[v];
+                    uint64_t left = ((uint64_t)uniform((uint32_t)(has >> 32)) << 32) | uniform((uint32_t)has);
+                    const uint2 state = s_state[v];
+                    uint32_t P = uniform(state.x), least = uniform(state.y);
+                    const uint32_t rows = min(CHUNK, last + 1 - c * CHUNK);
+                    for (uint32_t i = 0; i < rows && left; ++i) {
+                        Entries R;
+                        R.load_halves(buf, CHUNK * ROWE, i);
+                        uint32_t e[E], before[E], free_[E];
+                        const uint32_t incl = batch_ends(R, bound, e);
+                        batch_holes(R, e, incl, P, before, free_);
+                        uint32_t f = free_[0];
 #pragma unroll
-            for (uint32_t q = 0; q < V; ++q) {
-                const uint32_t v = q * NW + wave;
-                if (!((all >> v) & 1)) continue;
-                const uint32_t mine = read_lane(lives, v);
-                const uint32_t rank = (uint32_t)__popcll(ballot(lives > mine || (lives == mine && l < v)) & all);
-                if (l == 0) s_order[rank] = v;
-            }
-            __syncthreads();
-            const uint32_t firsts = (uint32_t)__popcll(all);
-            const uint32_t last = r / ROWE;
-            uint32_t lf[V], P[V], least[V];
-            uint64_t left[V], some = 0;
-#pragma unroll
-            for (uint32_t q = 0; q < V; ++q) {
-                const bool is = q * NW + wave < firsts;
-                const uint32_t v = is ? uniform(s_order[q * NW + wave]) : 0;
-                lf[q] = uniform(s_rec[(r + v) % AHEAD].x);
-                const uint64_t m = s_meets[v];
-                left[q] = is ? ((uint64_t)uniform((uint32_t)(m >> 32)) << 32) | uniform((uint32_t)m) : 0;
-                least[q] = 0;
-                P[q] = 0;
-                some |= left[q];
-            }
-            Entries R;
-            if (some) R.load(s_off, s_end, s_life, 0);
-            for (uint32_t i = 0; i <= last && some; ++i) {
-                Entries N;
-                N.load(s_off, s_end, s_life, min(i + 1, last));
-                some = 0;
-#pragma unroll
-                for (uint32_t q = 0; q < V; ++q) {
-                    if (!left[q]) continue;
-                    uint32_t e[E], before[E], free_[E];
-                    const uint32_t incl = batch_ends(R, bound_of(lf[q]), e);
-                    batch_holes(R, e, incl, P[q], before, free_);
-                    uint32_t f = free_[0];
-#pragma unroll
-                    for (int j = 1; j < E; ++j) f = max(f, free_[j]);
-                    if (ballot(f >= least[q])) {
-                        // those whose size it takes are answered; the smallest size of the others
-                        least[q] = NOTHING;
-                        for (uint64_t m = left[q]; m; m &= m - 1) {
-                            const uint32_t k = first_lane(m), s = uniform(s_rec[(r + k) % AHEAD].y);
-                            const uint64_t any = ballot(f >= s);
-                            if (any) {
-                                uint32_t at, hole;
-                                uint2 next = make_uint2(0, 0);
-                                row_answer(R, e, before, free_, any, s, at, hole, next);
-                                if (l == 0) { s_ask[k] = make_uint4(at, s, lf[q], hole); s_next[k] = next; }
-                                left[q] &= ~(1ull << k);
-                            } else least[q] = min(least[q], s);
+                        for (int j = 1; j < E; ++j) f = max(f, free_[j]);
+                        if (ballot(f >= least)) {
+                            // those whose size it takes are answered; the smallest size of the others
+                            least = NOTHING;
+                            for (uint64_t m = left; m; m &= m - 1) {
+                                const uint32_t k = first_lane(m), s = uniform(s_rec[(r + k) % AHEAD].y);
+                                const uint64_t any = ballot(f >= s);
+                                if (any) {
+                                    uint32_t at, hole;
+                                    uint2 next = make_uint2(0, 0);
+                                    row_answer(R, e, before, free_, any, s, at, hole, next);
+                                    if (l == 0) { s_ask[k] = make_uint4(at, s, lf, hole); s_next[k] = next; }
+                                    left &= ~(1ull << k);
+                                } else least = min(least, s);
+                            }
                         }
+                        P = max(P, read_lane(incl, WAVE - 1));
                     }
-                    P[q] = max(P[q], read_lane(incl, WAVE - 1));
-                    some |= left[q];
+                    if (l == 0) {
+                        s_meets[v] = left;
+                        s_state[v] = make_uint2(P, least);
+                        if (!left) atomicOr(&s_done[c % 2 * 2 + v / 32], 1u << v % 32);
+                    }
                 }
-                R = N;
+                if (!more) break;
+                put(c + 1);
+                __syncthreads();
+                // (the next chunk's go to the other two words, which all have read by now)
+                open &= ~(((uint64_t)uniform(s_done[c % 2 * 2 + 1]) << 32) | uniform(s_done[c % 2 * 2]));
+                if (!open) break;
             }
         } else
         for (uint32_t v = wave, v_after; v < lim; v = uniform(v_after)) {
@@ -385,8 +404,8 @@ __global__ __launch_bounds__(NW *WAVE, 4) void k_place_batch(BatchArgs A)
                 fp = max(fp, e);
             }
             if (l == 0) { s_acc = acc; s_task = NW; }
-            if (l < 4) s_hit[l] = 0;
-            if (l < 2) s_first[l] = 0;
+            if (l < 4) { s_hit[l] = 0; s_done[l] = 0; }
+            if (l < 2) s_open[l] = 0;
         }
         __syncthreads();
         // ---- insert: lane k has the batch's block k.  First how many entries each has below it (or at the same offset):
@@ -480,7 +499,7 @@ __global__ __launch_bounds__(NW *WAVE, 4) void k_place_batch(BatchArgs A)
 template <int NW, int RPW, bool NEAR>
 hipError_t launch_one(const BatchArgs &A, uint32_t B, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_place_batch<NW, RPW, NEAR>), dim3(B), dim3(NW * WAVE), NEAR ? (size_t)A.cap * 12 : 0, st, A);
+    hipLaunchKernelGGL((k_place_batch<NW, RPW, NEAR>), dim3(B), dim3(NW * WAVE), (size_t)(NEAR ? A.cap : 2 * NW * WAVE * 4) * 12, st, A);
     return hipGetLastError();
 }
 
@@ -491,8 +510,11 @@ hipError_t launch_place_batch(uint32_t n, uint32_t B, const uint32_t *perm,
                               uint64_t *ticks, hipStream_t st)
 {
     const BatchArgs A{n, (n / ROWE + 1) * ROWE, (const uint4 *)vrec, perm, hdr, blocks, offs, fps, ticks};
-    if (n > PLAN_BATCH_LDS_VARS) return launch_one<16, 2, false>(A, B, st);
-    // 16 waves where an ordering has a compute unit to itself, 8 where two share one (registers: 20 waves a unit); ms with 8
+    // 16 waves where an ordering has a compute unit to itself, else 8, two orderings to a unit; ms with 16 and with 8, of a
+    // residual chain of 20 000 variables: 300 orderings 23.6 and 22.1, 1024 51.3 and 43.5; 4096 of 50 000 929 and 811 (with four
+    // waves, four to a unit, 842; 512 of 33 000 53 with 8 and 81 with 4).
+    if (n > PLAN_BATCH_LDS_VARS) return B <= 256 ? launch_one<16, 2, false>(A, B, st) : launch_one<8, 2, false>(A, B, st);
+    // In LDS likewise (registers: 20 waves a unit); ms with 8
     // and with 16 waves, of a residual chain of 5000 variables: 256 orderings 2.49 and 2.25, 512 2.49 and 3.59, 1024
     // 4.78 and 6.39; of 6400, whose blocks take more than half of the LDS: 300 orderings 4.81 and 3.95, 1024 10.5 and 8.8.
     // (Four waves, four orderings to a unit: 1024 orderings of 3000 2.68 ms, 2.86 in registers, but random lifetimes and few

@@ -33,12 +33,12 @@ def _lives(tr, alloc, free):
     return tr
 
 
-# rows of 512 blocks, one more and one less; 16 and 8 waves; the last size whose blocks are in LDS and the next one; the last of the
-# registers and the next one
+# rows of 512 blocks, one more and one less; 16 and 8 waves, in LDS and in memory; the last size whose blocks are in LDS and the
+# next one; the last of the registers and the next one
 @pytest.mark.parametrize("n,T,B", [(1025, 70, 6), (1535, 65535, 6), (1536, 300, 6), (1537, 300, 6), (2048, 300, 257), (2049, 300, 513),
                                    (4096, 500, 257), (4097, 500, 769), (6143, 900, 257), (6144, 900, 257), (8192, 900, 6),
                                    (13311, 1500, 5), (13312, 1500, 5), (13313, 65535, 5), (16384, 1500, 5),
-                                   (32768, 3000, 5), (32769, 3000, 5)])
+                                   (32768, 3000, 5), (32769, 3000, 5), (14000, 700, 257)])
 def test_sizes(lap, oracle_mod, n, T, B):
     _check(lap, oracle_mod, random_trace(9000 + n, n, T, size_choices=[1, 1, 2, 3, 5, 8, 13, 64]), B,
            sorted({0, 1, 2, 3, 4, B - 1}))

@@ -31,7 +31,8 @@ def test_every_stamped_summary_matches_the_kernel_sources():
     kernel family the file is named for"""
     bench = _bench()
     families = {"k_place_fast": ("place_fast.hip", "block_rows.h", "lap_dev.h"),
-                "k_place_seg": ("place_seg.hip", "seg_core.h", "lap_dev.h")}
+                "k_place_seg": ("place_seg.hip", "seg_core.h", "lap_dev.h"),
+                "k_place_batch": ("place_batch.hip", "block_rows.h", "lap_dev.h")}
     seen = 0
     for name in sorted(os.listdir(os.path.join(ROOT, "profiles"))):
         tv = bench.read_profile_values(os.path.join(ROOT, "profiles", name))
