@@ -478,9 +478,9 @@ int lap_plan_pool(const lap_trace *tr, const lap_ordering *ords, uint32_t B, uin
     const uint64_t seg_min_vars = g_seg_min_vars;
     const bool may_seg = n >= seg_min_vars;         // below, the header rules the segment lists out: no launches for them
     // from a number of variables that was set, the segment lists are used wherever they apply
-    const uint32_t batches = !lap::batch_places(n, T, B, any_best) ? 0u : seg_min_vars == SEG_MIN_VARS_DEFAULT ? 2u : 1u;
+    const bool batches = lap::batch_places(n, T, B, any_best), batches_first = batches && seg_min_vars == SEG_MIN_VARS_DEFAULT;
     LAP_HIP(lap::launch_plan_prep(n, T, B, tr->size, tr->alloc, tr->free_, cntd, lstart, hdr, vrec,
-                                  seg_pool_entries(n, B), seg_min_vars, batches, st));
+                                  seg_pool_entries(n, B), seg_min_vars, batches_first, st));
     if (may_seg)
         LAP_HIP(lap::launch_seg_prep(n, T, B, tr->alloc, tr->free_, hdr, seg_cnt, seg_lst, (uint32_t)dir_cap,
                                      seg_pool_entries(n, B), st));
@@ -489,9 +489,13 @@ int lap_plan_pool(const lap_trace *tr, const lap_ordering *ords, uint32_t B, uin
         for (uint32_t b = 0; b < B && trial_b < 0; ++b)
             if (ords[b].fit == LAP_FIT_FIRST) trial_b = (int)b;
         ProfScope p(LAP_K_PLACE, st);
-        if (may_seg)
+        if (may_seg) {
             LAP_HIP(lap::launch_seg_trial(n, T, B, perm, fits, trial_b, (uint32_t)g_seg_trial_percent, hdr, vrec, seg_lst,
                                           seg_pool, seg_len, (uint32_t)dir_cap, offs, fps, ticks, st));
+            // (before the batches, which leave their mark in the header where they place in the lists' stead)
+            LAP_HIP(lap::launch_place_seg(n, T, B, perm, fits, any_first, hdr, vrec, seg_lst, seg_pool, seg_len,
+                                          (uint32_t)dir_cap, offs, fps, ticks, st));
+        }
         if (batches)
             LAP_HIP(lap::launch_place_batch(n, B, perm, hdr, vrec, (uint32_t *)f_oe, offs, fps, ticks, st));
         else
@@ -501,9 +505,6 @@ int lap_plan_pool(const lap_trace *tr, const lap_ordering *ords, uint32_t B, uin
                                        f_life2, f_roe, f_rlife, f_roe2, f_rlife2, f_L, capL, l_ns, l_nu, offs, fps, ticks, st));
         LAP_HIP(lap::launch_place_wide(n, B, tr->size, tr->alloc, tr->free_, perm, fits, hdr, m_off, m_end, m_life, offs,
                                        fps, ticks, st));
-        if (may_seg)
-            LAP_HIP(lap::launch_place_seg(n, T, B, perm, fits, any_first, hdr, vrec, seg_lst, seg_pool, seg_len,
-                                          (uint32_t)dir_cap, offs, fps, ticks, st));
     }
     LAP_HIP(lap::launch_select(n, B, fps, offs, perm, best_footprint, best_ordering, best_offsets, all_offsets, st));
     return LAP_OK;

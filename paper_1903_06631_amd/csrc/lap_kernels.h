@@ -22,7 +22,7 @@ struct PlanHeader {
     uint32_t part[2];              // placement workgroups that have started, per fit policy
     uint32_t progress[2];          // their progress, in units of 512 ranks, summed
     // segment lists (place_seg.hip), used when per-step lists are not and the pool has room
-    uint32_t mode2;                // 1: the segment kernel places this trace
+    uint32_t mode2;                // 1: the segment kernel places this trace; 2: the batches have, though it has too many variables for registers
     uint32_t seg_shift;            // log2 of the segment width in steps
     uint32_t seg_K;                // number of segments
     uint32_t seg_slots;            // orderings that have room in the list pool at once
@@ -31,15 +31,14 @@ struct PlanHeader {
     uint32_t seg_trial_rounds;     // trial run: search rounds of its multi-step variables, summed
     uint32_t seg_trial_vars;       // ... and how many those were
     uint32_t seg_next;             // next ordering to hand to a workgroup of the segment kernel
-    uint32_t batches;              // not 0: what would be placed in registers, or swept, is placed in batches (place_batch.hip); 2: these may go
-                                   // before the segment lists
+    uint32_t seg_pad;
 };
 constexpr uint32_t PLAN_CL = 6;
 
-// Placed blocks in registers (place_reg.hip; 128 rows of 256 entries), or in batches (place_batch.hip): whether they may be used
-// (16-bit steps) ...
-constexpr uint32_t PLAN_REG_MAX_VARS = 128 * 256, PLAN_BATCH_MAX_VARS = 1 << 17;
-inline bool reg_may_place(uint32_t n, uint32_t T) { return n <= PLAN_BATCH_MAX_VARS && T <= 0xFFFFu; }
+// Placed blocks in registers (place_reg.hip): whether they may be used: 128 rows of 256 entries, 16-bit
+// steps ...
+constexpr uint32_t PLAN_REG_MAX_VARS = 128 * 256;
+inline bool reg_may_place(uint32_t n, uint32_t T) { return n <= PLAN_REG_MAX_VARS && T <= 0xFFFFu; }
 // ... and whether they are, as far as the trace decides it: where per-step lists are not in use.  Up to 128 variables,
 // and up to 768 where the second rule says so (the preparation asks it), these are not used although lifetimes are short
 // enough for them.  A one-step variable costs the lists next to nothing and a multi-step one 3 to 5 us, while every
@@ -54,7 +53,6 @@ constexpr uint32_t PLAN_REG_ALWAYS_VARS = 128, PLAN_REG_FEW_VARS = 3 * 256;
 __device__ __forceinline__ bool reg_places(const PlanHeader *hdr, uint32_t n, bool best_fit)
 {
     if (!hdr->fast || (hdr->mode2 && !best_fit)) return false;
-    if (n > PLAN_REG_MAX_VARS && !hdr->batches) return false;
     return !hdr->mode1 || n <= PLAN_REG_ALWAYS_VARS;
 }
 __device__ __forceinline__ bool reg_before_lists(uint32_t n, uint32_t T, uint32_t n_multi, uint32_t B)
@@ -78,10 +76,11 @@ __device__ __forceinline__ bool reg_before_lists(uint32_t n, uint32_t T, uint32_
 // and 8.6, of 20 000 38.2 and 14.4, of 32 767 98 and 32; 1024 of 20 000 152 and 43; random lifetimes and six sizes: 100 of 15 000
 // 23.4 and 19.7, 200 of 25 000 62.9 and 42.5.  More than 32 768 take the place of the sweep
 // (40 000, random: 3.2 s by the sweep, 0.08 in batches).
+constexpr uint32_t PLAN_BATCH_MAX_VARS = 1 << 17;
 constexpr uint32_t PLAN_BATCH_LDS_VARS = 52 * 256 - 1;      // rows of 512 entries of 12 bytes in 160 KB, less 4 KB
 inline bool batch_places(uint32_t n, uint32_t T, uint32_t B, bool any_best)
 {
-    return !any_best && reg_may_place(n, T) && (n > 4096 || (n > 2048 && B <= 768) || (n > 1024 && B <= 512));
+    return !any_best && n <= PLAN_BATCH_MAX_VARS && T <= 0xFFFFu && (n > 4096 || (n > 2048 && B <= 768) || (n > 1024 && B <= 512));
 }
 
 // Whether they go before the segment lists.  All placed blocks are gone through for every batch, one ordering of 16 waves or two of
@@ -122,7 +121,7 @@ hipError_t launch_sort_perm(uint32_t n, uint32_t B, const uint64_t *size, const 
                             bool any_explicit, hipStream_t st);
 hipError_t launch_plan_prep(uint32_t n, uint32_t T, uint32_t B, const uint64_t *size, const uint32_t *alloc,
                             const uint32_t *free_, uint32_t *cntd, uint32_t *lstart, PlanHeader *hdr, void *vrec,
-                            uint64_t seg_pool_entries, uint64_t seg_min_vars, uint32_t batches, hipStream_t st);
+                            uint64_t seg_pool_entries, uint64_t seg_min_vars, bool batches_first, hipStream_t st);
 hipError_t launch_seg_prep(uint32_t n, uint32_t T, uint32_t B, const uint32_t *alloc, const uint32_t *free_,
                            PlanHeader *hdr, uint32_t *cnt, uint32_t *lst, uint32_t dir_cap, uint64_t pool_entries,
                            hipStream_t st);
@@ -140,7 +139,7 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
                             const PlanHeader *hdr, const void *vrec, uint64_t *offs, uint64_t *fps, uint64_t *ticks,
                             hipStream_t st);
 // blocks [B][4 n]: scratch
-hipError_t launch_place_batch(uint32_t n, uint32_t B, const uint32_t *perm, const PlanHeader *hdr, const void *vrec,
+hipError_t launch_place_batch(uint32_t n, uint32_t B, const uint32_t *perm, PlanHeader *hdr, const void *vrec,
                               uint32_t *blocks, uint64_t *offs, uint64_t *fps, uint64_t *ticks, hipStream_t st);
 hipError_t launch_place_fast(uint32_t n, uint32_t T, uint32_t B, const uint64_t *size, const uint32_t *alloc,
                              const uint32_t *free_, const uint32_t *perm, const uint32_t *fits, bool any_first,

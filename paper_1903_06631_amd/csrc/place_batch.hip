@@ -50,7 +50,7 @@ struct BatchArgs {
     uint32_t n, cap;             // cap: entries of the three arrays
     const uint4 *vrec;           // [n] (first step, end of life, size in granules, -)
     const uint32_t *perm;        // [B][n]
-    const PlanHeader *hdr;
+    PlanHeader *hdr;
     uint32_t *blocks;            // [B][4 n] the three arrays where they do not fit the LDS
     uint64_t *offs;              // [B][n] in rank order
     uint64_t *fps;               // [B]
@@ -163,7 +163,9 @@ __global__ __launch_bounds__(NW *WAVE, 4) void k_place_batch(BatchArgs A)
     uint2 *const s_pos = s_next;                           // where a new block goes: entries below it, and its index
 
     const uint32_t b = blockIdx.x;
-    if (!reg_places(A.hdr, A.n, false)) return;
+    if (!A.hdr->fast || A.hdr->mode1 || A.hdr->mode2 == 1) return;
+    // the sweep, which comes after this and leaves only traces of fewer variables to others by itself, has to know
+    if (A.n > PLAN_REG_MAX_VARS && b == 0 && threadIdx.x == 0) A.hdr->mode2 = 2;
     const long long t_begin = wall_clock64();
     const uint32_t n = A.n, sh = A.hdr->shift, cap = A.cap;
     uint32_t *s_off;
@@ -506,7 +508,7 @@ hipError_t launch_one(const BatchArgs &A, uint32_t B, hipStream_t st)
 }  // namespace
 
 hipError_t launch_place_batch(uint32_t n, uint32_t B, const uint32_t *perm,
-                              const PlanHeader *hdr, const void *vrec, uint32_t *blocks, uint64_t *offs, uint64_t *fps,
+                              PlanHeader *hdr, const void *vrec, uint32_t *blocks, uint64_t *offs, uint64_t *fps,
                               uint64_t *ticks, hipStream_t st)
 {
     const BatchArgs A{n, (n / ROWE + 1) * ROWE, (const uint4 *)vrec, perm, hdr, blocks, offs, fps, ticks};

@@ -108,7 +108,7 @@ __device__ __forceinline__ uint64_t prep_block_scan(uint64_t v, uint64_t *wtmp, 
 // live[t] = number of variables live at step t; lstart = exclusive prefix sum of live + 1; one workgroup
 __device__ __forceinline__ void prep_lists(uint32_t n, uint32_t T, uint32_t B, const uint32_t *cntd,
                                            uint32_t *__restrict__ lstart, PlanHeader *hdr, uint64_t *wtmp,
-                                           uint64_t seg_pool_entries, uint64_t seg_min_vars, uint32_t batches)
+                                           uint64_t seg_pool_entries, uint64_t seg_min_vars, bool batches_first)
 {
     const uint32_t tid = threadIdx.x;
     uint64_t c1 = 0, c2 = 0, tot;
@@ -133,7 +133,6 @@ __device__ __forceinline__ void prep_lists(uint32_t n, uint32_t T, uint32_t B, c
         hdr->shift = shift;
         hdr->fast = fast ? 1u : 0u;
         hdr->mode1 = lists && !reg_before_lists(n, T, hdr->n_multi, B) ? 1u : 0u;
-        hdr->batches = batches;
         if (n < seg_min_vars) return;            // no segment lists, and none of their figures (the header is zero)
         // Segment lists: the width that enters the fewest blocks into lists; every list has one
         // entry more than the blocks it sees.  Taken when per-step lists are not, the trace has
@@ -161,7 +160,7 @@ __device__ __forceinline__ void prep_lists(uint32_t n, uint32_t T, uint32_t B, c
         const uint64_t slots = best_need ? seg_pool_entries / best_need : 0;
         const bool seg = fast && !lists && (sum >> shift) < 0xFFFFFFFEull &&
                          best_need < 0xFFFFFFFFull && T < 0x7FFF0000u && slots >= 1 &&
-                         !(batches == 2 && batches_before_segments(n, B, best_need));
+                         !(batches_first && batches_before_segments(n, B, best_need));
         hdr->mode2 = seg ? 1u : 0u;
         hdr->seg_shift = ssh;
         hdr->seg_K = (uint32_t)K;
@@ -174,10 +173,10 @@ __global__ __launch_bounds__(PREP_THREADS) void k_plan_prep2(uint32_t n, uint32_
                                                              const uint32_t *__restrict__ cntd,
                                                              uint32_t *__restrict__ lstart, PlanHeader *hdr,
                                                              uint64_t seg_pool_entries, uint64_t seg_min_vars,
-                                                             uint32_t batches)
+                                                             bool batches_first)
 {
     __shared__ uint64_t wtmp[PREP_THREADS / WAVE];
-    prep_lists(n, T, B, cntd, lstart, hdr, wtmp, seg_pool_entries, seg_min_vars, batches);
+    prep_lists(n, T, B, cntd, lstart, hdr, wtmp, seg_pool_entries, seg_min_vars, batches_first);
 }
 
 // What the placement kernel reads of a variable, in one 16-byte record (one gather per rank
@@ -204,7 +203,7 @@ __global__ __launch_bounds__(PREP_THREADS) void k_plan_prep_small(uint32_t n, ui
                                                                   const uint32_t *__restrict__ free_,
                                                                   uint32_t *__restrict__ lstart, PlanHeader *hdr,
                                                                   uint4 *__restrict__ vrec, uint64_t seg_pool_entries,
-                                                                  uint64_t seg_min_vars, uint32_t batches)
+                                                                  uint64_t seg_min_vars, bool batches_first)
 {
     __shared__ PlanHeader h;
     __shared__ uint32_t cntd[PREP_SMALL_STEPS + 1];
@@ -215,7 +214,7 @@ __global__ __launch_bounds__(PREP_THREADS) void k_plan_prep_small(uint32_t n, ui
     __syncthreads();
     prep_sums(tid, PREP_THREADS, n, T, size, alloc, free_, cntd, &h, n >= seg_min_vars);
     __syncthreads();
-    prep_lists(n, T, B, cntd, lstart, &h, wtmp, seg_pool_entries, seg_min_vars, batches);
+    prep_lists(n, T, B, cntd, lstart, &h, wtmp, seg_pool_entries, seg_min_vars, batches_first);
     __syncthreads();
     if (tid < HDR_WORDS) ((uint64_t *)hdr)[tid] = ((const uint64_t *)&h)[tid];
     if (!h.fast) return;
@@ -227,11 +226,11 @@ __global__ __launch_bounds__(PREP_THREADS) void k_plan_prep_small(uint32_t n, ui
 
 hipError_t launch_plan_prep(uint32_t n, uint32_t T, uint32_t B, const uint64_t *size, const uint32_t *alloc,
                             const uint32_t *free_, uint32_t *cntd, uint32_t *lstart, PlanHeader *hdr, void *vrec,
-                            uint64_t seg_pool_entries, uint64_t seg_min_vars, uint32_t batches, hipStream_t st)
+                            uint64_t seg_pool_entries, uint64_t seg_min_vars, bool batches_first, hipStream_t st)
 {
     if (n <= PREP_SMALL_VARS && T <= PREP_SMALL_STEPS) {
         hipLaunchKernelGGL(k_plan_prep_small, dim3(1), dim3(PREP_THREADS), 0, st, n, T, B, size, alloc, free_, lstart, hdr,
-                           (uint4 *)vrec, seg_pool_entries, seg_min_vars, batches);
+                           (uint4 *)vrec, seg_pool_entries, seg_min_vars, batches_first);
         return hipGetLastError();
     }
     // the header and the counters lie one after the other: one fill clears both
@@ -241,7 +240,7 @@ hipError_t launch_plan_prep(uint32_t n, uint32_t T, uint32_t B, const uint64_t *
     blocks = blocks > 1024 ? 1024 : blocks;
     hipLaunchKernelGGL(k_plan_prep1, dim3(blocks > 128 ? 128 : blocks), dim3(256), 0, st, n, T, size, alloc, free_, cntd, hdr, n >= seg_min_vars);
     hipLaunchKernelGGL(k_plan_prep2, dim3(1), dim3(PREP_THREADS), 0, st, n, T, B, cntd, lstart, hdr, seg_pool_entries,
-                       seg_min_vars, batches);
+                       seg_min_vars, batches_first);
     hipLaunchKernelGGL(k_plan_pack, dim3(blocks), dim3(256), 0, st, n, size, alloc, free_, hdr, (uint4 *)vrec);
     return hipGetLastError();
 }
