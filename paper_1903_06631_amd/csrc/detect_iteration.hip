@@ -355,10 +355,15 @@ __global__ __launch_bounds__(DI_THREADS) void k_detect_compare(const uint64_t *_
     }
 }
 
+// A barrier of the workgroup does not wait for its waves' stores and atomics to global memory.  Where one thread then tells other
+// workgroups that all of them have been made, every wave waits for its own before the barrier.
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Adds the tiles that this wave has finished, and waits until all are.  The workgroup's stores reach memory once, with the
 // counter: a write-back by every wave took three times as long as all of the hashes.
 __device__ __forceinline__ void wait_tiles(uint32_t *ready, uint32_t mine, uint32_t n_tiles, uint32_t *s_sum)
 {
+    wait_stores();
     if (threadIdx.x == 0) *s_sum = 0;
     __syncthreads();
     if (lane_id() == 0 && mine) atomicAdd(s_sum, mine);
@@ -444,6 +449,7 @@ __global__ __launch_bounds__(DI_THREADS) void k_detect_hash(const uint64_t *__re
         const uint64_t p = p0 + tid;
         if (p <= most && halves_hash_alike(Q, M, (uint32_t)p, pow_base((uint32_t)p))) atomicMin(&S->candidate, (uint32_t)p);
     }
+    wait_stores();
     __syncthreads();
     if (tid == 0) {
         __threadfence();

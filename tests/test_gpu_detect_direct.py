@@ -59,3 +59,34 @@ def test_scratch_of_an_earlier_call_does_not_matter(lap, oracle_mod):
     for s, mp in [(run, m // 4 + 1), (plain, 64), (run, m // 4 + 1), (run, 3), (plain, 64), (plain, m // 3 + 1)]:
         t = torch.from_numpy(s.view(np.int64)).cuda()
         assert int(lap.detect_iteration(t, mp).item()) == oracle_mod.detect_iteration(s, mp)
+
+
+def _marked(rng, m, period, at, again):
+    """a list of a short period but for one token `at` places from the end, and another one like it `again` places before that:
+    every multiple of the period above at / 2 differs in that one token, `again` excepted"""
+    s = np.tile(rng.integers(0, 300, period), m // period + 1)[:m].astype(np.uint64)
+    s[m - at] += 1000
+    if again:
+        s[m - at - again] += 1000
+    return s
+
+
+# more distances remain than are compared directly, so that it comes to the hashes: in the one workgroup, with tiles of 1024 tokens
+# and the first larger ones (beyond 1024 * 1024 tokens), with as many workgroups as there are compute units, and where the list
+# starts between two 16-byte words.  The answers are known by construction: the oracle compares every multiple.
+@pytest.mark.parametrize("m", [6000, 6145, 70001, 1 << 20, (1 << 20) + 1, 2000003])
+@pytest.mark.parametrize("cut", [0, 1])
+def test_lists_that_come_to_the_hashes(lap, oracle_mod, m, cut):
+    import torch
+    rng = np.random.default_rng(m)
+    period, at = 7, m // 8 if m > 9000 else 1100 if m > 6144 else 100
+    again = m // 3 // period * period
+    for second, want in ((0, 0), (again, again)):
+        s = _marked(rng, m, period, at, second)
+        if m < 9000:
+            assert oracle_mod.detect_iteration(s, at // 2 + 1) == want
+        t = torch.empty(m + cut, dtype=torch.int64, device="cuda")[cut:]
+        t.copy_(torch.from_numpy(s.view(np.int64)))
+        assert t.data_ptr() % 16 == 8 * cut
+        for _ in range(3):
+            assert int(lap.detect_iteration(t, at // 2 + 1).item()) == want
