@@ -1,22 +1,30 @@
 // Iteration detection on a recorded request stream (Section V): the list ends with two equal
 // consecutive subsequences of length p; the smallest such p (>= min_period) is reported.
 //
-// First the direct way.  The last DI_SUFFIX tokens are looked for at every distance p (nearly every one is refused by its first
-// token, so half of the list is read once).  A workgroup goes on with the smallest distances that remain of its own: a wave
-// compares up to DI_DEEP more tokens of each, which refuses most of what a repeated piece inside an iteration leaves, and settles
-// short repeats.  The DI_FEW smallest that are still open and below the smallest that is settled are then compared element by element by all
-// workgroups, the last of which has the answer -- unless all of them differ and there are more.  Only then it
-// comes to hashes, whose cost does not depend on what is in the list: a polynomial hash of every prefix (mod 2^64, odd
-// base) is built with a scan; the two halves of a candidate p then compare in O(1):
+// First the direct way.  Every distance p is looked at: whether the last p tokens end and start as the p before them (nearly every
+// one is refused by its last token, so half of the list is read once).  A workgroup goes on with the smallest distances that
+// remain of its own: a wave compares up to DI_DEEP tokens of each, which refuses most of what a repeated piece inside an
+// iteration leaves, and settles short repeats.  The DI_FEW smallest that are still open and below the smallest that is settled are then
+// compared element by element by all workgroups, the last of which has the answer -- unless all of them differ and there are
+// more.  Then the places where they differ refuse most of the others, and up to DI_LEFT that remain are compared in the
+// same way.  Only where more do it comes to hashes, whose cost does not depend on what is in the list: a polynomial hash of every
+// prefix (mod 2^64, odd base) is built with a scan; the two halves of a candidate p then compare in O(1):
 //     (P[M-p] - P[M-2p]) * r^p == P[M] - P[M-p]
 // and the smallest candidate whose hashes agree is checked element by element (hashes mod 2^64 can
 // collide, the answer never depends on them); if the check fails the search resumes behind it.
 //
-// Short lists (up to DI_ONE requests) are one workgroup's work in one launch.  Longer ones take three, the last of which nearly
-// always finds nothing to do.  An iteration in 2 000 003 requests: 16 us, of which the first launch takes 6 and the second 9; by
-// hashes it took 38.  One in 4000: 9.5 and 14.7 us.  700 000 requests that end in a short period: 24 us, 64 and more by hashes.  What
-// it comes to hashes for -- a run of a short period that is shorter than twice the smallest iteration asked for, of thousands of
-// requests -- takes 51 us for 40 000 of them and 154 for 2 000 003 (20 and 32 by hashes at once).
+// Short lists (up to DI_ONE requests) are one workgroup's work in one launch, which refuses distances by places until none is left.
+// Longer ones take three, the last of which nearly always finds nothing to do.  us of calls that follow each other, by
+// hashes at once, and now:
+//     an iteration in 4000 requests                       14.7   9.5   in 40 000   22.3  15.3   in 2 000 003   38.7  16.3
+//     iterations that end in a run, or in equal layers    21.5  10.8               22.7  15.5                  38.6  19.5
+//     a run of a short period, too short to be asked for  19.0   9.3               20.9  15.3                  33.7  17.7
+//     one of it that is asked for                         20.5  14.8               54.5  18.3                 125    27.7
+//     a list of a short period with single other tokens   20.5  25                 22    50                    36   114
+//     a Fibonacci word, where it comes to hashes          18.9  12.9               20.8  70                    32   240
+// (6144 requests in the left column from the second line on).  The last two are slower than by hashes at once: many distances are
+// looked at in vain, and a hand-over between workgroups writes the caches back.  An iteration in a list of 2 000 003 that
+// no cache holds yet: 51 and 33.
 #include "lap_dev.h"
 #include "lap_kernels.h"
 
@@ -27,8 +35,8 @@ constexpr int DI_WAVES = DI_THREADS / WAVE;
 constexpr uint64_t DI_BASE = 0x9E3779B97F4A7C15ull | 1ull;
 constexpr uint32_t DI_NONE = 0xFFFFFFFFu;
 constexpr uint32_t DI_CHUNK = 4 * WAVE;        // tokens a wave takes per step: 4 neighbours per lane
-constexpr uint32_t DI_SUFFIX = 32, DI_DEEP = 1024;       // tokens that a distance has to agree in, and more
-constexpr uint32_t DI_FEW = 4;                 // distances that are compared by all workgroups, at most
+constexpr uint32_t DI_DEEP = 1024;             // tokens that a distance has to agree in to be compared by all
+constexpr uint32_t DI_FEW = 4, DI_LEFT = 8;    // distances that are compared by all workgroups, at most: first, and of those left
 constexpr uint32_t DI_SPAN = 8;                // distances per thread
 constexpr uint32_t DI_ONE = 6144;             // requests that one workgroup looks at
 constexpr uint32_t DI_TILES = 1024, DI_LISTS = 512;      // at most
@@ -94,15 +102,17 @@ __device__ uint32_t search_from(const uint64_t *tok, const uint64_t *Q, uint32_t
     return 0;
 }
 
-// whether the last tokens, DI_SUFFIX of them or p, are also found at distance p (2 p <= M)
-__device__ __forceinline__ bool suffix_repeats(const uint64_t *__restrict__ tok, uint32_t M, uint32_t p)
+// The first look at distance p (2 p <= M): whether the p tokens before the last p end and start as these do.  The end is read by
+// neighbouring lanes anyway.  The start refuses what a run of a short period at the end of the list leaves: a distance
+// that is shorter than the run and longer than half of it reaches out of the run there.
+__device__ __forceinline__ bool ends_alike(const uint64_t *__restrict__ tok, uint32_t M, uint32_t p)
 {
-    const uint32_t most = min(p, DI_SUFFIX);
-    for (uint32_t j = 1; j <= most; j += 8) {            // eight at a time: a wave waits for each round
+#pragma unroll
+    for (uint32_t half = 0; half < 2; ++half) {          // eight at a time: a wave waits for each round
         uint64_t differ = 0;
 #pragma unroll
         for (uint32_t k = 0; k < 8; ++k) {
-            const uint32_t e = M - min(j + k, most);
+            const uint32_t e = half ? M - p + min(k, p - 1) : M - min(k + 1, p);
             differ |= tok[e] ^ tok[e - p];
         }
         if (differ) return false;
@@ -110,86 +120,84 @@ __device__ __forceinline__ bool suffix_repeats(const uint64_t *__restrict__ tok,
     return true;
 }
 
-// What a wave finds out about distance p, whose last DI_SUFFIX tokens agree, from `deep` more
+// What a wave finds out about distance p from its last `deep` tokens; at: one that differs from the one p before it
 enum { DI_DIFFERS, DI_OPEN, DI_SAME };
-__device__ __forceinline__ uint32_t look_deep(const uint64_t *__restrict__ tok, uint32_t M, uint32_t p, uint32_t deep)
+__device__ __forceinline__ uint32_t look_deep(const uint64_t *__restrict__ tok, uint32_t M, uint32_t p, uint32_t deep, uint32_t &at)
 {
     constexpr uint32_t STEP = 4 * WAVE;
-    const uint32_t most = min(p, DI_SUFFIX + deep);
-    for (uint32_t j = DI_SUFFIX + 1 + (uint32_t)lane_id(); ballot(j <= most); j += STEP) {
-        uint64_t differ = 0;
+    const uint32_t most = min(p, deep);
+    for (uint32_t j = 1 + (uint32_t)lane_id(); ballot(j <= most); j += STEP) {
+        uint32_t mine = 0;
 #pragma unroll
         for (uint32_t k = 0; k < 4; ++k) {
             const uint32_t e = M - min(j + k * WAVE, most);
-            differ |= tok[e] ^ tok[e - p];
+            mine = tok[e] != tok[e - p] ? e : mine;
         }
-        if (ballot(differ != 0)) return DI_DIFFERS;
+        const uint64_t differ = ballot(mine != 0);
+        if (differ) { at = read_lane(mine, __builtin_ctzll(differ)); return DI_DIFFERS; }
     }
     return most == p ? DI_SAME : DI_OPEN;
 }
 
-// the smallest of the listed distances that are not marked as different, 0 if there is none
-__device__ __forceinline__ uint32_t smallest_same(const uint32_t *list, uint32_t found, uint32_t differ)
+// Where one distance differs others mostly do: those of a run differ in what comes before it, nearly equal pieces in what is not
+// equal.  Whether the token x at place w is also found at distance p, before or behind it, if it is among the last 2 p.
+__device__ __forceinline__ bool place_repeats(const uint64_t *__restrict__ tok, uint32_t M, uint32_t p, uint32_t w, uint64_t x)
 {
-    uint32_t best = DI_NONE;
-    for (uint32_t q = 0; q < found; ++q)
-        if (!((differ >> q) & 1)) best = min(best, list[q]);
-    return best == DI_NONE ? 0 : best;
+    const uint32_t back = M - w;                         // (2 p <= M)
+    return tok[back > 2 * p ? w : back > p ? w + p : w - p] == x;
 }
 
 __global__ __launch_bounds__(DI_THREADS) void k_detect_short(const uint64_t *__restrict__ tok, uint32_t M,
-                                                             uint32_t min_period, uint64_t *Q,
-                                                             uint32_t *__restrict__ period)
+                                                             uint32_t min_period, uint32_t *__restrict__ period)
 {
-    __shared__ uint64_t wsum[DI_WAVES];
-    constexpr uint32_t DEEP = 4 * DI_WAVES;              // distances that waves compare, at most
-    __shared__ uint32_t s_bits[2 * WAVE], s_list[DEEP], s_found, s_same;
+    __shared__ uint32_t s_bits[2 * WAVE], s_list[DI_WAVES], s_at[DI_WAVES], s_found, s_same;
     static_assert(DI_ONE / 2 < 2 * WAVE * 32, "a bit per distance");
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
     if (tid < 2 * WAVE) s_bits[tid] = 0;
     if (tid == 0) s_same = DI_NONE;
     __syncthreads();
+    const uint64_t last = tok[M - 1];
     for (uint32_t p = min_period + tid; p >= min_period && p <= M / 2; p += DI_THREADS)
-        if (suffix_repeats(tok, M, p)) atomicOr(&s_bits[p / 32], 1u << (p % 32));
-    __syncthreads();
-    if (wave == 0) {                                       // the smallest of them, in ascending order
-        uint64_t bits = (uint64_t)s_bits[2 * lane + 1] << 32 | s_bits[2 * lane];
-        const uint32_t own = (uint32_t)__popcll(bits);
-        uint32_t at = own;
-        for (int d = 1; d < WAVE; d <<= 1) { const uint32_t y = (uint32_t)__shfl_up((int)at, d, WAVE); if ((int)lane >= d) at += y; }
-        if (lane == WAVE - 1) s_found = at;
-        for (at -= own; bits && at < DEEP; bits &= bits - 1, ++at) s_list[at] = lane * 64 + (uint32_t)__ffsll((unsigned long long)bits) - 1;
-    }
-    __syncthreads();
-    const uint32_t found = s_found;
-    uint32_t same = DI_NONE;
-    for (uint32_t base = 0; base < min(found, DEEP) && same == DI_NONE; base += DI_WAVES) {
-        const uint32_t q = base + wave;
-        if (q < min(found, DEEP) && look_deep(tok, M, s_list[q], M) == DI_SAME && lane == 0) atomicMin(&s_same, s_list[q]);
+        if (tok[M - 1 - p] == last && ends_alike(tok, M, p)) atomicOr(&s_bits[p / 32], 1u << (p % 32));
+    for (;;) {                                             // each turn leaves out the distances that it has looked at
         __syncthreads();
-        same = s_same;
+        if (wave == 0) {                                   // the smallest of them, in ascending order
+            uint64_t bits = (uint64_t)s_bits[2 * lane + 1] << 32 | s_bits[2 * lane];
+            const uint32_t own = (uint32_t)__popcll(bits);
+            uint32_t at = own;
+            for (int d = 1; d < WAVE; d <<= 1) { const uint32_t y = (uint32_t)__shfl_up((int)at, d, WAVE); if ((int)lane >= d) at += y; }
+            if (lane == WAVE - 1) s_found = at;
+            for (at -= own; bits && at < DI_WAVES; bits &= bits - 1, ++at) s_list[at] = lane * 64 + (uint32_t)__ffsll((unsigned long long)bits) - 1;
+        }
         __syncthreads();
-    }
-    if (same != DI_NONE || found <= DEEP) {
-        if (tid == 0) *period = same != DI_NONE ? same : 0;
-        return;
-    }
-    uint64_t carry = 0;
-    for (uint32_t base = 0; base < M; base += DI_THREADS) {
-        const uint32_t j = base + tid;
-        const uint64_t v = j < M ? tok_hash(tok[j]) * pow_base(j) : 0;
-        const uint64_t incl = wave_scan_add(v);
-        if (lane == WAVE - 1) wsum[wave] = incl;
+        const uint32_t found = s_found, look = min(found, (uint32_t)DI_WAVES);
+        if (wave < look) {
+            uint32_t at = 0;
+            const uint32_t p = s_list[wave], what = look_deep(tok, M, p, M, at);
+            if (lane == 0) {
+                s_at[wave] = at;
+                if (what == DI_SAME) atomicMin(&s_same, p);
+                else atomicAnd(&s_bits[p / 32], ~(1u << (p % 32)));
+            }
+        }
         __syncthreads();
-        uint64_t pre = 0, tot = 0;
-        for (int q = 0; q < DI_WAVES; ++q) { const uint64_t x = wsum[q]; if (q < (int)wave) pre += x; tot += x; }
-        __syncthreads();
-        if (j < M) Q[j] = carry + pre + incl;
-        carry += tot;
+        if (s_same != DI_NONE || found <= look) {
+            if (tid == 0) *period = s_same != DI_NONE ? s_same : 0;
+            return;
+        }
+        // the others where those differed (all of them did)
+#pragma unroll 1
+        for (uint32_t p = min_period + tid; p >= min_period && p <= M / 2; p += DI_THREADS) {
+            bool stays = (s_bits[p / 32] >> (p % 32)) & 1;
+            if (!stays) continue;
+#pragma unroll 1
+            for (uint32_t q = 0; q < DI_WAVES && stays; ++q) {
+                const uint32_t w = s_at[q], v = w - s_list[q];
+                stays = place_repeats(tok, M, p, w, tok[w]) && place_repeats(tok, M, p, v, tok[v]);
+            }
+            if (!stays) atomicAnd(&s_bits[p / 32], ~(1u << (p % 32)));
+        }
     }
-    __syncthreads();
-    const uint32_t p = search_from(tok, Q, M, min_period);
-    if (tid == 0) *period = p;
 }
 
 // the 4 neighbouring tokens of a lane (hash 0 beyond the list); vec: the list is 16-byte aligned
@@ -216,8 +224,11 @@ struct DiScratch {
     uint64_t totals[DI_TILES];
     uint32_t counts[DI_LISTS], lists[DI_LISTS * DI_FEW];      // of a workgroup: its open distances, and the smallest of them
     uint32_t settled[DI_LISTS];                // the smallest of its distances that is known to be a repeat
-    uint32_t done, differ, hashes;             // workgroups that have compared, which distances differ, whether it comes to hashes
-    uint32_t next[2], ready[2];                // tiles given out and finished: totals, hashes
+    uint32_t done, more, top;                  // workgroups that have compared; whether that was not all, up to which distance
+    uint32_t at[DI_FEW];                       // 1 + the last of the distance's tokens that differs from the one before, 0: none
+    uint32_t places[2 * DI_FEW];               // where those are in the list, and the ones that they differ from
+    uint32_t n_left, left[DI_LEFT], differs[DI_LEFT], checked;           // distances that are left, and which of them differ; workgroups that have compared
+    uint32_t next[3], ready[3];                // tiles given out and finished: distances, totals, hashes
     uint32_t candidate, searched;              // the smallest distance whose hashes agree; workgroups that have searched
 };
 static_assert(sizeof(DiScratch) <= DI_MAX_TILES * 8, "");
@@ -229,7 +240,10 @@ __global__ __launch_bounds__(256) void k_detect_suffix(const uint64_t *__restric
     __shared__ uint32_t s_bits[SPAN / 32], s_list[DEEP + DI_FEW], s_what[DEEP], s_found;
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
     if (blockIdx.x == 0 && tid == 0) {
-        S->done = 0; S->differ = 0; S->hashes = 0; S->next[0] = S->next[1] = S->ready[0] = S->ready[1] = 0; S->candidate = DI_NONE; S->searched = 0;
+        S->done = 0; S->more = 0; S->n_left = 0; S->checked = 0; S->candidate = DI_NONE; S->searched = 0;
+        for (uint32_t q = 0; q < DI_FEW; ++q) S->at[q] = 0;
+        for (uint32_t q = 0; q < DI_LEFT; ++q) S->differs[q] = 0;
+        for (int k = 0; k < 3; ++k) S->next[k] = S->ready[k] = 0;
     }
     const uint64_t last = tok[M - 1];
     const uint32_t most = M / 2;
@@ -247,7 +261,7 @@ __global__ __launch_bounds__(256) void k_detect_suffix(const uint64_t *__restric
 #pragma unroll
         for (uint32_t k = 0; k < DI_SPAN; ++k) {
             const uint64_t p = base + k * 256 + tid;
-            if (x[k] == last && p <= most && suffix_repeats(tok, M, (uint32_t)p)) {
+            if (x[k] == last && p <= most && ends_alike(tok, M, (uint32_t)p)) {
                 atomicOr(&s_bits[(k * 256 + tid) / 32], 1u << (tid % 32));
                 s_found = 1;
             }
@@ -268,7 +282,8 @@ __global__ __launch_bounds__(256) void k_detect_suffix(const uint64_t *__restric
         __syncthreads();
         const uint32_t found = s_found, look = min(found, DEEP);
         for (uint32_t q = wave; q < look; q += 4) {
-            const uint32_t what = look_deep(tok, M, s_list[q], DI_DEEP);
+            uint32_t at;
+            const uint32_t what = look_deep(tok, M, s_list[q], DI_DEEP, at);
             if (lane == 0) s_what[q] = what;
             if (what == DI_SAME) break;        // (those above do not matter)
         }
@@ -298,9 +313,10 @@ __global__ __launch_bounds__(DI_THREADS) void k_detect_compare(const uint64_t *_
                                                                uint32_t n_lists, uint32_t *__restrict__ period)
 {
     static_assert(DI_LISTS <= DI_THREADS, "a thread per list");
-    __shared__ uint32_t s_best, s_list[DI_FEW + 1], s_more, s_last;
+    __shared__ uint32_t s_best, s_list[DI_FEW + 1], s_at[DI_FEW], s_more, s_last;
     const uint32_t tid = threadIdx.x;
     if (tid == 0) { s_best = DI_NONE; s_more = 0; }
+    if (tid < DI_FEW) s_at[tid] = 0;
     if (tid <= DI_FEW) s_list[tid] = DI_NONE;
     __syncthreads();
     uint32_t mine[DI_FEW], count = 0;
@@ -332,26 +348,35 @@ __global__ __launch_bounds__(DI_THREADS) void k_detect_compare(const uint64_t *_
     if (count > DI_FEW && mine[DI_FEW - 1] < best) s_more = 1;
     if (tid == 0 && s_list[DI_FEW] != DI_NONE) s_more = 1;
     __syncthreads();
-    uint32_t differ = 0;
     for (uint32_t q = 0; q < found; ++q) {
         const uint32_t c = s_list[q];
-        bool bad = false;
+        uint32_t at = 0;
 #pragma unroll 4
         for (uint64_t i = (uint64_t)blockIdx.x * DI_THREADS + tid; i < c; i += (uint64_t)gridDim.x * DI_THREADS)
-            bad |= tok[M - 2 * c + (uint32_t)i] != tok[M - c + (uint32_t)i];
-        if (__syncthreads_or(bad ? 1 : 0)) differ |= 1u << q;
+            at = tok[M - 2 * c + (uint32_t)i] != tok[M - c + (uint32_t)i] ? (uint32_t)i + 1 : at;
+        at = wave_scan_max_u32(at);
+        if (lane_id() == WAVE - 1 && at) atomicMax(&s_at[q], at);
     }
+    __syncthreads();
     if (tid == 0) {
-        if (differ) atomicOr(&S->differ, differ);
+        for (uint32_t q = 0; q < found; ++q)
+            if (s_at[q]) atomicMax(&S->at[q], s_at[q]);
         __threadfence();
         s_last = atomicAdd(&S->done, 1u) + 1 == gridDim.x ? 1u : 0u;
     }
     __syncthreads();
     if (s_last && tid == 0) {
         __threadfence();
-        const uint32_t p = smallest_same(s_list, found, atomicOr(&S->differ, 0u));
-        if (!p && s_more) S->hashes = 1;
-        *period = p ? p : best == DI_NONE ? 0 : best;
+        uint32_t p = best;
+        for (uint32_t q = found; q-- > 0;) {
+            const uint32_t at = atomicMax(&S->at[q], 0u);
+            if (!at) p = s_list[q];
+            S->places[2 * q] = M - s_list[q] + at - 1;
+            S->places[2 * q + 1] = M - 2 * s_list[q] + at - 1;
+        }
+        if (s_more && p == best) S->more = 1;              // (all DI_FEW of them differ)
+        S->top = min(best, M / 2);
+        *period = p == DI_NONE ? 0 : p;
     }
 }
 
@@ -376,30 +401,74 @@ __device__ __forceinline__ void wait_tiles(uint32_t *ready, uint32_t mine, uint3
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 }
 
-// the workgroup's next tiles, one for each of its waves (a counter for single waves took 0.2 ms: the chip adds to one address one
-// after the other)
-__device__ __forceinline__ uint32_t next_tiles(uint32_t *next, uint32_t *s_next)
+// the workgroup's next `take` tiles (a counter for single waves took 0.2 ms: the chip adds to one address one after the other)
+__device__ __forceinline__ uint32_t next_tiles(uint32_t *next, uint32_t take, uint32_t *s_next)
 {
     __syncthreads();
-    if (threadIdx.x == 0) *s_next = atomicAdd(next, (uint32_t)DI_WAVES);
+    if (threadIdx.x == 0) *s_next = atomicAdd(next, take);
     __syncthreads();
     return *s_next;
 }
 
-// The hashes: the totals of tiles of `tile` tokens (a multiple of DI_CHUNK), the hash of every prefix, the candidates; the last
-// workgroup to finish checks the smallest.  A workgroup takes tiles from a counter, so what others wait for is held by one
-// that runs already, and every wait ends.
-__global__ __launch_bounds__(DI_THREADS) void k_detect_hash(const uint64_t *__restrict__ tok, uint32_t M, uint32_t min_period,
+// What is left: the distances that repeat what the DI_FEW did not, of which a few are compared by all workgroups.  Else the hashes:
+// the totals of tiles of `tile` tokens (a multiple of DI_CHUNK), the hash of every prefix, the candidates; the last workgroup to
+// finish checks the smallest.  A workgroup takes tiles from a counter, so what others wait for is held by one that runs
+// already, and every wait ends.
+__global__ __launch_bounds__(DI_THREADS) void k_detect_left(const uint64_t *__restrict__ tok, uint32_t M, uint32_t min_period,
                                                             uint32_t tile, uint32_t n_tiles, DiScratch *S, uint64_t *Q,
                                                             uint32_t *__restrict__ period)
 {
     __shared__ uint32_t s_last, s_sum, s_next;
-    if (!S->hashes) return;
+    if (!S->more) return;
     const uint32_t lane = threadIdx.x & (WAVE - 1), tid = threadIdx.x;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / WAVE));
     const bool vec = ((uintptr_t)tok & 15) == 0;
+    const uint64_t last = tok[M - 1];
+    uint32_t places[2 * DI_FEW];
+    uint64_t tokens[2 * DI_FEW];
+#pragma unroll
+    for (uint32_t q = 0; q < 2 * DI_FEW; ++q) { places[q] = S->places[q]; tokens[q] = tok[places[q]]; }
+    const uint32_t top = S->top, n_spans = (top - min_period) / DI_THREADS + 1;
     uint32_t mine = 0;
-    for (uint32_t t0 = next_tiles(&S->next[0], &s_next); t0 < n_tiles; t0 = next_tiles(&S->next[0], &s_next)) {
+    for (uint32_t t0 = next_tiles(&S->next[0], 4, &s_next); t0 < n_spans; t0 = next_tiles(&S->next[0], 4, &s_next)) {
+        for (uint32_t t = t0; t < min(n_spans, t0 + 4); ++t, mine += wave == 0) {
+            const uint64_t p = (uint64_t)min_period + (uint64_t)t * DI_THREADS + tid;
+            bool stays = p <= top && tok[M - 1 - (uint32_t)p] == last && ends_alike(tok, M, (uint32_t)p);
+            if (stays) {
+#pragma unroll
+                for (uint32_t q = 0; q < 2 * DI_FEW; ++q) stays &= place_repeats(tok, M, (uint32_t)p, places[q], tokens[q]);
+            }
+            const uint64_t who = ballot(stays);
+            if (!who) continue;
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&S->n_left, (uint32_t)__popcll(who));
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(who & ((1ull << lane) - 1));
+            if (stays && at < DI_LEFT) S->left[at] = (uint32_t)p;
+        }
+    }
+    wait_tiles(&S->ready[0], mine, n_spans, &s_sum);
+    const uint32_t left = __hip_atomic_load(&S->n_left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (left <= DI_LEFT) {
+        for (uint32_t q = 0; q < left; ++q) {
+            const uint32_t c = S->left[q];
+            bool bad = false;
+#pragma unroll 4
+            for (uint64_t i = (uint64_t)blockIdx.x * DI_THREADS + tid; i < c; i += (uint64_t)gridDim.x * DI_THREADS)
+                bad |= tok[M - 2 * c + (uint32_t)i] != tok[M - c + (uint32_t)i];
+            if (__syncthreads_or(bad ? 1 : 0) && tid == 0) atomicOr(&S->differs[q], 1u);
+        }
+        if (tid != 0) return;
+        __threadfence();
+        if (atomicAdd(&S->checked, 1u) + 1 != gridDim.x) return;
+        __threadfence();
+        uint32_t p = DI_NONE;
+        for (uint32_t q = 0; q < left; ++q)
+            if (!atomicOr(&S->differs[q], 0u)) p = min(p, S->left[q]);
+        *period = p == DI_NONE ? 0 : p;
+        return;
+    }
+    mine = 0;
+    for (uint32_t t0 = next_tiles(&S->next[1], DI_WAVES, &s_next); t0 < n_tiles; t0 = next_tiles(&S->next[1], DI_WAVES, &s_next)) {
         const uint32_t t = t0 + wave;
         if (t >= n_tiles) continue;
         const uint32_t first = t * tile, end = M - first < tile ? M : first + tile;
@@ -413,9 +482,9 @@ __global__ __launch_bounds__(DI_THREADS) void k_detect_hash(const uint64_t *__re
         if (lane == 0) S->totals[t] = total;
         ++mine;
     }
-    wait_tiles(&S->ready[0], mine, n_tiles, &s_sum);
+    wait_tiles(&S->ready[1], mine, n_tiles, &s_sum);
     mine = 0;
-    for (uint32_t t0 = next_tiles(&S->next[1], &s_next); t0 < n_tiles; t0 = next_tiles(&S->next[1], &s_next)) {
+    for (uint32_t t0 = next_tiles(&S->next[2], DI_WAVES, &s_next); t0 < n_tiles; t0 = next_tiles(&S->next[2], DI_WAVES, &s_next)) {
         const uint32_t t = t0 + wave;
         if (t >= n_tiles) continue;
         const uint32_t first = t * tile, end = M - first < tile ? M : first + tile;
@@ -443,7 +512,7 @@ __global__ __launch_bounds__(DI_THREADS) void k_detect_hash(const uint64_t *__re
         }
         ++mine;
     }
-    wait_tiles(&S->ready[1], mine, n_tiles, &s_sum);
+    wait_tiles(&S->ready[2], mine, n_tiles, &s_sum);
     const uint32_t most = M / 2;
     for (uint64_t p0 = (uint64_t)min_period + (uint64_t)blockIdx.x * DI_THREADS; p0 <= most; p0 += (uint64_t)gridDim.x * DI_THREADS) {
         const uint64_t p = p0 + tid;
@@ -466,7 +535,7 @@ hipError_t launch_detect_iteration(const uint64_t *tokens, uint32_t M, uint32_t 
                                    uint64_t *totals, uint32_t *period, hipStream_t st)
 {
     if (M <= DI_ONE) {
-        hipLaunchKernelGGL(k_detect_short, dim3(1), dim3(DI_THREADS), 0, st, tokens, M, min_period, Q, period);
+        hipLaunchKernelGGL(k_detect_short, dim3(1), dim3(DI_THREADS), 0, st, tokens, M, min_period, period);
         return hipGetLastError();
     }
     // tiles of at least 1024 tokens (four steps of a wave), at most DI_TILES of them
@@ -480,7 +549,7 @@ hipError_t launch_detect_iteration(const uint64_t *tokens, uint32_t M, uint32_t 
     DiScratch *S = (DiScratch *)totals;
     hipLaunchKernelGGL(k_detect_suffix, dim3(n_lists), dim3(256), 0, st, tokens, M, min_period, S);
     hipLaunchKernelGGL(k_detect_compare, dim3(blocks), dim3(DI_THREADS), 0, st, tokens, M, S, n_lists, period);
-    hipLaunchKernelGGL(k_detect_hash, dim3(blocks), dim3(DI_THREADS), 0, st, tokens, M, min_period, tile, nt, S, Q, period);
+    hipLaunchKernelGGL(k_detect_left, dim3(blocks), dim3(DI_THREADS), 0, st, tokens, M, min_period, tile, nt, S, Q, period);
     return hipGetLastError();
 }
 
