@@ -58,7 +58,7 @@ size_t ws_plan_lists(uint32_t n, uint32_t T, uint32_t B)
 size_t ws_plan(uint32_t n, uint32_t T, uint32_t B)
 {
     const size_t bn = (size_t)B * n;
-    return up(sizeof(lap::PlanHeader)) + 2 * up(((size_t)T + 2) * 4)   // header, step counts, list starts
+    return up(2 * sizeof(lap::PlanHeader)) + 2 * up(((size_t)T + 2) * 4)   // header, step counts, list starts
            + 2 * up((size_t)B * 4) + 2 * up((size_t)B * 8)            // kinds, fit policies, seeds, durations
            + 2 * up(bn * 4)                                            // perm, sort scratch
            + up((size_t)B * 8)                                         // footprints
@@ -320,7 +320,7 @@ int lap_profile_ordering_ms(uint32_t n_vars, uint32_t n_steps, uint32_t B, const
     if (rc) return rc;
     // same steps as lap_plan_pool takes to its `ticks` region
     Carver c(const_cast<void *>(ws));
-    c.take<lap::PlanHeader>(1);
+    c.take<lap::PlanHeader>(2);
     c.take<uint32_t>((size_t)n_steps + 2);
     c.take<uint32_t>((size_t)n_steps + 2);
     c.take<uint32_t>(B);
@@ -348,7 +348,7 @@ int lap_plan_pool_orders(uint32_t n_vars, uint32_t n_steps, uint32_t B, const vo
     if (rc) return rc;
     // same steps as lap_plan_pool takes to its `perm` region
     Carver c(const_cast<void *>(ws));
-    c.take<lap::PlanHeader>(1);
+    c.take<lap::PlanHeader>(2);
     c.take<uint32_t>((size_t)n_steps + 2);
     c.take<uint32_t>((size_t)n_steps + 2);
     c.take<uint32_t>(B);
@@ -422,7 +422,7 @@ int lap_plan_pool(const lap_trace *tr, const lap_ordering *ords, uint32_t B, uin
     hipStream_t st = (hipStream_t)hip_stream;
     const size_t bn = (size_t)B * n;
     Carver c(ws);
-    lap::PlanHeader *hdr = c.take<lap::PlanHeader>(1);
+    lap::PlanHeader *hdr = c.take<lap::PlanHeader>(2);
     uint32_t *cntd = c.take<uint32_t>((size_t)T + 2);
     uint32_t *lstart = c.take<uint32_t>((size_t)T + 2);
     uint32_t *kinds = c.take<uint32_t>(B);
@@ -478,9 +478,13 @@ int lap_plan_pool(const lap_trace *tr, const lap_ordering *ords, uint32_t B, uin
     const uint64_t seg_min_vars = g_seg_min_vars;
     const bool may_seg = n >= seg_min_vars;         // below, the header rules the segment lists out: no launches for them
     // from a number of variables that was set, the segment lists are used wherever they apply
-    const bool batches = lap::batch_places(n, T, B, any_best), batches_first = batches && seg_min_vars == SEG_MIN_VARS_DEFAULT;
+    const bool batches = lap::batch_places(n, T, B, any_best);
+    // (where the segment lists may turn out not to place, the batches do)
+    lap::BatchTrial look{batches && seg_min_vars == SEG_MIN_VARS_DEFAULT, batches && !may_seg && n <= lap::PLAN_REG_MAX_VARS, false};
+    for (uint32_t b = 0; b < B && !look.by_trace; ++b)
+        look.by_trace = ords[b].kind != LAP_ORD_SEEDED && ords[b].kind != LAP_ORD_CLASS_SEEDED;
     LAP_HIP(lap::launch_plan_prep(n, T, B, tr->size, tr->alloc, tr->free_, cntd, lstart, hdr, vrec,
-                                  seg_pool_entries(n, B), seg_min_vars, batches_first, st));
+                                  seg_pool_entries(n, B), seg_min_vars, look, st));
     if (may_seg)
         LAP_HIP(lap::launch_seg_prep(n, T, B, tr->alloc, tr->free_, hdr, seg_cnt, seg_lst, (uint32_t)dir_cap,
                                      seg_pool_entries(n, B), st));
@@ -497,8 +501,8 @@ int lap_plan_pool(const lap_trace *tr, const lap_ordering *ords, uint32_t B, uin
                                           (uint32_t)dir_cap, offs, fps, ticks, st));
         }
         if (batches)
-            LAP_HIP(lap::launch_place_batch(n, B, perm, hdr, vrec, (uint32_t *)f_oe, offs, fps, ticks, st));
-        else
+            LAP_HIP(lap::launch_place_batch(n, B, perm, look.look ? hdr + 1 : hdr, vrec, (uint32_t *)f_oe, offs, fps, ticks, st));
+        if (!batches || look.look)
             LAP_HIP(lap::launch_place_reg(n, T, B, perm, fits, any_best, hdr, vrec, offs, fps, ticks, st));
         LAP_HIP(lap::launch_place_fast(n, T, B, tr->size, tr->alloc, tr->free_, perm, fits, any_first, any_best, hdr, vrec,
                                        lstart, f_oe, f_life, f_oe2,

@@ -22,7 +22,7 @@ struct PlanHeader {
     uint32_t part[2];              // placement workgroups that have started, per fit policy
     uint32_t progress[2];          // their progress, in units of 512 ranks, summed
     // segment lists (place_seg.hip), used when per-step lists are not and the pool has room
-    uint32_t mode2;                // 1: the segment kernel places this trace; 2: the batches have, though it has too many variables for registers
+    uint32_t mode2;                // 1: the segment kernel places this trace; 2: the batches do, or have
     uint32_t seg_shift;            // log2 of the segment width in steps
     uint32_t seg_K;                // number of segments
     uint32_t seg_slots;            // orderings that have room in the list pool at once
@@ -61,9 +61,9 @@ __device__ __forceinline__ bool reg_before_lists(uint32_t n, uint32_t T, uint32_
 }
 
 // Up to 64 variables placed at a time (place_batch.hip): whether that takes the place of the registers, and of the sweep.
-// First-fit calls only: with best-fit orderings among them the registers place all in one launch.  ms in registers and in
-// batches, of a residual chain, a pyramid of feature maps, and random lifetimes with six sizes, whose holes take one
-// variable each (the alloc-ascending order then needs two to three times as long as the others):
+// First-fit calls only: with best-fit orderings among them the registers place all in one launch.  What the trace has to do with
+// it is batches_lose's.  ms in registers and in batches, of a residual chain, a pyramid of feature maps, and random lifetimes
+// with six sizes:
 //     256 orderings of   700   0.31 0.32 0.31 and 0.28 0.28 0.53      512 of   700   0.35 0.34 0.35 and 0.30 0.31 0.60
 //                       1500   0.97 0.97      and 0.54 0.66                   1500   1.04 1.04      and 0.59 0.72
 //                       3000   2.42 2.43 2.43 and 1.18 1.54 2.25              3000   2.95           and 1.34 1.74 2.64
@@ -81,6 +81,47 @@ constexpr uint32_t PLAN_BATCH_LDS_VARS = 52 * 256 - 1;      // rows of 512 entri
 inline bool batch_places(uint32_t n, uint32_t T, uint32_t B, bool any_best)
 {
     return !any_best && n <= PLAN_BATCH_MAX_VARS && T <= 0xFFFFu && (n > 4096 || (n > 2048 && B <= 768) || (n > 1024 && B <= 512));
+}
+
+// Whether the registers are the faster ones all the same (where they may place: up to PLAN_REG_MAX_VARS).  A batch ends where a
+// variable has been shown too few holes.  In a training iteration blocks are freed in the reverse order of their allocation and
+// a hole takes many; where lifetimes cross, holes lie apart and are taken by one variable each, so that of equal sizes few
+// go into a batch in an order that follows the trace (shuffled orderings place variables that are apart in time).
+// meet, cross, equal: of 2048 pairs of variables that are listed close to each other, those that meet in time, those of them
+// of which the one allocated first is freed first, and those of one size.  cross is at most 2 % of meet in the three families of
+// training iterations and 15 % and more with lifetimes at random.  Times in registers over times in batches, lifetimes at
+// random (18 shapes: short to long, some of one step, uniform and heavy-tailed), by the number of sizes:
+//     orderings  variables      one       six        40         1000      shuffled only, 1 to 1000 sizes
+//     16            1100     0.4        0.6  0.9                0.7 0.8   1.2  2.1
+//                   1600                0.7  0.9                0.8 1.0   1.4  2.4
+//                   2200                0.7  1.1                0.9 1.1   1.6  2.9
+//                   3000     0.5  0.8   0.75 1.0   0.9  1.1     1.0
+//                   9000     0.6  0.9   0.9  1.3   1.1  1.4     1.2
+//                 14 000     0.5        0.75 1.1   0.9  1.2     1.15
+//                 20 000     0.6        0.75 1.1   0.95 1.25    1.2
+//                 30 000     0.65       0.95 1.3                1.4
+//     512           1100     0.4        0.6                               0.8  1.4
+//                   2200                                                  1.1  1.9
+//                   3000     0.5  0.8   0.8  1.1   0.95 1.2               1.1  2.2
+//                   9000     0.7  1.3   0.8  1.5   0.9  1.6               1.0  2.2
+//           14 000, 20 000              1.2  1.8   1.5  1.9
+//     1024          5000     1.0        1.3
+//                   9000     0.8        0.85
+//           13 000, 14 000   1.2        1.4
+struct BatchTrial {
+    bool first;                  // batches go before the segment lists where batches_before_segments says so
+    bool look;                   // batches_lose decides about registers and batches (the second header is for the batches:
+                                 // `fast` is not set there where the registers are to place)
+    bool by_trace;               // there are other orderings than shuffles
+};
+__device__ __forceinline__ bool batches_lose(uint32_t n, uint32_t B, bool by_trace, uint32_t meet, uint32_t cross, uint32_t equal)
+{
+    if (cross * 8 < meet) return false;
+    if (!by_trace) return n < 1536 && B > 256;
+    if (equal * 3 > meet) return B <= 512 || n <= 10240;
+    if (equal * 10 <= meet) return n < 2560;
+    if (n > PLAN_BATCH_LDS_VARS) return n <= 24576 && B <= 256;
+    return n < 4096 || (cross * 5 > meet * 2 && (B <= 512 || (n > 6143 && n <= 10240)));
 }
 
 // Whether they go before the segment lists.  All placed blocks are gone through for every batch, one ordering of 16 waves or two of
@@ -121,7 +162,7 @@ hipError_t launch_sort_perm(uint32_t n, uint32_t B, const uint64_t *size, const 
                             bool any_explicit, hipStream_t st);
 hipError_t launch_plan_prep(uint32_t n, uint32_t T, uint32_t B, const uint64_t *size, const uint32_t *alloc,
                             const uint32_t *free_, uint32_t *cntd, uint32_t *lstart, PlanHeader *hdr, void *vrec,
-                            uint64_t seg_pool_entries, uint64_t seg_min_vars, bool batches_first, hipStream_t st);
+                            uint64_t seg_pool_entries, uint64_t seg_min_vars, BatchTrial batches, hipStream_t st);
 hipError_t launch_seg_prep(uint32_t n, uint32_t T, uint32_t B, const uint32_t *alloc, const uint32_t *free_,
                            PlanHeader *hdr, uint32_t *cnt, uint32_t *lst, uint32_t dir_cap, uint64_t pool_entries,
                            hipStream_t st);
@@ -138,7 +179,7 @@ hipError_t launch_place_seg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
 hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *perm, const uint32_t *fits, bool any_best,
                             const PlanHeader *hdr, const void *vrec, uint64_t *offs, uint64_t *fps, uint64_t *ticks,
                             hipStream_t st);
-// blocks [B][4 n]: scratch
+// hdr: the second one where the preparation has looked at registers and batches; blocks [B][4 n]: scratch
 hipError_t launch_place_batch(uint32_t n, uint32_t B, const uint32_t *perm, PlanHeader *hdr, const void *vrec,
                               uint32_t *blocks, uint64_t *offs, uint64_t *fps, uint64_t *ticks, hipStream_t st);
 hipError_t launch_place_fast(uint32_t n, uint32_t T, uint32_t B, const uint64_t *size, const uint32_t *alloc,

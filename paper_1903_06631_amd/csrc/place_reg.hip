@@ -289,7 +289,7 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
     } else {
         if (rows <= 16) return launch_one<1, 16>(A, B, st);
         if (rows <= 24) return launch_one<8, 3>(A, B, st);
-        if (rows <= 32 && B > 512 && B <= 768) return launch_one<4, 10>(A, B, st);
+        if (rows <= (any_best ? 32u : 40u) && B > 512 && B <= 768) return launch_one<4, 10>(A, B, st);
         if (rows <= 32) return launch_one<8, 4>(A, B, st);
         if (rows <= 40) return launch_one<8, 5>(A, B, st);
     }

@@ -105,10 +105,45 @@ __device__ __forceinline__ uint64_t prep_block_scan(uint64_t v, uint64_t *wtmp, 
     return pre + incl;
 }
 
+// Two pairs of variables a thread that are listed close to each other, read before anything else so that nobody waits for them
+struct PrepPairs {
+    static constexpr uint32_t PAIRS = 2;
+    uint64_t si[PAIRS], sj[PAIRS];
+    uint32_t ai[PAIRS], fi[PAIRS], aj[PAIRS], fj[PAIRS];
+    bool turned[PAIRS];          // j is listed before i
+    __device__ __forceinline__ void load(uint32_t n, const uint64_t *__restrict__ size, const uint32_t *__restrict__ alloc,
+                                         const uint32_t *__restrict__ free_)
+    {
+#pragma unroll
+        for (uint32_t k = 0; k < PAIRS; ++k) {
+            const uint32_t q = threadIdx.x * PAIRS + k, i = (uint32_t)((uint64_t)q * n / (PREP_THREADS * PAIRS)),
+                           d = i + 1 + q * 37 % 63, j = d < n ? d : d - n;
+            turned[k] = d >= n;
+            ai[k] = alloc[i]; fi[k] = free_[i]; si[k] = size[i];
+            aj[k] = alloc[j]; fj[k] = free_[j]; sj[k] = size[j];
+        }
+    }
+    // adds to three counts of 16 bits: pairs that meet, cross, and have one size (batches_lose)
+    __device__ __forceinline__ void count(unsigned long long *sum) const
+    {
+        unsigned long long mine = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < PAIRS; ++k) {
+            const bool meet = ai[k] < fj[k] && aj[k] < fi[k];
+            // of two allocated in one step the first in the list
+            const bool cross = ai[k] == aj[k] ? (fi[k] < fj[k]) != turned[k] && fi[k] != fj[k] : (ai[k] < aj[k]) == (fi[k] < fj[k]) && fi[k] != fj[k];
+            mine += (unsigned long long)__popcll(ballot(meet)) | (unsigned long long)__popcll(ballot(meet && cross)) << 16 |
+                    (unsigned long long)__popcll(ballot(meet && si[k] == sj[k])) << 32;
+        }
+        if ((threadIdx.x & (WAVE - 1)) == 0) atomicAdd(sum, mine);
+    }
+};
+
 // live[t] = number of variables live at step t; lstart = exclusive prefix sum of live + 1; one workgroup
 __device__ __forceinline__ void prep_lists(uint32_t n, uint32_t T, uint32_t B, const uint32_t *cntd,
-                                           uint32_t *__restrict__ lstart, PlanHeader *hdr, uint64_t *wtmp,
-                                           uint64_t seg_pool_entries, uint64_t seg_min_vars, bool batches_first)
+                                           uint32_t *__restrict__ lstart, PlanHeader *hdr, PlanHeader *for_batches,
+                                           uint64_t *wtmp, const unsigned long long *pairs,
+                                           uint64_t seg_pool_entries, uint64_t seg_min_vars, BatchTrial batches)
 {
     const uint32_t tid = threadIdx.x;
     uint64_t c1 = 0, c2 = 0, tot;
@@ -133,6 +168,14 @@ __device__ __forceinline__ void prep_lists(uint32_t n, uint32_t T, uint32_t B, c
         hdr->shift = shift;
         hdr->fast = fast ? 1u : 0u;
         hdr->mode1 = lists && !reg_before_lists(n, T, hdr->n_multi, B) ? 1u : 0u;
+        if (batches.look) {                      // (only where n < seg_min_vars)
+            const uint64_t c = *pairs;
+            const bool batch = fast && !lists && !batches_lose(n, B, batches.by_trace, (uint32_t)c & 0xFFFF, (uint32_t)(c >> 16) & 0xFFFF, (uint32_t)(c >> 32));
+            hdr->mode2 = batch ? 2u : 0u;
+            for_batches->fast = batch ? 1u : 0u;
+            for_batches->shift = shift;
+            for_batches->mode1 = for_batches->mode2 = 0;
+        }
         if (n < seg_min_vars) return;            // no segment lists, and none of their figures (the header is zero)
         // Segment lists: the width that enters the fewest blocks into lists; every list has one
         // entry more than the blocks it sees.  Taken when per-step lists are not, the trace has
@@ -160,7 +203,7 @@ __device__ __forceinline__ void prep_lists(uint32_t n, uint32_t T, uint32_t B, c
         const uint64_t slots = best_need ? seg_pool_entries / best_need : 0;
         const bool seg = fast && !lists && (sum >> shift) < 0xFFFFFFFEull &&
                          best_need < 0xFFFFFFFFull && T < 0x7FFF0000u && slots >= 1 &&
-                         !(batches_first && batches_before_segments(n, B, best_need));
+                         !(batches.first && batches_before_segments(n, B, best_need));
         hdr->mode2 = seg ? 1u : 0u;
         hdr->seg_shift = ssh;
         hdr->seg_K = (uint32_t)K;
@@ -170,13 +213,25 @@ __device__ __forceinline__ void prep_lists(uint32_t n, uint32_t T, uint32_t B, c
 }
 
 __global__ __launch_bounds__(PREP_THREADS) void k_plan_prep2(uint32_t n, uint32_t T, uint32_t B,
+                                                             const uint64_t *__restrict__ size,
+                                                             const uint32_t *__restrict__ alloc,
+                                                             const uint32_t *__restrict__ free_,
                                                              const uint32_t *__restrict__ cntd,
                                                              uint32_t *__restrict__ lstart, PlanHeader *hdr,
                                                              uint64_t seg_pool_entries, uint64_t seg_min_vars,
-                                                             bool batches_first)
+                                                             BatchTrial batches)
 {
     __shared__ uint64_t wtmp[PREP_THREADS / WAVE];
-    prep_lists(n, T, B, cntd, lstart, hdr, wtmp, seg_pool_entries, seg_min_vars, batches_first);
+    __shared__ unsigned long long pairs;
+    PrepPairs P;
+    if (batches.look) {
+        P.load(n, size, alloc, free_);
+        if (threadIdx.x == 0) pairs = 0;
+        __syncthreads();
+        P.count(&pairs);
+        __syncthreads();
+    }
+    prep_lists(n, T, B, cntd, lstart, hdr, hdr + 1, wtmp, &pairs, seg_pool_entries, seg_min_vars, batches);
 }
 
 // What the placement kernel reads of a variable, in one 16-byte record (one gather per rank
@@ -203,18 +258,23 @@ __global__ __launch_bounds__(PREP_THREADS) void k_plan_prep_small(uint32_t n, ui
                                                                   const uint32_t *__restrict__ free_,
                                                                   uint32_t *__restrict__ lstart, PlanHeader *hdr,
                                                                   uint4 *__restrict__ vrec, uint64_t seg_pool_entries,
-                                                                  uint64_t seg_min_vars, bool batches_first)
+                                                                  uint64_t seg_min_vars, BatchTrial batches)
 {
     __shared__ PlanHeader h;
     __shared__ uint32_t cntd[PREP_SMALL_STEPS + 1];
     __shared__ uint64_t wtmp[PREP_THREADS / WAVE];
+    __shared__ unsigned long long pairs;
     const uint32_t tid = threadIdx.x;
+    PrepPairs P;
+    if (batches.look) P.load(n, size, alloc, free_);
+    if (tid == 0) pairs = 0;
     for (uint32_t t = tid; t <= T; t += PREP_THREADS) cntd[t] = 0;
     if (tid < HDR_WORDS) ((uint64_t *)&h)[tid] = 0;
     __syncthreads();
     prep_sums(tid, PREP_THREADS, n, T, size, alloc, free_, cntd, &h, n >= seg_min_vars);
+    if (batches.look) P.count(&pairs);
     __syncthreads();
-    prep_lists(n, T, B, cntd, lstart, &h, wtmp, seg_pool_entries, seg_min_vars, batches_first);
+    prep_lists(n, T, B, cntd, lstart, &h, hdr + 1, wtmp, &pairs, seg_pool_entries, seg_min_vars, batches);
     __syncthreads();
     if (tid < HDR_WORDS) ((uint64_t *)hdr)[tid] = ((const uint64_t *)&h)[tid];
     if (!h.fast) return;
@@ -226,11 +286,11 @@ __global__ __launch_bounds__(PREP_THREADS) void k_plan_prep_small(uint32_t n, ui
 
 hipError_t launch_plan_prep(uint32_t n, uint32_t T, uint32_t B, const uint64_t *size, const uint32_t *alloc,
                             const uint32_t *free_, uint32_t *cntd, uint32_t *lstart, PlanHeader *hdr, void *vrec,
-                            uint64_t seg_pool_entries, uint64_t seg_min_vars, bool batches_first, hipStream_t st)
+                            uint64_t seg_pool_entries, uint64_t seg_min_vars, BatchTrial batches, hipStream_t st)
 {
     if (n <= PREP_SMALL_VARS && T <= PREP_SMALL_STEPS) {
         hipLaunchKernelGGL(k_plan_prep_small, dim3(1), dim3(PREP_THREADS), 0, st, n, T, B, size, alloc, free_, lstart, hdr,
-                           (uint4 *)vrec, seg_pool_entries, seg_min_vars, batches_first);
+                           (uint4 *)vrec, seg_pool_entries, seg_min_vars, batches);
         return hipGetLastError();
     }
     // the header and the counters lie one after the other: one fill clears both
@@ -239,8 +299,8 @@ hipError_t launch_plan_prep(uint32_t n, uint32_t T, uint32_t B, const uint64_t *
     uint32_t blocks = (n + 255) / 256;
     blocks = blocks > 1024 ? 1024 : blocks;
     hipLaunchKernelGGL(k_plan_prep1, dim3(blocks > 128 ? 128 : blocks), dim3(256), 0, st, n, T, size, alloc, free_, cntd, hdr, n >= seg_min_vars);
-    hipLaunchKernelGGL(k_plan_prep2, dim3(1), dim3(PREP_THREADS), 0, st, n, T, B, cntd, lstart, hdr, seg_pool_entries,
-                       seg_min_vars, batches_first);
+    hipLaunchKernelGGL(k_plan_prep2, dim3(1), dim3(PREP_THREADS), 0, st, n, T, B, size, alloc, free_, cntd, lstart, hdr, seg_pool_entries,
+                       seg_min_vars, batches);
     hipLaunchKernelGGL(k_plan_pack, dim3(blocks), dim3(256), 0, st, n, size, alloc, free_, hdr, (uint4 *)vrec);
     return hipGetLastError();
 }

