@@ -125,13 +125,22 @@ __device__ __forceinline__ bool batches_lose(uint32_t n, uint32_t B, bool by_tra
 }
 
 // Whether they go before the segment lists.  All placed blocks are gone through for every batch, one ordering of 16 waves or two of
-// 8 to a compute unit; the lists take a time that goes with their entries, and from some 1000 orderings on with these as
-// well.  ms with the lists and in batches:
-//         residual chain, 33 000 variables, 58 entries each     256 orderings 427 32      1024  500 103     4096  757 387
-//                         50 000            75                                848 65            764 215          1114 811
-//                         70 000                                             1920 122
-//         feature maps,   33 000            18                                133  39            176 121           552 452
-//                         50 000            22                                209  72            274 256           908 955
+// 8 to a compute unit; the lists take a time that goes with their entries (and with how their searches converge, which this
+// does not know), and from some 1000 orderings on with these as well.  ms with the lists and in batches, with the entries of a
+// variable, of a residual chain, a pyramid of feature maps, and feature maps among one-step temporaries of random sizes:
+//     orderings          16        256         600         1024        2048      4096
+//     chain     33 000 (49)        427 32                  500 103               757 387
+//               50 000 (63)        848 65                  764 215               1114 811
+//               70 000 (79) 885 109 826 113    954 323     1011 413
+//     pyramid   33 000 (20)        133 39                  176 121               552 452
+//               50 000 (22) 183 68 209 71      255 200     282 256     514 493   908 955
+//               70 000 (25) 253 125 296 133    364 375     405 480
+//              100 000 (31) 734 251 857 261    921 737     991 951
+//              131 072 (37) 922 407 1159 432   1278 1259   1337 1368
+//     maps      33 000 (18)        172 46      177 95      183 125     280 241
+//               50 000 (19)        364 95      374 203     381 268     423 511
+//               70 000 (22)        465 177     484 381     489 509     604 952
+// It is wrong by more than a tenth for the pyramid of 70 000 with 1024 orderings only.
 __device__ __forceinline__ bool batches_before_segments(uint32_t n, uint32_t B, uint64_t need)
 {
     const uint64_t rounds = (B + 255) / 256;

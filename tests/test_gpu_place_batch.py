@@ -169,6 +169,22 @@ def test_other_ways(lap, oracle_mod, T, forced, best):
         assert np.array_equal(all_off[b], off) and u64(got["footprints"])[b] == fp, f"ordering {b}"
 
 
+# the last number of variables of the batches, and the next one, which the sweep places; short lives, so that the oracle is done
+# in half a minute
+@pytest.mark.parametrize("n,T", [(131072, 65535), (131073, 65535)])
+def test_last_size(lap, oracle_mod, n, T):
+    rng = np.random.default_rng(n)
+    tr = random_trace(9650, 64, T, size_choices=[1])
+    a = np.sort(rng.integers(0, T - 12, n))
+    tr.size = rng.integers(1, 50, n).astype(np.uint64) * 512
+    _lives(tr, a, a + rng.integers(7, 13, n))
+    kinds, seeds = make_orderings(5)
+    with _batches(lap):
+        got = lap.plan_pool(lap.DeviceTrace(tr), kinds, seeds)
+    for b, (_, off, fp) in oracle_all_orderings(oracle_mod, tr, kinds, seeds, None, [3, 4], None).items():
+        assert np.array_equal(u64(got["all_offsets"])[b], off) and u64(got["footprints"])[b] == fp, f"ordering {b}"
+
+
 # blocks in memory: plans in two streams at once, then the two in a graph that is replayed with other work between
 def test_streams_and_graph(lap):
     import torch
