@@ -322,11 +322,11 @@ const char *lap_status_string(int status);
  *       else, for first-fit orderings, free lists per time segment when the trace has at least
  *       this many variables and the workspace has room for them, else, where all orderings are
  *       first-fit, 64 variables at a time against the placed blocks sorted by offset (up to 131072
- *       variables and 65535 steps; small traces under many orderings excepted), else such blocks
- *       in registers for up to 32768 variables and 65535 steps, else a sweep over such a list in
- *       memory.  All five give the same offsets.  At the default, 32768, the segment lists also
- *       leave those traces to the third way that it places faster; 0 = segment lists whenever
- *       they apply.
+ *       variables and 65535 steps; small traces under many orderings excepted, and some whose
+ *       lifetimes cross), else such blocks in registers for up to 32768 variables and 65535 steps,
+ *       else a sweep over such a list in memory.  All five give the same offsets.  At the default,
+ *       32768, and above the segment lists also leave those traces to the third way that it places
+ *       faster; below, they are used whenever they apply (0: for any number of variables).
  *   LAP_OPT_SEG_TRIAL_PERCENT  whether the segment lists pay also depends on how their searches
  *       converge (two to three rounds on traces with nested lifetimes, as a training iteration
  *       has; six to eight with lifetimes at random, where the others are faster).  Before they are

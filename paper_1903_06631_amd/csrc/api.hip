@@ -477,10 +477,10 @@ int lap_plan_pool(const lap_trace *tr, const lap_ordering *ords, uint32_t B, uin
     }
     const uint64_t seg_min_vars = g_seg_min_vars;
     const bool may_seg = n >= seg_min_vars;         // below, the header rules the segment lists out: no launches for them
-    // from a number of variables that was set, the segment lists are used wherever they apply
+    // a number below the default asks for the segment lists wherever they apply
     const bool batches = lap::batch_places(n, T, B, any_best);
     // (where the segment lists may turn out not to place, the batches do)
-    lap::BatchTrial look{batches && seg_min_vars == SEG_MIN_VARS_DEFAULT, batches && !may_seg && n <= lap::PLAN_REG_MAX_VARS, false};
+    lap::BatchTrial look{batches && seg_min_vars >= SEG_MIN_VARS_DEFAULT, batches && !may_seg && n <= lap::PLAN_REG_MAX_VARS, false};
     for (uint32_t b = 0; b < B && !look.by_trace; ++b)
         look.by_trace = ords[b].kind != LAP_ORD_SEEDED && ords[b].kind != LAP_ORD_CLASS_SEEDED;
     LAP_HIP(lap::launch_plan_prep(n, T, B, tr->size, tr->alloc, tr->free_, cntd, lstart, hdr, vrec,

@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 from gpu_util import oracle_all_orderings, u64
-from traces import make_orderings, random_trace
+from traces import make_config, make_orderings, random_trace
 
 pytestmark = pytest.mark.gpu
 
@@ -159,7 +159,7 @@ def test_other_ways(lap, oracle_mod, T, forced, best):
     kinds, seeds = make_orderings(B)
     fits = np.zeros(B, np.uint32)
     fits[3] = lap.FIT_BEST if best else lap.FIT_FIRST
-    lap.set_option(lap.OPT_SEG_MIN_VARS, n if forced else lap.SEG_MIN_VARS_DEFAULT)
+    lap.set_option(lap.OPT_SEG_MIN_VARS, 0 if forced else lap.SEG_MIN_VARS_DEFAULT)
     try:
         got = lap.plan_pool(lap.DeviceTrace(tr), kinds, seeds, fits=fits)
     finally:
@@ -167,6 +167,31 @@ def test_other_ways(lap, oracle_mod, T, forced, best):
     all_off = u64(got["all_offsets"])
     for b, (_, off, fp) in oracle_all_orderings(oracle_mod, tr, kinds, seeds, None, [1, 2], None).items():
         assert np.array_equal(all_off[b], off) and u64(got["footprints"])[b] == fp, f"ordering {b}"
+
+
+def test_time_of_numbers_for_the_segment_lists(lap):
+    """from its default on the option is a number of variables for the segment lists, which leave to the batches what these
+    place faster; only below does it ask for the lists (a residual chain of 50 000 variables, measured: 65 and 510 ms)"""
+    dt = lap.DeviceTrace(make_config(4))
+    kinds, seeds = make_orderings(4)
+
+    def ms(number):
+        lap.set_option(lap.OPT_SEG_MIN_VARS, number)
+        low = float("inf")
+        for _ in range(2):
+            lap.plan_pool(dt, kinds, seeds, want_all=False)
+            low = min(low, lap.profile_last_ms(lap.K_PLACE))
+        return low
+
+    lap.profile_enable(True)
+    try:
+        got = {number: ms(number) for number in (lap.SEG_MIN_VARS_DEFAULT, lap.SEG_MIN_VARS_DEFAULT + 1, 1 << 30, lap.SEG_MIN_VARS_DEFAULT - 1)}
+    finally:
+        lap.set_option(lap.OPT_SEG_MIN_VARS, lap.SEG_MIN_VARS_DEFAULT)
+        lap.profile_enable(False)
+    print({k: round(v, 2) for k, v in got.items()})
+    chosen, more, most, forced = got.values()
+    assert more < 1.3 * chosen and most < 1.3 * chosen and forced > 2 * chosen
 
 
 # the last number of variables of the batches, and the next one, which the sweep places; short lives, so that the oracle is done
