@@ -559,10 +559,13 @@ __device__ void sim_run_narrow(const SimArgs &A, uint32_t shift, NarrowWin &W)
             if constexpr (OUT && IN) { oplace = read_lane(c_oplace, (int)oe); iplace = read_lane(c_iplace, (int)ie); }
             // all of them before the first scalar instruction: one that follows a read of a lane waits 20 cycles, and they
             // would alternate
-            asm volatile("" : "+s"(need), "+s"(rel), "+s"(dt));
-            if constexpr (OUT) asm volatile("" : "+s"(olo), "+s"(odur), "+s"(osize));
-            if constexpr (IN) asm volatile("" : "+s"(ihi), "+s"(issue), "+s"(isize), "+s"(idur));
-            if constexpr (OUT && IN) asm volatile("" : "+s"(oplace), "+s"(iplace));
+            if constexpr (OUT && IN)
+                asm volatile("" : "+s"(need), "+s"(rel), "+s"(dt), "+s"(olo), "+s"(odur), "+s"(osize), "+s"(oplace), "+s"(ihi),
+                             "+s"(issue), "+s"(isize), "+s"(iplace), "+s"(idur));
+            else if constexpr (OUT)
+                asm volatile("" : "+s"(need), "+s"(rel), "+s"(dt), "+s"(olo), "+s"(odur), "+s"(osize));
+            else
+                asm volatile("" : "+s"(need), "+s"(rel), "+s"(dt), "+s"(ihi), "+s"(issue), "+s"(isize), "+s"(idur));
             // starts: swap-out, step, swap-in (its variable is out if the current swap-out is one behind it)
             if constexpr (OUT) out = negative(out & (olo - t)) ? odur : out;
             uint32_t step_may = step;
@@ -585,7 +588,7 @@ __device__ void sim_run_narrow(const SimArgs &A, uint32_t shift, NarrowWin &W)
                 // nothing will change by itself: the limit is overridden once
                 if (negative(step_may)) { soon = step = dt & SIM_NEVER; left = after_step; }
                 else if (negative(in_may)) { soon = in = idur; left = after_in; }
-                else { nforced = SIM_NONE - 1; t = T; }    // an inconsistent trace; leave rather than spin
+                else { nforced = SIM_NONE - 1; t = T; te = ~0u; }          // an inconsistent trace; leave rather than spin
                 ++nforced;
             }
             least = (uint32_t)min((int32_t)left, (int32_t)least);
@@ -624,12 +627,12 @@ __device__ void sim_run_narrow(const SimArgs &A, uint32_t shift, NarrowWin &W)
             while (!negative(te | (oe - oe_last) | (quiet - 1u - t)));
         } else if (negative(out) && read_lane(c_olo, (int)oe) == SIM_NEVER) {
             do event(std::false_type{}, std::true_type{});
-            while (!negative(te | ie | (T - 1u - t)));
+            while (!negative(te | ie));
         } else {
-            // (a few events before the question is asked again)
-            uint32_t more = 16;
+            // (some events before the question is asked again; after the last step there is no next one)
+            uint32_t more = 64;
             do event(std::true_type{}, std::true_type{});
-            while (!negative(te | oe | ie | (T - 1u - t) | (--more - 1u)));
+            while (!negative(te | oe | ie | (--more - 1u)));
         }
     } while (t != T);
     if (lane == 0) {
