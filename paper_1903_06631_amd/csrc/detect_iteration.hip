@@ -1,14 +1,15 @@
 // Iteration detection on a recorded request stream (Section V): the list ends with two equal
 // consecutive subsequences of length p; the smallest such p (>= min_period) is reported.
 //
-// First the direct way.  Every distance p is looked at: whether the last p tokens end and start as the p before them (nearly every
-// one is refused by its last token, so half of the list is read once).  A workgroup goes on with the smallest distances that
-// remain of its own: a wave compares up to DI_DEEP tokens of each, which refuses most of what a repeated piece inside an
-// iteration leaves, and settles short repeats.  The DI_FEW smallest that are still open and below the smallest that is settled are then
-// compared element by element by all workgroups, the last of which has the answer -- unless all of them differ and there are
-// more.  Then the places where they differ refuse most of the others, and up to DI_LEFT that remain are compared in the
-// same way.  Only where more do it comes to hashes, whose cost does not depend on what is in the list: a polynomial hash of every
-// prefix (mod 2^64, odd base) is built with a scan; the two halves of a candidate p then compare in O(1):
+// First the direct way.  Every distance p is looked at: whether the last p tokens end as the p before them (nearly every one is
+// refused by its last token, so half of the list is read once).  A workgroup goes on with the smallest distances that
+// remain of its own, where these are many only with those that start alike as well: a wave compares up to DI_DEEP tokens of
+// each, which refuses most of what a repeated piece inside an iteration leaves, and settles short repeats.  The DI_FEW smallest that
+// are still open and below the smallest that is settled are then compared element by element by all workgroups, the last
+// of which has the answer -- unless all of them differ and there are more.  Then the places where they differ refuse most of the
+// others, and up to DI_LEFT that remain are compared in the same way.  Only where more do it comes to hashes, whose cost does
+// not depend on what is in the list: a polynomial hash of every prefix (mod 2^64, odd base) is built with a scan; the two
+// halves of a candidate p then compare in O(1):
 //     (P[M-p] - P[M-2p]) * r^p == P[M] - P[M-p]
 // and the smallest candidate whose hashes agree is checked element by element (hashes mod 2^64 can
 // collide, the answer never depends on them); if the check fails the search resumes behind it.
@@ -16,15 +17,15 @@
 // Short lists (up to DI_ONE requests) are one workgroup's work in one launch, which refuses distances by places until none is left.
 // Longer ones take three, the last of which nearly always finds nothing to do.  us of calls that follow each other, by
 // hashes at once, and now:
-//     an iteration in 4000 requests                       14.7   9.5   in 40 000   22.3  15.3   in 2 000 003   38.7  16.3
-//     iterations that end in a run, or in equal layers    21.5  10.8               22.7  15.5                  38.6  19.5
-//     a run of a short period, too short to be asked for  19.0   9.3               20.9  15.3                  33.7  17.7
-//     one of it that is asked for                         20.5  14.8               54.5  18.3                 125    27.7
-//     a list of a short period with single other tokens   20.5  25                 22    50                    36   114
-//     a Fibonacci word, where it comes to hashes          18.9  12.9               20.8  70                    32   240
-// (6144 requests in the left column from the second line on).  The last two are slower than by hashes at once: many distances are
-// looked at in vain, and a hand-over between workgroups writes the caches back.  An iteration in a list of 2 000 003 that
-// no cache holds yet: 51 and 33.
+//     requests                                             6144        40 000       2 000 003
+//     an iteration                                         21.6   9.2   22.2  14.1   38.5  15.2
+//     iterations that end in a run, or in equal layers     21.5   9.3   22.5  18.1   38.4  24.4
+//     a run of a short period, too short to be asked for   19.0   9.0   20.9  16.8   33.3  22.5
+//     one of it that is asked for                          20.5  14.8   54.3  20.6  127    30.4
+//     a list of a short period with single other tokens    20.5  24     22    49     36   114
+//     a Fibonacci word, where it comes to hashes           19.0  12.2   21.1  69     32   220
+// The last two are slower than by hashes at once: many distances are looked at in vain, and a hand-over between workgroups writes
+// the caches back.  An iteration in a list of 2 000 003 that no cache holds yet: 50 and 29.
 #include "lap_dev.h"
 #include "lap_kernels.h"
 
@@ -102,22 +103,23 @@ __device__ uint32_t search_from(const uint64_t *tok, const uint64_t *Q, uint32_t
     return 0;
 }
 
-// The first look at distance p (2 p <= M): whether the p tokens before the last p end and start as these do.  The end is read by
+// The first looks at distance p (2 p <= M): whether the p tokens before the last p end, and start, as these do.  The end is read by
 // neighbouring lanes anyway.  The start refuses what a run of a short period at the end of the list leaves: a distance
 // that is shorter than the run and longer than half of it reaches out of the run there.
+template <bool START>
+__device__ __forceinline__ bool alike(const uint64_t *__restrict__ tok, uint32_t M, uint32_t p)
+{
+    uint64_t differ = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) {                   // (at once: a wave waits for each round)
+        const uint32_t e = START ? M - p + min(k, p - 1) : M - min(k + 1, p);
+        differ |= tok[e] ^ tok[e - p];
+    }
+    return differ == 0;
+}
 __device__ __forceinline__ bool ends_alike(const uint64_t *__restrict__ tok, uint32_t M, uint32_t p)
 {
-#pragma unroll
-    for (uint32_t half = 0; half < 2; ++half) {          // eight at a time: a wave waits for each round
-        uint64_t differ = 0;
-#pragma unroll
-        for (uint32_t k = 0; k < 8; ++k) {
-            const uint32_t e = half ? M - p + min(k, p - 1) : M - min(k + 1, p);
-            differ |= tok[e] ^ tok[e - p];
-        }
-        if (differ) return false;
-    }
-    return true;
+    return alike<false>(tok, M, p) && alike<true>(tok, M, p);
 }
 
 // What a wave finds out about distance p from its last `deep` tokens; at: one that differs from the one p before it
@@ -127,14 +129,18 @@ __device__ __forceinline__ uint32_t look_deep(const uint64_t *__restrict__ tok, 
     constexpr uint32_t STEP = 4 * WAVE;
     const uint32_t most = min(p, deep);
     for (uint32_t j = 1 + (uint32_t)lane_id(); ballot(j <= most); j += STEP) {
-        uint32_t mine = 0;
+        uint64_t differ[4];                              // (read at once, looked at one by one only if there is a reason)
 #pragma unroll
         for (uint32_t k = 0; k < 4; ++k) {
             const uint32_t e = M - min(j + k * WAVE, most);
-            mine = tok[e] != tok[e - p] ? e : mine;
+            differ[k] = tok[e] ^ tok[e - p];
         }
-        const uint64_t differ = ballot(mine != 0);
-        if (differ) { at = read_lane(mine, __builtin_ctzll(differ)); return DI_DIFFERS; }
+        const uint64_t who = ballot((differ[0] | differ[1] | differ[2] | differ[3]) != 0);
+        if (who) {
+            const uint32_t k = differ[0] ? 0 : differ[1] ? 1 : differ[2] ? 2 : 3;
+            at = read_lane(M - min(j + k * WAVE, most), __builtin_ctzll(who));
+            return DI_DIFFERS;
+        }
     }
     return most == p ? DI_SAME : DI_OPEN;
 }
@@ -240,10 +246,8 @@ __global__ __launch_bounds__(256) void k_detect_suffix(const uint64_t *__restric
     __shared__ uint32_t s_bits[SPAN / 32], s_list[DEEP + DI_FEW], s_what[DEEP], s_found;
     const uint32_t tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
     if (blockIdx.x == 0 && tid == 0) {
-        S->done = 0; S->more = 0; S->n_left = 0; S->checked = 0; S->candidate = DI_NONE; S->searched = 0;
+        S->done = 0; S->more = 0;
         for (uint32_t q = 0; q < DI_FEW; ++q) S->at[q] = 0;
-        for (uint32_t q = 0; q < DI_LEFT; ++q) S->differs[q] = 0;
-        for (int k = 0; k < 3; ++k) S->next[k] = S->ready[k] = 0;
     }
     const uint64_t last = tok[M - 1];
     const uint32_t most = M / 2;
@@ -258,28 +262,39 @@ __global__ __launch_bounds__(256) void k_detect_suffix(const uint64_t *__restric
             const uint64_t p = base + k * 256 + tid;
             x[k] = tok[M - 1 - (p <= most ? (uint32_t)p : 0u)];
         }
+        uint32_t hits = 0;
 #pragma unroll
-        for (uint32_t k = 0; k < DI_SPAN; ++k) {
-            const uint64_t p = base + k * 256 + tid;
-            if (x[k] == last && p <= most && ends_alike(tok, M, (uint32_t)p)) {
-                atomicOr(&s_bits[(k * 256 + tid) / 32], 1u << (tid % 32));
+        for (uint32_t k = 0; k < DI_SPAN; ++k) hits |= x[k] == last && base + k * 256 + tid <= most ? 1u << k : 0u;
+        // (few lanes have one: the longer look once in the code, not once for each of them)
+#pragma unroll 1
+        for (; hits; hits &= hits - 1) {
+            const uint32_t at = (uint32_t)__builtin_ctz(hits) * 256 + tid;
+            if (alike<false>(tok, M, (uint32_t)base + at)) {
+                atomicOr(&s_bits[at / 32], 1u << (at % 32));
                 s_found = 1;
             }
         }
         __syncthreads();
         if (!s_found) continue;
-        // the smallest of them, in ascending order
         static_assert(SPAN / 32 == WAVE, "");
-        if (wave == 0) {
-            uint32_t bits = s_bits[lane];
-            const uint32_t own = (uint32_t)__popc(bits);
-            uint32_t at = own;
-            for (int d = 1; d < WAVE; d <<= 1) { const uint32_t y = (uint32_t)__shfl_up((int)at, d, WAVE); if ((int)lane >= d) at += y; }
-            if (lane == WAVE - 1) s_found = at;
-            for (at -= own; bits && at < DEEP + DI_FEW; bits &= bits - 1, ++at)
-                s_list[at] = (uint32_t)base + lane * 32 + (uint32_t)__ffs((int)bits) - 1;
+        for (bool again = false;; again = true) {
+            if (wave == 0) {                               // the smallest of them, in ascending order
+                uint32_t bits = s_bits[lane];
+                const uint32_t own = (uint32_t)__popc(bits);
+                uint32_t at = own;
+                for (int d = 1; d < WAVE; d <<= 1) { const uint32_t y = (uint32_t)__shfl_up((int)at, d, WAVE); if ((int)lane >= d) at += y; }
+                if (lane == WAVE - 1) s_found = at;
+                for (at -= own; bits && at < DEEP + DI_FEW; bits &= bits - 1, ++at)
+                    s_list[at] = (uint32_t)base + lane * 32 + (uint32_t)__ffs((int)bits) - 1;
+            }
+            __syncthreads();
+            if (again || s_found <= DEEP) break;
+            // too many to look at: those whose starts differ go
+#pragma unroll 1
+            for (uint32_t at = tid; at < SPAN; at += 256)
+                if (((s_bits[at / 32] >> (at % 32)) & 1) && !alike<true>(tok, M, (uint32_t)base + at)) atomicAnd(&s_bits[at / 32], ~(1u << (at % 32)));
+            __syncthreads();
         }
-        __syncthreads();
         const uint32_t found = s_found, look = min(found, DEEP);
         for (uint32_t q = wave; q < look; q += 4) {
             uint32_t at;
@@ -374,8 +389,12 @@ __global__ __launch_bounds__(DI_THREADS) void k_detect_compare(const uint64_t *_
             S->places[2 * q] = M - s_list[q] + at - 1;
             S->places[2 * q + 1] = M - 2 * s_list[q] + at - 1;
         }
-        if (s_more && p == best) S->more = 1;              // (all DI_FEW of them differ)
-        S->top = min(best, M / 2);
+        if (s_more && p == best) {                         // (all DI_FEW of them differ)
+            S->more = 1; S->top = min(best, M / 2);
+            S->n_left = 0; S->checked = 0; S->candidate = DI_NONE; S->searched = 0;
+            for (uint32_t q = 0; q < DI_LEFT; ++q) S->differs[q] = 0;
+            for (int k = 0; k < 3; ++k) S->next[k] = S->ready[k] = 0;
+        }
         *period = p == DI_NONE ? 0 : p;
     }
 }
