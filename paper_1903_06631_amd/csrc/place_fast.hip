@@ -1456,7 +1456,7 @@ __global__ __launch_bounds__(PW *WAVE, 4) void k_place_fast(FastArgs A)
     const bool best = A.fits[blockIdx.x] != 0;
     if (POLICY != 2 && best != (POLICY == 1)) return;
     if (A.reg && reg_places(A.hdr, A.n, best)) return;
-    if (A.hdr->mode2 && !best) return;      // the segment kernel places the first-fit orderings of this trace
+    if (A.hdr->mode2 && !best) return;      // the segment kernel or the batches place the first-fit orderings of this trace
     if (POLICY == 1 || (POLICY == 2 && best)) place_ordering<LT, PW, META, true>(A, S, meta);
     else place_ordering<LT, PW, META, false>(A, S, meta);
 }

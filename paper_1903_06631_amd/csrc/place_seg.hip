@@ -488,10 +488,10 @@ struct SegArgs {
 
 // Whether these lists pay depends on how the searches converge, which depends on the trace: with
 // nested lifetimes and a tight packing (a training iteration) two to three rounds, with lifetimes
-// at random six to eight, and then the sweep over the sorted blocks is the faster way.  So the
+// at random six to eight, and then the sorted blocks are the faster way.  So the
 // first ranks of one ordering are placed ahead of time by one workgroup (TRIAL = true), counting
 // the rounds of the multi-step variables; above `trial_percent` / 100 rounds per variable the
-// trace is handed back to the sweep (mode2 = 0), before any placement kernel looks at that flag.
+// trace is handed back to the batches, the registers or the sweep (mode2 = 0), before any placement kernel looks at that flag.
 constexpr uint32_t SEG_TRIAL_RANKS = 2048;
 
 template <bool TRIAL>

@@ -124,12 +124,22 @@ def test_full_size_plan_transformer(lap, oracle_mod):
 
 
 def test_full_size_plan_deep_chain(lap, oracle_mod):
-    """Config 4: 4096 orderings of 50 000 variables on 14 000 steps (dense interval graph; the segment-list
-    kernel), every one of them compared with the oracle's stored result.  The pairwise check runs on every
+    """Config 4: 4096 orderings of 50 000 variables on 14 000 steps (dense interval graph; placed in batches),
+    every one of them compared with the oracle's stored result.  The pairwise check runs on every
     61st allocation step for all orderings and on every step for 16 of them.  (Best-fit is not run at this size: on a dense trace it looks at thousands of holes per
     variable and takes minutes per ordering.)"""
     _full_size(lap, oracle_mod, 4, False, live_sample=[0, 1, 2, 3, 63, 127, 4, 9, 800, 1500, 2048, 2600, 3100, 3600, 4000, 4095],
                all_steps_rows=list(range(5, 4096, 273)), step_stride=61, stored_all=True)
+
+
+def test_full_size_plan_deep_chain_segment_lists(lap, oracle_mod):
+    """The same orderings by the segment lists, which are asked for: every one of them against the oracle's stored result.  The
+    orderings share the slots of the pool."""
+    lap.set_option(lap.OPT_SEG_MIN_VARS, 0)
+    try:
+        _full_size(lap, oracle_mod, 4, False, live_sample=[0, 4], all_steps_rows=[5], step_stride=601, stored_all=True)
+    finally:
+        lap.set_option(lap.OPT_SEG_MIN_VARS, lap.SEG_MIN_VARS_DEFAULT)
 
 
 def test_full_size_best_fit_transformer(lap, oracle_mod):

@@ -56,10 +56,10 @@ def test_per_step_lists(lap, oracle_mod, B, n, T, n_multi, fits):
 
 # eight and four waves, the step words (which such traces do not have) with room in LDS and without, every policy
 @pytest.mark.parametrize("B,T,fits", [(8, 3000, "best"), (8, 3000, "both"), (8, 700, "best"), (8, 700, "both"), (513, 3000, "first"),
-                                      (513, 3000, "best"), (513, 3000, "both"), (513, 700, "both")])
+                                      (513, 3000, "best"), (513, 3000, "both"), (513, 700, "both"), (513, 66000, "first")])
 def test_sweep(lap, oracle_mod, B, T, fits):
     """one variable more than fits the registers, lifetimes that sum to more than per-step lists take, and no segment
-    lists: the sweep's forms"""
+    lists: the sweep's forms (first-fit orderings alone go to the batches up to 65 535 steps, and are swept beyond)"""
     tr = random_trace(9601, 32769, T, size_choices=[1, 2, 3, 7, 20, 50], max_life=40)
     assert int((tr.free - tr.alloc).sum()) > 6 * tr.n_vars
     lap.set_option(lap.OPT_SEG_MIN_VARS, 1 << 30)

@@ -1,7 +1,7 @@
 """GPU parity of lap_plan_pool on the segment-list path (free lists per time segment, the structure
 for traces whose variables live long), forced on small traces through LAP_OPT_SEG_MIN_VARS = 0 so
 that the oracle can recompute every ordering: offsets and footprints element by element, first-fit
-and best-fit.  At full size the same path places configuration 4 (tests/test_gpu_fullsize.py)."""
+and best-fit.  At full size the same path places configuration 4, where it is asked for (tests/test_gpu_fullsize.py)."""
 import numpy as np
 import pytest
 
@@ -155,11 +155,11 @@ def test_segment_lists_configs(lap, oracle_mod, cfg):
     _check(lap, oracle_mod, tr, kinds[:32], seeds[:32], fits=[1] * min(32, B))
 
 
-# The registers take up to 32 768 variables and 65 535 steps: the second trace is placed there too, the third one is swept
+# The first two traces are placed in registers or in batches, which take up to 65 535 steps; the third one is swept
 @pytest.mark.parametrize("n,T,max_life", [(2000, 300, None), (28700, 3000, 40), (3000, 66000, 400)])
 def test_default_threshold_keeps_small_traces_off_the_segment_lists(lap, oracle_mod, n, T, max_life):
-    """Same results whichever structure places the trace: the default threshold (registers, or the sweep) against the
-    forced path."""
+    """Same results whichever structure places the trace: the default threshold (registers, batches, or the sweep)
+    against the forced path."""
     tr = _long_lived(30, n, T, max_life=max_life)
     kinds, seeds = make_orderings(16)
     dt = lap.DeviceTrace(tr)
@@ -172,16 +172,19 @@ def test_default_threshold_keeps_small_traces_off_the_segment_lists(lap, oracle_
     assert np.array_equal(forced, default)
 
 
-# what is handed back is placed in registers up to 32 768 variables, and swept beyond
+# what is handed back is placed in batches, with best-fit orderings in the call in registers up to 32 768 variables and swept
+# beyond
 @pytest.mark.parametrize("n,T,max_life", [(3000, 900, None), (28700, 3000, 40), (32768, 3000, 40), (32769, 3000, 40)])
 def test_trial_run_hands_random_lifetimes_back(lap, oracle_mod, n, T, max_life):
-    """With the trial on, a trace with lifetimes at random (searches of many rounds) is placed by the registers or the
-    sweep and a nested one by the lists; the offsets are the oracle's either way."""
+    """With the trial on, a trace with lifetimes at random (searches of many rounds) is placed in batches and a nested one
+    by the lists; the offsets are the oracle's either way."""
     lap.set_option(lap.OPT_SEG_TRIAL_PERCENT, lap.SEG_TRIAL_PERCENT_DEFAULT)
     try:
         tr = _long_lived(40, n, T, max_life=max_life)
         kinds, seeds = make_orderings(8)
         _check(lap, oracle_mod, tr, kinds, seeds)
+        if n < 30000:
+            _check(lap, oracle_mod, tr, kinds[:4], seeds[:4], fits=[0, 1, 0, 0])
         _check(lap, oracle_mod, make_config(3), kinds, seeds)
     finally:
         lap.set_option(lap.OPT_SEG_TRIAL_PERCENT, 0)
