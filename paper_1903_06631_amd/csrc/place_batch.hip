@@ -29,7 +29,8 @@
 // chunk's lifetimes do not come out even over the waves (22 us), and one variable after the other where a batch is settled,
 // 200 cycles each (half of the time where all variables of a step follow each other).  A second ordering on the compute unit
 // fills those waits.  Rows that every wave reads for itself, four lifetimes at a time, took as long under one ordering a unit and
-// read them 2.5 times over (4096 orderings: 5.3 TB/s; 948 ms).
+// read them 2.5 times over (4096 orderings: 5.3 TB/s; 948 ms).  Where holes take one variable each and sizes are few, an order
+// that follows the trace fills a batch with 5 to 8 variables only, and the registers are faster (batches_lose).
 #include "block_rows.h"
 #include "lap_kernels.h"
 

@@ -275,6 +275,8 @@ hipError_t launch_place_reg(uint32_t n, uint32_t T, uint32_t B, const uint32_t *
     // 36.2 and 37.1).  More rows than 40 need 16.
     // Rows that a trace cannot fill cost all the same (193 orderings of 9001: 11.5 ms with 12 waves of 3 rows, 11.8
     // with 16), and up to 5 rows a wave keeps their ends (100 of 15 000: 24 ms with 4 rows, 30 with 7).
+    // First-fit calls of more than 1024 variables go to the batches (place_batch.hip); here come those of them whose
+    // lifetimes cross and that have few sizes, and all with a best-fit ordering among them.
     const bool alone = B <= 256;
     if (rows <= 1) return launch_one<1, 1>(A, B, st);
     if (rows <= 2) return launch_one<1, 2>(A, B, st);

@@ -419,9 +419,10 @@ __device__ void sim_run_wide(const SimArgs &A, SimWin &W)
 // from its lane whether it has changed or not, and conditions are signs, so that several are one `and`.  An actor's word
 // is its remaining time less one, and -1 when it does nothing: max(word - elapsed, -1) is the next word in all cases.
 // The limit is kept as what it leaves.  A stretch in which only one of the two streams can be at work leaves the other one
-// out: 125 to 140 ns an event there, 250 where both are.  14 000 steps and 11 000 transfers, every one blocked, with
-// both at work in half of the events: 6.7 ms (7.4 ms when every event looked at both, 14.8 with 64-bit state and a branch a
-// question); the same under limits that can be met 4.0 to 1.8 ms; 348 steps and 257 transfers 0.15 ms (0.18, 0.36).
+// out: some 125 ns an event there, 200 where both are.  14 000 steps and 11 000 transfers, every one blocked, with
+// both at work in half of the events: 6.3 ms (7.4 ms when every event looked at both, 14.8 with 64-bit state and a branch a
+// question); 348 steps and 257 transfers 0.145 ms (0.18, 0.36).  8000 steps and 4000 transfers without a limit: nested idle
+// gaps 2.2 ms (2.9), gaps of a few steps, whose transfers take turns, 2.85 (2.87).
 struct NarrowWin {
     uint32_t need[RUN_WIN], rel[RUN_WIN], dt[RUN_WIN];               // dt, like all times here, less one
     uint32_t osize[RUN_WIN], odur[RUN_WIN], olo[RUN_WIN], oplace[RUN_WIN];
